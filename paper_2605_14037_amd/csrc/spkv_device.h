@@ -11,6 +11,7 @@
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) float f32x8;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define SPKV_NEG_INF (-__builtin_inff())
 
@@ -113,6 +114,15 @@ __device__ __forceinline__ int batch_page(const SpkvView& v, const PageBatch& pb
 // reads is the workgroup barrier, which neither the asm nor the reads may cross.)
 __device__ __forceinline__ void load_row_to_lds(const uint16_t* src, unsigned lds_row) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(src), "s"(lds_row)
+                 : "m0");
+}
+
+// The same for data that no other workgroup reads (non-temporal: its lines do not push out of
+// the L2 what is shared).
+__device__ __forceinline__ void load_row_to_lds_once(const uint16_t* src, unsigned lds_row) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
                  :
                  : "v"(src), "s"(lds_row)
                  : "m0");

@@ -163,139 +163,238 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-// Many tokens, d_hidden <= 256: the same tiling with the operands staged through LDS.  The
-// register-tiled kernel above fetches its MFMA operands straight from memory in 64-byte
-// pieces, 16 cache lines per load instruction, and every wave fetches the token rows again;
-// that, not the MFMAs, sets its speed.  Here a workgroup (one wave per 64 hidden units) copies
-// a block of 64 elements of d_model -- 128 bytes of every W1 row and of every one of its 64
-// token rows -- straight into LDS, eight lanes per row (whole cache lines, each fetched once
-// per workgroup), one block ahead of the one it computes on.  Chunk c (16 bytes) of row r is
-// stored at position c ^ (r & 7) of the row, so that the eight lanes of an operand read that
-// share a bank phase hit eight different bank groups.
-constexpr int kGemmTokens = 64;      // tokens per workgroup
+// Many tokens, d_hidden <= 256: the operands staged through LDS.  A workgroup takes TT tokens
+// and the whole hidden layer (so every token row is fetched once from memory, whatever
+// d_hidden is): TT / 64 x NHW waves, each with a 64 x 64 (hidden x token) tile of fp32 sums in
+// four MFMA 32x32x16 accumulators.  Blocks of 64 elements of d_model -- 128 bytes of every W1
+// row and token row -- are copied straight into LDS, eight lanes per row, two blocks ahead of
+// the one in use (ring of three), and a wave waits only for its own copies of the next block,
+// not for the newest.  The token rows are copied non-temporal: kept in the L2 they pushed W1
+// out of it (35 % more traffic behind the L2 by counters, 2 % of the time).  Chunk c (16 bytes)
+// of row r lies at position c ^ ((r >> 1) & 7) of the row: the sixteen rows an operand read
+// touches at a time then cover all 64 banks once.
+// What bounds it, 32 768 tokens of 4096 -> 256 -> 8: the compute side of a stage alone takes
+// 0.7 us, the copies alone 1.0 (per compute unit one 1 KB copy of eight rows takes about 30
+// clocks of the address unit), both together 1.2; 118 us with 64-token workgroups, two stages
+// in LDS and 16x16x32 products, 82 us now.  Stages half as wide and five ahead: 100 us (the
+// copies are bound by rows, not by latency).  The epilogue's loads go out together: one by one,
+// behind a branch each, they were 9 us of every call.
+// Sums of kGemmFlush stages are added up outside the MFMA accumulators: the relative error
+// against 64 bits is 5.7e-8 (one chain over d_model: 1.55e-7) for 2 us.
 constexpr int kGemmK = 64;           // elements of d_model per stage
+constexpr int kGemmBufs = 3;         // stages in LDS: one in use, two on their way
+#ifndef FLUSH
+#define FLUSH 8
+#endif
+constexpr int kGemmFlush = FLUSH;        // stages summed in the MFMA accumulators before they are added up
+constexpr int kGemmHeads = 32;       // KV heads per pass of the output layer
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_predictor_gemm(
+template <int NHW, int TT>
+__global__ __launch_bounds__(TT * NHW) void spkv_predictor_gemm(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w1, const float* __restrict__ b1,
     const uint16_t* __restrict__ w2, const float* __restrict__ b2, float* __restrict__ logits,
     int n_tokens, int d_model, int d_hidden, int n_kv_heads) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
-    const int tid = threadIdx.x, lane = tid & 63, kc = lane >> 4, n = lane & 15;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), n_waves = d_hidden / 64;
-    const int t0 = blockIdx.x * kGemmTokens;
-    const int rows = d_hidden + kGemmTokens;               // rows of a stage: W1 rows, then token rows
-    const unsigned stage_bytes = (unsigned)rows * 128;
+    constexpr int NW = NHW * (TT / 64);                    // waves
+    constexpr int kRows = NHW * 64 + TT;                   // rows of a stage: W1 rows, then token rows
+    constexpr int kRowBytes = kGemmK * 2, kStageBytes = kRows * kRowBytes;
+    constexpr int kCopies = kRows / 8 / NW;                // 1 KB copies (8 rows) per wave and stage
+    constexpr int kWCopies = NHW * 8 / NW;                 // of which the first are W1 rows
+    static_assert(kRows % (8 * NW) == 0 && NHW * 8 % NW == 0, "whole copies per wave");
+    __shared__ __attribute__((aligned(16))) unsigned char s_raw[kGemmBufs * kStageBytes];
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, n = lane & 31;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wh = wv % NHW, wt = wv / NHW;                // hidden units 64 wh .., tokens 64 wt ..
+    const int t0 = blockIdx.x * TT;
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)s_raw;
-    // this wave's copies: 8 rows (1 KB) per load, rows 8 i .. 8 i + 7 for i = wv, wv + n_waves, ...
-    const int r_in = lane >> 3, c_in = (lane & 7) ^ r_in;  // row within the 8, chunk fetched (swizzle)
-    auto copy_stage = [&](int k0, int buf) {
-        for (int i = wv; i < rows / 8; i += n_waves) {
-            const int r = i * 8 + r_in;
-            const uint16_t* src = r < d_hidden
-                                      ? w1 + (size_t)r * d_model
-                                      : x + (size_t)min(t0 + r - d_hidden, n_tokens - 1) * d_model;
-            load_row_to_lds(src + k0 + c_in * 8,
-                            __builtin_amdgcn_readfirstlane(lds0 + (unsigned)buf * stage_bytes + (unsigned)i * 1024));
+    const int n_stages = d_model / kGemmK;                 // at least 2 (d_model is a multiple of 128)
+    // this wave's copies: rows 8 i .. 8 i + 7 for i = wv, wv + NW, ...  (rows past d_hidden or
+    // past the last token repeat the last one; their results are not used)
+    const uint16_t* src[kCopies];
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u) {
+        const int r = (wv + u * NW) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        src[u] = (u < kWCopies ? w1 + (size_t)min(r, d_hidden - 1) * d_model
+                               : x + (size_t)min(t0 + r - NHW * 64, n_tokens - 1) * d_model) + c * 8;
+    }
+    // copies u0 .. u1 - 1 of stage st (past the end: the last stage again, never used, so that
+    // the count of copies in flight stays the same)
+    auto copy_stage = [&](int st, int buf, int u0, int u1) {
+        const int k0 = min(st, n_stages - 1) * kGemmK;
+#pragma unroll
+        for (int u = 0; u < kCopies; ++u) {
+            if (u < u0 || u >= u1) continue;
+            const unsigned dst = lds0 + (unsigned)(buf * kStageBytes + (wv + u * NW) * 1024);
+            if (u < kWCopies) load_row_to_lds(src[u] + k0, dst);
+            else load_row_to_lds_once(src[u] + k0, dst);
         }
     };
-    f32x4 acc[4][4];
+    f32x16 acc[2][2];
 #pragma unroll
-    for (int hs = 0; hs < 4; ++hs)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int ts = 0; ts < 4; ++ts) acc[hs][ts] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    __builtin_amdgcn_s_waitcnt(0x0f70);          // nothing of ours is in flight yet: vmcnt(0)
-    copy_stage(0, 0);
-    wait_loads_but<0>();
+    f32x16 sum[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) sum[i][j] = acc[i][j];
+    copy_stage(0, 0, 0, kCopies);
+    copy_stage(1, 1, 0, kCopies);
+    wait_loads_but<kCopies>();                             // stage 0 has landed
     __syncthreads();
-    const int n_stages = d_model / kGemmK;
+    // byte offsets of this lane's operand rows inside a stage, and their swizzle
+    const int ra = (wh * 64 + n) * kRowBytes, rb = (NHW * 64 + wt * 64 + n) * kRowBytes, sw = (n >> 1) & 7;
+    bf16x8 a[2][2], b[2][2];
+    auto operands = [&](const unsigned char* tile, int u) {
+        const int c = ((2 * u + half) ^ sw) << 4;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            a[u & 1][i] = *reinterpret_cast<const bf16x8*>(tile + ra + i * 32 * kRowBytes + c);
+            b[u & 1][i] = *reinterpret_cast<const bf16x8*>(tile + rb + i * 32 * kRowBytes + c);
+        }
+    };
+    auto products = [&](int u) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u & 1][i], b[u & 1][j], acc[i][j], 0, 0, 0);
+    };
+    operands(s_raw, 0);
+    int buf = 0;
     for (int st = 0; st < n_stages; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < n_stages) copy_stage((st + 1) * kGemmK, buf ^ 1);
-        const unsigned char* tile = s_raw + (size_t)buf * stage_bytes;
+        const unsigned char* tile = s_raw + buf * kStageBytes;
+        const int nbuf = buf >= 1 ? buf - 1 : kGemmBufs - 1;       // stage st + 2 goes where st - 1 was
+        buf = buf == kGemmBufs - 1 ? 0 : buf + 1;
+        // Four MFMA steps of 16.  The operands of a step are read during the step before it, the
+        // next stage's copies go out a third at a time between them (all at once they hold up
+        // the waves' own reads), and the barrier stands before the last step, so that the first
+        // operands of the next stage are on their way while the last products of this one run.
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {            // two MFMA steps of 32 per stage
-            bf16x8 a[4], b[4];
-            const int c = 4 * u + kc;            // chunk of the row this lane feeds
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int ra = wv * 64 + i * 16 + n, rb = d_hidden + i * 16 + n;
-                a[i] = *reinterpret_cast<const bf16x8*>(tile + ra * 128 + ((c ^ (ra & 7)) << 4));
-                b[i] = *reinterpret_cast<const bf16x8*>(tile + rb * 128 + ((c ^ (rb & 7)) << 4));
-            }
-#pragma unroll
-            for (int hs = 0; hs < 4; ++hs)
-#pragma unroll
-                for (int ts = 0; ts < 4; ++ts)
-                    acc[hs][ts] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[hs], b[ts], acc[hs][ts], 0, 0, 0);
+        for (int u = 0; u < 3; ++u) {
+            operands(tile, u + 1);
+            copy_stage(st + 2, nbuf, u * kCopies / 3, (u + 1) * kCopies / 3);
+            products(u);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        wait_loads_but<0>();
+        wait_loads_but<kCopies>();                         // all but the newest: stage st + 1 has landed
         __syncthreads();
-    }
-    // lane (kc, n) holds hidden units 64 wv + 16 hs + 4 kc + i of tokens t0 + 16 ts + n
-    const int j0 = wv * 64;
+        operands(s_raw + buf * kStageBytes, 0);
+        products(3);
+        __builtin_amdgcn_sched_barrier(0);
+        if ((st + 1) % kGemmFlush == 0 || st + 1 == n_stages) {
 #pragma unroll
-    for (int hs = 0; hs < 4; ++hs)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float bias = b1 != nullptr ? b1[j0 + hs * 16 + 4 * kc + i] : 0.f;
+                for (int j = 0; j < 2; ++j) {
+                    sum[i][j] += acc[i][j];
 #pragma unroll
-            for (int ts = 0; ts < 4; ++ts) {
-                const float h = acc[hs][ts][i] + bias;
-                acc[hs][ts][i] = h / (1.f + __expf(-h));                           // SiLU
-            }
-        }
-    float* s_logit = reinterpret_cast<float*>(s_raw);      // [waves][64 tokens][n_kv_heads]
-    for (int hd = 0; hd < n_kv_heads; ++hd) {
-        float w[4][4];
-#pragma unroll
-        for (int hs = 0; hs < 4; ++hs)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned bits = w2[(size_t)hd * d_hidden + j0 + hs * 16 + 4 * kc + i];
-                w[hs][i] = __builtin_bit_cast(float, bits << 16);
-            }
-#pragma unroll
-        for (int ts = 0; ts < 4; ++ts) {
-            float p = 0.f;
-#pragma unroll
-            for (int hs = 0; hs < 4; ++hs)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) p += w[hs][i] * acc[hs][ts][i];
-            p += __shfl_xor(p, 16);
-            p += __shfl_xor(p, 32);
-            if (kc == 0) s_logit[((size_t)wv * 64 + ts * 16 + n) * n_kv_heads + hd] = p;
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                }
         }
     }
-    __syncthreads();
-    for (int o = tid; o < kGemmTokens * n_kv_heads; o += 64 * n_waves) {
-        const int tok = o / n_kv_heads, hd = o - tok * n_kv_heads;
-        if (t0 + tok >= n_tokens) continue;
-        float sum = b2 != nullptr ? b2[hd] : 0.f;
-        for (int w8 = 0; w8 < n_waves; ++w8) sum += s_logit[((size_t)w8 * 64 + tok) * n_kv_heads + hd];
-        logits[(size_t)(t0 + tok) * n_kv_heads + hd] = sum;
+    wait_loads_but<0>();                                   // LDS is written again below
+    // lane (half, n) holds hidden units j0 + 32 i + 8 g + 4 half + e (register 4 g + e) of tokens
+    // t0 + 64 wt + 32 j + n
+    const int j0 = wh * 64;
+    float bias[2][16];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {                     // (units past d_hidden: any value)
+            const int unit = min(j0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3), d_hidden - 1);
+            bias[i][r] = b1 != nullptr ? b1[unit] : 0.f;
+        }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const bool real = j0 + i * 32 + (r >> 2) * 8 + half * 4 < d_hidden;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float h = sum[i][j][r] + bias[i][r];
+                const float act = h / (1.f + __expf(-h));                          // SiLU
+                sum[i][j][r] = real ? act : 0.f;
+            }
+        }
+    // Output layer, kGemmHeads heads at a time: their W2 rows go to LDS in one round of loads
+    uint16_t* s_w2 = reinterpret_cast<uint16_t*>(s_raw);                           // [heads][NHW * 64]
+    float* s_logit = reinterpret_cast<float*>(s_raw + kGemmHeads * NHW * 128);     // [NHW][heads][TT]
+    static_assert(kGemmHeads * NHW * 128 + NHW * kGemmHeads * TT * 4 <= kGemmBufs * kStageBytes, "LDS");
+    for (int h0 = 0; h0 < n_kv_heads; h0 += kGemmHeads) {
+        const int nh = min(kGemmHeads, n_kv_heads - h0);
+        __syncthreads();
+        for (int e = tid; e < nh * NHW * 32; e += 64 * NW) {       // pairs of hidden units
+            const int hd = e / (NHW * 32), u2 = (e - hd * (NHW * 32)) * 2;
+            reinterpret_cast<unsigned*>(s_w2)[e] =
+                u2 < d_hidden ? *reinterpret_cast<const unsigned*>(w2 + (size_t)(h0 + hd) * d_hidden + u2) : 0u;
+        }
+        __syncthreads();
+        for (int hd = 0; hd < nh; ++hd) {
+            float p[2] = {0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {                      // four consecutive hidden units
+                    float t[2] = {0.f, 0.f};                       // (short chains: half the rounding error)
+                    const uint2 w = *reinterpret_cast<const uint2*>(s_w2 + hd * (NHW * 64) + j0 + i * 32 + g * 8 + half * 4);
+                    const float wf[4] = {__builtin_bit_cast(float, w.x << 16), __builtin_bit_cast(float, w.x & 0xffff0000u),
+                                         __builtin_bit_cast(float, w.y << 16), __builtin_bit_cast(float, w.y & 0xffff0000u)};
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[j] += wf[e] * sum[i][j][g * 4 + e];
+                    p[0] += t[0];
+                    p[1] += t[1];
+                }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                p[j] += __shfl_xor(p[j], 32);
+                if (half == 0) s_logit[(wh * kGemmHeads + hd) * TT + wt * 64 + j * 32 + n] = p[j];
+            }
+        }
+        __syncthreads();
+        for (int o = tid; o < TT * nh; o += 64 * NW) {
+            const int tok = o / nh, hd = o - tok * nh;
+            if (t0 + tok >= n_tokens) continue;
+            float t = 0.f;
+#pragma unroll
+            for (int w = 0; w < NHW; ++w) t += s_logit[(w * kGemmHeads + hd) * TT + tok];
+            logits[(size_t)(t0 + tok) * n_kv_heads + h0 + hd] = t + (b2 != nullptr ? b2[h0 + hd] : 0.f);
+        }
     }
+}
+
+template <int NHW, int TT>
+static hipError_t launch_predictor_gemm(const uint16_t* x, const uint16_t* w1, const float* b1,
+                                        const uint16_t* w2, const float* b2, float* logits, int n_tokens,
+                                        int d_model, int d_hidden, int n_kv_heads, hipStream_t s) {
+    spkv_predictor_gemm<NHW, TT><<<dim3((n_tokens + TT - 1) / TT), dim3(TT * NHW), 0, s>>>(
+        x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads);
+    return hipGetLastError();
 }
 
 hipError_t spkv_launch_predictor(const uint16_t* x, const uint16_t* w1, const float* b1,
                                  const uint16_t* w2, const float* b2, float* logits, float* act,
                                  int n_tokens, int d_model, int d_hidden, int n_kv_heads,
                                  hipStream_t s) {
-    // A workgroup of the LDS-staged kernel takes about 80 us for d_model = 4096 (64 stages, each
-    // waiting for its copy), so it pays once there are enough tokens to fill the chip with
-    // workgroups: 32 768 tokens 125 us, 4096 tokens 83 us (two-kernel path: 1.0 ms, 128 us).
-    if (n_tokens >= 4096 && d_hidden % 64 == 0 && d_hidden <= 256 && d_model % kGemmK == 0 &&
-        n_kv_heads <= 64) {
-        const int n_waves = d_hidden / 64;
-        const size_t lds = std::max((size_t)2 * (d_hidden + kGemmTokens) * 128,
-                                    (size_t)n_waves * 64 * n_kv_heads * sizeof(float));
-        // more than the 64 KB of dynamic LDS a kernel gets by default
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(spkv_predictor_gemm),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        spkv_predictor_gemm<<<dim3((n_tokens + kGemmTokens - 1) / kGemmTokens), dim3(64 * n_waves), lds, s>>>(
-            x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads);
-        return hipGetLastError();
+    // The staged kernel takes the same time for any number of tokens up to a workgroup per compute
+    // unit (d_model 4096, 256 units: 51 us; 1024, 64: 19 us), the pair of launches below grows with
+    // tokens x units (1024 tokens 36 us, 1400 about 49, 2048 65; 64 units: 2048 tokens 14 us).
+    // 128 tokens per workgroup halve the fetches of W1 once 64 would need a second round (16 384
+    // tokens: 58 us with 64 each; 20 000: 65 us with 128, 100 with 64).
+    if ((n_tokens >= 4096 || (int64_t)n_tokens * d_hidden >= 350000) && d_hidden <= 256) {
+        const bool wide = n_tokens > 16384;
+        if (d_hidden <= 64) return wide ? launch_predictor_gemm<1, 128>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s)
+                                        : launch_predictor_gemm<1, 64>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s);
+        if (d_hidden <= 128) return wide ? launch_predictor_gemm<2, 128>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s)
+                                         : launch_predictor_gemm<2, 64>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s);
+        return wide ? launch_predictor_gemm<4, 128>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s)
+                    : launch_predictor_gemm<4, 64>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s);
     }
     // Wider hidden layers (up to 512 units): the register-tiled kernel, about 120 us per
     // workgroup for d_model = 4096 (32 768 tokens: 242 us).

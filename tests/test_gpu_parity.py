@@ -790,6 +790,26 @@ def test_utility_predictor(n, dm, dh, Hk):
         cache.close()
 
 
+@pytest.mark.parametrize("n,dm,dh,Hk", [(4096, 128, 16, 1), (4160, 256, 48, 33), (16385, 128, 80, 5),
+                                        (16500, 384, 208, 64), (1400, 512, 256, 100),
+                                        (16447, 1664, 144, 8)])
+def test_utility_predictor_staged_kernel(n, dm, dh, Hk):
+    """Edges of the LDS-staged predictor: hidden layers that do not fill a wave's 64 units, token
+    counts one past a workgroup or a size rule, two to many stages, more heads than one pass of the
+    output layer.  fp32 sums of dm + dh products of unit scale: a few thousand roundings of 6e-8
+    add up to less than 1e-5."""
+    from oracle.spkv_oracle import utility_logits as oracle_logits
+    g = torch.Generator(device="cuda").manual_seed(n + dh)
+    x = torch.randn(n, dm, generator=g, device="cuda").to(torch.bfloat16)
+    w1 = (torch.randn(dh, dm, generator=g, device="cuda") / dm ** 0.5).to(torch.bfloat16)
+    w2 = (torch.randn(Hk, dh, generator=g, device="cuda") / dh ** 0.5).to(torch.bfloat16)
+    biases = (torch.randn(dh, generator=g, device="cuda"), torch.randn(Hk, generator=g, device="cuda"))
+    for b1, b2 in (biases, (None, None)):
+        got = spkv.utility_logits(x, w1, b1, w2, b2)
+        ref = oracle_logits(*(None if t is None else to_numpy_f32(t) for t in (x, w1, b1, w2, b2)))
+        assert np.abs(got.cpu().numpy() - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+
+
 @pytest.mark.parametrize("B,Hq,Hk,D,dm,dh,bias", [(16, 32, 8, 128, 4096, 256, True),
                                                    (3, 8, 2, 64, 256, 48, True),
                                                    (33, 16, 4, 128, 1024, 64, False),
