@@ -24,7 +24,8 @@
 struct SpkvPrefill {
     uint16_t* stage;     // [n_pairs][shp] half-pages
     int32_t*  prefix;    // [total tokens][H_kv]
-    float*    bias;      // soft gating only: [n_pairs][shp][32] log2 u of every staging row
+    float*    bias;      // soft gating only: [n_pairs][shp][32] log2 u of every staging row, in units of a score
+    float     bias_unit; // soft gating only: 1 / (sm_scale log2 e)
     int32_t   shp;       // staging half-pages per pair
     int32_t   tb;        // tokens per wave (16 nq / G)
     int32_t   nblk;      // workgroups (spans of nw tb tokens) per pair in the grid
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(256) void spkv_prefill_stage(SpkvView v, const uint
                 // log u = log sigmoid(f) = -softplus(-f) (Eq. 1 and the soft gate), in log2
                 const float x = f[((size_t)row0 + (u - v.w)) * v.Hkv + h];
                 const float ls = x < -20.f ? x : -log1pf(__expf(-x));
-                lb = ls * 1.4426950408889634f;
+                lb = ls * 1.4426950408889634f * pf.bias_unit;
             }
             pf.bias[((size_t)pair * pf.shp + sh) * kHalfTokens + wave * 8 + row] = lb;
         }
@@ -536,6 +537,316 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 }
 
+// The same for long chunks and for the soft-gated forward: eight waves, each with 32 columns as
+// ONE group of MFMA 32x32x16, software-pipelined over half-pages.
+template <int D, bool SOFT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_prefill_attend32(
+    SpkvView v, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
+    float scale_log2e, SpkvPrefill pf, SpkvCu cu) {
+    constexpr int NW = 8, NS = D / 16, NB = D / 32;
+    constexpr int kHalfElems = 2 * kHalfTokens * D;
+    constexpr int kStepElems = 2 * kHalfElems;              // a step: two half-pages, 64 keys
+    constexpr int kRowsPerWave = kStepElems / 512 / NW;     // 1 KB rows of a step per wave
+    constexpr int kBufs = 4;
+    __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kStepElems];
+    __shared__ __attribute__((aligned(16))) float s_bias[SOFT ? kBufs : 1][SOFT ? NW : 1][SOFT ? 64 : 4];
+    int pair, qblk, kr;      // (sequence, KV head), span, tile range of the span
+    if (pf.pin_xcd) {        // see spkv_prefill_attend
+        const int local = blockIdx.x >> 3, lp = local / (pf.nblk * pf.ks);
+        const int rem = local - lp * pf.nblk * pf.ks;
+        qblk = rem / pf.ks;
+        kr = rem - qblk * pf.ks;
+        const int rot = (lp * 8 + 8 <= v.n_pairs) ? lp : 0;
+        pair = lp * 8 + (((blockIdx.x & 7) + rot) & 7);
+        if (pair >= v.n_pairs) return;
+    } else {
+        pair = blockIdx.x / (pf.nblk * pf.ks);
+        const int rem = blockIdx.x - pair * pf.nblk * pf.ks;
+        qblk = rem / pf.ks;
+        kr = rem - qblk * pf.ks;
+    }
+    qblk = pf.nblk - 1 - qblk;            // longest prefixes first
+    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
+    const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
+    const int span0 = qblk * NW * pf.tb;
+    if (span0 >= n_tok) return;
+    const int span_last = min(span0 + NW * pf.tb, n_tok) - 1;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i0 = span0 + wv * pf.tb;
+    const int tbv = max(0, min(pf.tb, n_tok - i0)), i_last = i0 + tbv - 1, cols = tbv * v.G;
+    const bool active = tbv > 0;
+    const int T0 = SOFT ? 0 : v.t_pair[pair] - n_tok, L = SOFT ? 0 : v.kept_len[pair];
+    const int u_min = max(0, v.w - T0);     // first staging row that holds a position
+
+    auto prefix_of = [&](int i) -> int {   // long-term entries at least w behind token i
+        if (SOFT || T0 + i - v.w < 0) return 0;
+        return min(max(pf.prefix[((size_t)row0 + i) * v.Hkv + h], 0), L);
+    };
+    const bool valid = col < cols;
+    const int tok = valid ? i0 + col / v.G : -1;
+    const int cnt = valid ? prefix_of(tok) : 0;
+    bf16x8 qb[NS];
+    {
+        const uint16_t* qrow = q + ((size_t)(row0 + (valid ? tok : i0)) * v.Hq + (size_t)h * v.G + (col - (col / v.G) * v.G)) * D + half * 8;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) {
+            uint4 raw = {0u, 0u, 0u, 0u};
+            if (valid) raw = *reinterpret_cast<const uint4*>(qrow + sl * 16);
+            qb[sl] = __builtin_bit_cast(bf16x8, raw);
+        }
+    }
+    const int nA = (prefix_of(span_last) + kHalfTokens - 1) >> 5;
+    const int nA_wave = active ? (prefix_of(i_last) + kHalfTokens - 1) >> 5 : 0;
+    const int fullA = active ? prefix_of(i0) >> 5 : 0;
+    const int sB0 = (SOFT ? u_min : max(span0 + 1, u_min)) >> 5;
+    const int nB = ((span_last + v.w) >> 5) - sB0 + 1;
+    const int lo_w = SOFT ? u_min : max(i0 + 1, u_min), hi_w = i_last + v.w;
+    const int n_hp = nA + nB, last = n_hp - 1;
+    const int x_begin = (int)(((long long)kr * n_hp) / pf.ks);
+    const int x_end = (int)(((long long)(kr + 1) * n_hp) / pf.ks);
+
+    const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
+    const uint16_t* stage = pf.stage + (size_t)pair * pf.shp * (size_t)kHalfElems;
+    int page_lane0 = -64, my_page = 0;
+    auto page_of = [&](int lp) -> int {
+        if (lp >= page_lane0 + 64) {
+            page_lane0 = lp;
+            my_page = pt[min(lp + lane, v.pt_cap - 1)];
+            __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+        }
+        return __builtin_amdgcn_readlane(my_page, lp - page_lane0);
+    };
+    auto base_of = [&](int x) -> const uint16_t* {
+        x = min(x, last);
+        if (x < nA) {
+            const int page = min(max(page_of(min(x >> 1, v.pt_cap - 1)), 0), v.n_pages - 1);
+            return pool_page(v, page) + (x & 1) * kHalfElems;
+        }
+        return stage + (size_t)min(sB0 + x - nA, pf.shp - 1) * kHalfElems;
+    };
+
+    // Copies of a step: waves 0-3 the first half-page, 4-7 the second, a quarter each.  K rows of
+    // tile t = 1 (the second quarter) are stored with their keys m at m ^ 8, so that the rows of
+    // one operand read -- keys 0-7 of both tiles -- do not share banks.
+    const int quarter = wv & 3;
+    const int my_off = (quarter * kRowsPerWave * 64 + (quarter == 1 ? lane ^ 8 : lane)) * 8;
+    const unsigned lds_rows = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&s_tile[0][0] +
+                              (unsigned)wv * (kRowsPerWave * 1024);
+    const unsigned lds_bias = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)&s_bias[0][0][0] +
+                              (unsigned)wv * 256;
+    constexpr int kCopies = kRowsPerWave + (SOFT ? 1 : 0);
+    auto stage_step = [&](int x, int buf) {                 // half-pages x, x + 1
+        const uint16_t* p = base_of(x + (wv >> 2)) + my_off;
+#pragma unroll
+        for (int r = 0; r < kRowsPerWave; ++r)
+            load_row_to_lds(p + r * 512, lds_rows + (unsigned)buf * (kStepElems * 2) + r * 1024);
+        if (SOFT) {
+            const int hp = min(sB0 + min(x + (lane >> 5), last) - nA, pf.shp - 1);
+            load_word_to_lds(pf.bias + ((size_t)pair * pf.shp + hp) * kHalfTokens + (lane & 31),
+                             lds_bias + (unsigned)buf * (NW * 256));
+        }
+    };
+
+    f32x16 acc[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+    float m = valid ? SPKV_NEG_INF : 0.f, l = 0.f;
+
+    // operand addresses inside a half-page (elements)
+    const int krow = ((((col >> 3) & 1) * (D / 8) + half) * 16 +
+                      ((8 * (col >> 4) + 4 * ((col >> 2) & 1) + (col & 3)) ^ (8 * ((col >> 3) & 1)))) * 8;
+    const int vrow = kHalfTokens * D + (((col >> 4) * 4 + half) * 16 + (col & 15)) * 8;
+    bf16x8 kf[NS];
+    auto load_k = [&](const uint16_t* hp) {
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + krow + sl * 256);
+    };
+    auto mine = [&](int x) -> bool {
+        if (x >= x_end) return false;
+        if (x < nA) return x < nA_wave;
+        const int u = (sB0 + x - nA) * kHalfTokens;
+        return active && u <= hi_w && u + kHalfTokens > lo_w;
+    };
+    // soft gating: every row of the half-page lies outside every window of the wave
+    auto all_biased = [&](int x) -> bool { return (sB0 + x - nA) * kHalfTokens + kHalfTokens - 1 <= i0; };
+    // scores of a half-page from kf; with soft gating started at the bias (in units of a score)
+    auto scores = [&](f32x16& s, int x, const float* bias) {
+        f32x16 c;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) c[e] = 0.f;
+        if (SOFT && all_biased(x)) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 t = *reinterpret_cast<const float4*>(bias + (g >> 1) * 16 + half * 8 + (g & 1) * 4);
+                c[4 * g] = t.x; c[4 * g + 1] = t.y; c[4 * g + 2] = t.z; c[4 * g + 3] = t.w;
+            }
+        }
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qb[0], c, 0, 0, 0);
+#pragma unroll
+        for (int sl = 1; sl < NS; ++sl) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qb[sl], s, 0, 0, 0);
+    };
+    auto mask = [&](f32x16& s, int x, const float* bias) {
+        if (x < nA) {
+            if (x < fullA) return;
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const unsigned ok = bit_range8(0, cnt - (x * kHalfTokens + 16 * g + 8 * half) - 1);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s[8 * g + e] = ((ok >> e) & 1u) ? s[8 * g + e] : SPKV_NEG_INF;
+            }
+            return;
+        }
+        const int u = (sB0 + x - nA) * kHalfTokens;
+        if (SOFT && u >= u_min && all_biased(x)) return;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int u0 = u + 16 * g + 8 * half;
+            const unsigned ok = tok >= 0 ? bit_range8((SOFT ? u_min : max(tok + 1, u_min)) - u0, tok + v.w - u0) : 0u;
+            if (SOFT && !all_biased(x)) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s[8 * g + e] += u0 + e <= tok ? bias[16 * g + 8 * half + e] : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[8 * g + e] = ((ok >> e) & 1u) ? s[8 * g + e] : SPKV_NEG_INF;
+        }
+    };
+    f32x8 p[2];
+    float psum;
+    auto weights = [&](const f32x16& s) -> bool {
+        const bool unset = m == SPKV_NEG_INF;
+        const float neg_ref = unset ? 0.f : -m;
+        float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], scale_log2e, neg_ref));
+            p[e >> 3][e & 7] = w;
+            s4[e & 3] += w;
+        }
+        psum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        return __ballot(unset || !(psum <= kWeightSumLimit)) != 0ull;
+    };
+    auto rescale = [&](const f32x16& s) {
+        float cm = s[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) cm = fmaxf(cm, s[e]);
+        cm *= scale_log2e;
+        cm = fmaxf(cm, __shfl_xor(cm, 32));
+        const float m_new = fmaxf(m, cm);
+        const float m_ref = (m_new == SPKV_NEG_INF) ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m - m_ref);
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < NB; ++db) acc[db] *= alpha;
+        m = m_new;
+        (void)weights(s);
+    };
+    // One half-page x: its scores are in sc (if `have`); the scores of x + 1 go to sn.
+    bool have = false;
+    auto unit = [&](f32x16& sc, f32x16& sn, int x, const uint16_t* hp, const float* bias,
+                    const uint16_t* hp2, const float* bias1) {
+        const bool nm = mine(x + 1);
+        if (have) {
+            mask(sc, x, bias);
+            bool low;
+            bf16x8 va[2][NB];
+            if (nm) {
+                scores(sn, x + 1, bias1);
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int db = 0; db < NB; ++db)
+                        va[g][db] = *reinterpret_cast<const bf16x8*>(hp + vrow + db * 1024 + g * 256);
+                low = weights(sc);
+            } else {
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int db = 0; db < NB; ++db)
+                        va[g][db] = *reinterpret_cast<const bf16x8*>(hp + vrow + db * 1024 + g * 256);
+                low = weights(sc);
+            }
+            if (low) rescale(sc);
+            load_k(hp2);
+            l += psum;
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                const bf16x8 pb = __builtin_convertvector(p[g], bf16x8);
+#pragma unroll
+                for (int db = 0; db < NB; ++db)
+                    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[g][db], pb, acc[db], 0, 0, 0);
+            }
+        } else {
+            if (nm) scores(sn, x + 1, bias1);
+            load_k(hp2);
+        }
+        have = nm;
+    };
+
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): queries and counts
+    stage_step(x_begin, 0);
+    stage_step(x_begin + 2, 1);
+    stage_step(x_begin + 4, 2);
+    wait_loads_but<kCopies>();                   // the first two steps have landed
+    __syncthreads();
+    f32x16 s0, s1;
+    load_k(s_tile[0]);
+    have = mine(x_begin);
+    if (have) scores(s0, x_begin, &s_bias[0][SOFT ? wv : 0][0]);
+    load_k(s_tile[0] + kHalfElems);
+    int buf = 0;
+    for (int x = x_begin; x < x_end; x += 2) {
+        const int nb = (buf + 1) & 3;
+        stage_step(x + 6, (buf + 3) & 3);
+        const uint16_t* t0 = s_tile[buf];
+        const uint16_t* t1 = s_tile[nb];
+        const float* b0 = &s_bias[SOFT ? buf : 0][SOFT ? wv : 0][0];
+        const float* b1 = &s_bias[SOFT ? nb : 0][SOFT ? wv : 0][0];
+        unit(s0, s1, x, t0, b0, t1, b0 + (SOFT ? 32 : 0));
+        unit(s1, s0, x + 1, t0 + kHalfElems, b0 + (SOFT ? 32 : 0), t1 + kHalfElems, b1);
+        wait_loads_but<kCopies>();               // all but the newest: the step after next has landed
+        __syncthreads();
+        buf = nb;
+    }
+    wait_loads_but<0>();
+
+    l += __shfl_xor(l, 32);
+    if (!valid) return;
+    if (pf.ks > 1) {
+        const size_t n_cols = (size_t)v.n_pairs * pf.nblk * pf.ks * (NW * 32);
+        const size_t pc = (((size_t)pair * pf.nblk + qblk) * pf.ks + kr) * (NW * 32) + wv * 32 + col;
+        float* pa = pf.part + pc * D + half * 4;
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<f32x4*>(pa + db * 32 + g * 8) =
+                    (f32x4){acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]};
+        if (half == 0) {
+            pf.part[n_cols * D + pc * 2] = m;
+            pf.part[n_cols * D + pc * 2 + 1] = l;
+        }
+        return;
+    }
+    const size_t o = (size_t)(row0 + tok) * v.Hq + (size_t)h * v.G + (col - (col / v.G) * v.G);
+    const float inv = 1.0f / l;
+    uint16_t* po = out + o * D + half * 4;
+#pragma unroll
+    for (int db = 0; db < NB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const __bf16 r0 = (__bf16)(acc[db][4 * g] * inv), r1 = (__bf16)(acc[db][4 * g + 1] * inv);
+            const __bf16 r2 = (__bf16)(acc[db][4 * g + 2] * inv), r3 = (__bf16)(acc[db][4 * g + 3] * inv);
+            uint2 pk;
+            pk.x = (unsigned)__builtin_bit_cast(uint16_t, r0) | ((unsigned)__builtin_bit_cast(uint16_t, r1) << 16);
+            pk.y = (unsigned)__builtin_bit_cast(uint16_t, r2) | ((unsigned)__builtin_bit_cast(uint16_t, r3) << 16);
+            *reinterpret_cast<uint2*>(po + db * 32 + g * 8) = pk;
+        }
+    if (lse != nullptr && half == 0) lse[o] = (m + log2f(l)) * 0.6931471805599453f;
+}
+
 // Merge of the tile ranges of one (span, column): out = sum_r 2^(m_r - M) acc_r /
 // sum_r 2^(m_r - M) l_r.  A workgroup of 256 threads takes 256 / (D / 4) consecutive columns
 // of a span's workgroup; a thread owns four consecutive output elements of one column.
@@ -589,8 +900,10 @@ static SpkvPrefill prefill_params(const SpkvView& v, int n_max, uint16_t* stage,
     pf.stage = stage;
     pf.prefix = prefix;
     pf.bias = bias;
+    pf.bias_unit = 0.f;
     pf.shp = shp;
-    const SpkvPrefillShape sh = prefill_shape(v.G, n_max);
+    SpkvPrefillShape sh = prefill_shape(v.G, n_max);
+    if (bias != nullptr) sh = SpkvPrefillShape{2, 8, 32 / v.G};       // soft gating: one shape
     pf.tb = sh.tb;
     pf.nw = sh.nw;
     pf.nq = sh.nq;
@@ -620,7 +933,7 @@ template <int D, bool SOFT>
 static void launch_attend(const SpkvView& v, const uint16_t* q, uint16_t* out, float* lse, float sl,
                           const SpkvPrefill& pf, const SpkvCu& cu, unsigned grid, hipStream_t s) {
     if (pf.nq == 2 && pf.nw == 8)
-        spkv_prefill_attend<D, SOFT, 8, 2><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend32<D, SOFT><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     else if (pf.nq == 2)
         spkv_prefill_attend<D, SOFT, 4, 2><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
     else if (pf.nw == 4)
@@ -662,8 +975,9 @@ hipError_t spkv_launch_soft_gated(const SpkvView& v, const uint16_t* k, const ui
                                   const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                   float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
                                   float* bias, int shp, hipStream_t s) {
-    const SpkvPrefill pf = prefill_params(v, n_max, stage, nullptr, bias, shp);
+    SpkvPrefill pf = prefill_params(v, n_max, stage, nullptr, bias, shp);
     const float sl = sm_scale * 1.4426950408889634f;
+    pf.bias_unit = 1.0f / sl;
     const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
     const unsigned grid = prefill_grid(v, pf);
     if (v.D == 128) {
