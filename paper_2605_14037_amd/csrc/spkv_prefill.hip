@@ -550,6 +550,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int kBufs = 4;
     __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kStepElems];
     __shared__ __attribute__((aligned(16))) float s_bias[SOFT ? kBufs : 1][SOFT ? NW : 1][SOFT ? 64 : 4];
+    __shared__ __attribute__((aligned(16))) float s_zero[32];
+    if (SOFT && threadIdx.x < 32) s_zero[threadIdx.x] = 0.f;      // (the barrier before the loop)
     int pair, qblk, kr;      // (sequence, KV head), span, tile range of the span
     if (pf.pin_xcd) {        // see spkv_prefill_attend
         const int local = blockIdx.x >> 3, lp = local / (pf.nblk * pf.ks);
@@ -630,17 +632,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // tile t = 1 (the second quarter) are stored with their keys m at m ^ 8, so that the rows of
     // one operand read -- keys 0-7 of both tiles -- do not share banks.
     const int quarter = wv & 3;
-    const int my_off = (quarter * kRowsPerWave * 64 + (quarter == 1 ? lane ^ 8 : lane)) * 8;
+    const unsigned my_off = (quarter * kRowsPerWave * 64 + (quarter == 1 ? lane ^ 8 : lane)) * 16;      // bytes
     const unsigned lds_rows = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&s_tile[0][0] +
                               (unsigned)wv * (kRowsPerWave * 1024);
     const unsigned lds_bias = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)&s_bias[0][0][0] +
                               (unsigned)wv * 256;
     constexpr int kCopies = kRowsPerWave + (SOFT ? 1 : 0);
     auto stage_step = [&](int x, int buf) {                 // half-pages x, x + 1
-        const uint16_t* p = base_of(x + (wv >> 2)) + my_off;
-#pragma unroll
-        for (int r = 0; r < kRowsPerWave; ++r)
-            load_row_to_lds(p + r * 512, lds_rows + (unsigned)buf * (kStepElems * 2) + r * 1024);
+        load_rows_to_lds<kRowsPerWave>(base_of(x + (wv >> 2)), my_off,
+                                       lds_rows + (unsigned)buf * (kStepElems * 2));
         if (SOFT) {
             const int hp = min(sB0 + min(x + (lane >> 5), last) - nA, pf.shp - 1);
             load_word_to_lds(pf.bias + ((size_t)pair * pf.shp + hp) * kHalfTokens + (lane & 31),
@@ -659,11 +659,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int krow = ((((col >> 3) & 1) * (D / 8) + half) * 16 +
                       ((8 * (col >> 4) + 4 * ((col >> 2) & 1) + (col & 3)) ^ (8 * ((col >> 3) & 1)))) * 8;
     const int vrow = kHalfTokens * D + (((col >> 4) * 4 + half) * 16 + (col & 15)) * 8;
+    // K operands and (soft gating) biases of the half-page after the current one
     bf16x8 kf[NS];
-    auto load_k = [&](const uint16_t* hp) {
+    f32x16 cb;
+    auto load_k_hi = [&](const uint16_t* hp) {
 #pragma unroll
-        for (int sl = 0; sl < NS; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + krow + sl * 256);
+        for (int sl = NS / 2; sl < NS; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + krow + sl * 256);
     };
+    auto load_k_lo = [&](const uint16_t* hp, const float* bias) {
+#pragma unroll
+        for (int sl = 0; sl < NS / 2; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + krow + sl * 256);
+        if (SOFT) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 t = *reinterpret_cast<const float4*>(bias + (g >> 1) * 16 + half * 8 + (g & 1) * 4);
+                cb[4 * g] = t.x;
+                cb[4 * g + 1] = t.y;
+                cb[4 * g + 2] = t.z;
+                cb[4 * g + 3] = t.w;
+            }
+        }
+    };
+    // Does any token of the wave see a key of the half-page?  The values of the others are not
+    // touched at all (a weight of zero would still turn an infinity among them into a NaN).
     auto mine = [&](int x) -> bool {
         if (x >= x_end) return false;
         if (x < nA) return x < nA_wave;
@@ -673,60 +691,55 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // soft gating: every row of the half-page lies outside every window of the wave
     auto all_biased = [&](int x) -> bool { return (sB0 + x - nA) * kHalfTokens + kHalfTokens - 1 <= i0; };
     // scores of a half-page from kf; with soft gating started at the bias (in units of a score)
-    auto scores = [&](f32x16& s, int x, const float* bias) {
-        f32x16 c;
+    auto scores = [&](f32x16& s) {
+        if (SOFT) {
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qb[0], cb, 0, 0, 0);
+        } else {
+            f32x16 zero;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) c[e] = 0.f;
-        if (SOFT && all_biased(x)) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 t = *reinterpret_cast<const float4*>(bias + (g >> 1) * 16 + half * 8 + (g & 1) * 4);
-                c[4 * g] = t.x; c[4 * g + 1] = t.y; c[4 * g + 2] = t.z; c[4 * g + 3] = t.w;
-            }
+            for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qb[0], zero, 0, 0, 0);
         }
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qb[0], c, 0, 0, 0);
 #pragma unroll
         for (int sl = 1; sl < NS; ++sl) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qb[sl], s, 0, 0, 0);
     };
+    // Excluded keys to -inf: past the list prefix of the column's token, outside its window, past
+    // this workgroup's range.  Soft gating: the bias of the rows that only some tokens have outside
+    // their windows.
     auto mask = [&](f32x16& s, int x, const float* bias) {
-        if (x < nA) {
-            if (x < fullA) return;
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const unsigned ok = bit_range8(0, cnt - (x * kHalfTokens + 16 * g + 8 * half) - 1);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) s[8 * g + e] = ((ok >> e) & 1u) ? s[8 * g + e] : SPKV_NEG_INF;
-            }
-            return;
-        }
         const int u = (sB0 + x - nA) * kHalfTokens;
-        if (SOFT && u >= u_min && all_biased(x)) return;
+        const bool some_biased = SOFT && !all_biased(x);
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-            const int u0 = u + 16 * g + 8 * half;
-            const unsigned ok = tok >= 0 ? bit_range8((SOFT ? u_min : max(tok + 1, u_min)) - u0, tok + v.w - u0) : 0u;
-            if (SOFT && !all_biased(x)) {
+            const int k0 = 16 * g + 8 * half, u0 = u + k0;
+            unsigned ok = 0u;
+            if (x >= x_end) ok = 0u;
+            else if (x < nA) ok = bit_range8(0, cnt - (x * kHalfTokens + k0) - 1);
+            else if (tok >= 0) ok = bit_range8((SOFT ? u_min : max(tok + 1, u_min)) - u0, tok + v.w - u0);
+            if (some_biased) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) s[8 * g + e] += u0 + e <= tok ? bias[16 * g + 8 * half + e] : 0.f;
+                for (int e = 0; e < 8; ++e) s[8 * g + e] += u0 + e <= tok ? bias[k0 + e] : 0.f;
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) s[8 * g + e] = ((ok >> e) & 1u) ? s[8 * g + e] : SPKV_NEG_INF;
         }
     };
-    f32x8 p[2];
-    float psum;
+    // weights against the column reference as it stands: bf16 operands of P V and their sum;
+    // true (wave-uniform) if a reference is too low or not set yet
+    bf16x8 pb[2];
+    float psum, neg_ref = valid ? 0.f : -m, limit = valid ? -1.f : kWeightSumLimit;
     auto weights = [&](const f32x16& s) -> bool {
-        const bool unset = m == SPKV_NEG_INF;
-        const float neg_ref = unset ? 0.f : -m;
-        float s4[4] = {0.f, 0.f, 0.f, 0.f};
+        f32x8 p[2];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], scale_log2e, neg_ref));
-            p[e >> 3][e & 7] = w;
-            s4[e & 3] += w;
-        }
+        for (int e = 0; e < 16; ++e)
+            p[e >> 3][e & 7] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], scale_log2e, neg_ref));
+        float s4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s4[e] = (p[0][e] + p[0][4 + e]) + (p[1][e] + p[1][4 + e]);
         psum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-        return __ballot(unset || !(psum <= kWeightSumLimit)) != 0ull;
+        pb[0] = __builtin_convertvector(p[0], bf16x8);
+        pb[1] = __builtin_convertvector(p[1], bf16x8);
+        return __builtin_amdgcn_ballot_w64(!(psum <= limit)) != 0ull;
     };
     auto rescale = [&](const f32x16& s) {
         float cm = s[0];
@@ -735,54 +748,56 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         cm *= scale_log2e;
         cm = fmaxf(cm, __shfl_xor(cm, 32));
         const float m_new = fmaxf(m, cm);
-        const float m_ref = (m_new == SPKV_NEG_INF) ? 0.f : m_new;
+        const bool unset = m_new == SPKV_NEG_INF;      // every key so far excluded
+        const float m_ref = unset ? 0.f : m_new;
         const float alpha = __builtin_amdgcn_exp2f(m - m_ref);
         l *= alpha;
 #pragma unroll
         for (int db = 0; db < NB; ++db) acc[db] *= alpha;
         m = m_new;
+        neg_ref = -m_ref;
+        limit = unset ? -1.f : kWeightSumLimit;
         (void)weights(s);
     };
-    // One half-page x: its scores are in sc (if `have`); the scores of x + 1 go to sn.
-    bool have = false;
+    bf16x8 va[2][NB];
+    auto load_v = [&](const uint16_t* hp, int g) {
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+            va[g][db] = *reinterpret_cast<const bf16x8*>(hp + vrow + db * 1024 + g * 256);
+    };
+    auto accumulate = [&](int g) {
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+            acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[g][db], pb[g], acc[db], 0, 0, 0);
+    };
+    // half-pages fast_begin <= x < fast_end need no mask
+    int fast_begin = 0, fast_end = min(x_end, fullA);
+    if (SOFT) {
+        fast_begin = (u_min + kHalfTokens - 1) / kHalfTokens - sB0;
+        fast_end = active ? min(x_end, (i0 + 1) / kHalfTokens - sB0) : 0;
+    }
+    // One half-page x at hp: its scores are in sc, those of the next one (hp1) go to sn; the first
+    // half of the K operands of hp1 is in kf, that of hp2 will be.
     auto unit = [&](f32x16& sc, f32x16& sn, int x, const uint16_t* hp, const float* bias,
-                    const uint16_t* hp2, const float* bias1) {
-        const bool nm = mine(x + 1);
-        if (have) {
-            mask(sc, x, bias);
-            bool low;
-            bf16x8 va[2][NB];
-            if (nm) {
-                scores(sn, x + 1, bias1);
-#pragma unroll
-                for (int g = 0; g < 2; ++g)
-#pragma unroll
-                    for (int db = 0; db < NB; ++db)
-                        va[g][db] = *reinterpret_cast<const bf16x8*>(hp + vrow + db * 1024 + g * 256);
-                low = weights(sc);
-            } else {
-#pragma unroll
-                for (int g = 0; g < 2; ++g)
-#pragma unroll
-                    for (int db = 0; db < NB; ++db)
-                        va[g][db] = *reinterpret_cast<const bf16x8*>(hp + vrow + db * 1024 + g * 256);
-                low = weights(sc);
-            }
-            if (low) rescale(sc);
-            load_k(hp2);
+                    const uint16_t* hp1, const uint16_t* hp2, const float* bias2) {
+        const bool edge = x < fast_begin || x >= fast_end, seen = !edge || mine(x);
+        if (edge) mask(sc, x, bias);
+        load_k_hi(hp1);
+        load_v(hp, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        scores(sn);
+        const bool low = weights(sc);
+        __builtin_amdgcn_sched_barrier(0);
+        if (__builtin_expect(low && seen, 0)) rescale(sc);
+        load_v(hp, 1);
+        load_k_lo(hp2, SOFT && !all_biased(x + 2) ? s_zero : bias2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (seen) {
             l += psum;
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                const bf16x8 pb = __builtin_convertvector(p[g], bf16x8);
-#pragma unroll
-                for (int db = 0; db < NB; ++db)
-                    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[g][db], pb, acc[db], 0, 0, 0);
-            }
-        } else {
-            if (nm) scores(sn, x + 1, bias1);
-            load_k(hp2);
+            accumulate(0);
+            accumulate(1);
         }
-        have = nm;
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): queries and counts
@@ -792,20 +807,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     wait_loads_but<kCopies>();                   // the first two steps have landed
     __syncthreads();
     f32x16 s0, s1;
-    load_k(s_tile[0]);
-    have = mine(x_begin);
-    if (have) scores(s0, x_begin, &s_bias[0][SOFT ? wv : 0][0]);
-    load_k(s_tile[0] + kHalfElems);
+    const int wb = SOFT ? wv : 0, b32 = SOFT ? 32 : 0;
+    load_k_lo(s_tile[0], SOFT && !all_biased(x_begin) ? s_zero : &s_bias[0][wb][0]);
+    load_k_hi(s_tile[0]);
+    scores(s0);
+    load_k_lo(s_tile[0] + kHalfElems, SOFT && !all_biased(x_begin + 1) ? s_zero : &s_bias[0][wb][b32]);
     int buf = 0;
     for (int x = x_begin; x < x_end; x += 2) {
         const int nb = (buf + 1) & 3;
         stage_step(x + 6, (buf + 3) & 3);
         const uint16_t* t0 = s_tile[buf];
         const uint16_t* t1 = s_tile[nb];
-        const float* b0 = &s_bias[SOFT ? buf : 0][SOFT ? wv : 0][0];
-        const float* b1 = &s_bias[SOFT ? nb : 0][SOFT ? wv : 0][0];
-        unit(s0, s1, x, t0, b0, t1, b0 + (SOFT ? 32 : 0));
-        unit(s1, s0, x + 1, t0 + kHalfElems, b0 + (SOFT ? 32 : 0), t1 + kHalfElems, b1);
+        const float* b0 = &s_bias[SOFT ? buf : 0][wb][0];
+        const float* b1 = &s_bias[SOFT ? nb : 0][wb][0];
+        unit(s0, s1, x, t0, b0, t0 + kHalfElems, t1, b1);
+        unit(s1, s0, x + 1, t0 + kHalfElems, b0 + b32, t1, t1 + kHalfElems, b1 + b32);
         wait_loads_but<kCopies>();               // all but the newest: the step after next has landed
         __syncthreads();
         buf = nb;
