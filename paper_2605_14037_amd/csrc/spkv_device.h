@@ -136,29 +136,12 @@ __device__ __forceinline__ void load_word_to_lds(const float* src, unsigned lds_
                  : "m0");
 }
 
-// N consecutive 1 KB rows at base (wave-uniform) + voff bytes (per lane) into consecutive rows of
-// LDS; the instruction's offset counts on both sides.
-template <int N>
-__device__ __forceinline__ void load_rows_to_lds(const uint16_t* base, unsigned voff, unsigned lds_row) {
-    static_assert(N == 1 || N == 2 || N == 4, "rows");
-    if (N == 4)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
-                     "global_load_lds_dwordx4 %0, %1 offset:1024\n\t"
-                     "global_load_lds_dwordx4 %0, %1 offset:2048\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072"
-                     :
-                     : "v"(voff), "s"(base), "s"(lds_row)
-                     : "m0");
-    else if (N == 2)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
-                     "global_load_lds_dwordx4 %0, %1 offset:1024"
-                     :
-                     : "v"(voff), "s"(base), "s"(lds_row)
-                     : "m0");
-    else
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     :
-                     : "v"(voff), "s"(base), "s"(lds_row)
-                     : "m0");
+// The same with a wave-uniform base and a byte offset per lane.
+__device__ __forceinline__ void load_row_to_lds(const char* base, unsigned voff, unsigned lds_row) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(voff), "s"(base), "s"(lds_row)
+                 : "m0");
 }
 
 // Waits until at most N of this wave's vector memory loads are still in flight (they

@@ -40,7 +40,8 @@ struct SpkvPrefill {
 // without a position (before the sequence start, past the chunk) are zero, so that a
 // masked key never meets a non-finite V element.  Runs BEFORE the append (reads the ring
 // and the token count as they were).
-// With pf.bias set (soft gating) it also stores log2 u = log2 sigmoid(f) of every new row.
+// With pf.bias set (soft gating) it also stores log2 u = log2 sigmoid(f) of every new row,
+// divided by the score scale.
 template <int D>
 __global__ __launch_bounds__(256) void spkv_prefill_stage(SpkvView v, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ vv,
@@ -239,19 +240,15 @@ __device__ __forceinline__ void rescale_columns(const float (&x)[NQ][8], float s
     }
 }
 
-// One workgroup of NW (8, for short chunks 4 or 2) waves per span of NW * tb consecutive tokens of one
-// (sequence, KV head); wave wv owns tokens i0 = span start + wv * tb .. + tb - 1 as its
+// Short chunks (long ones: spkv_prefill_attend32 below).  One workgroup of NW (4 or 2) waves per
+// span of NW * tb consecutive tokens of one (sequence, KV head); wave wv owns tokens i0 = span start + wv * tb .. + tb - 1 as its
 // 16 NQ MFMA columns (tb = 16 NQ / G tokens times G heads; NQ = 2 groups of 16, one for the
 // shortest chunks).  The waves walk the
 // same half-pages, so each 16 KB tile is fetched from memory once per workgroup into a ring
 // of LDS buffers (every wave copies its share of a tile straight from memory into LDS, two
 // tiles ahead of the one all waves consume) and each wave reads its MFMA A operands from LDS
-// with conflict-free 16-byte reads; 256 query columns share one tile fetch.  With 32 columns a wave needs about 200 VGPRs and
-// no accumulation registers, so two waves fit a SIMD and one wave's vector work (weights)
-// can run beside the other's MFMAs.  (Measured alternatives: four waves of 64 columns, one
-// per SIMD, 15 % slower -- every latency is exposed; the same with the tile loop software-
-// pipelined by hand, slower still; issue priority for one wave of each SIMD, 27 % slower.)
-template <int D, bool SOFT, int NW, int NQ>
+// with conflict-free 16-byte reads.
+template <int D, int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_prefill_attend(SpkvView v, const uint16_t* __restrict__ q,
                                                            uint16_t* __restrict__ out,
                                                            float* __restrict__ lse, float scale_log2e,
@@ -298,11 +295,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int tbv = max(0, min(pf.tb, n_tok - i0)), i_last = i0 + tbv - 1, cols = tbv * v.G;
     const bool active = tbv > 0;
     // the cache is in the state after the append
-    const int T0 = SOFT ? 0 : v.t_pair[pair] - n_tok, L = SOFT ? 0 : v.kept_len[pair];
+    const int T0 = v.t_pair[pair] - n_tok, L = v.kept_len[pair];
     const int u_min = max(0, v.w - T0);     // first staging row that holds a position
 
     auto prefix_of = [&](int i) -> int {   // long-term entries at least w behind token i
-        if (SOFT || T0 + i - v.w < 0) return 0;
+        if (T0 + i - v.w < 0) return 0;
         return min(max(pf.prefix[((size_t)row0 + i) * v.Hkv + h], 0), L);
     };
 
@@ -330,9 +327,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int fullA = active ? prefix_of(i0) >> 5 : 0;
     // staging half-pages: rows (span0, span_last + w] that hold a position; this wave's
     // windows cover rows [lo_w, hi_w]
-    const int sB0 = (SOFT ? u_min : max(span0 + 1, u_min)) >> 5;
+    const int sB0 = max(span0 + 1, u_min) >> 5;
     const int nB = ((span_last + v.w) >> 5) - sB0 + 1;
-    const int lo_w = SOFT ? u_min : max(i0 + 1, u_min), hi_w = i_last + v.w;
+    const int lo_w = max(i0 + 1, u_min), hi_w = i_last + v.w;
     const int n_hp = nA + nB, last = n_hp - 1;
     // split-K: this workgroup takes tiles [x_begin, x_end) of the span's n_hp
     const int x_begin = (int)(((long long)kr * n_hp) / pf.ks);
@@ -379,33 +376,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int my_off = (wv * kRowsPerWave * 64 + lane) * 8;     // this lane's part of a tile
     const unsigned lds_rows = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&s_tile[0][0] +
                               (unsigned)wv * (kRowsPerWave * 1024);
-    // Soft gating: the 32 biases log2 u of a tile's rows travel the same way, every wave
-    // fetching a copy of its own (lanes 32-63 repeat lanes 0-31), so that the tile loop
-    // issues no load whose wait would also wait for the copies in flight.
-    __shared__ __attribute__((aligned(16))) float s_bias[SOFT ? kBufs : 1][SOFT ? NW : 1][SOFT ? 64 : 4];
-    const unsigned lds_bias = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)&s_bias[0][0][0] +
-                              (unsigned)wv * 256;
-    constexpr int kCopiesPerTile = kRowsPerWave + (SOFT ? 1 : 0);   // loads a wave issues per tile
-    auto stage_tile = [&](const uint16_t* base, int xt, int buf) {    // tile xt (for the biases)
+    auto stage_tile = [&](const uint16_t* base, int buf) {
         const uint16_t* p = base + my_off;
 #pragma unroll
         for (int r = 0; r < kRowsPerWave; ++r)
             load_row_to_lds(p + r * 512, lds_rows + (unsigned)buf * (kHalfElems * 2) + r * 1024);
-        if (SOFT) {
-            const int hp = min(sB0 + min(xt, last) - nA, pf.shp - 1);
-            load_word_to_lds(pf.bias + ((size_t)pair * pf.shp + hp) * kHalfTokens + (lane & 31),
-                             lds_bias + (unsigned)buf * (NW * 256));
-        }
     };
     // Everything loaded so far (queries, counts) is waited for here, once: left pending, the
     // first use inside the tile loop would carry a wait for all loads in flight -- on every
     // tile, tile copies included.
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
-    stage_tile(base_of(x_begin), x_begin, 0);
+    stage_tile(base_of(x_begin), 0);
 #pragma unroll
-    for (int a = 1; a < kAhead; ++a) stage_tile(base_of(x_begin + a), x_begin + a, a);
+    for (int a = 1; a < kAhead; ++a) stage_tile(base_of(x_begin + a), a);
     const uint16_t* p_next = base_of(x_begin + kAhead);
-    wait_loads_but<(kAhead - 1) * kCopiesPerTile>();        // tile x_begin has landed
+    wait_loads_but<(kAhead - 1) * kRowsPerWave>();        // tile x_begin has landed
     __syncthreads();
 
     // Tile loop.  The inner loop never touches the accumulators except by MFMA; when the
@@ -418,11 +403,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     bool resume = false, pending = false;
     float xs[NQ][8];
     while (x < x_end) {
-        if (pending) rescale_columns<D, NQ>(xs, SOFT ? 1.0f : scale_log2e, acc, m, l);
+        if (pending) rescale_columns<D, NQ>(xs, scale_log2e, acc, m, l);
         for (; x < x_end; ++x) {
             if (!resume) {
                 // the tile after next (past the last one: the last tile again, never used)
-                stage_tile(p_next, x + kAhead, buf >= 1 ? buf - 1 : kBufs - 1);
+                stage_tile(p_next, buf >= 1 ? buf - 1 : kBufs - 1);
                 p_next = base_of(x + kAhead + 1);
             }
             resume = false;
@@ -447,44 +432,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                         for (int c = 0; c < NQ; ++c) kill[c] = bit_range8(0, cnt[c] - k0 - 1) ^ 0xffu;
                     }
                 } else {
-                    // soft gating: a tile of rows that all hold a position and all lie at or
-                    // before every token of the wave needs no mask
-                    if (SOFT && u_tile >= u_min && u_tile + kHalfTokens - 1 <= i0 + v.w) any = false;
                     const int u0 = u_tile + kc * 8;
-                    // window of token i: rows i < u <= i + w that hold a position (soft
-                    // gating: every earlier row as well)
+                    // window of token i: rows i < u <= i + w that hold a position
 #pragma unroll
                     for (int c = 0; c < NQ; ++c)
-                        kill[c] = (tok[c] >= 0 ? bit_range8((SOFT ? u_min : max(tok[c] + 1, u_min)) - u0,
+                        kill[c] = (tok[c] >= 0 ? bit_range8(max(tok[c] + 1, u_min) - u0,
                                                             tok[c] + v.w - u0)
                                                : 0u) ^ 0xffu;
                 }
                 tile_scores<D, NQ>(tile, lane, qb, kill, any, xs);
-                if (SOFT) {
-                    // scores to the log2 domain plus the gate bias log2 u of every key outside
-                    // the window of its query (row u <= i); masked scores stay -inf
-                    const int u0 = u_tile + kc * 8;
-                    const float4* bp = reinterpret_cast<const float4*>(&s_bias[SOFT ? buf : 0][SOFT ? wv : 0][SOFT ? kc * 8 : 0]);
-                    const float4 b0 = bp[0], b1 = bp[1];
-                    const float bias[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                    if (u_tile + kHalfTokens - 1 <= i0) {       // outside every window of the wave
-#pragma unroll
-                        for (int c = 0; c < NQ; ++c)
-#pragma unroll
-                            for (int e = 0; e < 8; ++e)
-                                xs[c][e] = __builtin_fmaf(xs[c][e], scale_log2e, bias[e]);
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < NQ; ++c)
-#pragma unroll
-                            for (int e = 0; e < 8; ++e)
-                                xs[c][e] = __builtin_fmaf(xs[c][e], scale_log2e,
-                                                          u0 + e <= tok[c] ? bias[e] : 0.f);
-                    }
-                }
                 f32x8 pw[NQ];
                 float psum[NQ];
-                if (tile_weights<NQ>(xs, SOFT ? 1.0f : scale_log2e, m, pw, psum) && !pending) {
+                if (tile_weights<NQ>(xs, scale_log2e, m, pw, psum) && !pending) {
                     pending = true;
                     resume = true;
                     break;
@@ -492,7 +451,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 pending = false;
                 tile_accumulate<D, NQ>(tile, lane, pw, psum, acc, l);
             }
-            wait_loads_but<(kAhead - 1) * kCopiesPerTile>();    // all but the newest copies: tile x + 1 has landed
+            wait_loads_but<(kAhead - 1) * kRowsPerWave>();    // all but the newest copies: tile x + 1 has landed
             __syncthreads();
             buf = buf == kBufs - 1 ? 0 : buf + 1;
         }
@@ -537,8 +496,24 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 }
 
-// The same for long chunks and for the soft-gated forward: eight waves, each with 32 columns as
-// ONE group of MFMA 32x32x16, software-pipelined over half-pages.
+// Long chunks and the soft-gated forward: one workgroup of eight waves per span of 8 tb tokens,
+// each wave with 32 columns (token, head) as ONE group of MFMA 32x32x16, so that 256 query columns
+// share one tile fetch.  Half the matrix instructions of two groups of 16x16x32 for the same
+// flops: what a matrix instruction holds back of a SIMD's vector issue counts half as often
+// (probe: four 32x32x16 with eight fma each, two waves per SIMD, 154 ns; eight 16x16x32 with four
+// each 204 ns; the products alone 115 ns either way).
+// Software pipeline over half-pages x (32 keys): the products K Q^T of x + 1 stand beside the
+// weights of x, then V P of x; LDS holds four steps of two half-pages, copied two steps ahead,
+// and every operand read goes out half a unit or more before its use, also across the one
+// barrier per step.  One code path for all half-pages: masks are a branch around the scores
+// alone, and a wave that sees no key of a half-page skips the product with V.
+// Soft gating: the bias log2 u of a key, in units of a score, is what its products start from.
+// 4 sequences of 16 384 tokens, 32 query / 8 KV heads of 128 (8.5 TFLOP): 9.33 -> 7.92 ms =
+// 1.09 PFLOP/s (two groups of 16 columns, reads and products of a tile one after the other,
+// before; a large matrix product reaches 1.35 here); prompts of 3 to 19.5 thousand tokens, keep rates 0.1 to
+// 0.33, 4 sequences: 2.27 -> 1.91 ms.  What is left: the matrix units are busy 53 % of the
+// cycles, the vector units beside them, 27 % of the wave time is the barrier; the clock falls
+// as the load rises (2.0 GHz).
 template <int D, bool SOFT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_prefill_attend32(
     SpkvView v, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
@@ -578,16 +553,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int i0 = span0 + wv * pf.tb;
     const int tbv = max(0, min(pf.tb, n_tok - i0)), i_last = i0 + tbv - 1, cols = tbv * v.G;
     const bool active = tbv > 0;
-    const int T0 = SOFT ? 0 : v.t_pair[pair] - n_tok, L = SOFT ? 0 : v.kept_len[pair];
-    const int u_min = max(0, v.w - T0);     // first staging row that holds a position
-
-    auto prefix_of = [&](int i) -> int {   // long-term entries at least w behind token i
-        if (SOFT || T0 + i - v.w < 0) return 0;
-        return min(max(pf.prefix[((size_t)row0 + i) * v.Hkv + h], 0), L);
-    };
     const bool valid = col < cols;
     const int tok = valid ? i0 + col / v.G : -1;
-    const int cnt = valid ? prefix_of(tok) : 0;
+    // Counters, prefix counts and the first page ids are fetched together, before any of them is
+    // looked at (prefix counts of tokens whose window starts at 0 are never written: any value).
+    const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
+    int page_lane0 = 0, my_page = 0;        // logical page held by lane 0; this lane's page id
+    int T0 = 0, L = 0, p_span = 0, p_first = 0, p_last = 0, p_tok = 0;
+    if (!SOFT) {
+        const int32_t* pp = pf.prefix + (size_t)row0 * v.Hkv + h;
+        my_page = pt[min(lane, v.pt_cap - 1)];
+        T0 = v.t_pair[pair] - n_tok;
+        L = v.kept_len[pair];
+        p_span = pp[(size_t)span_last * v.Hkv];
+        p_first = pp[(size_t)min(i0, n_tok - 1) * v.Hkv];
+        p_last = pp[(size_t)min(max(i_last, i0), n_tok - 1) * v.Hkv];
+        p_tok = pp[(size_t)(valid ? tok : span0) * v.Hkv];
+    }
+    const int u_min = max(0, v.w - T0);     // first staging row that holds a position
+    // long-term entries at least w behind token i
+    auto prefix_of = [&](int i, int p) -> int { return T0 + i - v.w < 0 ? 0 : min(max(p, 0), L); };
+    const int cnt = valid ? prefix_of(tok, p_tok) : 0;
     bf16x8 qb[NS];
     {
         const uint16_t* qrow = q + ((size_t)(row0 + (valid ? tok : i0)) * v.Hq + (size_t)h * v.G + (col - (col / v.G) * v.G)) * D + half * 8;
@@ -598,9 +584,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             qb[sl] = __builtin_bit_cast(bf16x8, raw);
         }
     }
-    const int nA = (prefix_of(span_last) + kHalfTokens - 1) >> 5;
-    const int nA_wave = active ? (prefix_of(i_last) + kHalfTokens - 1) >> 5 : 0;
-    const int fullA = active ? prefix_of(i0) >> 5 : 0;
+    const int nA = (prefix_of(span_last, p_span) + kHalfTokens - 1) >> 5;
+    const int nA_wave = active ? (prefix_of(i_last, p_last) + kHalfTokens - 1) >> 5 : 0;
+    const int fullA = active ? prefix_of(i0, p_first) >> 5 : 0;
     const int sB0 = (SOFT ? u_min : max(span0 + 1, u_min)) >> 5;
     const int nB = ((span_last + v.w) >> 5) - sB0 + 1;
     const int lo_w = SOFT ? u_min : max(i0 + 1, u_min), hi_w = i_last + v.w;
@@ -608,9 +594,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int x_begin = (int)(((long long)kr * n_hp) / pf.ks);
     const int x_end = (int)(((long long)(kr + 1) * n_hp) / pf.ks);
 
-    const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
     const uint16_t* stage = pf.stage + (size_t)pair * pf.shp * (size_t)kHalfElems;
-    int page_lane0 = -64, my_page = 0;
     auto page_of = [&](int lp) -> int {
         if (lp >= page_lane0 + 64) {
             page_lane0 = lp;
@@ -628,19 +612,28 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         return stage + (size_t)min(sB0 + x - nA, pf.shp - 1) * kHalfElems;
     };
 
-    // Copies of a step: waves 0-3 the first half-page, 4-7 the second, a quarter each.  K rows of
-    // tile t = 1 (the second quarter) are stored with their keys m at m ^ 8, so that the rows of
-    // one operand read -- keys 0-7 of both tiles -- do not share banks.
+    // Copies of a step: waves 0-3 the first half-page, 4-7 the second, a quarter each.  Rows land
+    // in LDS in operand order, so that every operand read is 1 KB in lane order: K row sl holds,
+    // for lane (half, r), 16 bytes (d = 16 sl + 8 half ..) of key 16 (r >> 4) + 8 ((r >> 2) & 1) +
+    // 4 ((r >> 3) & 1) + (r & 3) -- the score of row r of an MFMA then comes out in the register
+    // and lane in which the product with V wants the weight of that key; V row (g, db) holds
+    // keys 16 g + 8 half .. + 7 of d = 32 db + r.
     const int quarter = wv & 3;
-    const unsigned my_off = (quarter * kRowsPerWave * 64 + (quarter == 1 ? lane ^ 8 : lane)) * 16;      // bytes
+    const unsigned k_lane = ((((col >> 3) & 1) * (D / 8) + half) * 16 + 8 * (col >> 4) + 4 * ((col >> 2) & 1) + (col & 3)) * 16;
+    const unsigned v_lane = (((col >> 4) * 4 + half) * 16 + (col & 15)) * 16;
+    const unsigned my_off = quarter < 2 ? k_lane + quarter * kRowsPerWave * 512
+                                        : v_lane + kHalfTokens * D * 2 + (quarter - 2) * 512;
+    const int row_bytes = quarter < 2 ? 512 : 2048;
     const unsigned lds_rows = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)&s_tile[0][0] +
                               (unsigned)wv * (kRowsPerWave * 1024);
     const unsigned lds_bias = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)&s_bias[0][0][0] +
                               (unsigned)wv * 256;
     constexpr int kCopies = kRowsPerWave + (SOFT ? 1 : 0);
     auto stage_step = [&](int x, int buf) {                 // half-pages x, x + 1
-        load_rows_to_lds<kRowsPerWave>(base_of(x + (wv >> 2)), my_off,
-                                       lds_rows + (unsigned)buf * (kStepElems * 2));
+        const char* p = reinterpret_cast<const char*>(base_of(x + (wv >> 2)));
+#pragma unroll
+        for (int r = 0; r < kRowsPerWave; ++r)
+            load_row_to_lds(p + r * row_bytes, my_off, lds_rows + (unsigned)buf * (kStepElems * 2) + r * 1024);
         if (SOFT) {
             const int hp = min(sB0 + min(x + (lane >> 5), last) - nA, pf.shp - 1);
             load_word_to_lds(pf.bias + ((size_t)pair * pf.shp + hp) * kHalfTokens + (lane & 31),
@@ -655,20 +648,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
     float m = valid ? SPKV_NEG_INF : 0.f, l = 0.f;
 
-    // operand addresses inside a half-page (elements)
-    const int krow = ((((col >> 3) & 1) * (D / 8) + half) * 16 +
-                      ((8 * (col >> 4) + 4 * ((col >> 2) & 1) + (col & 3)) ^ (8 * ((col >> 3) & 1)))) * 8;
-    const int vrow = kHalfTokens * D + (((col >> 4) * 4 + half) * 16 + (col & 15)) * 8;
     // K operands and (soft gating) biases of the half-page after the current one
     bf16x8 kf[NS];
     f32x16 cb;
-    auto load_k_hi = [&](const uint16_t* hp) {
+    auto load_k = [&](const uint16_t* hp, const float* bias) {
 #pragma unroll
-        for (int sl = NS / 2; sl < NS; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + krow + sl * 256);
-    };
-    auto load_k_lo = [&](const uint16_t* hp, const float* bias) {
-#pragma unroll
-        for (int sl = 0; sl < NS / 2; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + krow + sl * 256);
+        for (int sl = 0; sl < NS; ++sl) kf[sl] = *reinterpret_cast<const bf16x8*>(hp + sl * 512 + lane * 8);
         if (SOFT) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -763,7 +748,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto load_v = [&](const uint16_t* hp, int g) {
 #pragma unroll
         for (int db = 0; db < NB; ++db)
-            va[g][db] = *reinterpret_cast<const bf16x8*>(hp + vrow + db * 1024 + g * 256);
+            va[g][db] = *reinterpret_cast<const bf16x8*>(hp + kHalfTokens * D + (g * NB + db) * 512 + lane * 8);
     };
     auto accumulate = [&](int g) {
 #pragma unroll
@@ -776,31 +761,37 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         fast_begin = (u_min + kHalfTokens - 1) / kHalfTokens - sB0;
         fast_end = active ? min(x_end, (i0 + 1) / kHalfTokens - sB0) : 0;
     }
-    // One half-page x at hp: its scores are in sc, those of the next one (hp1) go to sn; the first
-    // half of the K operands of hp1 is in kf, that of hp2 will be.
+    // One half-page x at hp: its scores are in sc and its first V operands in va[0]; the scores of
+    // the next one (hp1) go to sn from the K operands in kf, which are then those of hp2.  Every
+    // LDS read is issued half a unit or more before its use, also across the barrier of a step
+    // (what is read was announced by the barrier before); `more` runs between the products.
     auto unit = [&](f32x16& sc, f32x16& sn, int x, const uint16_t* hp, const float* bias,
-                    const uint16_t* hp1, const uint16_t* hp2, const float* bias2) {
+                    const uint16_t* hp1, const uint16_t* hp2, const float* bias2, auto&& more) {
         const bool edge = x < fast_begin || x >= fast_end, seen = !edge || mine(x);
         if (edge) mask(sc, x, bias);
-        load_k_hi(hp1);
-        load_v(hp, 0);
         __builtin_amdgcn_sched_barrier(0);
         scores(sn);
         const bool low = weights(sc);
         __builtin_amdgcn_sched_barrier(0);
         if (__builtin_expect(low && seen, 0)) rescale(sc);
         load_v(hp, 1);
-        load_k_lo(hp2, SOFT && !all_biased(x + 2) ? s_zero : bias2);
+        load_k(hp2, SOFT && !all_biased(x + 2) ? s_zero : bias2);
         __builtin_amdgcn_sched_barrier(0);
         if (seen) {
             l += psum;
             accumulate(0);
-            accumulate(1);
         }
+        load_v(hp1, 0);
+        more();
+        __builtin_amdgcn_sched_barrier(0);
+        if (seen) accumulate(1);
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): queries and counts
+    // Queries and counts, and the kernel arguments the loop uses (a scalar load still pending at
+    // its head makes the first operand wait of every pass wait for all LDS reads).
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+    asm volatile("" : : "s"(scale_log2e));
     stage_step(x_begin, 0);
     stage_step(x_begin + 2, 1);
     stage_step(x_begin + 4, 2);
@@ -808,20 +799,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();
     f32x16 s0, s1;
     const int wb = SOFT ? wv : 0, b32 = SOFT ? 32 : 0;
-    load_k_lo(s_tile[0], SOFT && !all_biased(x_begin) ? s_zero : &s_bias[0][wb][0]);
-    load_k_hi(s_tile[0]);
+    load_k(s_tile[0], SOFT && !all_biased(x_begin) ? s_zero : &s_bias[0][wb][0]);
     scores(s0);
-    load_k_lo(s_tile[0] + kHalfElems, SOFT && !all_biased(x_begin + 1) ? s_zero : &s_bias[0][wb][b32]);
+    load_k(s_tile[0] + kHalfElems, SOFT && !all_biased(x_begin + 1) ? s_zero : &s_bias[0][wb][b32]);
+    load_v(s_tile[0], 0);
     int buf = 0;
     for (int x = x_begin; x < x_end; x += 2) {
         const int nb = (buf + 1) & 3;
-        stage_step(x + 6, (buf + 3) & 3);
         const uint16_t* t0 = s_tile[buf];
         const uint16_t* t1 = s_tile[nb];
         const float* b0 = &s_bias[SOFT ? buf : 0][wb][0];
         const float* b1 = &s_bias[SOFT ? nb : 0][wb][0];
-        unit(s0, s1, x, t0, b0, t0 + kHalfElems, t1, b1);
-        unit(s1, s0, x + 1, t0 + kHalfElems, b0 + b32, t1, t1 + kHalfElems, b1 + b32);
+        unit(s0, s1, x, t0, b0, t0 + kHalfElems, t1, b1, [&]() { stage_step(x + 6, (buf + 3) & 3); });
+        unit(s1, s0, x + 1, t0 + kHalfElems, b0 + b32, t1, t1 + kHalfElems, b1 + b32, [&]() {});
         wait_loads_but<kCopies>();               // all but the newest: the step after next has landed
         __syncthreads();
         buf = nb;
@@ -945,17 +935,17 @@ size_t spkv_prefill_partial_bytes(int spans, int ks, SpkvPrefillShape sh, int he
 }
 
 // The attention launch of the shape chosen for the call.
-template <int D, bool SOFT>
+template <int D>
 static void launch_attend(const SpkvView& v, const uint16_t* q, uint16_t* out, float* lse, float sl,
                           const SpkvPrefill& pf, const SpkvCu& cu, unsigned grid, hipStream_t s) {
-    if (pf.nq == 2 && pf.nw == 8)
-        spkv_prefill_attend32<D, SOFT><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
+    if (pf.nw == 8)
+        spkv_prefill_attend32<D, false><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     else if (pf.nq == 2)
-        spkv_prefill_attend<D, SOFT, 4, 2><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend<D, 4, 2><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
     else if (pf.nw == 4)
-        spkv_prefill_attend<D, SOFT, 4, 1><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend<D, 4, 1><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
     else
-        spkv_prefill_attend<D, SOFT, 2, 1><<<dim3(grid), dim3(128), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend<D, 2, 1><<<dim3(grid), dim3(128), 0, s>>>(v, q, out, lse, sl, pf, cu);
 }
 
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
@@ -970,13 +960,13 @@ hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint1
     if (v.D == 128) {
         spkv_prefill_stage<128><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
         if ((e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, prefix, s)) != hipSuccess) return e;
-        launch_attend<128, false>(v, q, out, lse, sl, pf, cu, grid, s);
+        launch_attend<128>(v, q, out, lse, sl, pf, cu, grid, s);
         if (ks > 1)
             spkv_prefill_combine<128><<<dim3(v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / 8), dim3(256), 0, s>>>(v, out, lse, pf, cu);
     } else {
         spkv_prefill_stage<64><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
         if ((e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, prefix, s)) != hipSuccess) return e;
-        launch_attend<64, false>(v, q, out, lse, sl, pf, cu, grid, s);
+        launch_attend<64>(v, q, out, lse, sl, pf, cu, grid, s);
         if (ks > 1)
             spkv_prefill_combine<64><<<dim3(v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / 16), dim3(256), 0, s>>>(v, out, lse, pf, cu);
     }
@@ -992,16 +982,17 @@ hipError_t spkv_launch_soft_gated(const SpkvView& v, const uint16_t* k, const ui
                                   float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
                                   float* bias, int shp, hipStream_t s) {
     SpkvPrefill pf = prefill_params(v, n_max, stage, nullptr, bias, shp);
-    const float sl = sm_scale * 1.4426950408889634f;
+    // (below 1e-30 a score no longer shows beside the biases: keeps bias / scale finite)
+    const float sl = std::max(sm_scale * 1.4426950408889634f, 1e-30f);
     pf.bias_unit = 1.0f / sl;
     const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
     const unsigned grid = prefill_grid(v, pf);
     if (v.D == 128) {
         spkv_prefill_stage<128><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
-        launch_attend<128, true>(v, q, out, lse, sl, pf, cu, grid, s);
+        spkv_prefill_attend32<128, true><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     } else {
         spkv_prefill_stage<64><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
-        launch_attend<64, true>(v, q, out, lse, sl, pf, cu, grid, s);
+        spkv_prefill_attend32<64, true><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     }
     return hipGetLastError();
 }

@@ -152,6 +152,28 @@ def test_prefill_calls_with_the_shortest_chunks():
     _run_prefill(wl, [[1, 1, 1], [1, 0, 2], [1, 1, 1], [4, 3, 1], [5, 4, 4], [1, 1, 1]])
 
 
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 8, 2), (64, 6, 2)])
+def test_prefill_tokens_ahead_of_an_infinite_value_are_untouched(D, Hq, Hkv):
+    """A workgroup fetches keys that only some of its waves see.  An infinite value at the end of
+    a chunk must leave every token alone that lies more than a half-page (32 keys) plus a wave's
+    tokens before it: bit for bit what the same call gives without it."""
+    n, tb = 200, 32 // (Hq // Hkv)
+    outs = []
+    for bad in (False, True):
+        wl = small_workload("pinf", 1, Hq, Hkv, D, [700], 0.4, window=64, seed=3)
+        stream = TokenStream(wl, device="cuda")
+        cache = H.make_cache(wl, pool_tokens=8000, extra_context=n + 8)
+        H.prefill(cache, None, stream, wl, 4096)
+        k, v, f, cu = stream.next_tokens([n])
+        q = stream.next_query(rows=n)
+        if bad:
+            v[n - 1] = float("inf")
+        outs.append(cache.prefill_attention(k, v, f, q, cu))
+        cache.close()
+    safe = n - 32 - tb
+    assert torch.equal(outs[0][:safe], outs[1][:safe]) and not torch.isfinite(outs[1][n - 1].float()).any()
+
+
 def test_prefill_rejects_small_workspace_and_leaves_cache_unchanged():
     wl = small_workload("pbad", 1, 8, 2, 64, [0], 0.5, seed=2)
     stream = TokenStream(wl, device="cuda")

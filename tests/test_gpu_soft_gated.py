@@ -75,3 +75,19 @@ def test_soft_gated_rejects_bad_arguments():
     assert e.value.code == -1
     with pytest.raises(spkv.SPKVError):
         spkv.soft_gated_attention(q, k, v, f, cu, window=0)
+
+
+def test_soft_gated_vanishing_scale_leaves_the_biases():
+    """With a score scale far below fp32's resolution of the biases the weights are the gates
+    alone, however small the scale is."""
+    g = torch.Generator(device="cuda").manual_seed(11)
+    n = 700
+    q, k, v = (torch.randn(n, h, 128, generator=g, device="cuda").to(torch.bfloat16) for h in (4, 2, 2))
+    f = torch.randn(n, 2, generator=g, device="cuda")
+    a = spkv.soft_gated_attention(q, k, v, f, [0, n], window=33, sm_scale=1e-20)
+    b = spkv.soft_gated_attention(q, k, v, f, [0, n], window=33, sm_scale=1e-37)
+    i = n - 1                                     # the last token against the gates by hand
+    w = torch.sigmoid(f[:, 0].double())
+    w[i - 32:] = 1.0
+    ref = (w[:, None] * v[:, 0].double()).sum(0) / w.sum()
+    assert (a[i, 0].double() - ref).abs().max() < 2e-3 and (b.float() - a.float()).abs().max() < 2e-3
