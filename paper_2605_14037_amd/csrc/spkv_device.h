@@ -382,26 +382,18 @@ __device__ __forceinline__ void attend_half_page(const bf16x8 (&ka)[2][D / 32],
 }
 
 // Eight V rows held in LDS (s_rows[row][d]) leave as 16-byte units: eight consecutive keys
-// of one head-dim element, rows dk0 .. dk0 + 7 of page (or half-page) dp.  Lanes < D / 2.
+// of one head-dim element, rows dk0 .. dk0 + 7 of page (or half-page) dp.  Lane l takes elements
+// l and 64 + l, so that a store covers runs of 256 bytes (two neighbouring units per lane, half
+// of every 64-byte piece per store, were a third more store requests).
 template <int D>
 __device__ __forceinline__ void store_v_units(uint16_t* dp, int dk0, const uint16_t (*s_rows)[D],
                                               int lane) {
-    if (lane < D / 2) {
-        unsigned dw[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) dw[r] = *reinterpret_cast<const unsigned*>(&s_rows[r][2 * lane]);
-        uint4 lo, hi;
-        lo.x = (dw[0] & 0xffffu) | (dw[1] << 16);
-        lo.y = (dw[2] & 0xffffu) | (dw[3] << 16);
-        lo.z = (dw[4] & 0xffffu) | (dw[5] << 16);
-        lo.w = (dw[6] & 0xffffu) | (dw[7] << 16);
-        hi.x = (dw[0] >> 16) | (dw[1] & 0xffff0000u);
-        hi.y = (dw[2] >> 16) | (dw[3] & 0xffff0000u);
-        hi.z = (dw[4] >> 16) | (dw[5] & 0xffff0000u);
-        hi.w = (dw[6] >> 16) | (dw[7] & 0xffff0000u);
-        uint16_t* vd = dp + spkv_v_off(D, dk0, 2 * lane);   // unit of d = 2 lane; d + 1 follows
-        *reinterpret_cast<uint4*>(vd) = lo;
-        *reinterpret_cast<uint4*>(vd + 8) = hi;
+    for (int d = lane; d < D; d += 64) {
+        unsigned w[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            w[r] = (unsigned)s_rows[2 * r][d] | ((unsigned)s_rows[2 * r + 1][d] << 16);
+        *reinterpret_cast<uint4*>(dp + spkv_v_off(D, dk0, d)) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
-

@@ -51,6 +51,8 @@ struct SpkvCu {
 };
 
 hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s);
+// Zeroes the pool pages handed out since the pool was last all zero.
+hipError_t spkv_launch_clear_pages(const SpkvView& v, hipStream_t s);
 hipError_t spkv_launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // Streaming read of n_runs runs (chunks_per_run chunks of 16 KB each) of a region of
 // total_runs runs by n_workgroups one-wave workgroups; sink: n_workgroups KB.

@@ -24,6 +24,22 @@ hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
+// The pages below the bump counter (which a failed allocation can leave past the pool's end).
+__global__ __launch_bounds__(256) void spkv_clear_pages(SpkvView v) {
+    const size_t n16 = (size_t)min(max(*v.pool_next, 0), v.n_pages) * (spkv_page_elems(v.D) / 8);
+    uint4* p = reinterpret_cast<uint4*>(v.pool);
+    const uint4 z = {0u, 0u, 0u, 0u};
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16;
+         i += (size_t)gridDim.x * blockDim.x)
+        p[i] = z;
+}
+
+hipError_t spkv_launch_clear_pages(const SpkvView& v, hipStream_t s) {
+    const size_t n16 = (size_t)v.n_pages * (spkv_page_elems(v.D) / 8);
+    spkv_clear_pages<<<dim3((unsigned)std::min<size_t>((n16 + 255) / 256, 256 * 32)), dim3(256), 0, s>>>(v);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------- plain copy (reference)
 __global__ __launch_bounds__(256) void spkv_plain_copy(uint4* __restrict__ d,
                                                        const uint4* __restrict__ s, size_t n16) {
@@ -227,7 +243,9 @@ __device__ __forceinline__ int block_excl_scan(int x, int* s_w, int& total) {
 // job for its pair (the per-segment counts from the logits, every wave's popcounts parked in
 // LDS and summed after one barrier), so that the call is two launches instead of three.
 constexpr int kCountSegs = 16;
-template <int D, bool SMALL, bool COUNT>
+//
+// MOVE = false: the kept ring rows are moved by stage 3 (rings of at most kScatterThreads slots).
+template <int D, bool SMALL, bool COUNT, bool MOVE>
 __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int32_t* prefix,
                                                       const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ vv,
@@ -368,6 +386,10 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
             prefix[((size_t)cu.v[b] + i) * v.Hkv + (pair - b * v.Hkv)] = L_old + done + rank + (flag ? 1 : 0);
         }
         __syncthreads();
+        if (!MOVE) {
+            done += tot;
+            continue;
+        }
         const int c = lane & 15;
         // four rows per lane at a time: all their loads go out before the first store
         for (int rb = wave * 4; rb < tot; rb += 64) {
@@ -427,23 +449,16 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
     }
 }
 
-// Stage 3: per (256-token segment, pair).  Thread i owns token j0 + i: gate flag, rank
-// (mbcnt inside the wave + the popcounts of the lower waves + the segment offset from
-// stage 2); the kept tokens' indices are compacted into LDS and their rows moved in groups
-// of eight consecutive destination rows (whole 16-byte V units, transposed through LDS),
-// stragglers row by row; the last min(n, w) tokens of the call are written into the ring.
-// The last min(n, w) tokens of the call go into the ring: workgroup rb of the ring part takes
-// the ring slots [32 rb, 32 rb + 32), a wave eight consecutive slots -- one 16-byte V unit per
-// head-dim element.  Slot s receives the newest position p < T_new with p mod w = s if the call
+// The last min(n, w) tokens of the call go into the ring: a wave takes eight consecutive slots
+// s0 .. s0 + 7 -- one 16-byte V unit per head-dim element.  Slot s receives the newest position p < T_new with p mod w = s if the call
 // brought it (p >= T_new - min(n, w)).  A unit whose eight slots are all written goes out as
 // whole 16-byte units, transposed through LDS; otherwise the written rows go one by one.
 template <int D>
 __device__ __forceinline__ void bulk_ring_rows(const SpkvView& v, const uint16_t* __restrict__ k,
                                                const uint16_t* __restrict__ vv,
                                                const float* __restrict__ f, int pair, int h, int row0,
-                                               int n, int T_old, int rb, uint16_t (*s_rows)[D],
-                                               int lane, int wave) {
-    const int s0 = rb * kHalfTokens + wave * 8;
+                                               int n, int T_old, int s0, uint16_t (*s_rows)[D],
+                                               int lane) {
     if (s0 >= v.w) return;
     const int T_new = T_old + n, m = min(n, v.w), c = lane & 15;
     // token index (row of the call) landing in slot s, or -1
@@ -493,118 +508,160 @@ __device__ __forceinline__ void bulk_ring_rows(const SpkvView& v, const uint16_t
     }
 }
 
+// Stage 3: per (kScatterSegs segments = 512 tokens, pair).  Thread i owns token j0 + i: gate flag,
+// rank (mbcnt inside the wave + the popcounts of the lower waves + the offset from stage 2); the
+// kept tokens' indices are compacted into LDS and their rows moved in groups of eight consecutive
+// destination rows (whole 16-byte V units, transposed through LDS), two groups per wave at a
+// time so that all their loads are in flight together; rows before the first and after the
+// last whole group go one by one, their V elements as 2-byte stores.  The last workgroup of a
+// pair (ring_here: at most a ring slot per thread) moves the kept rows that leave the ring in the
+// same way and then writes the last min(n, w) tokens of the call into the ring; for longer rings
+// workgroups of their own write the slots, eight per wave, and stage 2 has moved the rows.
+// Bound by the requests in flight of a few dependent rounds (logits, rows, stores) more than by
+// bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
+// written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
+// pairs; 46 us now with the leaving ring rows, whose move took 7 of the 18 us of stage 2.
+// 256 tokens per workgroup 52 us, 1024 tokens 49.
+constexpr int kScatterSegs = 2, kScatterThreads = kScatterSegs * kSegTokens;
+
 template <int D>
-__global__ __launch_bounds__(256) void spkv_bulk_scatter(SpkvView v, const uint16_t* __restrict__ k,
-                                                         const uint16_t* __restrict__ vv,
-                                                         const float* __restrict__ f, SpkvCu cu,
-                                                         int32_t* prefix, int segs_all) {
-    const int pair = blockIdx.y, seg = blockIdx.x;
+__global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v, const uint16_t* __restrict__ k,
+                                                                     const uint16_t* __restrict__ vv,
+                                                                     const float* __restrict__ f, SpkvCu cu,
+                                                                     int32_t* prefix, int quads, int ring_here) {
+    constexpr int NW = kScatterThreads / 64;
+    const int pair = blockIdx.y, quad = blockIdx.x;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b];
     const int n = cu.v[b + 1] - row0;
-    const int j0 = seg * kSegTokens;
-    if (n == 0 || (seg < segs_all && j0 >= n)) return;
+    const int j0 = quad * kScatterThreads;
+    if (n == 0 || (quad < quads && j0 >= n)) return;
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_ev = max(0, n - v.w);
+    const int j = j0 + tid;
+    const float fj = (quad < quads && j < n) ? f[((size_t)row0 + j) * v.Hkv + h] : 0.f;
+    const int seg_off = (quad < quads && j0 < n_ev) ? v.seg_count[(size_t)pair * v.n_seg_cap + quad * kScatterSegs] : 0;
     const BulkInfo bi = *reinterpret_cast<const BulkInfo*>(v.bulk_info + (size_t)pair * 8);
     if (bi.ok == 0) return;
-    const int n_ev = max(0, n - v.w);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15;
-    __shared__ int s_cnt[4];
-    __shared__ uint16_t s_list[256];
-    __shared__ __attribute__((aligned(16))) uint16_t s_v[4][8][D];
-    if (seg >= segs_all) {      // the ring part of the grid: independent of the segments
-        bulk_ring_rows<D>(v, k, vv, f, pair, h, row0, n, bi.T_old, seg - segs_all, s_v[wave], lane, wave);
+    __shared__ int s_cnt[2][NW];
+    __shared__ uint16_t s_list[2 * kScatterThreads];
+    __shared__ __attribute__((aligned(16))) uint16_t s_v[NW][8][D];
+    if (quad >= quads && ring_here == 0) {      // the ring part of the grid (ring_here = 0): independent of the segments
+        bulk_ring_rows<D>(v, k, vv, f, pair, h, row0, n, bi.T_old, (quad - quads) * (NW * 8) + wave * 8, s_v[wave], lane);
         return;
     }
-
-    const int j = j0 + tid;
-    const bool on = j < n && gate_passes(v, f[((size_t)row0 + j) * v.Hkv + h], bi.T_old + j);
-    const bool ev = on && j < n_ev;
-    const unsigned long long mask = __ballot(ev);
-    if (lane == 0) s_cnt[wave] = __popcll(mask);
-    __syncthreads();
-    int woff = 0, total = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (i < wave) woff += s_cnt[i];
-        total += s_cnt[i];
+    // rows leaving the ring: positions r0 .. r0 + nr - 1, thread i looks at r0 + i
+    const float* rl = v.ring_logit + (size_t)pair * v.w;
+    const int r0 = max(0, bi.T_old - v.w);
+    const bool ring_wg = quad >= quads;
+    const int nr = ring_wg ? max(0, min(bi.T_old, max(0, bi.T_old + n - v.w)) - r0) : 0;
+    const bool rev = tid < nr && gate_passes(v, rl[(r0 + tid) % v.w], r0 + tid);
+    const bool ev = !ring_wg && j < n_ev && gate_passes(v, fj, bi.T_old + j);
+    const unsigned long long rmask = __ballot(rev), mask = __ballot(ev);
+    if (lane == 0) {
+        s_cnt[0][wave] = __popcll(rmask);
+        s_cnt[1][wave] = __popcll(mask);
     }
-    if (ev) s_list[woff + mbcnt64(mask)] = (uint16_t)tid;
-    if (prefix != nullptr && j < n_ev)       // token j leaves the window of token j + w
+    __syncthreads();
+    int roff = 0, woff = 0, n_ring = 0, n_new = 0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int a0 = s_cnt[0][i], a1 = s_cnt[1][i];
+        if (i < wave) {
+            roff += a0;
+            woff += a1;
+        }
+        n_ring += a0;
+        n_new += a1;
+    }
+    constexpr unsigned kFromRing = 0x8000u;
+    if (rev) s_list[roff + mbcnt64(rmask)] = (uint16_t)(kFromRing | (unsigned)tid);
+    if (ev) s_list[n_ring + woff + mbcnt64(mask)] = (uint16_t)tid;
+    if (prefix != nullptr && !ring_wg && j < n_ev)       // token j leaves the window of token j + w
         prefix[((size_t)row0 + j + v.w) * v.Hkv + h] =
-            bi.new_base + v.seg_count[(size_t)pair * v.n_seg_cap + seg] + woff + mbcnt64(mask) + (ev ? 1 : 0);
+            bi.new_base + seg_off + woff + mbcnt64(mask) + (ev ? 1 : 0);
     __syncthreads();
 
+    const int total = n_ring + n_new;
+    // chunk c of the row of a list entry (nothing for lanes past the row)
+    struct Row {
+        uint4 k, v;
+    };
+    auto load_row = [&](unsigned e) -> Row {
+        Row r = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u)};
+        if (c >= D / 8) return r;
+        if (e & kFromRing) {
+            const int slot = (r0 + (int)(e & 0x7fffu)) % v.w;
+            const uint16_t* sp = ring_page(v, pair, slot >> 6);
+            const uint16_t* vs = sp + spkv_v_off(D, slot & 63, c * 8);
+            r.k = *reinterpret_cast<const uint4*>(sp + spkv_k_off(D, slot & 63, c * 8));
+            r.v.x = (unsigned)vs[0] | ((unsigned)vs[8] << 16);
+            r.v.y = (unsigned)vs[16] | ((unsigned)vs[24] << 16);
+            r.v.z = (unsigned)vs[32] | ((unsigned)vs[40] << 16);
+            r.v.w = (unsigned)vs[48] | ((unsigned)vs[56] << 16);
+        } else {
+            const size_t src = ((size_t)(row0 + j0 + (int)e) * v.Hkv + h) * D + c * 8;
+            r.k = *reinterpret_cast<const uint4*>(k + src);
+            r.v = *reinterpret_cast<const uint4*>(vv + src);
+        }
+        return r;
+    };
+    auto store_meta = [&](unsigned e, int page, int dk) {
+        const bool ring = (e & kFromRing) != 0u;
+        const int i = (int)(e & 0x7fffu);
+        v.pos_pool[(size_t)page * kPageTokens + dk] = ring ? r0 + i : bi.T_old + j0 + i;
+        v.logit_pool[(size_t)page * kPageTokens + dk] =
+            ring ? rl[(r0 + i) % v.w] : f[((size_t)row0 + j0 + i) * v.Hkv + h];
+    };
+    const int lr = lane >> 4;                  // a lane's row of four
+    auto store_group = [&](int e0, int page, int dk0, const Row& a, const Row& b2) {
+        uint16_t* dp = pool_page(v, page);
+        if (c < D / 8) {
+            *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk0 + lr, c * 8)) = a.k;
+            *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk0 + 4 + lr, c * 8)) = b2.k;
+            *reinterpret_cast<uint4*>(&s_v[wave][lr][c * 8]) = a.v;
+            *reinterpret_cast<uint4*>(&s_v[wave][4 + lr][c * 8]) = b2.v;
+        }
+        __builtin_amdgcn_wave_barrier();
+        store_v_units<D>(dp, dk0, s_v[wave], lane);
+        if (lane < 8) store_meta(s_list[e0 + lane], page, dk0 + lane);
+        __builtin_amdgcn_wave_barrier();
+    };
     if (total > 0) {
-        const int g0 = bi.new_base + v.seg_count[(size_t)pair * v.n_seg_cap + seg];
+        const int g0 = ring_wg ? bi.new_base - n_ring : bi.new_base + seg_off;
         const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
         const int gend = g0 + total;
         const int ga = min(gend, (g0 + 7) & ~7);   // destination indices [ga, gb) are whole
         const int gb = max(ga, gend & ~7);         // groups of 8 aligned to 8: whole V units
 
-        // Whole groups, one wave each: K chunks go straight out; the eight V rows meet in
-        // LDS and leave as 16-byte units (eight keys of one head-dim element).
-        for (int G8 = ga + wave * 8; G8 < gb; G8 += 32) {
-            const int page = pt[G8 >> 6];
-            uint16_t* dp = pool_page(v, page);
-            const int dk0 = G8 & 63;
-#pragma unroll
-            for (int pass = 0; pass < 2; ++pass) {
-                const int row = pass * 4 + (lane >> 4);
-                if (c < D / 8) {
-                    const int jj = j0 + s_list[G8 - g0 + row];
-                    const size_t src = ((size_t)(row0 + jj) * v.Hkv + h) * D + c * 8;
-                    const uint4 kk = *reinterpret_cast<const uint4*>(k + src);
-                    const uint4 vl = *reinterpret_cast<const uint4*>(vv + src);
-                    *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk0 + row, c * 8)) = kk;
-                    *reinterpret_cast<uint4*>(&s_v[wave][row][c * 8]) = vl;
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (lane < D / 2) {
-                unsigned dw[8];
-#pragma unroll
-                for (int r = 0; r < 8; ++r)
-                    dw[r] = *reinterpret_cast<const unsigned*>(&s_v[wave][r][2 * lane]);
-                uint4 lo, hi;
-                lo.x = (dw[0] & 0xffffu) | (dw[1] << 16);
-                lo.y = (dw[2] & 0xffffu) | (dw[3] << 16);
-                lo.z = (dw[4] & 0xffffu) | (dw[5] << 16);
-                lo.w = (dw[6] & 0xffffu) | (dw[7] << 16);
-                hi.x = (dw[0] >> 16) | (dw[1] & 0xffff0000u);
-                hi.y = (dw[2] >> 16) | (dw[3] & 0xffff0000u);
-                hi.z = (dw[4] >> 16) | (dw[5] & 0xffff0000u);
-                hi.w = (dw[6] >> 16) | (dw[7] & 0xffff0000u);
-                uint16_t* vd = dp + spkv_v_off(D, dk0, 2 * lane);   // unit of d = 2 lane; d + 1 follows
-                *reinterpret_cast<uint4*>(vd) = lo;
-                *reinterpret_cast<uint4*>(vd + 8) = hi;
-            }
-            if (lane < 8) {
-                const int jj = j0 + s_list[G8 - g0 + lane];
-                v.pos_pool[(size_t)page * kPageTokens + dk0 + lane] = bi.T_old + jj;
-                v.logit_pool[(size_t)page * kPageTokens + dk0 + lane] = f[((size_t)row0 + jj) * v.Hkv + h];
-            }
-            __builtin_amdgcn_wave_barrier();
+        for (int G8 = ga + wave * 8; G8 < gb; G8 += 2 * NW * 8) {
+            const int G2 = G8 + NW * 8;
+            const bool two = G2 < gb;
+            const int e1 = G8 - g0, e2 = two ? G2 - g0 : e1;
+            const int page1 = pt[G8 >> 6], page2 = two ? pt[G2 >> 6] : 0;
+            const Row a0 = load_row(s_list[e1 + lr]), a1 = load_row(s_list[e1 + 4 + lr]);
+            const Row b0 = load_row(s_list[e2 + lr]), b1 = load_row(s_list[e2 + 4 + lr]);
+            store_group(e1, page1, G8 & 63, a0, a1);
+            if (two) store_group(e2, page2, G2 & 63, b0, b1);
         }
-        // The rows before the first and after the last whole group, one row per 16 lanes,
-        // V elements as 2-byte stores.
+        // The rows before the first and after the last whole group, one row per 16 lanes.
         const int n_head = ga - g0, n_tail = gend - gb;
-        for (int rb = wave * 4; rb < n_head + n_tail; rb += 16) {
+        for (int rb = wave * 4; rb < n_head + n_tail; rb += NW * 4) {
             const int x = rb + (lane >> 4);
             if (x < n_head + n_tail && c < D / 8) {
                 const int r = x < n_head ? x : (gb - g0) + (x - n_head);
-                const int jj = j0 + s_list[r];
-                const size_t src = ((size_t)(row0 + jj) * v.Hkv + h) * D + c * 8;
-                const uint4 kk = *reinterpret_cast<const uint4*>(k + src);
-                const uint4 vl = *reinterpret_cast<const uint4*>(vv + src);
-                const int gi = g0 + r;
-                const int page = pt[gi >> 6];
-                store_row_chunk<D>(pool_page(v, page), gi & 63, c, kk, vl);
-                if (c == 0) {
-                    v.pos_pool[(size_t)page * kPageTokens + (gi & 63)] = bi.T_old + jj;
-                    v.logit_pool[(size_t)page * kPageTokens + (gi & 63)] = f[((size_t)row0 + jj) * v.Hkv + h];
-                }
+                const int gi = g0 + r, page = pt[gi >> 6];
+                const Row a = load_row(s_list[r]);
+                store_row_chunk<D>(pool_page(v, page), gi & 63, c, a.k, a.v);
+                if (c == 0) store_meta(s_list[r], page, gi & 63);
             }
         }
+    }
+    if (ring_wg) {            // the rows that leave have been read: the new ones take their slots
+        __syncthreads();
+        for (int s0 = wave * 8; s0 < v.w; s0 += NW * 8)
+            bulk_ring_rows<D>(v, k, vv, f, pair, h, row0, n, bi.T_old, s0, s_v[wave], lane);
     }
 }
 
@@ -612,23 +669,25 @@ hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const u
                                    const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
                                    hipStream_t s) {
     if (n_max <= v.w && n_max <= kSegTokens) {      // short chunks: one launch
-        if (v.D == 128) spkv_bulk_ring<128, true, false><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
-        else spkv_bulk_ring<64, true, false><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
+        if (v.D == 128) spkv_bulk_ring<128, true, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
+        else spkv_bulk_ring<64, true, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
         return hipGetLastError();
     }
     const int segs_all = (n_max + kSegTokens - 1) / kSegTokens;
-    const int ring_blocks = (v.w + kHalfTokens - 1) / kHalfTokens;
-    const dim3 grid3(segs_all + ring_blocks, v.n_pairs);
+    const int quads = (n_max + kScatterThreads - 1) / kScatterThreads;
+    const bool ring_here = v.w <= kScatterThreads;  // a thread per ring slot
+    const dim3 grid3(quads + (ring_here ? 1 : (v.w + kScatterThreads / 8 - 1) / (kScatterThreads / 8)), v.n_pairs);
     const bool fold = segs_all <= kCountSegs;       // the per-pair launch counts for itself
     if (!fold) spkv_bulk_count<<<dim3(segs_all, v.n_pairs), dim3(256), 0, s>>>(v, f, cu);
+    auto stage2 = [&](auto kernel) { kernel<<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f); };
     if (v.D == 128) {
-        if (fold) spkv_bulk_ring<128, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
-        else spkv_bulk_ring<128, false, false><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
-        spkv_bulk_scatter<128><<<grid3, dim3(256), 0, s>>>(v, k, vv, f, cu, prefix, segs_all);
+        if (fold) ring_here ? stage2(spkv_bulk_ring<128, false, true, false>) : stage2(spkv_bulk_ring<128, false, true, true>);
+        else ring_here ? stage2(spkv_bulk_ring<128, false, false, false>) : stage2(spkv_bulk_ring<128, false, false, true>);
+        spkv_bulk_scatter<128><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here);
     } else {
-        if (fold) spkv_bulk_ring<64, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
-        else spkv_bulk_ring<64, false, false><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
-        spkv_bulk_scatter<64><<<grid3, dim3(256), 0, s>>>(v, k, vv, f, cu, prefix, segs_all);
+        if (fold) ring_here ? stage2(spkv_bulk_ring<64, false, true, false>) : stage2(spkv_bulk_ring<64, false, true, true>);
+        else ring_here ? stage2(spkv_bulk_ring<64, false, false, false>) : stage2(spkv_bulk_ring<64, false, false, true>);
+        spkv_bulk_scatter<64><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here);
     }
     return hipGetLastError();
 }

@@ -149,6 +149,45 @@ def test_bulk_append_chunk_sizes_around_the_launch_paths(w):
     cache.close()
 
 
+@pytest.mark.parametrize("w,D", [(512, 128), (513, 64), (700, 128), (7, 64)])
+def test_bulk_append_ring_rows_by_their_own_workgroup_or_not(w, D):
+    """Windows on both sides of a scatter workgroup's 512 threads (the kept rows that leave the
+    ring are moved by it, or by the stage before), chunks around one and two workgroups of
+    tokens, keep rates from none to all: lists, positions and the attention over them exact."""
+    B = 2
+    wl = small_workload("ringwg", B, 6, 3, D, [0, 0], [[0.4, 1.0, 0.0]], window=w, seed=70 + w)
+    stream = TokenStream(wl, device="cuda")
+    plan = [[w + 300, 511], [512, 513], [1024, 1030], [257, 1500], [600, 3]]
+    cache = spkv.SPKVCache(B, 6, 3, D, max_context=8000, max_total_kept_tokens=40000, window=w)
+    oracle = H.make_oracle(wl)
+    for counts in plan:
+        k, v, f, cu = stream.next_tokens(counts)
+        H.feed(cache, oracle, k, v, f, cu)
+        H.check_state(cache, oracle, wl, label=f"after {counts}")
+        q = stream.next_query()
+        H.check_output(cache.decode_attention(q), oracle.decode(to_numpy_f32(q))[0], f"after {counts}")
+    cache.close()
+
+
+def test_reset_clears_what_the_pages_held():
+    """Infinite values of an earlier prompt must not show after a reset, in rows of a page that
+    the new, shorter lists do not fill."""
+    wl = small_workload("resetinf", 1, 4, 2, 128, [900], 1.0, window=32, seed=8)
+    stream = TokenStream(wl, device="cuda")
+    cache = H.make_cache(wl)
+    k, v, f, cu = stream.next_tokens([900])
+    v[:] = float("inf")
+    cache.append(k, v, f, cu)
+    cache.reset()
+    oracle = H.make_oracle(wl)
+    k, v, f, cu = stream.next_tokens([77])
+    H.feed(cache, oracle, k, v, f, cu)
+    q = stream.next_query()
+    H.check_output(cache.decode_attention(q), oracle.decode(to_numpy_f32(q))[0])
+    H.check_state(cache, oracle, wl)
+    cache.close()
+
+
 def test_sequences_that_skip_a_step():
     """cu_seqlens may give a sequence no token in a step."""
     wl = small_workload("skip", 3, 4, 2, 64, [140, 150, 160], 0.5, seed=3)
