@@ -168,6 +168,7 @@ struct spkv_cache {
     int step_launches;            // SPKV_OPT_STEP_LAUNCHES (0 = per call)
     int n_sink;                   // always-kept first positions (SPKV_OPT_SINK_TOKENS)
     int one_round_items;          // items the chip runs in one resident round, with a margin
+    int compact_items;            // item target under the gapless numbering
     int chunk_round_items[3];     // the same for the chunk kernel with 1, 2, 4 column groups
     SpkvSplit split;              // partition used by the last decode call
     bool timing;
@@ -326,6 +327,7 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
     sp.hp_per_item = (int32_t)per;
     sp.slots = (int32_t)((max_hp + per * mw - 1) / (per * mw)) | 1;   // odd: see spkv_decode_split
     sp.mw = mw;
+    sp.compact = 0;
     if (n_items != nullptr) {
         *n_items = 0;
         for (int p = 0; p < n_pairs; ++p)
@@ -345,19 +347,28 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // (keep rates that depend on the head) every sequence adds the same uneven pattern -- in
 // units of whole workgroups -- until some XCD is handed more waves than it holds and runs
 // the surplus in a second round.  Hence the limit of kMergePairs pairs.
-constexpr int kMergePairs = 32;
+// Caches of more pairs, and those where no wider workgroup fits, take one item per workgroup
+// under the gapless numbering (spkv_decode_split_compact has both sides' figures), seven items per
+// compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
+// one-launch step keep the plain numbering.
+constexpr int kMergePairs = 32, kCompactItemsPerCu = 7;
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
-    int64_t items_one = 0;
-    const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
-    if (c->merge_waves == 1) return one;
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
-    if (c->carve.n_pairs > kMergePairs) return one;
-    for (int mw = 4; mw > 1; mw >>= 1) {
-        int64_t items = 0;
-        const SpkvSplit sp = choose_split_mw(c, one_round_items, slots_total_cap, mw, &items);
-        if (sp.hp_per_item <= one.hp_per_item && items >= items_one) return sp;
+    int64_t items_one = 0;
+    if (c->carve.n_pairs <= kMergePairs || c->merge_waves == 1 || c->item_target > 0 ||
+        c->step_launches == 1 || c->carve.n_pairs > kCompactPairs) {
+        const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
+        if (c->merge_waves == 1 || c->carve.n_pairs > kMergePairs) return one;
+        for (int mw = 4; mw > 1; mw >>= 1) {
+            int64_t items = 0;
+            const SpkvSplit sp = choose_split_mw(c, one_round_items, slots_total_cap, mw, &items);
+            if (sp.hp_per_item <= one.hp_per_item && items >= items_one) return sp;
+        }
+        if (c->item_target > 0 || c->step_launches == 1) return one;
     }
-    return one;
+    SpkvSplit sp = choose_split_mw(c, c->compact_items, slots_total_cap, 1, &items_one);
+    sp.compact = (int32_t)std::max<int64_t>(1, items_one);
+    return sp;
 }
 
 SpkvSplit choose_split(const spkv_cache* c) {
@@ -466,9 +477,11 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
         // compute units already queue a second item and the launch takes 15-20 % longer.
         const int resident = spkv_split_resident_items(cfg->head_dim);
         c->one_round_items = resident > 0 ? resident - resident / 24 : kFallbackItems;
+        const int cus = spkv_compute_units();
+        c->compact_items = kCompactItemsPerCu * (cus > 0 ? cus : 256);
         c->chunk_round_items[0] = c->chunk_round_items[1] = c->chunk_round_items[2] = 0;
     }
-    c->split = SpkvSplit{1, 1, 1};
+    c->split = SpkvSplit{1, 1, 1, 0};
     c->timing = false;
     c->split_only = false;
     c->n_timed = 0;

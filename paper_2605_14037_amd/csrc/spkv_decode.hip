@@ -417,6 +417,68 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split(SpkvView v, const u
     decode_split_item<D, MODE, MW>(v, q, scale_log2e, sp, blockIdx.x, s_split, &s_page, io);
 }
 
+// The same with workgroups numbered without gaps (host: SpkvSplit.compact of them, one item per
+// wave): id -> (pair, item) by a prefix sum of the pairs' item counts, which every wave takes for
+// itself from the exact lengths.  Under the plain numbering the ids of short pairs that have no
+// work lie between the items, and which compute units the dispatcher fills with how many
+// items depends on the pattern of the lengths; the compute unit (or die) that gets the most sets
+// the time.  Without gaps the items spread evenly whatever the lengths are, and fewer of them
+// do: seven waves per compute unit (1792 items) keep enough bytes in flight, store fewer partials
+// and leave room for a compute unit that is handed one more.  Measured, plain with 2944 items
+// against this with 1792 (step time, us): 64 sequences of 1k-64k tokens with a quarter of the heads
+// dense and a quarter local (3.0 GB) 535 -> 466; the same with sparse heads only (1.6 GB) 263 -> 266;
+// 24 of 1k-40k mixed 139 -> 118; 40 of 16k 101 -> 88; 16 of 32k 83.3 -> 81.5; 16 dense of 32k
+// 322 -> 313; head_dim 64, 60 of 1k-64k mixed 100 -> 90.  1300 items: 2 to 19 % more than 1792;
+// 2944: 1 to 4 % more.  The prefix sum costs about 1 us of every wave's start.
+// n_wg comes from the host's bound of the lengths; when a replayed graph has outgrown it,
+// workgroups take a second item.
+template <int D, bool FUSED>
+__device__ __forceinline__ void decode_split_compact(const SpkvView& v, const uint16_t* __restrict__ q,
+                                                     float scale_log2e, SpkvSplit sp, int wg, int n_wg) {
+    const int lane = threadIdx.x & 63;
+    const int per_lane = (v.n_pairs + 63) >> 6;            // consecutive pairs of a lane
+    const int p0 = lane * per_lane, p1 = min(p0 + per_lane, v.n_pairs);
+    auto groups_of = [&](int p) -> int { return p < p1 ? pair_split(v, min(p, v.n_pairs - 1), sp).groups : 0; };
+    int id = wg, total;
+    do {
+        int sum = 0;
+#pragma unroll 4
+        for (int i = 0; i < per_lane; ++i) sum += groups_of(p0 + i);
+        int incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(incl, o);
+            if (lane >= o) incl += t;
+        }
+        total = __builtin_amdgcn_readlane(incl, 63);
+        if (FUSED && id == 0)                              // item counts for the merge launch
+            for (int p = p0; p < p1; ++p) v.pair_items[p] = groups_of(p);
+        if (id >= total) return;
+        int mine = -1, first = 0, run = incl - sum;
+#pragma unroll 4
+        for (int i = 0; i < per_lane; ++i) {
+            const int g = groups_of(p0 + i);
+            if (id >= run && id < run + g) {
+                mine = p0 + i;
+                first = run;
+            }
+            run += g;
+        }
+        const int src = __builtin_ctzll(__ballot(mine >= 0));
+        const int pair = __builtin_amdgcn_readlane(mine, src);
+        const int jj = id - __builtin_amdgcn_readlane(first, src);
+        split_compute<D, FUSED, 1, false>(v, q, scale_log2e, sp, pair_split(v, pair, sp), pair, jj, nullptr);
+        id += n_wg;
+    } while (id < total);
+}
+
+// (Three waves per SIMD asked for by attribute: left alone the prefix sum takes it to two.)
+template <int D, bool FUSED>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void spkv_decode_split_compact(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp) {
+    decode_split_compact<D, FUSED>(v, q, scale_log2e, sp, blockIdx.x, gridDim.x);
+}
+
 // Fused step with the utility predictor (Eq. 1; the appendix builds it as Linear - SiLU -
 // Linear per token): the hidden layer rides in the split launch, the output layer in the
 // append workgroups of the second launch, so the gate logits of the new tokens cost no
@@ -425,21 +487,7 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split(SpkvView v, const u
 // units, 16 tokens and the ks-th of kPredictSplit ranges of d_model on MFMA 16x16x32 (W1 rows
 // as A operand, tokens as the 16 columns) and stores part[ks][token][unit], without bias.
 // The other workgroups are those of spkv_decode_split<D, true>.
-template <int D, int MW>
-__global__ __launch_bounds__(64 * MW) void spkv_decode_split_predict(SpkvView v,
-                                                                const uint16_t* __restrict__ q,
-                                                                float scale_log2e, SpkvSplit sp,
-                                                                SpkvPredict pr) {
-    extern __shared__ __attribute__((aligned(16))) float s_split[];
-    const int n_pred_wg = (pr.n_blocks + MW - 1) / MW;
-    if ((int)blockIdx.x >= n_pred_wg) {
-        const SpkvStepIO none = {};
-        decode_split_item<D, kSplitFusedTwo, MW>(v, q, scale_log2e, sp, (int)blockIdx.x - n_pred_wg,
-                                                 s_split, nullptr, none);
-        return;
-    }
-    const int unit = (int)blockIdx.x * MW + ((int)threadIdx.x >> 6);
-    if (unit >= pr.n_blocks) return;
+__device__ __forceinline__ void predict_hidden_part(const SpkvView& v, const SpkvPredict& pr, int unit) {
     const int n_jb = pr.d_hidden / 16;
     const int ks = unit % kPredictSplit, rest = unit / kPredictSplit;
     const int jb = rest % n_jb, tb = rest / n_jb;
@@ -454,6 +502,35 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split_predict(SpkvView v,
     // lane (kc, n) holds hidden units jb * 16 + 4 kc + i of token tb * 16 + n
     if (tok_ok)
         *reinterpret_cast<f32x4*>(pr.part + ((size_t)ks * v.B + tok) * pr.d_hidden + jb * 16 + 4 * kc) = acc;
+}
+
+template <int D, int MW>
+__global__ __launch_bounds__(64 * MW) void spkv_decode_split_predict(SpkvView v,
+                                                                const uint16_t* __restrict__ q,
+                                                                float scale_log2e, SpkvSplit sp,
+                                                                SpkvPredict pr) {
+    extern __shared__ __attribute__((aligned(16))) float s_split[];
+    const int n_pred_wg = (pr.n_blocks + MW - 1) / MW;
+    if ((int)blockIdx.x >= n_pred_wg) {
+        const SpkvStepIO none = {};
+        decode_split_item<D, kSplitFusedTwo, MW>(v, q, scale_log2e, sp, (int)blockIdx.x - n_pred_wg,
+                                                 s_split, nullptr, none);
+        return;
+    }
+    const int unit = (int)blockIdx.x * MW + ((int)threadIdx.x >> 6);
+    if (unit < pr.n_blocks) predict_hidden_part(v, pr, unit);
+}
+
+// The same under the gapless numbering.
+template <int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void spkv_decode_split_predict_compact(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp, SpkvPredict pr) {
+    if ((int)blockIdx.x < pr.n_blocks) {
+        predict_hidden_part(v, pr, blockIdx.x);
+        return;
+    }
+    decode_split_compact<D, true>(v, q, scale_log2e, sp, (int)blockIdx.x - pr.n_blocks,
+                                  (int)gridDim.x - pr.n_blocks);
 }
 
 // One wave folds the partials of one (pair, head) into a running (max, sum, acc) triple:
@@ -928,6 +1005,10 @@ int spkv_chunk_resident_items(int head_dim, int col_groups) {
 template <int D, int MODE>
 static void launch_split(const SpkvView& v, const uint16_t* q, float scale_log2e, SpkvSplit sp,
                          const SpkvStepIO& io, hipStream_t s) {
+    if (sp.compact > 0 && (MODE == kSplitPlain || MODE == kSplitFusedTwo)) {
+        spkv_decode_split_compact<D, MODE == kSplitFusedTwo><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp);
+        return;
+    }
     const dim3 grid((unsigned)v.n_pairs * (unsigned)sp.slots);
     const size_t lds = split_lds_bytes(sp.mw, v.G, D);
     if (sp.mw == 4) spkv_decode_split<D, MODE, 4><<<grid, dim3(256), lds, s>>>(v, q, scale_log2e, sp, io);
@@ -938,6 +1019,10 @@ static void launch_split(const SpkvView& v, const uint16_t* q, float scale_log2e
 template <int D>
 static void launch_split_predict(const SpkvView& v, const uint16_t* q, float scale_log2e,
                                  SpkvSplit sp, const SpkvPredict& pr, hipStream_t s) {
+    if (sp.compact > 0) {
+        spkv_decode_split_predict_compact<D><<<dim3(pr.n_blocks + sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, pr);
+        return;
+    }
     const dim3 grid((unsigned)((pr.n_blocks + sp.mw - 1) / sp.mw) + (unsigned)v.n_pairs * (unsigned)sp.slots);
     const size_t lds = split_lds_bytes(sp.mw, v.G, D);
     if (sp.mw == 4) spkv_decode_split_predict<D, 4><<<grid, dim3(256), lds, s>>>(v, q, scale_log2e, sp, pr);
@@ -976,6 +1061,13 @@ hipError_t spkv_launch_decode(const SpkvView& v, const uint16_t* q, uint16_t* ou
         else spkv_decode_combine<64, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp);
     }
     return hipGetLastError();
+}
+
+int spkv_compute_units() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return cus;
 }
 
 // One-wave work items the device holds at once (the registers decide, so the count is the

@@ -9,6 +9,7 @@
 
 constexpr int kSegTokens = 256;       // bulk append: tokens per compaction segment (one per thread)
 constexpr int kMaxItemTarget = 32768;
+constexpr int kCompactPairs = 1024;   // most (sequence, head) pairs the gapless numbering serves
 
 // Device-side view of one cache: plain pointers into the caller's arena.
 struct SpkvView {
@@ -77,6 +78,8 @@ struct SpkvSplit {
     int32_t hp_per_item;
     int32_t slots;
     int32_t mw;
+    int32_t compact;      // 0: workgroup id = pair * slots + item; else workgroups numbered without
+                          // gaps (spkv_decode_split_compact), this many of them
 };
 
 // one_launch: the last workgroup of every pair merges (and, in the step, appends) inside the
@@ -134,6 +137,7 @@ size_t spkv_prefill_partial_bytes(int spans, int ks, SpkvPrefillShape sh, int he
 // One-wave work items of the split-K kernel the current device holds at once (occupancy x
 // compute units); 0 if the runtime cannot tell.
 int spkv_split_resident_items(int head_dim);
+int spkv_compute_units();         // of the current device; 0 if the runtime cannot tell
 hipError_t spkv_launch_predictor(const uint16_t* x, const uint16_t* w1, const float* b1,
                                  const uint16_t* w2, const float* b2, float* logits, float* act,
                                  int n_tokens, int d_model, int d_hidden, int n_kv_heads,

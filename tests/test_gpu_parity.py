@@ -1105,6 +1105,73 @@ def test_sink_tokens_every_entry_point(n_sink, w):
 
 
 # ------------------------------------------------------------- replay from a HIP graph
+@pytest.mark.parametrize("B,Hk,G,D", [(33, 1, 4, 128), (13, 5, 3, 64), (64, 1, 16, 64), (512, 2, 1, 64),
+                                      (205, 5, 2, 64)])
+def test_gapless_numbering_of_ragged_batches(B, Hk, G, D):
+    """Pair counts on both sides of a lane's share of the prefix sum (64, 128, 1024 pairs and one
+    more), lengths from empty to long in one batch, keep rates from none to all; fused steps,
+    the two-call step and the static variant."""
+    rng = np.random.default_rng(B)
+    top = 900 if B < 200 else 150
+    ctx = [0 if b % 7 == 3 else int(rng.integers(1, top)) for b in range(B)]
+    keep = np.where(np.arange(B * Hk) % 3 == 0, 1.0, np.where(np.arange(B * Hk) % 3 == 1, 0.0, 0.3)).reshape(B, Hk)
+    wl = small_workload("gapless", B, Hk * G, Hk, D, ctx, keep, window=32, decode_steps=4, seed=B)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl), H.make_oracle(wl)
+    H.prefill(cache, oracle, stream, wl, 4096)
+    for step in range(3):
+        k, v, f, cu = stream.next_tokens([1] * B)
+        q = stream.next_query()
+        if step < 2:
+            out, lse = cache.decode_step(k, v, f, q, want_lse=True)
+            oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+        else:
+            H.feed(cache, oracle, k, v, f, cu)
+            out, lse = cache.decode_attention(q, want_lse=True)
+        ref_out, ref_lse = oracle.decode(to_numpy_f32(q))
+        H.check_output(out, ref_out, f"step {step}")
+        H.check_lse(lse, ref_lse, f"step {step}")
+    static = torch.empty_like(out)
+    cache.decode_attention_static(q, static)
+    H.check_output(static, ref_out, "static")
+    H.check_state(cache, oracle, wl, pairs=[(0, 0), (B - 1, Hk - 1)])
+    cache.close()
+
+
+def test_gapless_numbering_in_a_graph_that_its_lists_outgrow():
+    """A step captured while the lists are a few keys long and replayed until they need more
+    work items than the captured launch has workgroups: the workgroups take second items."""
+    B, Hk, n = 20, 2, 200
+    wl = small_workload("outgrow", B, 4 * Hk, Hk, 128, [20] * B, 1.0, window=16, decode_steps=n + 4, seed=4)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl), H.make_oracle(wl)
+    H.prefill(cache, oracle, stream, wl, 4096)
+    k, v, f, cu = stream.next_tokens([1] * B)
+    q = stream.next_query()
+    cache.decode_step(k, v, f, q)                     # one eager step: tightens the host's bound
+    oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+    assert cache.safe_steps() >= n
+    ks, vs, fs, qs, out = (torch.empty_like(t) for t in (k, v, f, q, q))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):                     # records the launches; runs nothing
+        cache.decode_step(ks, vs, fs, qs, out=out)
+    for i in range(n):
+        k, v, f, cu = stream.next_tokens([1] * B)
+        q = stream.next_query()
+        for dst, src in ((ks, k), (vs, v), (fs, f), (qs, q)):
+            dst.copy_(src)
+        if i > 0:                                     # the captured call itself counted one step
+            cache.advance(1)
+        graph.replay()
+        oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+        torch.cuda.synchronize()
+        if i % 40 == 39:
+            H.check_output(out, oracle.decode(to_numpy_f32(q))[0], f"replay {i}")
+    H.check_state(cache, oracle, wl)
+    cache.close()
+
+
 @pytest.mark.parametrize("launches", [1, 2])
 def test_decode_step_replayed_from_a_hip_graph(launches):
     """The fused step captured once into a HIP graph and replayed with new inputs in the same
