@@ -351,7 +351,7 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // under the gapless numbering (spkv_decode_split_compact has both sides' figures), seven items per
 // compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
 // one-launch step keep the plain numbering.
-constexpr int kMergePairs = 32, kCompactItemsPerCu = 7;
+constexpr int kMergePairs = 32, kCompactItemsPerCu = 7, kCompactChunkItemsPerCu = 4;
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     int64_t items_one = 0;
@@ -845,8 +845,11 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     // With two or four column groups a wave needs most of the register file and only one or
     // two fit a SIMD; one resident round of such items then reads too little at a time, and
     // about 1 800 items (two rounds of the widest kernel) measured 12-15 % faster.
-    c->split = choose_split_mw(c, std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
-                               slot_cap, 1);
+    const bool compact = groups == 1 && c->carve.n_pairs <= kCompactPairs && c->item_target <= 0;
+    int64_t items = 0;
+    c->split = choose_split_mw(c, compact ? c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu : std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
+                               slot_cap, 1, &items);
+    if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
 
     // every slot the launch may write must lie inside the partial buffers (they are sized
     // for this at create; checked again here because an overrun would be a wild device write)

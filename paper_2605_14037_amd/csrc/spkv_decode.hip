@@ -432,41 +432,49 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split(SpkvView v, const u
 // 2944: 1 to 4 % more.  The prefix sum costs about 1 us of every wave's start.
 // n_wg comes from the host's bound of the lengths; when a replayed graph has outgrown it,
 // workgroups take a second item.
-template <int D, bool FUSED>
-__device__ __forceinline__ void decode_split_compact(const SpkvView& v, const uint16_t* __restrict__ q,
-                                                     float scale_log2e, SpkvSplit sp, int wg, int n_wg) {
+// Item `id` of all pairs' items in order: its pair and its index there; false past the last one.
+// total: the number of items.  PUBLISH: the wave of id 0 stores every pair's item count.
+template <bool PUBLISH>
+__device__ __forceinline__ bool locate_item(const SpkvView& v, SpkvSplit sp, int id, int& total, int& pair, int& jj) {
     const int lane = threadIdx.x & 63;
     const int per_lane = (v.n_pairs + 63) >> 6;            // consecutive pairs of a lane
     const int p0 = lane * per_lane, p1 = min(p0 + per_lane, v.n_pairs);
     auto groups_of = [&](int p) -> int { return p < p1 ? pair_split(v, min(p, v.n_pairs - 1), sp).groups : 0; };
-    int id = wg, total;
-    do {
-        int sum = 0;
+    int sum = 0;
 #pragma unroll 4
-        for (int i = 0; i < per_lane; ++i) sum += groups_of(p0 + i);
-        int incl = sum;
+    for (int i = 0; i < per_lane; ++i) sum += groups_of(p0 + i);
+    int incl = sum;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(incl, o);
-            if (lane >= o) incl += t;
-        }
-        total = __builtin_amdgcn_readlane(incl, 63);
-        if (FUSED && id == 0)                              // item counts for the merge launch
-            for (int p = p0; p < p1; ++p) v.pair_items[p] = groups_of(p);
-        if (id >= total) return;
-        int mine = -1, first = 0, run = incl - sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    total = __builtin_amdgcn_readlane(incl, 63);
+    if (PUBLISH && id == 0)
+        for (int p = p0; p < p1; ++p) v.pair_items[p] = groups_of(p);
+    if (id >= total) return false;
+    int mine = -1, first = 0, run = incl - sum;
 #pragma unroll 4
-        for (int i = 0; i < per_lane; ++i) {
-            const int g = groups_of(p0 + i);
-            if (id >= run && id < run + g) {
-                mine = p0 + i;
-                first = run;
-            }
-            run += g;
+    for (int i = 0; i < per_lane; ++i) {
+        const int g = groups_of(p0 + i);
+        if (id >= run && id < run + g) {
+            mine = p0 + i;
+            first = run;
         }
-        const int src = __builtin_ctzll(__ballot(mine >= 0));
-        const int pair = __builtin_amdgcn_readlane(mine, src);
-        const int jj = id - __builtin_amdgcn_readlane(first, src);
+        run += g;
+    }
+    const int src = __builtin_ctzll(__ballot(mine >= 0));
+    pair = __builtin_amdgcn_readlane(mine, src);
+    jj = id - __builtin_amdgcn_readlane(first, src);
+    return true;
+}
+
+template <int D, bool FUSED>
+__device__ __forceinline__ void decode_split_compact(const SpkvView& v, const uint16_t* __restrict__ q,
+                                                     float scale_log2e, SpkvSplit sp, int wg, int n_wg) {
+    int id = wg, total, pair, jj;
+    do {
+        if (!locate_item<FUSED>(v, sp, id, total, pair, jj)) return;
         split_compute<D, FUSED, 1, false>(v, q, scale_log2e, sp, pair_split(v, pair, sp), pair, jj, nullptr);
         id += n_wg;
     } while (id < total);
@@ -744,14 +752,10 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
 // gate (Eq. 3-4).  The chunk's own keys (causal, always inside the window because the
 // chunk is not longer than the window) are added by spkv_chunk_combine.
 template <int D, int NQ>
-__global__ __launch_bounds__(64) void spkv_chunk_split(SpkvView v, const uint16_t* __restrict__ q,
-                                                       float scale_log2e, SpkvSplit sp, SpkvCu cu) {
+__device__ __forceinline__ void chunk_item(const SpkvView& v, const uint16_t* __restrict__ q,
+                                           float scale_log2e, SpkvSplit sp, const SpkvCu& cu,
+                                           const PairSplit& ps, int pair, int j) {
     constexpr int NS = D / 32, NB = D / 16;
-    const int pair = blockIdx.x / sp.slots;
-    const int j = blockIdx.x - pair * sp.slots;
-    const PairSplit ps = pair_split(v, pair, sp);
-    if (j == 0 && threadIdx.x == 0) v.pair_items[pair] = ps.items;
-    if (j >= ps.items) return;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
     if (n_tok == 0) return;
@@ -759,7 +763,7 @@ __global__ __launch_bounds__(64) void spkv_chunk_split(SpkvView v, const uint16_
     const int hbase = ps.nhp / ps.items, hrem = ps.nhp - hbase * ps.items;
     const int hp0 = j * hbase + min(j, hrem);
     const int hp1 = hp0 + hbase + (j < hrem ? 1 : 0);
-    const int lane = threadIdx.x, kc = lane >> 4, n = lane & 15;
+    const int lane = threadIdx.x & 63, kc = lane >> 4, n = lane & 15;
 
     bf16x8 qb[NQ][NS];
     int tok_of_col[NQ];
@@ -869,6 +873,31 @@ __global__ __launch_bounds__(64) void spkv_chunk_split(SpkvView v, const uint16_
     }
 }
 
+template <int D, int NQ>
+__global__ __launch_bounds__(64) void spkv_chunk_split(SpkvView v, const uint16_t* __restrict__ q,
+                                                       float scale_log2e, SpkvSplit sp, SpkvCu cu) {
+    const int pair = blockIdx.x / sp.slots;
+    const int j = blockIdx.x - pair * sp.slots;
+    const PairSplit ps = pair_split(v, pair, sp);
+    if (j == 0 && threadIdx.x == 0) v.pair_items[pair] = ps.items;
+    if (j < ps.items) chunk_item<D, NQ>(v, q, scale_log2e, sp, cu, ps, pair, j);
+}
+
+// One column group, workgroups numbered without gaps (see decode_split_compact), four waves per
+// compute unit: a partial result has 16 columns here, four times a decode item's, so fewer items
+// pay (16 sequences of 32k, 4 drafts: 103 us plain with 1960 items, 101.6 / 99.4 / 97.4 / 96.7 with
+// 1792 / 1536 / 1280 / 1024 without gaps; 40 of 2k-20k mixed 146 -> 133; 4 of 128k 56 -> 52).
+template <int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_chunk_split_compact(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp, SpkvCu cu) {
+    int id = blockIdx.x, total, pair, j;
+    do {
+        if (!locate_item<true>(v, sp, id, total, pair, j)) return;
+        chunk_item<D, 1>(v, q, scale_log2e, sp, cu, pair_split(v, pair, sp), pair, j);
+        id += (int)gridDim.x;
+    } while (id < total);
+}
+
 // Merge for one (pair, column = token i, head g): the split-K partials plus one term per
 // chunk token j <= i taken from the caller's k / v rows (score q_i . k_j in fp32, sum 1,
 // value v_j); bf16 output row cu[b] + i.  The waves share the partials and the chunk
@@ -963,7 +992,8 @@ static hipError_t launch_chunk(const SpkvView& v, const uint16_t* k, const uint1
                                const uint16_t* q, uint16_t* out, float* lse, float scale_log2e,
                                SpkvSplit sp, const SpkvCu& cu, hipStream_t s) {
     const unsigned grid = (unsigned)v.n_pairs * (unsigned)sp.slots;
-    spkv_chunk_split<D, NQ><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    if (NQ == 1 && sp.compact > 0) spkv_chunk_split_compact<D><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    else spkv_chunk_split<D, NQ><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
     spkv_chunk_combine<D><<<dim3(v.n_pairs * NQ * 16), dim3(256), 0, s>>>(
         v, q, k, vv, out, lse, scale_log2e, sp, cu, NQ * 16);
     return hipGetLastError();
