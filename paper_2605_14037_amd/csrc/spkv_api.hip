@@ -877,12 +877,19 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
 
 namespace {
 // Few spans (short chunks, small batch) leave most of the chip idle while each workgroup
-// walks a whole list: cut every span's tiles into ranges so that the launch has about as
+// walks a whole list: cut the tiles into ranges so that the launch has about as
 // many workgroups as the chip holds at once -- one eight-wave workgroup per compute unit,
-// two of four or two waves (measured: more ranges than that only add partial results to
-// write and merge; 16 sequences x 16 tokens at 32k context, 175 us per call with four
-// times as many, 150 us with this).
+// two of four or two waves; more ranges than that only add partial results to write and merge.
+// Eight-wave workgroups get the same number of ranges for every span, the smaller ones ranges
+// of equal length over all pairs (spkv_prefill_slots); whether there is anything to cut is
+// decided here for both.
 constexpr int kPrefillResident8 = 256, kPrefillResident = 512;
+// A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)
+// do not survive in it from one layer's call to its next, and loads that allocate nothing there
+// are then ahead (16 tokens: 16 sequences of 32k, 460 MB, 132 -> 118 us; 4 of 128k, 190 MB,
+// 76 -> 73; 40 of 2k-20k 207 -> 191); shorter lists may, and are read as usual (12 of 20k-30k with
+// head_dim 64, 50 MB: 43 against 45 us).
+constexpr int64_t kOnceBytes = (int64_t)128 << 20;
 int prefill_split_cap(int spans, int nw) {
     const int resident = nw == 8 ? kPrefillResident8 : kPrefillResident;
     if (spans <= 0) return 1;
@@ -923,7 +930,11 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
     // range keeps at least a few tiles (lengths from the host's upper bound)
     const int spans = spkv_prefill_spans(c->carve.n_pairs, c->carve.G, n_max);
     int64_t tiles = 0;
-    for (int p = 0; p < c->carve.n_pairs; ++p) tiles = std::max<int64_t>(tiles, c->L_ub[p] / kHalfTokens);
+    int64_t list_bytes = 0;
+    for (int p = 0; p < c->carve.n_pairs; ++p) {
+        tiles = std::max<int64_t>(tiles, c->L_ub[p] / kHalfTokens);
+        list_bytes += (int64_t)c->L_ub[p] * (4 * c->cfg.head_dim);
+    }
     tiles += (c->cfg.window + 64) / kHalfTokens;
     const SpkvPrefillShape sh = spkv_prefill_shape(c->carve.G, n_max);
     int ks = (int)std::max<int64_t>(1, std::min<int64_t>(prefill_split_cap(spans, sh.nw), tiles / 4));
@@ -932,9 +943,16 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
         if (exact_fit) return SPKV_E_INVAL;
         ks -= 1;                    // ks = 1 writes no partials
     }
+    // Workgroups of fewer waves take ranges of equal length over all pairs instead of ks per
+    // pair; where `part` is too small for that, none.
+    int slots = 0;
+    if (ks > 1 && sh.nw != 8) {
+        slots = spkv_prefill_slots(c->carve.n_pairs, sh, c->cfg.head_dim, part_bytes);
+        ks = 1;
+    }
     if (spkv_launch_prefill(c->view, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
                             util_logits, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),
-                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, part, s) != hipSuccess)
+                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, list_bytes > kOnceBytes, part, s) != hipSuccess)
         return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
     if (n_max > SPKV_MAX_CHUNK_TOKENS) c->bound_is_loose = true;   // short chunks: see tighten_bound

@@ -1,6 +1,7 @@
 // Read path of the SP-KV cache on gfx950 (MI355X, wave64, MFMA):
 //   spkv_decode_split    split-K flash decoding, one wave per work item, K/V tiles consumed
 //                        as MFMA operands straight from the page layout
+//                        (.._split_compact: the same items, workgroups numbered without gaps)
 //   spkv_decode_combine  log-sum-exp merge of the partials
 //   fused step           spkv_decode_split<.., true> + spkv_combine_append: append and decode
 //                        of one token per sequence in two launches instead of three; with

@@ -122,10 +122,13 @@ int spkv_chunk_resident_items(int head_dim, int col_groups);
 // (new token, KV head).
 // ks > 1: every span's tiles are cut into ks ranges, one workgroup each, and merged by a
 // combine launch; part: spkv_prefill_partial_bytes(spans, ks, shape, head_dim) bytes.
+// slots > 0 (workgroups of fewer than eight waves; ks is then not looked at): the pairs' tiles
+// are cut into at most `slots` ranges of about equal length instead (spkv_prefill_slots).
+// once: workgroups of fewer than eight waves load the lists past the caches.
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
-                               int32_t* prefix, int shp, int ks, float* part, hipStream_t s);
+                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part, hipStream_t s);
 // Workgroups (spans of tokens per (sequence, KV head)) of a prefill call, and the bytes of
 // split-K partials for them.
 struct SpkvPrefillShape {
@@ -133,6 +136,9 @@ struct SpkvPrefillShape {
 };
 SpkvPrefillShape spkv_prefill_shape(int group, int n_max);   // for chunks of at most n_max tokens
 int spkv_prefill_spans(int n_pairs, int group, int n_max);
+// Ranges of about equal length that `part_bytes` hold, at most what the device takes at once;
+// 0: not for this shape, or not more than one per pair.
+int spkv_prefill_slots(int n_pairs, SpkvPrefillShape sh, int head_dim, size_t part_bytes);
 size_t spkv_prefill_partial_bytes(int spans, int ks, SpkvPrefillShape sh, int head_dim);
 // One-wave work items of the split-K kernel the current device holds at once (occupancy x
 // compute units); 0 if the runtime cannot tell.

@@ -12,9 +12,9 @@
 //      rows i < u <= i + w in its window.
 //   2. the bulk append runs and records, per new token, how long a prefix of the long-term
 //      list lies at least w behind it (see spkv_bulk_ring).
-//   3. spkv_prefill_attend: one wave per block of tb = 32 / G consecutive tokens of one
-//      (sequence, KV head) -- 32 MFMA columns (token, head) in two groups of 16; one group
-//      for the shortest chunks -- walks the long-term prefix and then the staging rows of
+//   3. spkv_prefill_attend32 (long chunks) or spkv_prefill_attend: one wave per block of
+//      tb = 32 / G consecutive tokens of one (sequence, KV head) -- 32 MFMA columns (token,
+//      head), in two groups of 16 or, for the shortest chunks, one of 16 in the latter -- walks the long-term prefix and then the staging rows of
 //      the block's windows, one online softmax per column, and writes the normalised bf16
 //      rows (or, when a span's keys are cut into ranges, partial results that
 //      spkv_prefill_combine merges).
@@ -32,8 +32,11 @@ struct SpkvPrefill {
     int32_t   pin_xcd;   // 1: all blocks of a pair run on one XCD (shared L2)
     int32_t   nw;        // waves per workgroup (2, 4 or 8): a span is nw * tb tokens
     int32_t   nq;        // column groups of 16 per wave (1 or 2)
-    int32_t   ks;        // workgroups per span: the span's tiles are cut into ks ranges (split-K)
-    float*    part;      // ks > 1: partial (acc, m, l) of every (span, range, column)
+    int32_t   ks;        // eight waves: workgroups per span, its tiles are cut into ks ranges (split-K)
+    int32_t   slots;     // fewer waves: ranges of about equal length, at most this many in all; 0: no split
+    int32_t   once;      // fewer waves: the lists pass through the caches once (kOnceBytes)
+    float*    part;      // partial (acc, m, l) of every (range, column); slots > 0: then [n_pairs] int2
+                         // (first range, ranges) of every pair
 };
 
 // One workgroup per (staging half-page, pair): wave wv fills rows 8 wv .. 8 wv + 7.  Rows
@@ -121,8 +124,8 @@ __device__ __forceinline__ unsigned bit_range8(int a, int b) {
 //                    sums and accumulators; the tile loop leaves its inner loop for this
 //                    (rare once a few tiles have been seen) and then redoes the tile
 constexpr float kWeightSumLimit = 2048.0f;
-// Shape of a workgroup: long chunks take eight waves of two column groups of 16 (two waves
-// per SIMD, one workgroup per compute unit, 256 query columns per tile fetch).  Chunks of
+// Shape of a workgroup: long chunks take eight waves of 32 columns (spkv_prefill_attend32: two
+// waves per SIMD, one workgroup per compute unit, 256 query columns per tile fetch).  Chunks of
 // fewer tokens than eight such waves hold would leave waves without a token, so they get
 // four waves of two groups, and the shortest four or two waves of one group each (measured
 // on 16-token chunks: as fast as two waves of two groups on 16 sequences at 32k, 10 % faster
@@ -240,6 +243,84 @@ __device__ __forceinline__ void rescale_columns(const float (&x)[NQ][8], float s
     }
 }
 
+// Ranges of about equal length for the workgroups of a short chunk: pair p's tiles (at most, by
+// its kept length) in units of `unit` tiles, rounded up, give its number of ranges.  The unit is
+// the smallest of eight whose ranges fit `slots` (all tiles / unit from slots down to
+// slots - pairs; the last one always fits), at least kRangeMinTiles.  Every wave works it out
+// from the lengths: a handful of loads per lane, nine wave sums and a prefix sum.  Equal pairs
+// are cut alike.  Heads differ several-fold in kept length, so the same number of ranges for
+// every pair left the launch waiting for the longest (16 tokens, per call: 16 sequences of 32k
+// 124 -> 118 us, 40 of 2k-20k with dense and local-only heads 291 -> 191, 12 of 20k-30k with
+// head_dim 64 48 -> 43).  512 slots are one round of two workgroups per compute unit; 640 take
+// 145 / 227 / 55 us.  Ranges below eight tiles cost more to merge than they hide (2 sequences of
+// 5k: 34 us, 35.5 with four).
+constexpr int kRangePairsPerLane = 6, kRangeSlots = 512, kRangeMinTiles = 8, kRangeCap = 64;
+// Range `id` of all pairs' ranges in order: its pair, the id of the pair's first range and the
+// pair's number of ranges; false past the last one.  n_pairs <= 64 kRangePairsPerLane, < slots.
+__device__ __forceinline__ bool locate_range(const SpkvView& v, const SpkvCu& cu, int slots, int id,
+                                             int& pair, int& first, int& ranges) {
+    constexpr int kTries = 8;
+    const int lane = threadIdx.x & 63, per_lane = (v.n_pairs + 63) >> 6, p0 = lane * per_lane;
+    int tiles[kRangePairsPerLane], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kRangePairsPerLane; ++i) {
+        const int p = min(p0 + i, v.n_pairs - 1), b = p / v.Hkv;
+        const bool mine = i < per_lane && p0 + i < v.n_pairs && cu.v[b + 1] > cu.v[b];
+        tiles[i] = mine ? ((v.kept_len[p] + kHalfTokens - 1) >> 5) + (v.w >> 5) + 1 : 0;
+        sum += tiles[i];
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
+    const int all = __builtin_amdgcn_readfirstlane(sum);
+    // ceil(tiles / unit) in floats: the half keeps the truncation exact below 2^21 tiles
+    auto ranges_of = [](int t, int unit, float inv) -> int {
+        return min((int)(((float)(t + unit - 1) + 0.5f) * inv), kRangeCap);
+    };
+    int unit = 0;
+    float inv = 0.f;
+#pragma unroll
+    for (int k = kTries - 1; k >= 0; --k) {
+        const int target = slots - (v.n_pairs * k + kTries - 2) / (kTries - 1);
+        const int u = max(kRangeMinTiles, (all + target - 1) / target);
+        const float iu = 1.0f / (float)u;
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < kRangePairsPerLane; ++i) n += ranges_of(tiles[i], u, iu);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o);
+        if (k == kTries - 1 || __builtin_amdgcn_readfirstlane(n) <= slots) {
+            unit = u;
+            inv = iu;
+        }
+    }
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < kRangePairsPerLane; ++i) mine += ranges_of(tiles[i], unit, inv);
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+    }
+    if (id >= __builtin_amdgcn_readlane(incl, 63)) return false;
+    int run = incl - mine, at = -1, at_first = 0, at_ranges = 0;
+#pragma unroll
+    for (int i = 0; i < kRangePairsPerLane; ++i) {
+        const int r = ranges_of(tiles[i], unit, inv);
+        if (id >= run && id < run + r) {
+            at = p0 + i;
+            at_first = run;
+            at_ranges = r;
+        }
+        run += r;
+    }
+    const int src = __builtin_ctzll(__ballot(at >= 0));
+    pair = __builtin_amdgcn_readlane(at, src);
+    first = __builtin_amdgcn_readlane(at_first, src);
+    ranges = __builtin_amdgcn_readlane(at_ranges, src);
+    return true;
+}
+
 // Short chunks (long ones: spkv_prefill_attend32 below).  One workgroup of NW (4 or 2) waves per
 // span of NW * tb consecutive tokens of one (sequence, KV head); wave wv owns tokens i0 = span start + wv * tb .. + tb - 1 as its
 // 16 NQ MFMA columns (tb = 16 NQ / G tokens times G heads; NQ = 2 groups of 16, one for the
@@ -261,27 +342,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // chunks and for the two-wave workgroups of short ones alike).
     constexpr int kAhead = 2, kBufs = kAhead + 1;
     __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kHalfElems];
-    int pair, qblk, kr;      // (sequence, KV head), span, tile range of the span
-    if (pf.pin_xcd) {
-        // workgroups go round-robin to the 8 XCDs: id % 8 picks the XCD, and every pair
-        // lives on XCD pair % 8, so its list is fetched into one L2 and re-read there
-        const int local = blockIdx.x >> 3, lp = local / (pf.nblk * pf.ks);
-        const int rem = local - lp * pf.nblk * pf.ks;
-        qblk = rem / pf.ks;
-        kr = rem - qblk * pf.ks;
-        // rotate inside every full group of 8 pairs by the group index: with 8 KV heads a
-        // plain pair % 8 would give each XCD one head of every sequence, and heads differ
-        // several-fold in kept length
-        const int rot = (lp * 8 + 8 <= v.n_pairs) ? lp : 0;
-        pair = lp * 8 + (((blockIdx.x & 7) + rot) & 7);
-        if (pair >= v.n_pairs) return;
-    } else {
-        pair = blockIdx.x / (pf.nblk * pf.ks);
-        const int rem = blockIdx.x - pair * pf.nblk * pf.ks;
-        qblk = rem / pf.ks;
-        kr = rem - qblk * pf.ks;
+    // One span holds a whole chunk here, so a workgroup is a (pair, tile range of its list).
+    int pair = blockIdx.x, kr = 0, ranges = 1;
+    if (pf.slots > 0) {
+        int first;
+        if (!locate_range(v, cu, pf.slots, blockIdx.x, pair, first, ranges)) return;
+        kr = (int)blockIdx.x - first;
+        if (kr == 0 && threadIdx.x == 0)
+            reinterpret_cast<int2*>(pf.part + (size_t)pf.slots * (NW * NQ * 16) * (D + 2))[pair] =
+                make_int2(first, ranges);
     }
-    qblk = pf.nblk - 1 - qblk;            // longest prefixes first
+    constexpr int qblk = 0;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
     const int span0 = qblk * NW * pf.tb;
@@ -332,8 +403,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int lo_w = max(i0 + 1, u_min), hi_w = i_last + v.w;
     const int n_hp = nA + nB, last = n_hp - 1;
     // split-K: this workgroup takes tiles [x_begin, x_end) of the span's n_hp
-    const int x_begin = (int)(((long long)kr * n_hp) / pf.ks);
-    const int x_end = (int)(((long long)(kr + 1) * n_hp) / pf.ks);
+    const int x_begin = (int)(((long long)kr * n_hp) / ranges);
+    const int x_end = (int)(((long long)(kr + 1) * n_hp) / ranges);
 
     const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
     const uint16_t* stage = pf.stage + (size_t)pair * pf.shp * (size_t)kHalfElems;
@@ -379,8 +450,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     auto stage_tile = [&](const uint16_t* base, int buf) {
         const uint16_t* p = base + my_off;
 #pragma unroll
-        for (int r = 0; r < kRowsPerWave; ++r)
-            load_row_to_lds(p + r * 512, lds_rows + (unsigned)buf * (kHalfElems * 2) + r * 1024);
+        for (int r = 0; r < kRowsPerWave; ++r) {
+            const unsigned dst = lds_rows + (unsigned)buf * (kHalfElems * 2) + r * 1024;
+            if (pf.once) load_row_to_lds_once(p + r * 512, dst);
+            else load_row_to_lds(p + r * 512, dst);
+        }
     };
     // Everything loaded so far (queries, counts) is waited for here, once: left pending, the
     // first use inside the tile loop would carry a wait for all loads in flight -- on every
@@ -463,12 +537,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         float lc = l[c];
         lc += __shfl_xor(lc, 16);
         lc += __shfl_xor(lc, 32);
-        if (tok[c] >= 0 && pf.ks > 1) {
+        if (tok[c] >= 0 && pf.slots > 0) {
             // partial of this tile range: un-normalised accumulators, reference, sum
             // layout: [all columns][D] accumulators, then [all columns][2] (m, l)
-            const size_t n_cols = (size_t)v.n_pairs * pf.nblk * pf.ks * (NW * NQ * 16);
-            const size_t pc = (((size_t)pair * pf.nblk + qblk) * pf.ks + kr) * (NW * NQ * 16) +
-                              wv * (NQ * 16) + c * 16 + n;
+            const size_t n_cols = (size_t)pf.slots * (NW * NQ * 16);
+            const size_t pc = (size_t)blockIdx.x * (NW * NQ * 16) + wv * (NQ * 16) + c * 16 + n;
             float* pa = pf.part + pc * D + kc * 4;
 #pragma unroll
             for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(pa + db * 16) = acc[c][db];
@@ -874,14 +947,16 @@ __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t
     const int tbv = max(0, min(pf.tb, n_tok - i0));
     if (col >= tbv * v.G) return;
     const int i = i0 + col / v.G, g = col - (col / v.G) * v.G;
-    const size_t n_cols = (size_t)v.n_pairs * pf.nblk * pf.ks * kCols;
-    const size_t pc0 = (size_t)span * pf.ks * kCols + cs;      // range r: pc0 + r * kCols
+    const size_t n_cols = (size_t)(pf.slots > 0 ? pf.slots : v.n_pairs * pf.nblk * pf.ks) * kCols;
+    int2 cut = make_int2(span * pf.ks, pf.ks);                 // first range, ranges
+    if (pf.slots > 0) cut = reinterpret_cast<const int2*>(pf.part + n_cols * (D + 2))[pair];
+    const size_t pc0 = (size_t)cut.x * kCols + cs;             // range r: pc0 + r * kCols
     const float* ml = pf.part + n_cols * D;
     float M = SPKV_NEG_INF;
-    for (int r = 0; r < pf.ks; ++r) M = fmaxf(M, ml[(pc0 + (size_t)r * kCols) * 2]);
+    for (int r = 0; r < cut.y; ++r) M = fmaxf(M, ml[(pc0 + (size_t)r * kCols) * 2]);
     f32x4 num = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
-    for (int r = 0; r < pf.ks; ++r) {
+    for (int r = 0; r < cut.y; ++r) {
         const size_t pc = pc0 + (size_t)r * kCols;
         const float sc = __builtin_amdgcn_exp2f(ml[pc * 2] - M);      // 0 for a range without keys
         num += *reinterpret_cast<const f32x4*>(pf.part + pc * D + d) * sc;
@@ -899,9 +974,12 @@ __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t
 }
 
 static SpkvPrefill prefill_params(const SpkvView& v, int n_max, uint16_t* stage, int32_t* prefix,
-                                  float* bias, int shp, int ks = 1, float* part = nullptr) {
+                                  float* bias, int shp, int ks = 1, float* part = nullptr,
+                                  int slots = 0, bool once = false) {
     SpkvPrefill pf;
+    pf.once = once ? 1 : 0;
     pf.ks = ks;
+    pf.slots = slots;
     pf.part = part;
     pf.stage = stage;
     pf.prefix = prefix;
@@ -919,6 +997,7 @@ static SpkvPrefill prefill_params(const SpkvView& v, int n_max, uint16_t* stage,
 }
 
 static unsigned prefill_grid(const SpkvView& v, const SpkvPrefill& pf) {
+    if (pf.slots > 0) return (unsigned)pf.slots;
     return pf.pin_xcd ? 8u * (unsigned)((v.n_pairs + 7) / 8) * (unsigned)(pf.nblk * pf.ks)
                       : (unsigned)v.n_pairs * (unsigned)(pf.nblk * pf.ks);
 }
@@ -928,6 +1007,15 @@ SpkvPrefillShape spkv_prefill_shape(int group, int n_max) { return prefill_shape
 int spkv_prefill_spans(int n_pairs, int group, int n_max) {
     const SpkvPrefillShape sh = prefill_shape(group, n_max);
     return n_pairs * ((n_max + sh.nw * sh.tb - 1) / (sh.nw * sh.tb));
+}
+
+int spkv_prefill_slots(int n_pairs, SpkvPrefillShape sh, int head_dim, size_t part_bytes) {
+    const size_t table = (size_t)n_pairs * sizeof(int2);
+    const size_t slot = (size_t)(sh.nw * sh.nq * 16) * (head_dim + 2) * 4;
+    if (sh.nw == 8 || n_pairs > 64 * kRangePairsPerLane || part_bytes < table) return 0;
+    const size_t fit = (part_bytes - table) / slot;
+    const int slots = fit < (size_t)kRangeSlots ? (int)fit : kRangeSlots;
+    return slots > n_pairs ? slots : 0;
 }
 
 size_t spkv_prefill_partial_bytes(int spans, int ks, SpkvPrefillShape sh, int head_dim) {
@@ -951,8 +1039,8 @@ static void launch_attend(const SpkvView& v, const uint16_t* q, uint16_t* out, f
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
-                               int32_t* prefix, int shp, int ks, float* part, hipStream_t s) {
-    const SpkvPrefill pf = prefill_params(v, n_max, stage, prefix, nullptr, shp, ks, part);
+                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part, hipStream_t s) {
+    const SpkvPrefill pf = prefill_params(v, n_max, stage, prefix, nullptr, shp, ks, part, slots, once);
     const float sl = sm_scale * 1.4426950408889634f;
     const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
     const unsigned grid = prefill_grid(v, pf);
@@ -961,13 +1049,13 @@ hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint1
         spkv_prefill_stage<128><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
         if ((e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, prefix, s)) != hipSuccess) return e;
         launch_attend<128>(v, q, out, lse, sl, pf, cu, grid, s);
-        if (ks > 1)
+        if (ks > 1 || slots > 0)
             spkv_prefill_combine<128><<<dim3(v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / 8), dim3(256), 0, s>>>(v, out, lse, pf, cu);
     } else {
         spkv_prefill_stage<64><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
         if ((e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, prefix, s)) != hipSuccess) return e;
         launch_attend<64>(v, q, out, lse, sl, pf, cu, grid, s);
-        if (ks > 1)
+        if (ks > 1 || slots > 0)
             spkv_prefill_combine<64><<<dim3(v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / 16), dim3(256), 0, s>>>(v, out, lse, pf, cu);
     }
     return hipGetLastError();

@@ -145,6 +145,27 @@ def test_prefill_one_workspace_for_every_chunk_length(Hq, Hkv, D):
     _run_prefill(wl, [[n, max(1, n // 3)] for n in lens], sample=24, seed=Hq, shared_workspace=True)
 
 
+@pytest.mark.parametrize("B,Hkv,G,D,top,n", [
+    (1, 1, 4, 128, 3000, 16),      # one pair: the cap of ranges per pair; four waves
+    (65, 1, 4, 64, 1500, 8),       # a lane with two pairs; two waves
+    (113, 3, 4, 64, 700, 16),      # 339 pairs: almost every slot taken by a first range
+    (171, 2, 4, 64, 500, 16),      # 342 pairs: not cut
+    (5, 13, 3, 128, 2000, 40),     # two column groups; a group that does not divide 16
+    (2, 8, 4, 128, 17000, 16),     # lists of more than half the last-level cache
+])
+def test_prefill_short_chunks_in_ranges_of_equal_length(B, Hkv, G, D, top, n):
+    """Few query columns per pair: the tiles of all pairs are cut into ranges of about equal
+    length.  Lengths from empty to long, keep rates from none to all, and sequences without
+    a token in the call."""
+    rng = np.random.default_rng(B)
+    ctx = [top if B <= 2 else (0 if b % 7 == 3 else int(rng.integers(1, top))) for b in range(B)]
+    kinds = np.array([1.0, 1.0, 0.0, 0.3]) if B > 2 else np.array([1.0])
+    keep = kinds[np.arange(B * Hkv) % len(kinds)].reshape(B, Hkv)
+    wl = small_workload("ranges", B, Hkv * G, Hkv, D, ctx, keep, window=64, seed=B)
+    counts = [0 if b % 5 == 4 else (n if b % 3 == 0 else int(rng.integers(1, n + 1))) for b in range(B)]
+    _run_prefill(wl, [counts, [n] * B], sample=200)
+
+
 def test_prefill_calls_with_the_shortest_chunks():
     """One token for every sequence (handed to the fused decode step), one or two tokens for
     some (the multi-token step), then lengths just above the hand-over."""
