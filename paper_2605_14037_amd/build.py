@@ -22,8 +22,7 @@ FLAGS = [
 # register count depends on how the compiler schedules loads against MFMAs): the library
 # adapts its work-item count to whatever the runtime reports, but a drop costs bandwidth.
 EXPECTED_OCCUPANCY = {"spkv_decode_splitILi128E": 3,      # every mode and merge width at head_dim 128
-                      "spkv_decode_split_compactILi128E": 3,
-                      "spkv_decode_split_predict_compactILi128E": 3}
+                      "spkv_decode_split_compactILi128E": 3}
 
 
 def _check_occupancy(remarks: str) -> list:

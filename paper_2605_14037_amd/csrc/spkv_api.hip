@@ -350,13 +350,17 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // Caches of more pairs, and those where no wider workgroup fits, take one item per workgroup
 // under the gapless numbering (spkv_decode_split_compact has both sides' figures), seven items per
 // compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
-// one-launch step keep the plain numbering.
+// one-launch step keep the plain numbering, and so does the step with the predictor (gapless =
+// false): its workgroups come first in the launch and shift the items' start, and the gapless
+// numbering gave 82.6 us against 84.4 on 16 sequences of 32k but 64.2 against 62.9 on 32 of 16k
+// and 121.5 against 116.3 on 64 of 1k-30k.
 constexpr int kMergePairs = 32, kCompactItemsPerCu = 7, kCompactChunkItemsPerCu = 4;
-SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
+SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap,
+                       bool gapless = true) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     int64_t items_one = 0;
     if (c->carve.n_pairs <= kMergePairs || c->merge_waves == 1 || c->item_target > 0 ||
-        c->step_launches == 1 || c->carve.n_pairs > kCompactPairs) {
+        c->step_launches == 1 || c->carve.n_pairs > kCompactPairs || !gapless) {
         const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
         if (c->merge_waves == 1 || c->carve.n_pairs > kMergePairs) return one;
         for (int mw = 4; mw > 1; mw >>= 1) {
@@ -364,11 +368,22 @@ SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_t
             const SpkvSplit sp = choose_split_mw(c, one_round_items, slots_total_cap, mw, &items);
             if (sp.hp_per_item <= one.hp_per_item && items >= items_one) return sp;
         }
-        if (c->item_target > 0 || c->step_launches == 1) return one;
+        if (c->item_target > 0 || c->step_launches == 1 || !gapless) return one;
     }
     SpkvSplit sp = choose_split_mw(c, c->compact_items, slots_total_cap, 1, &items_one);
     sp.compact = (int32_t)std::max<int64_t>(1, items_one);
     return sp;
+}
+
+// A captured launch is replayed while the lists grow: until every pair has gained a whole item,
+// one workgroup more per pair has a place for every item.  Without them a replay gives some
+// workgroups a second item and waits for those (33 replays of a step at 16 sequences of 32k:
+// 89 us per step against 77 eager).  Eager launches take none: the host's bound is never short.
+void room_to_grow(spkv_cache* c, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->split.compact > 0 &&
+        (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone))
+        c->split.compact += c->carve.n_pairs;
 }
 
 SpkvSplit choose_split(const spkv_cache* c) {
@@ -645,6 +660,7 @@ int spkv_decode_step(spkv_cache_t* c, const void* k, const void* v, const float*
     const int rc = reserve_capacity(c, nullptr, s);
     if (rc != SPKV_OK) return rc;
     c->split = choose_split(c);          // partition of the state BEFORE the append
+    room_to_grow(c, s);
     if (spkv_launch_decode_step(c->view, static_cast<const uint16_t*>(k),
                                 static_cast<const uint16_t*>(v), util_logits,
                                 static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out), lse,
@@ -687,7 +703,7 @@ int spkv_decode_step_predict(spkv_cache_t* c, const void* hidden, const void* w1
     // the predictor's workgroups share the launch: leave them room in the resident round
     const int n_pred = spkv_predict_blocks(c->cfg.batch, d_hidden);
     c->split = choose_split(c, std::max(c->carve.n_pairs, c->one_round_items - n_pred),
-                            c->carve.max_items);
+                            c->carve.max_items, false);
     SpkvPredict pr = {};
     pr.x = static_cast<const uint16_t*>(hidden);
     pr.w1 = static_cast<const uint16_t*>(w1);
@@ -737,6 +753,7 @@ int spkv_decode_attention(spkv_cache_t* c, const void* q, void* out, float* lse,
         c->n_timed += 1;
     }
     c->split = choose_split(c);
+    room_to_grow(c, s);
     if (spkv_launch_decode(c->view, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),
                            lse, sm_scale, c->split, c->split_only, one_launch(c, s), ev0, ev1, s) != hipSuccess)
         return SPKV_E_HIP;
@@ -762,6 +779,7 @@ int spkv_decode_attention_static(spkv_cache_t* c, const void* q, void* out, floa
     v.part_ml = reinterpret_cast<float*>(base + align_up((size_t)cap * G * D * sizeof(float)));
     v.max_items = (int32_t)std::min<int64_t>(cap, INT32_MAX);
     c->split = choose_split(c, c->one_round_items, cap);
+    room_to_grow(c, static_cast<hipStream_t>(stream));
     if ((int64_t)c->carve.n_pairs * c->split.slots > cap) return SPKV_E_CAPACITY;
     if (spkv_launch_decode(v, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out), lse,
                            sm_scale, c->split, false, false, nullptr, nullptr,
@@ -850,6 +868,7 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     c->split = choose_split_mw(c, compact ? c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu : std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
                                slot_cap, 1, &items);
     if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
+    room_to_grow(c, s);
 
     // every slot the launch may write must lie inside the partial buffers (they are sized
     // for this at create; checked again here because an overrun would be a wild device write)
@@ -980,9 +999,8 @@ int spkv_prefill_attention(spkv_cache_t* c, const void* k, const void* v, const 
         return spkv_decode_step(c, k, v, util_logits, q, out, lse, sm_scale, stream);
     // The shortest chunks go to the multi-token step: with one group of 16 query columns its
     // one-wave items read the lists at the decode step's rate, and it needs fewer launches
-    // (measured on 16 sequences of 32k tokens: 2 tokens 122 us against 140 us here, 4 tokens
-    // 128 against 140, 8 tokens 144 against 141; on 4 sequences of 128k this call is ahead
-    // from 2 tokens on, by 4 %).
+    // (measured on 16 sequences of 32k tokens: 2 / 4 tokens there 94 / 97 us, 5 / 8 tokens here
+    // 113; on 4 sequences of 128k 51 / 52 there, 69 here).
     if (n_max <= SPKV_MAX_CHUNK_TOKENS && n_max <= c->cfg.window && n_max * c->carve.G <= 16)
         return spkv_decode_chunk(c, k, v, util_logits, q, cu_seqlens, out, lse, sm_scale, stream);
     if (k == nullptr || v == nullptr || util_logits == nullptr || q == nullptr || out == nullptr ||

@@ -530,18 +530,6 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split_predict(SpkvView v,
     if (unit < pr.n_blocks) predict_hidden_part(v, pr, unit);
 }
 
-// The same under the gapless numbering.
-template <int D>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void spkv_decode_split_predict_compact(
-    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp, SpkvPredict pr) {
-    if ((int)blockIdx.x < pr.n_blocks) {
-        predict_hidden_part(v, pr, blockIdx.x);
-        return;
-    }
-    decode_split_compact<D, true>(v, q, scale_log2e, sp, (int)blockIdx.x - pr.n_blocks,
-                                  (int)gridDim.x - pr.n_blocks);
-}
-
 // One wave folds the partials of one (pair, head) into a running (max, sum, acc) triple:
 // with M the running max,  acc = sum_i 2^(m_i - M) acc_i,  den = sum_i 2^(m_i - M) l_i.
 // The loads of successive items are independent; only the cheap rescaling is chained.
@@ -1050,10 +1038,6 @@ static void launch_split(const SpkvView& v, const uint16_t* q, float scale_log2e
 template <int D>
 static void launch_split_predict(const SpkvView& v, const uint16_t* q, float scale_log2e,
                                  SpkvSplit sp, const SpkvPredict& pr, hipStream_t s) {
-    if (sp.compact > 0) {
-        spkv_decode_split_predict_compact<D><<<dim3(pr.n_blocks + sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, pr);
-        return;
-    }
     const dim3 grid((unsigned)((pr.n_blocks + sp.mw - 1) / sp.mw) + (unsigned)v.n_pairs * (unsigned)sp.slots);
     const size_t lds = split_lds_bytes(sp.mw, v.G, D);
     if (sp.mw == 4) spkv_decode_split_predict<D, 4><<<grid, dim3(256), lds, s>>>(v, q, scale_log2e, sp, pr);
