@@ -347,29 +347,48 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // (keep rates that depend on the head) every sequence adds the same uneven pattern -- in
 // units of whole workgroups -- until some XCD is handed more waves than it holds and runs
 // the surplus in a second round.  Hence the limit of kMergePairs pairs.
-// Caches of more pairs, and those where no wider workgroup fits, take one item per workgroup
-// under the gapless numbering (spkv_decode_split_compact has both sides' figures), seven items per
+// Caches of more pairs take one item per workgroup, and where their lists are uneven
+// (worth_gapless) the gapless numbering (spkv_decode_split_compact) with seven items per
 // compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
 // one-launch step keep the plain numbering, and so does the step with the predictor (gapless =
 // false): its workgroups come first in the launch and shift the items' start, and the gapless
 // numbering gave 82.6 us against 84.4 on 16 sequences of 32k but 64.2 against 62.9 on 32 of 16k
 // and 121.5 against 116.3 on 64 of 1k-30k.
-constexpr int kMergePairs = 32, kCompactItemsPerCu = 7, kCompactChunkItemsPerCu = 4;
+constexpr int kMergePairs = 32, kCompactItemsPerCu = 7, kCompactChunkItemsPerCu = 4,
+              kCompactChunkPairs = 384;
+// Where the gapless numbering is worth its search and its longer items: at least three slots to
+// an item.  Step, plain -> gapless: dense, sparse and local-only heads mixed, 64 sequences of
+// 1k-64k 604 -> 500 us, 40 of 2k-20k 131 -> 110, 24 of 1k-30k 116 -> 96, 16 of 4k-8k 36 -> 33; but
+// with less between the lists, equal ones of 32 sequences of 16k (one slot to an item)
+// 63.2 -> 65.8, 64 of 1k-30k 117 -> 123 and 163 -> 169, 128 of 0.5k-16k 195 -> 207.
+// The search costs more with more lengths per lane: above 384 pairs the lists must be worth it (64
+// sequences x 8 heads mixed, 300-3000 tokens, 400 keys a pair: 45 -> 51; 100 x 8 of 1k-12k,
+// 2300 keys: 201 -> 181).
+constexpr int kGapRatio = 3, kGapFewPairs = 384, kGapMeanKeys = 1024;
+bool worth_gapless(const spkv_cache* c, const SpkvSplit& plain, int64_t items) {
+    const int n = c->carve.n_pairs;
+    if (n > kCompactPairs || (int64_t)n * plain.slots < kGapRatio * items) return false;
+    if (n <= kGapFewPairs) return true;
+    int64_t keys = 0;
+    for (int p = 0; p < n; ++p) keys += c->L_ub[p];
+    return keys >= (int64_t)n * kGapMeanKeys;
+}
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap,
                        bool gapless = true) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     int64_t items_one = 0;
-    if (c->carve.n_pairs <= kMergePairs || c->merge_waves == 1 || c->item_target > 0 ||
-        c->step_launches == 1 || c->carve.n_pairs > kCompactPairs || !gapless) {
-        const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
-        if (c->merge_waves == 1 || c->carve.n_pairs > kMergePairs) return one;
+    const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
+    if (c->merge_waves == 1) return one;
+    if (c->carve.n_pairs <= kMergePairs) {
         for (int mw = 4; mw > 1; mw >>= 1) {
             int64_t items = 0;
             const SpkvSplit sp = choose_split_mw(c, one_round_items, slots_total_cap, mw, &items);
             if (sp.hp_per_item <= one.hp_per_item && items >= items_one) return sp;
         }
-        if (c->item_target > 0 || c->step_launches == 1 || !gapless) return one;
+        return one;
     }
+    if (!gapless || c->item_target > 0 || c->step_launches == 1 || !worth_gapless(c, one, items_one))
+        return one;
     SpkvSplit sp = choose_split_mw(c, c->compact_items, slots_total_cap, 1, &items_one);
     sp.compact = (int32_t)std::max<int64_t>(1, items_one);
     return sp;
@@ -863,7 +882,10 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     // With two or four column groups a wave needs most of the register file and only one or
     // two fit a SIMD; one resident round of such items then reads too little at a time, and
     // about 1 800 items (two rounds of the widest kernel) measured 12-15 % faster.
-    const bool compact = groups == 1 && c->carve.n_pairs <= kCompactPairs && c->item_target <= 0;
+    // One column group takes the gapless numbering with few items (spkv_chunk_split_compact) while
+    // a pair has several of them on average (4 tokens: 48 sequences x 8 heads of 2k-4k
+    // 57.7 -> 56.7 us, 64 x 8 of 1k-30k 185.7 -> 186.8, 128 x 8 of 0.5k-16k 233 -> 275).
+    const bool compact = groups == 1 && c->carve.n_pairs <= kCompactChunkPairs && c->item_target <= 0;
     int64_t items = 0;
     c->split = choose_split_mw(c, compact ? c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu : std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
                                slot_cap, 1, &items);

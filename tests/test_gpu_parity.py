@@ -1106,13 +1106,13 @@ def test_sink_tokens_every_entry_point(n_sink, w):
 
 # ------------------------------------------------------------- replay from a HIP graph
 @pytest.mark.parametrize("B,Hk,G,D", [(33, 1, 4, 128), (13, 5, 3, 64), (64, 1, 16, 64), (512, 2, 1, 64),
-                                      (205, 5, 2, 64)])
+                                      (205, 5, 2, 64), (49, 8, 1, 64)])
 def test_gapless_numbering_of_ragged_batches(B, Hk, G, D):
     """Pair counts on both sides of a lane's share of the prefix sum (64, 128, 1024 pairs and one
-    more), lengths from empty to long in one batch, keep rates from none to all; fused steps,
+    more; more than 384 with short and with long lists), lengths from empty to long in one batch, keep rates from none to all; fused steps,
     the two-call step and the static variant."""
     rng = np.random.default_rng(B)
-    top = 900 if B < 200 else 150
+    top = 6000 if Hk == 8 else 900 if B < 200 else 150
     ctx = [0 if b % 7 == 3 else int(rng.integers(1, top)) for b in range(B)]
     keep = np.where(np.arange(B * Hk) % 3 == 0, 1.0, np.where(np.arange(B * Hk) % 3 == 1, 0.0, 0.3)).reshape(B, Hk)
     wl = small_workload("gapless", B, Hk * G, Hk, D, ctx, keep, window=32, decode_steps=4, seed=B)
@@ -1142,7 +1142,8 @@ def test_gapless_numbering_in_a_graph_that_its_lists_outgrow():
     """A step captured while the lists are a few keys long and replayed until they need more
     work items than the captured launch has workgroups: the workgroups take second items."""
     B, Hk, n = 20, 2, 200
-    wl = small_workload("outgrow", B, 4 * Hk, Hk, 128, [20] * B, 1.0, window=16, decode_steps=n + 4, seed=4)
+    # one long sequence: mostly empty slots under the plain numbering
+    wl = small_workload("outgrow", B, 4 * Hk, Hk, 128, [600] + [20] * (B - 1), 1.0, window=16, decode_steps=n + 4, seed=4)
     stream = TokenStream(wl, device="cuda")
     cache, oracle = H.make_cache(wl), H.make_oracle(wl)
     H.prefill(cache, oracle, stream, wl, 4096)
