@@ -431,8 +431,10 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split(SpkvView v, const u
 // 24 of 1k-40k mixed 139 -> 118; 40 of 16k 101 -> 88; 16 of 32k 83.3 -> 81.5; 16 dense of 32k
 // 322 -> 313; head_dim 64, 60 of 1k-64k mixed 100 -> 90.  1300 items: 2 to 19 % more than 1792;
 // 2944: 1 to 4 % more.  The prefix sum costs about 1 us of every wave's start.
-// n_wg comes from the host's bound of the lengths; when a replayed graph has outgrown it,
-// workgroups take a second item.
+// Even lists gain or lose a few percent either way, so the host takes this numbering for uneven
+// ones only (worth_gapless).
+// n_wg comes from the host's bound of the lengths, with a workgroup more per pair in a captured
+// launch; when a replayed graph has outgrown that, workgroups take a second item.
 // Item `id` of all pairs' items in order: its pair and its index there; false past the last one.
 // total: the number of items.  PUBLISH: the wave of id 0 stores every pair's item count.
 template <bool PUBLISH>
