@@ -399,10 +399,13 @@ SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_t
 // workgroups a second item and waits for those (33 replays of a step at 16 sequences of 32k:
 // 89 us per step against 77 eager).  Eager launches take none: the host's bound is never short.
 void room_to_grow(spkv_cache* c, hipStream_t s) {
+    if (c->split.compact == 0) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (c->split.compact > 0 &&
-        (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone))
-        c->split.compact += c->carve.n_pairs;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();      // no answer is not an error of the next launch
+        cap = hipStreamCaptureStatusActive;
+    }
+    if (cap != hipStreamCaptureStatusNone) c->split.compact += c->carve.n_pairs;
 }
 
 SpkvSplit choose_split(const spkv_cache* c) {
