@@ -382,12 +382,20 @@ hipError_t spkv_launch_predictor(const uint16_t* x, const uint16_t* w1, const fl
                                  const uint16_t* w2, const float* b2, float* logits, float* act,
                                  int n_tokens, int d_model, int d_hidden, int n_kv_heads,
                                  hipStream_t s) {
-    // The staged kernel takes the same time for any number of tokens up to a workgroup per compute
-    // unit (d_model 4096, 256 units: 51 us; 1024, 64: 19 us), the pair of launches below grows with
-    // tokens x units (1024 tokens 36 us, 1400 about 49, 2048 65; 64 units: 2048 tokens 14 us).
+    // The staged kernel takes about the same time for any number of tokens up to a workgroup per
+    // compute unit (d_model 1024: 18 us, 4096: 42, 50 with 256 units), the pair of launches below
+    // grows with tokens x (units + what reading a token and storing its heads costs, which weighs
+    // the more the shorter the rows are).  Pair / staged on either side of the line, us, 8 heads: 4096
+    // tokens of 4096, 16 / 48 units 19 / 33 against 42, 96 units 55 / 42; 6000 of 4096, 32 units 36 / 42,
+    // 48 units 51 / 42; 4096 of 1024, 32 units 15 / 18, 64 units 20 / 18; 6000 of 1024, 16 units 18 / 17;
+    // one head: 12 000 of 4096, 16 units 29 / 40, 32 units 50 / 41.  Up to 512 elements per row one
+    // launch is faster because it is one (11 us against 13).
     // 128 tokens per workgroup halve the fetches of W1 once 64 would need a second round (16 384
     // tokens: 58 us with 64 each; 20 000: 65 us with 128, 100 with 64).
-    if ((n_tokens >= 4096 || (int64_t)n_tokens * d_hidden >= 350000) && d_hidden <= 256) {
+    const int64_t units = (int64_t)n_tokens * d_hidden;
+    const bool staged = units >= 350000 ||
+                        (n_tokens >= 4096 && (d_model <= 512 || units * d_model + n_tokens * (4000 + 4500LL * n_kv_heads) >= 300000LL * d_model));
+    if (staged && d_hidden <= 256) {
         const bool wide = n_tokens > 16384;
         if (d_hidden <= 64) return wide ? launch_predictor_gemm<1, 128>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s)
                                         : launch_predictor_gemm<1, 64>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s);
@@ -398,7 +406,7 @@ hipError_t spkv_launch_predictor(const uint16_t* x, const uint16_t* w1, const fl
     }
     // Wider hidden layers (up to 512 units): the register-tiled kernel, about 120 us per
     // workgroup for d_model = 4096 (32 768 tokens: 242 us).
-    if (n_tokens >= 4096 && d_hidden % 64 == 0 && d_hidden <= 512 && n_kv_heads <= 64) {
+    if (n_tokens >= 4096 && d_hidden > 256 && d_hidden % 64 == 0 && d_hidden <= 512 && n_kv_heads <= 64) {
         const int n_waves = d_hidden / 64;
         const size_t lds = (size_t)n_waves * 64 * n_kv_heads * sizeof(float);
         spkv_predictor_tiled<<<dim3((n_tokens + 63) / 64), dim3(64 * n_waves), lds, s>>>(
