@@ -244,7 +244,7 @@ __device__ __forceinline__ int block_excl_scan(int x, int* s_w, int& total) {
 // LDS and summed after one barrier), so that the call is two launches instead of three.
 constexpr int kCountSegs = 16;
 //
-// MOVE = false: the kept ring rows are moved by stage 3 (rings of at most kScatterThreads slots).
+// MOVE = false: the kept ring rows are moved by stage 3 (ring_in_one_workgroup).
 template <int D, bool SMALL, bool COUNT, bool MOVE>
 __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int32_t* prefix,
                                                       const uint16_t* __restrict__ k,
@@ -449,62 +449,80 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
     }
 }
 
-// The last min(n, w) tokens of the call go into the ring: a wave takes eight consecutive slots
-// s0 .. s0 + 7 -- one 16-byte V unit per head-dim element.  Slot s receives the newest position p < T_new with p mod w = s if the call
-// brought it (p >= T_new - min(n, w)).  A unit whose eight slots are all written goes out as
-// whole 16-byte units, transposed through LDS; otherwise the written rows go one by one.
+// The last min(n, w) tokens of the call go into the ring: a wave takes units of eight consecutive
+// slots s0 .. s0 + 7 -- one 16-byte V unit per head-dim element.  Slot s receives the newest position
+// p < T_new with p mod w = s if the call brought it (p >= T_new - min(n, w)).  A unit whose eight
+// slots are all written goes out as whole 16-byte units, transposed through LDS; otherwise the
+// written rows go one by one.
 template <int D>
-__device__ __forceinline__ void bulk_ring_rows(const SpkvView& v, const uint16_t* __restrict__ k,
-                                               const uint16_t* __restrict__ vv,
-                                               const float* __restrict__ f, int pair, int h, int row0,
-                                               int n, int T_old, int s0, uint16_t (*s_rows)[D],
-                                               int lane) {
-    if (s0 >= v.w) return;
-    const int T_new = T_old + n, m = min(n, v.w), c = lane & 15;
-    // token index (row of the call) landing in slot s, or -1
-    auto token_of = [&](int s) -> int {
-        if (s >= v.w) return -1;
-        const int p = T_new - 1 - ((T_new - 1 - s) % v.w + v.w) % v.w;
-        return p >= T_new - m ? p - T_old : -1;
-    };
-    bool all = true;
+struct RingUnit {
+    int s0, age0;            // first slot; tokens between slot s0's newest position and the last one
+    bool all;
+    float logit;             // lanes 0-7: of slot s0 + lane
+    uint4 k[2], v[2];        // rows lane / 16 and 4 + lane / 16
+};
+// token index (row of the call) landing in slot s0 + r, or -1
+__device__ __forceinline__ int ring_token(int s0, int age0, int r, int n, int w) {
+    const int age = age0 >= r ? age0 - r : age0 - r + w;
+    return s0 + r < w && age < min(n, w) ? n - 1 - age : -1;
+}
+template <int D>
+__device__ __forceinline__ RingUnit<D> load_ring_unit(const SpkvView& v, const uint16_t* __restrict__ k,
+                                                      const uint16_t* __restrict__ vv,
+                                                      const float* __restrict__ f, int h, int row0,
+                                                      int n, int T_old, int s0, int lane) {
+    const int c = lane & 15;
+    RingUnit<D> u;
+    u.s0 = s0;
+    u.all = s0 < v.w;
+    u.age0 = s0 < v.w ? (T_old + n - 1 - s0 + v.w) % v.w : 0;
+    u.logit = 0.f;
 #pragma unroll
-    for (int r = 0; r < 8; ++r) all = all && token_of(s0 + r) >= 0;
-    uint16_t* dp = ring_page(v, pair, s0 >> 6);
-    const int dk0 = s0 & 63;
-    uint4 kk[2], vl[2];
-    int jj[2];
+    for (int r = 0; r < 8; ++r) u.all = u.all && ring_token(s0, u.age0, r, n, v.w) >= 0;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-        jj[pass] = token_of(s0 + pass * 4 + (lane >> 4));
-        kk[pass] = make_uint4(0u, 0u, 0u, 0u);
-        vl[pass] = make_uint4(0u, 0u, 0u, 0u);
-        if (jj[pass] >= 0 && c < D / 8) {
-            const size_t src = ((size_t)(row0 + jj[pass]) * v.Hkv + h) * D + c * 8;
-            kk[pass] = *reinterpret_cast<const uint4*>(k + src);
-            vl[pass] = *reinterpret_cast<const uint4*>(vv + src);
+        const int j = ring_token(s0, u.age0, pass * 4 + (lane >> 4), n, v.w);
+        u.k[pass] = make_uint4(0u, 0u, 0u, 0u);
+        u.v[pass] = make_uint4(0u, 0u, 0u, 0u);
+        if (j >= 0 && c < D / 8) {
+            const size_t src = ((size_t)(row0 + j) * v.Hkv + h) * D + c * 8;
+            u.k[pass] = *reinterpret_cast<const uint4*>(k + src);
+            u.v[pass] = *reinterpret_cast<const uint4*>(vv + src);
         }
     }
     if (lane < 8) {
-        const int j = token_of(s0 + lane);
-        if (j >= 0) v.ring_logit[(size_t)pair * v.w + s0 + lane] = f[((size_t)row0 + j) * v.Hkv + h];
+        const int j = ring_token(s0, u.age0, lane, n, v.w);
+        if (j >= 0) u.logit = f[((size_t)row0 + j) * v.Hkv + h];
     }
-    if (all) {
+    return u;
+}
+template <int D>
+__device__ __forceinline__ void store_ring_unit(const SpkvView& v, const RingUnit<D>& u, int pair, int n,
+                                                uint16_t (*s_rows)[D], int lane) {
+    if (u.s0 >= v.w) return;
+    const int c = lane & 15, dk0 = u.s0 & 63;
+    uint16_t* dp = ring_page(v, pair, u.s0 >> 6);
+    if (lane < 8 && ring_token(u.s0, u.age0, lane, n, v.w) >= 0)
+        v.ring_logit[(size_t)pair * v.w + u.s0 + lane] = u.logit;
+    if (u.all) {
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
             const int row = pass * 4 + (lane >> 4);
             if (c < D / 8) {
-                *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk0 + row, c * 8)) = kk[pass];
-                *reinterpret_cast<uint4*>(&s_rows[row][c * 8]) = vl[pass];
+                *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk0 + row, c * 8)) = u.k[pass];
+                *reinterpret_cast<uint4*>(&s_rows[row][c * 8]) = u.v[pass];
             }
         }
         __builtin_amdgcn_wave_barrier();
         store_v_units<D>(dp, dk0, s_rows, lane);
+        __builtin_amdgcn_wave_barrier();
     } else {
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass)
-            if (jj[pass] >= 0 && c < D / 8)
-                store_row_chunk<D>(dp, dk0 + pass * 4 + (lane >> 4), c, kk[pass], vl[pass]);
+        for (int pass = 0; pass < 2; ++pass) {
+            const int r = pass * 4 + (lane >> 4);
+            if (ring_token(u.s0, u.age0, r, n, v.w) >= 0 && c < D / 8)
+                store_row_chunk<D>(dp, dk0 + r, c, u.k[pass], u.v[pass]);
+        }
     }
 }
 
@@ -514,9 +532,10 @@ __device__ __forceinline__ void bulk_ring_rows(const SpkvView& v, const uint16_t
 // destination rows (whole 16-byte V units, transposed through LDS), two groups per wave at a
 // time so that all their loads are in flight together; rows before the first and after the
 // last whole group go one by one, their V elements as 2-byte stores.  The last workgroup of a
-// pair (ring_here: at most a ring slot per thread) moves the kept rows that leave the ring in the
-// same way and then writes the last min(n, w) tokens of the call into the ring; for longer rings
-// workgroups of their own write the slots, eight per wave, and stage 2 has moved the rows.
+// pair (ring_here) moves the kept rows that leave the ring in the
+// same way and then writes the last min(n, w) tokens of the call into the ring, two units' loads
+// at a time; without it (ring_in_one_workgroup) workgroups of their own write the slots, eight per
+// wave, and stage 2 has moved the rows.
 // Bound by the requests in flight of a few dependent rounds (logits, rows, stores) more than by
 // bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
 // written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
@@ -548,7 +567,8 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
     __shared__ uint16_t s_list[2 * kScatterThreads];
     __shared__ __attribute__((aligned(16))) uint16_t s_v[NW][8][D];
     if (quad >= quads && ring_here == 0) {      // the ring part of the grid (ring_here = 0): independent of the segments
-        bulk_ring_rows<D>(v, k, vv, f, pair, h, row0, n, bi.T_old, (quad - quads) * (NW * 8) + wave * 8, s_v[wave], lane);
+        const int s0 = (quad - quads) * (NW * 8) + wave * 8;
+        store_ring_unit<D>(v, load_ring_unit<D>(v, k, vv, f, h, row0, n, bi.T_old, s0, lane), pair, n, s_v[wave], lane);
         return;
     }
     // rows leaving the ring: positions r0 .. r0 + nr - 1, thread i looks at r0 + i
@@ -660,9 +680,25 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
     }
     if (ring_wg) {            // the rows that leave have been read: the new ones take their slots
         __syncthreads();
-        for (int s0 = wave * 8; s0 < v.w; s0 += NW * 8)
-            bulk_ring_rows<D>(v, k, vv, f, pair, h, row0, n, bi.T_old, s0, s_v[wave], lane);
+        for (int s0 = wave * 8; s0 < v.w; s0 += 2 * NW * 8) {       // two units' loads in flight
+            const RingUnit<D> a = load_ring_unit<D>(v, k, vv, f, h, row0, n, bi.T_old, s0, lane);
+            const RingUnit<D> b2 = load_ring_unit<D>(v, k, vv, f, h, row0, n, bi.T_old, s0 + NW * 8, lane);
+            store_ring_unit<D>(v, a, pair, n, s_v[wave], lane);
+            store_ring_unit<D>(v, b2, pair, n, s_v[wave], lane);
+        }
     }
+}
+
+// One workgroup per pair for the ring (a thread per slot), or stage 2 moves the leaving rows and a
+// workgroup per 64 slots writes the new ones.  The one workgroup works through its slots one
+// round after the other, which pays where other workgroups fill the chip meanwhile: short rings, and
+// longer ones beside several segments of many pairs.  Prompts of 4096 tokens, us per prompt, stage 2 /
+// one workgroup (8 KV heads of 128): in pieces of 270 and a ring of 256, 8 pairs 460 / 503, 256 pairs
+// 746 / 900; ring of 64, 128 pairs 410 / 392; in pieces of 700 and a ring of 128, 64 pairs 235 / 219;
+// ring of 512, 8 pairs 292 / 300, 128 pairs 413 / 380.
+static bool ring_in_one_workgroup(const SpkvView& v, int n_max) {
+    if (v.w > kScatterThreads) return false;
+    return v.w <= 64 || (n_max > kScatterThreads && (v.w <= 128 || v.n_pairs >= 64));
 }
 
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
@@ -675,7 +711,7 @@ hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const u
     }
     const int segs_all = (n_max + kSegTokens - 1) / kSegTokens;
     const int quads = (n_max + kScatterThreads - 1) / kScatterThreads;
-    const bool ring_here = v.w <= kScatterThreads;  // a thread per ring slot
+    const bool ring_here = ring_in_one_workgroup(v, n_max);
     const dim3 grid3(quads + (ring_here ? 1 : (v.w + kScatterThreads / 8 - 1) / (kScatterThreads / 8)), v.n_pairs);
     const bool fold = segs_all <= kCountSegs;       // the per-pair launch counts for itself
     if (!fold) spkv_bulk_count<<<dim3(segs_all, v.n_pairs), dim3(256), 0, s>>>(v, f, cu);

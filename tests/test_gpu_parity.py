@@ -149,16 +149,17 @@ def test_bulk_append_chunk_sizes_around_the_launch_paths(w):
     cache.close()
 
 
-@pytest.mark.parametrize("w,D", [(512, 128), (513, 64), (700, 128), (7, 64)])
-def test_bulk_append_ring_rows_by_their_own_workgroup_or_not(w, D):
-    """Windows on both sides of a scatter workgroup's 512 threads (the kept rows that leave the
-    ring are moved by it, or by the stage before), chunks around one and two workgroups of
-    tokens, keep rates from none to all: lists, positions and the attention over them exact."""
-    B = 2
-    wl = small_workload("ringwg", B, 6, 3, D, [0, 0], [[0.4, 1.0, 0.0]], window=w, seed=70 + w)
+@pytest.mark.parametrize("w,D,B", [(512, 128, 2), (513, 64, 2), (700, 128, 2), (7, 64, 2), (64, 128, 2), (128, 64, 2),
+                                   (512, 128, 22), (201, 64, 22)])
+def test_bulk_append_ring_rows_by_their_own_workgroup_or_not(w, D, B):
+    """Windows and batches on both sides of the rule that gives a pair's ring to one workgroup (the
+    kept rows that leave the ring are moved by it, or by the stage before), chunks around one and two
+    workgroups of tokens, keep rates from none to all: lists, positions and the attention over them
+    exact."""
+    wl = small_workload("ringwg", B, 6, 3, D, [0] * B, [[0.4, 1.0, 0.0]], window=w, seed=70 + w)
     stream = TokenStream(wl, device="cuda")
-    plan = [[w + 300, 511], [512, 513], [1024, 1030], [257, 1500], [600, 3]]
-    cache = spkv.SPKVCache(B, 6, 3, D, max_context=8000, max_total_kept_tokens=40000, window=w)
+    plan = [two * (B // 2) for two in ([w + 300, 511], [512, 513], [1024, 1030], [257, 1500], [600, 3])]
+    cache = spkv.SPKVCache(B, 6, 3, D, max_context=8000, max_total_kept_tokens=20000 * B, window=w)
     oracle = H.make_oracle(wl)
     for counts in plan:
         k, v, f, cu = stream.next_tokens(counts)

@@ -37,3 +37,17 @@ def test_predictor_kernel_by_size(tokens, d_model, d_hidden, kernel):
     narrow hidden layers took up to twice as long in it at 4096 tokens."""
     got = record(dict(batch=1), [["logits", tokens, d_model, d_hidden, 8]])[0]
     assert got.rc == 0 and got.launches[0][0] == kernel
+
+
+# ------------------------------------------------------------------ bulk append
+@pytest.mark.parametrize("batch,window,piece,ring_workgroups,move", [
+    (1, 512, 270, 8, 1), (1, 512, 2048, 8, 1), (32, 256, 270, 4, 1), (16, 512, 700, 1, 0),
+    (1, 128, 270, 2, 1), (1, 128, 700, 1, 0), (1, 64, 270, 1, 0), (8, 256, 513, 1, 0),
+    (7, 256, 513, 4, 1), (64, 513, 4096, 9, 1)])
+def test_bulk_append_who_writes_the_ring(batch, window, piece, ring_workgroups, move):
+    """One workgroup per pair works through a long ring slowly: few pairs and single segments have
+    it spread over workgroups."""
+    got = record(dict(batch=batch, window=window), [["append", [piece] * batch]])[0]
+    (ring, _, _), (scatter, grid, _) = got.launches
+    assert ring == f"spkv_bulk_ring<128, 0, 1, {move}>" and scatter == "spkv_bulk_scatter<128>"
+    assert grid == (-(-piece // 512) + ring_workgroups, batch * 8)
