@@ -75,7 +75,7 @@ bool carve(const spkv_config_t* c, Carve* out) {
     k.t_pair = take((size_t)k.n_pairs * 4);
     k.kept_len = take((size_t)k.n_pairs * 4);
     k.gate_on = take((size_t)k.n_pairs * 4);
-    k.pool_next = take(4);
+    k.pool_next = take(8);
     k.free_top = take(4);
     k.free_pages = take((size_t)k.n_pages * 4);
     k.err_flag = take(4);
@@ -571,7 +571,7 @@ int spkv_cache_grow(spkv_cache_t* c, const spkv_config_t* cfg, void* dev_arena, 
         {k.t_pair, q.t_pair, (size_t)q.n_pairs * 4},
         {k.kept_len, q.kept_len, (size_t)q.n_pairs * 4},
         {k.gate_on, q.gate_on, (size_t)q.n_pairs * 4},
-        {k.pool_next, q.pool_next, 4},
+        {k.pool_next, q.pool_next, 8},
         {k.free_top, q.free_top, 4},
         {k.free_pages, q.free_pages, (size_t)q.n_pages * 4},
         {k.err_flag, q.err_flag, 4},
@@ -615,14 +615,12 @@ int spkv_cache_reset(spkv_cache_t* c, void* stream) {
     if (c == nullptr) return SPKV_E_INVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     // Everything up to the pool (counters, ring, tables) is cleared; of the pool the pages that
-    // were ever handed out -- the others are zero since create, nothing else writes there (16
-    // sequences of 32k tokens, 0.9 GB arena half in use: 152 us for all of it, 64 this way);
-    // then the counters behind the pool.  What is left holds nothing that is read before it
-    // is written: positions and logits of entries, scratch, partial results.
+    // were ever handed out -- the others are zero since create, nothing else writes there; then
+    // the counters behind the pool.  What is left holds nothing that is read before it is written:
+    // positions and logits of entries, scratch, partial results.
     const Carve& k = c->carve;
-    if (spkv_launch_clear_pages(c->view, s) != hipSuccess ||
-        spkv_launch_fill_zero(c->arena, k.pool, s) != hipSuccess ||
-        spkv_launch_fill_zero(c->arena + k.pair_items, k.pos_scratch - k.pair_items, s) != hipSuccess)
+    if (spkv_launch_reset(c->view, c->arena, k.pool_next, k.pool, k.pair_items, k.pos_scratch - k.pair_items,
+                          s) != hipSuccess)
         return SPKV_E_HIP;
     std::fill(c->T.begin(), c->T.end(), 0);
     std::fill(c->L_ub.begin(), c->L_ub.end(), 0);

@@ -189,6 +189,29 @@ def test_reset_clears_what_the_pages_held():
     cache.close()
 
 
+def test_reset_again_and_again():
+    """Every reset leaves an empty cache, also of more pages than the one before it: no page in use,
+    the same pages handed out from the first on, nothing of the earlier values in them."""
+    wl = small_workload("resets", 2, 4, 2, 64, [3100, 3100], 1.0, window=32, seed=9)
+    stream = TokenStream(wl, device="cuda")
+    cache = H.make_cache(wl)
+    for n in (40, 3000, 1, 333):
+        k, v, f, cu = stream.next_tokens([n, max(1, n - 500)])
+        v[:] = float("inf")
+        cache.append(k, v, f, cu)
+        cache.reset()
+        st = cache.stats()
+        assert (st.pool_pages_used, st.kept_tokens, st.total_tokens, st.gate_on_tokens) == (0, 0, 0, 0)
+        oracle = H.make_oracle(wl)
+        k, v, f, cu = stream.next_tokens([n + 70, n + 1])
+        H.feed(cache, oracle, k, v, f, cu)
+        q = stream.next_query()
+        H.check_output(cache.decode_attention(q), oracle.decode(to_numpy_f32(q))[0], f"after {n}")
+        H.check_state(cache, oracle, wl, label=f"after {n}")
+        cache.reset()
+    cache.close()
+
+
 def test_sequences_that_skip_a_step():
     """cu_seqlens may give a sequence no token in a step."""
     wl = small_workload("skip", 3, 4, 2, 64, [140, 150, 160], 0.5, seed=3)
