@@ -708,9 +708,13 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
         __syncthreads();
         for (int s0 = wave * 8; s0 < v.w; s0 += 2 * NW * 8) {       // two units' loads in flight
             const RingUnit<D> a = load_ring_unit<D>(v, k, vv, f, h, row0, n, bi.T_old, s0, lane);
-            const RingUnit<D> b2 = load_ring_unit<D>(v, k, vv, f, h, row0, n, bi.T_old, s0 + NW * 8, lane);
-            store_ring_unit<D>(v, a, pair, n, s_v[wave], lane);
-            store_ring_unit<D>(v, b2, pair, n, s_v[wave], lane);
+            if (s0 + NW * 8 < v.w) {
+                const RingUnit<D> a2 = load_ring_unit<D>(v, k, vv, f, h, row0, n, bi.T_old, s0 + NW * 8, lane);
+                store_ring_unit<D>(v, a, pair, n, s_v[wave], lane);
+                store_ring_unit<D>(v, a2, pair, n, s_v[wave], lane);
+            } else {
+                store_ring_unit<D>(v, a, pair, n, s_v[wave], lane);
+            }
         }
     }
 }
