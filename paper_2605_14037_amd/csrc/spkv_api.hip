@@ -163,6 +163,12 @@ struct spkv_cache {
     hipEvent_t snap_event;
     bool snap_pending;
     std::vector<int32_t> snap_ev; // per sequence: pairs pushed out of the window since the copy
+    // What is known of the lengths themselves: L_ub less what `since_exact` (per sequence) added to
+    // it is the length when the bound was last exact -- from which the lists have grown by single
+    // tokens and short chunks only (lists_known), or by a prompt as well.
+    std::vector<int32_t> since_exact;
+    bool lists_known, snap_covers;    // snap_covers: no prompt since the copy was enqueued
+    bool chunk_since_prompt;          // a copy costs a call some 25 us: not for a single short chunk
     int item_target;
     int merge_waves;              // SPKV_OPT_MERGE_WAVES (0 = per call)
     int step_launches;            // SPKV_OPT_STEP_LAUNCHES (0 = per call)
@@ -236,6 +242,8 @@ int refresh_bound(spkv_cache* c, hipStream_t s, int32_t* kept_len_out) {
     c->pages_ub = pages;
     c->bound_is_loose = false;
     c->slack = 0;
+    std::fill(c->since_exact.begin(), c->since_exact.end(), 0);
+    c->lists_known = true;
     c->snap_pending = false;      // a copy still on its way is older than what was just read
     if (kept_len_out != nullptr) std::memcpy(kept_len_out, len.data(), len.size() * 4);
     return SPKV_OK;
@@ -244,9 +252,9 @@ int refresh_bound(spkv_cache* c, hipStream_t s, int32_t* kept_len_out) {
 // Keeps the host's bound of the lengths close to the truth during long runs of single-token
 // steps without ever waiting: adopts a finished copy of the device lengths (plus whatever has
 // left the windows since it was enqueued: still an upper bound), and enqueues a new copy when
-// the slack has grown past 1/16 of the bound.  Never while the stream is being captured (the
+// the slack has grown past 1/share of the bound.  Never while the stream is being captured (the
 // copy would become a graph node and the host would read it at the wrong time).
-void tighten_bound(spkv_cache* c, hipStream_t s) {
+void tighten_bound(spkv_cache* c, hipStream_t s, int share = 16) {
     if (c->snap_host == nullptr) return;
     const int n_pairs = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
     if (c->snap_pending) {
@@ -261,6 +269,8 @@ void tighten_bound(spkv_cache* c, hipStream_t s) {
             }
             c->pages_ub = pages;
             c->slack = slack;
+            c->since_exact = c->snap_ev;
+            if (c->snap_covers) c->lists_known = true;
             c->snap_pending = false;
         } else {
             (void)hipGetLastError();      // "not ready" is not an error of the next launch
@@ -269,7 +279,7 @@ void tighten_bound(spkv_cache* c, hipStream_t s) {
     }
     int64_t sum = 0;
     for (int p = 0; p < n_pairs; ++p) sum += c->L_ub[p] + std::min(c->T[p / Hkv], c->cfg.window);
-    if (c->slack * 16 <= sum) return;
+    if (c->slack * share <= sum) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
@@ -283,6 +293,7 @@ void tighten_bound(spkv_cache* c, hipStream_t s) {
     }
     std::fill(c->snap_ev.begin(), c->snap_ev.end(), 0);
     c->snap_pending = true;
+    c->snap_covers = true;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -452,6 +463,12 @@ int reserve_capacity(spkv_cache* c, const int32_t* cu, hipStream_t s) {
     }
 }
 
+// After an append whose keep rate says more about the lengths than the bound does.
+void prompt_appended(spkv_cache* c) {
+    c->bound_is_loose = true;
+    c->lists_known = c->snap_covers = c->chunk_since_prompt = false;
+}
+
 // Host bookkeeping after the launch: exact token counts, upper bounds of the lengths.
 void commit_lengths(spkv_cache* c, const int32_t* cu) {
     const int B = c->cfg.batch, Hkv = c->cfg.n_kv_heads, w = c->cfg.window;
@@ -468,6 +485,7 @@ void commit_lengths(spkv_cache* c, const int32_t* cu) {
         }
         c->slack += ev * Hkv;
         c->snap_ev[b] += (int32_t)ev;
+        c->since_exact[b] += (int32_t)ev;
     }
 }
 
@@ -505,6 +523,10 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     c->snap_event = nullptr;
     c->snap_pending = false;
     c->snap_ev.assign(cfg->batch, 0);
+    c->since_exact.assign(cfg->batch, 0);
+    c->lists_known = true;
+    c->snap_covers = false;
+    c->chunk_since_prompt = false;
     c->item_target = 0;
     c->merge_waves = 0;
     c->step_launches = 0;
@@ -627,6 +649,8 @@ int spkv_cache_reset(spkv_cache_t* c, void* stream) {
     c->pages_ub = 0;
     c->bound_is_loose = false;
     c->slack = 0;
+    std::fill(c->since_exact.begin(), c->since_exact.end(), 0);
+    c->lists_known = true;
     c->snap_pending = false;
     return SPKV_OK;
 }
@@ -658,7 +682,7 @@ int spkv_append(spkv_cache_t* c, const void* k, const void* v, const float* util
                        : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, s);
     if (e != hipSuccess) return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
-    if (n_max > SPKV_MAX_CHUNK_TOKENS) c->bound_is_loose = true;   // short chunks: see tighten_bound
+    if (n_max > SPKV_MAX_CHUNK_TOKENS) prompt_appended(c);         // short chunks: see tighten_bound
     return SPKV_OK;
 }
 
@@ -851,7 +875,6 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
         !aligned16(out) || (lse != nullptr && !aligned16(lse)))
         return SPKV_E_INVAL;
     if (!(sm_scale > 0.f)) sm_scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
-    if (!c->bound_is_loose) tighten_bound(c, s);
     const int cols = n_max * G;
     const int groups = cols <= 16 ? 1 : (cols <= 32 ? 2 : 4);
     if (append && groups > 1) {
@@ -867,6 +890,8 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     if (c->bound_is_loose) {       // the split-K partition below wants the exact lengths
         const int rc = refresh_bound(c, s, nullptr);
         if (rc != SPKV_OK) return rc;
+    } else {
+        tighten_bound(c, s);
     }
     if (append) {
         const int rc = reserve_capacity(c, cu_seqlens, s);
@@ -912,30 +937,38 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
                              : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, s);
     if (e != hipSuccess) return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
-    if (n_max > SPKV_MAX_CHUNK_TOKENS) c->bound_is_loose = true;   // short chunks: see tighten_bound
     return SPKV_OK;
 }
 }  // namespace
 
 namespace {
 // Few spans (short chunks, small batch) leave most of the chip idle while each workgroup
-// walks a whole list: cut the tiles into ranges so that the launch has about as
+// walks a whole list: cut every span's tiles into ranges so that the launch has about as
 // many workgroups as the chip holds at once -- one eight-wave workgroup per compute unit,
 // two of four or two waves; more ranges than that only add partial results to write and merge.
-// Eight-wave workgroups get the same number of ranges for every span, the smaller ones ranges
-// of equal length over all pairs (spkv_prefill_slots); whether there is anything to cut is
-// decided here for both.
 constexpr int kPrefillResident8 = 256, kPrefillResident = 512;
-// A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)
-// do not survive in it from one layer's call to its next, and loads that allocate nothing there
-// are then ahead (16 tokens: 16 sequences of 32k, 460 MB, 132 -> 118 us; 4 of 128k, 190 MB,
-// 76 -> 73; 40 of 2k-20k 207 -> 191); shorter lists may, and are read as usual (12 of 20k-30k with
-// head_dim 64, 50 MB: 43 against 45 us).
-constexpr int64_t kOnceBytes = (int64_t)128 << 20;
 int prefill_split_cap(int spans, int nw) {
     const int resident = nw == 8 ? kPrefillResident8 : kPrefillResident;
     if (spans <= 0) return 1;
     return std::max(1, std::min(32, (resident + spans / 2) / spans));
+}
+// Short chunks, one span per pair: ranges of about equal length over all pairs (spkv_prefill_slots) in
+// place of ks per pair?  In units of the time of a tile: ks per pair wait for the longest pair's
+// range, twice where the ranges do not fit the chip at once, and merge ks partial results; the equal
+// ranges cost every workgroup the search for its own (about five tiles) and are merged up to 64 per
+// pair.  ks ranges / equal ones, us per call of 16 tokens: heads of unlike lists, 16 sequences of 32k
+// 139 / 117, 4 of 128k 70 / 65, 40 of 2k-20k with dense and local-only heads 243 / 190; like or short
+// ones, 64 of 4k-8k with 2 heads of 64 36 / 39, one of 10k 29 / 33, one of 100k 44 / 48, 48 of 2k-4k
+// with 2 heads of 64 31 / 34, 16 of 250-500 36 / 39.  Before the lengths are known (after a prompt,
+// until a copy of them has arrived) the bound says nothing about how unlike they are: equal
+// ranges only where it is far above what the search costs.
+bool ranges_over_all_pairs(int ks, int pairs, int slots, int64_t longest, int64_t all, bool known) {
+    const int64_t each = (all + slots - 1) / slots;
+    if (!known) return each >= 64;
+    const int64_t rounds = ((int64_t)pairs * ks + kPrefillResident - 1) / kPrefillResident;
+    const int64_t unit = std::max<int64_t>(8, each);
+    return rounds * ((longest + ks - 1) / ks) + ks / 2 >
+           unit + 5 + std::min<int64_t>(64, (longest + unit - 1) / unit) / 2;
 }
 }  // namespace
 
@@ -970,34 +1003,46 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
     std::memcpy(cu.v, cu_seqlens, (size_t)(B + 1) * 4);
     // split-K over every span's tiles when the spans alone would not fill the chip; each
     // range keeps at least a few tiles (lengths from the host's upper bound)
-    const int spans = spkv_prefill_spans(c->carve.n_pairs, c->carve.G, n_max);
-    int64_t tiles = 0;
-    int64_t list_bytes = 0;
-    for (int p = 0; p < c->carve.n_pairs; ++p) {
-        tiles = std::max<int64_t>(tiles, c->L_ub[p] / kHalfTokens);
-        list_bytes += (int64_t)c->L_ub[p] * (4 * c->cfg.head_dim);
-    }
-    tiles += (c->cfg.window + 64) / kHalfTokens;
     const SpkvPrefillShape sh = spkv_prefill_shape(c->carve.G, n_max);
+    const bool short_chunk = sh.nw != 8;
+    if (short_chunk && (c->lists_known || c->chunk_since_prompt)) tighten_bound(c, s, 4);
+    c->chunk_since_prompt = short_chunk;
+    const int spans = spkv_prefill_spans(c->carve.n_pairs, c->carve.G, n_max);
+    const int64_t window_tiles = c->cfg.window / kHalfTokens + 1;
+    int64_t longest = 0, known_longest = 0, all = 0;               // in tiles; known_longest and all:
+    for (int p = 0; p < c->carve.n_pairs; ++p) {                   // of the lengths rather than the bound
+        const int64_t bound = c->L_ub[p];
+        const int64_t known = c->lists_known ? std::max<int64_t>(0, bound - c->since_exact[p / c->cfg.n_kv_heads]) : bound;
+        longest = std::max(longest, bound / kHalfTokens);
+        known_longest = std::max(known_longest, known / kHalfTokens + window_tiles);
+        all += known / kHalfTokens + window_tiles;
+    }
+    const int64_t tiles = longest + (c->cfg.window + 64) / kHalfTokens;
     int ks = (int)std::max<int64_t>(1, std::min<int64_t>(prefill_split_cap(spans, sh.nw), tiles / 4));
     // exactly what this call writes must fit
     while (spkv_prefill_partial_bytes(spans, ks, sh, c->cfg.head_dim) > part_bytes) {
         if (exact_fit) return SPKV_E_INVAL;
         ks -= 1;                    // ks = 1 writes no partials
     }
-    // Workgroups of fewer waves take ranges of equal length over all pairs instead of ks per
-    // pair; where `part` is too small for that, none.
     int slots = 0;
-    if (ks > 1 && sh.nw != 8) {
-        slots = spkv_prefill_slots(c->carve.n_pairs, sh, c->cfg.head_dim, part_bytes);
-        ks = 1;
+    bool once = false;
+    if (short_chunk) {
+        slots = ks > 1 ? spkv_prefill_slots(c->carve.n_pairs, sh, c->cfg.head_dim, part_bytes) : 0;
+        if (slots > 0 && !ranges_over_all_pairs(ks, spans, slots, known_longest, all, c->lists_known)) slots = 0;
+        if (slots > 0) ks = 1;      // (ranges cut on the device)
+        int64_t bound = 0;
+        for (int p = 0; p < c->carve.n_pairs; ++p) bound += c->L_ub[p];
+        once = bound * (4 * c->cfg.head_dim) > kOnceBytes;
     }
     if (spkv_launch_prefill(c->view, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
                             util_logits, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),
-                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, list_bytes > kOnceBytes, part, s) != hipSuccess)
+                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, once, part, s) != hipSuccess)
         return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
-    if (n_max > SPKV_MAX_CHUNK_TOKENS) c->bound_is_loose = true;   // short chunks: see tighten_bound
+    if (n_max > SPKV_MAX_CHUNK_TOKENS) {          // shorter ones: see tighten_bound
+        if (short_chunk) c->bound_is_loose = true;
+        else prompt_appended(c);
+    }
     return SPKV_OK;
 }
 }  // namespace
@@ -1183,6 +1228,7 @@ int spkv_cache_advance(spkv_cache_t* c, int64_t n_steps) {
         }
         c->slack += ev * Hkv;
         c->snap_ev[b] += (int32_t)ev;
+        c->since_exact[b] += (int32_t)ev;
     }
     return SPKV_OK;
 }

@@ -11,6 +11,13 @@ constexpr int kSegTokens = 256;       // bulk append: tokens per compaction segm
 constexpr int kMaxItemTarget = 32768;
 constexpr int kCompactPairs = 1024;   // most (sequence, head) pairs the gapless numbering serves
 
+// A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)
+// do not survive in it from one layer's call to its next, and loads that allocate nothing there
+// are then ahead (16 tokens: 16 sequences of 32k, 460 MB, 132 -> 118 us; 4 of 128k, 190 MB,
+// 76 -> 73; 40 of 2k-20k 207 -> 191); shorter lists may, and are read as usual (12 of 20k-30k with
+// head_dim 64, 50 MB: 43 against 45 us).
+constexpr int64_t kOnceBytes = (int64_t)128 << 20;
+
 // Device-side view of one cache: plain pointers into the caller's arena.
 struct SpkvView {
     int32_t B, Hq, Hkv, G, D, w;

@@ -32,9 +32,10 @@ struct SpkvPrefill {
     int32_t   pin_xcd;   // 1: all blocks of a pair run on one XCD (shared L2)
     int32_t   nw;        // waves per workgroup (2, 4 or 8): a span is nw * tb tokens
     int32_t   nq;        // column groups of 16 per wave (1 or 2)
-    int32_t   ks;        // eight waves: workgroups per span, its tiles are cut into ks ranges (split-K)
-    int32_t   slots;     // fewer waves: ranges of about equal length, at most this many in all; 0: no split
-    int32_t   once;      // fewer waves: the lists pass through the caches once (kOnceBytes)
+    int32_t   ks;        // workgroups per span, its tiles are cut into ks ranges (split-K)
+    int32_t   slots;     // > 0 (fewer than eight waves): ranges of about equal length over all pairs
+                         // instead, at most this many in all
+    int32_t   once;      // fewer than eight waves: the lists pass the caches by (kOnceBytes)
     float*    part;      // partial (acc, m, l) of every (range, column); slots > 0: then [n_pairs] int2
                          // (first range, ranges) of every pair
 };
@@ -243,22 +244,20 @@ __device__ __forceinline__ void rescale_columns(const float (&x)[NQ][8], float s
     }
 }
 
-// Ranges of about equal length for the workgroups of a short chunk: pair p's tiles (at most, by
-// its kept length) in units of `unit` tiles, rounded up, give its number of ranges.  The unit is
-// the smallest of eight whose ranges fit `slots` (all tiles / unit from slots down to
-// slots - pairs; the last one always fits), at least kRangeMinTiles.  Every wave works it out
-// from the lengths: a handful of loads per lane, nine wave sums and a prefix sum.  Equal pairs
-// are cut alike.  Heads differ several-fold in kept length, so the same number of ranges for
-// every pair left the launch waiting for the longest (16 tokens, per call: 16 sequences of 32k
-// 124 -> 118 us, 40 of 2k-20k with dense and local-only heads 291 -> 191, 12 of 20k-30k with
-// head_dim 64 48 -> 43).  512 slots are one round of two workgroups per compute unit; 640 take
-// 145 / 227 / 55 us.  Ranges below eight tiles cost more to merge than they hide (2 sequences of
-// 5k: 34 us, 35.5 with four).
+// Ranges of about equal length for the workgroups of a short chunk (host: ranges_over_all_pairs):
+// pair p's tiles (at most, by its kept length) in units of `unit` tiles, rounded up, give its number
+// of ranges.  The unit is the smallest of eight whose ranges fit `slots` (all tiles / unit from slots
+// down to slots - pairs; the last one always fits), at least kRangeMinTiles.  Every wave works it out
+// from the lengths: a handful of loads per lane, nine wave sums and a prefix sum, 3 to 4 us.  Equal
+// pairs are cut alike.  512 slots are one round of two workgroups per compute unit (16 tokens, per
+// call: 16 sequences of 32k 118 us, 40 of 2k-20k with dense and local-only heads 191); 640 take 145
+// and 227.  Ranges below eight tiles cost more to merge than they hide.
 constexpr int kRangePairsPerLane = 6, kRangeSlots = 512, kRangeMinTiles = 8, kRangeCap = 64;
 // Range `id` of all pairs' ranges in order: its pair, the id of the pair's first range and the
-// pair's number of ranges; false past the last one.  n_pairs <= 64 kRangePairsPerLane, < slots.
+// pair's number of ranges; false past the last one.  all: the tiles of all pairs.
+// n_pairs <= 64 kRangePairsPerLane, < slots.
 __device__ __forceinline__ bool locate_range(const SpkvView& v, const SpkvCu& cu, int slots, int id,
-                                             int& pair, int& first, int& ranges) {
+                                             int& pair, int& first, int& ranges, int& all) {
     constexpr int kTries = 8;
     const int lane = threadIdx.x & 63, per_lane = (v.n_pairs + 63) >> 6, p0 = lane * per_lane;
     int tiles[kRangePairsPerLane], sum = 0;
@@ -271,7 +270,7 @@ __device__ __forceinline__ bool locate_range(const SpkvView& v, const SpkvCu& cu
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
-    const int all = __builtin_amdgcn_readfirstlane(sum);
+    all = __builtin_amdgcn_readfirstlane(sum);
     // ceil(tiles / unit) in floats: the half keeps the truncation exact below 2^21 tiles
     auto ranges_of = [](int t, int unit, float inv) -> int {
         return min((int)(((float)(t + unit - 1) + 0.5f) * inv), kRangeCap);
@@ -343,10 +342,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     constexpr int kAhead = 2, kBufs = kAhead + 1;
     __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kHalfElems];
     // One span holds a whole chunk here, so a workgroup is a (pair, tile range of its list).
-    int pair = blockIdx.x, kr = 0, ranges = 1;
-    if (pf.slots > 0) {
-        int first;
-        if (!locate_range(v, cu, pf.slots, blockIdx.x, pair, first, ranges)) return;
+    int pair, kr, ranges;
+    const bool once = pf.once != 0;
+    if (pf.slots == 0) {
+        pair = blockIdx.x / pf.ks;
+        kr = (int)blockIdx.x - pair * pf.ks;
+        ranges = pf.ks;
+    } else {
+        int first, all;
+        if (!locate_range(v, cu, pf.slots, blockIdx.x, pair, first, ranges, all)) return;
         kr = (int)blockIdx.x - first;
         if (kr == 0 && threadIdx.x == 0)
             reinterpret_cast<int2*>(pf.part + (size_t)pf.slots * (NW * NQ * 16) * (D + 2))[pair] =
@@ -449,11 +453,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                               (unsigned)wv * (kRowsPerWave * 1024);
     auto stage_tile = [&](const uint16_t* base, int buf) {
         const uint16_t* p = base + my_off;
+        const unsigned dst = lds_rows + (unsigned)buf * (kHalfElems * 2);
+        if (once) {
 #pragma unroll
-        for (int r = 0; r < kRowsPerWave; ++r) {
-            const unsigned dst = lds_rows + (unsigned)buf * (kHalfElems * 2) + r * 1024;
-            if (pf.once) load_row_to_lds_once(p + r * 512, dst);
-            else load_row_to_lds(p + r * 512, dst);
+            for (int r = 0; r < kRowsPerWave; ++r) load_row_to_lds_once(p + r * 512, dst + r * 1024);
+        } else {
+#pragma unroll
+            for (int r = 0; r < kRowsPerWave; ++r) load_row_to_lds(p + r * 512, dst + r * 1024);
         }
     };
     // Everything loaded so far (queries, counts) is waited for here, once: left pending, the
@@ -537,10 +543,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         float lc = l[c];
         lc += __shfl_xor(lc, 16);
         lc += __shfl_xor(lc, 32);
-        if (tok[c] >= 0 && pf.slots > 0) {
+        if (tok[c] >= 0 && (pf.slots > 0 || pf.ks > 1)) {
             // partial of this tile range: un-normalised accumulators, reference, sum
             // layout: [all columns][D] accumulators, then [all columns][2] (m, l)
-            const size_t n_cols = (size_t)pf.slots * (NW * NQ * 16);
+            const size_t n_cols = (size_t)(pf.slots > 0 ? pf.slots : v.n_pairs * pf.ks) * (NW * NQ * 16);
             const size_t pc = (size_t)blockIdx.x * (NW * NQ * 16) + wv * (NQ * 16) + c * 16 + n;
             float* pa = pf.part + pc * D + kc * 4;
 #pragma unroll
@@ -952,10 +958,13 @@ __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t
     if (pf.slots > 0) cut = reinterpret_cast<const int2*>(pf.part + n_cols * (D + 2))[pair];
     const size_t pc0 = (size_t)cut.x * kCols + cs;             // range r: pc0 + r * kCols
     const float* ml = pf.part + n_cols * D;
+    // (unrolled: the loads of several ranges in flight together)
     float M = SPKV_NEG_INF;
+#pragma unroll 8
     for (int r = 0; r < cut.y; ++r) M = fmaxf(M, ml[(pc0 + (size_t)r * kCols) * 2]);
     f32x4 num = {0.f, 0.f, 0.f, 0.f};
     float den = 0.f;
+#pragma unroll 4
     for (int r = 0; r < cut.y; ++r) {
         const size_t pc = pc0 + (size_t)r * kCols;
         const float sc = __builtin_amdgcn_exp2f(ml[pc * 2] - M);      // 0 for a range without keys
@@ -992,7 +1001,7 @@ static SpkvPrefill prefill_params(const SpkvView& v, int n_max, uint16_t* stage,
     pf.nw = sh.nw;
     pf.nq = sh.nq;
     pf.nblk = (n_max + pf.nw * pf.tb - 1) / (pf.nw * pf.tb);   // spans of one workgroup
-    pf.pin_xcd = (v.n_pairs >= 8 && pf.nblk * pf.ks >= 4) ? 1 : 0;
+    pf.pin_xcd = (pf.nw == 8 && v.n_pairs >= 8 && pf.nblk * pf.ks >= 4) ? 1 : 0;
     return pf;
 }
 

@@ -5,10 +5,11 @@ process of its own against hip_recorder.cpp, a HIP runtime that writes launches 
     calls[-1].rc, calls[-1].launches      # [("spkv_decode_split<128, 1, 1>", (grid x, grid y), block), ...]
 
 Script entries: ["append" | "chunk" | "score" | "prefill", tokens per sequence], ["step"], ["attend"],
-["static"], ["predict", d_model, d_hidden], ["reset"], ["logits", tokens, d_model, d_hidden, heads],
+["static"], ["predict", d_model, d_hidden], ["stats"], ["reset"], ["logits", tokens, d_model, d_hidden, heads],
 ["soft", tokens per sequence], ["advance", n], ["option", id, value]; and what the runtime answers from
 there on: ["lengths", per pair] (any read-back of device lengths), ["capture", status, error],
-["event_ready", 0 | 1].
+["event_ready", 0 | 1], ["watch", kernel, argument, byte] (an entry ("watched", (value, 0), 0) before
+every launch of that kernel: the int at that byte of that argument).
 """
 
 import collections

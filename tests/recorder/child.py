@@ -47,6 +47,9 @@ def main():
             rows = (C.c_int32 * len(a[0]))(*a[0])
             rt.rec_device_bytes(rows, C.c_size_t(4 * len(a[0])))
             continue
+        if op == "watch":
+            rt.rec_watch(a[0].encode(), a[1], a[2])
+            continue
         if op in ("capture", "event_ready"):
             getattr(rt, "rec_" + op)(*a)
             continue
@@ -75,6 +78,8 @@ def main():
                                                cfg.head_dim, cfg.window, at, None, zero, at, C.c_size_t(ws), None)
         elif op == "logits":
             rc = lib.spkv_utility_logits(at, at, None, at, None, at, at, *a, None)
+        elif op == "stats":
+            rc = lib.spkv_cache_stats(handle, C.create_string_buffer(4096), None, None)
         elif op == "reset":
             rc = lib.spkv_cache_reset(handle, None)
         elif op == "advance":

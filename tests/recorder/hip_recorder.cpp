@@ -17,6 +17,8 @@ static std::map<const void*, std::string> g_kernel;       // host stub -> mangle
 static std::vector<std::string> g_log;
 static std::vector<unsigned char> g_device_bytes;         // what copies to the host deliver
 static int g_capture_status = 0, g_capture_error = 0, g_last_error = 0, g_event_ready = 1;
+static std::string g_watch;                               // kernels whose argument is read ...
+static int g_watch_arg, g_watch_at;                       // ... the int at this byte of this argument
 static Dim3 g_grid, g_block;
 static size_t g_shared;
 static void* g_stream;
@@ -29,6 +31,7 @@ void rec_device_bytes(const void* p, size_t n) {
 }
 void rec_capture(int status, int error) { g_capture_status = status, g_capture_error = error; }
 void rec_event_ready(int ready) { g_event_ready = ready; }
+void rec_watch(const char* kernel, int arg, int at) { g_watch = kernel, g_watch_arg = arg, g_watch_at = at; }
 int rec_take(char* buf, int cap) {                        // the oldest entry; -1: none
     if (g_log.empty()) return -1;
     std::string s = g_log.front();
@@ -57,7 +60,12 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* shared, void** st
     *grid = g_grid, *block = g_block, *shared = g_shared, *stream = g_stream;
     return 0;
 }
-int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void**, size_t, void*) {
+int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void** args, size_t, void*) {
+    if (!g_watch.empty() && g_kernel[host].find(g_watch) != std::string::npos) {
+        int v;
+        memcpy(&v, static_cast<char*>(args[g_watch_arg]) + g_watch_at, 4);
+        g_log.push_back("watched " + std::to_string(v) + " 0 0");
+    }
     g_log.push_back(g_kernel[host] + " " + std::to_string(grid.x) + " " + std::to_string(grid.y) + " " + std::to_string(block.x));
     return 0;
 }

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from tests import harness as H
+from tests.recorder import record
 import paper_2605_14037_amd as spkv
 from paper_2605_14037_amd.inputs import TokenStream, small_workload, to_numpy_f32
 
@@ -14,10 +15,11 @@ pytestmark = pytest.mark.gpu
 
 
 def _run_prefill(wl, chunk_counts, pre_chunk=4096, q_gain=1.0, sample=None, seed=0, decode_after=0,
-                 shared_workspace=False):
+                 shared_workspace=False, last_grid=None):
     """Feeds wl.ctx_lens through spkv_append, then every entry of chunk_counts through
     spkv_prefill_attention; compares all rows (or `sample` random rows per call).
-    shared_workspace: one workspace, sized once for the longest chunk, serves every call."""
+    shared_workspace: one workspace, sized once for the longest chunk, serves every call.
+    last_grid: workgroups that the attention of the last call is launched with."""
     stream = TokenStream(wl, device="cuda", q_gain=q_gain)
     extra = sum(max(c) for c in chunk_counts) + decode_after + 8
     pool = sum(c + extra for c in wl.ctx_lens) * wl.n_kv_heads      # room for "everything kept"
@@ -30,8 +32,15 @@ def _run_prefill(wl, chunk_counts, pre_chunk=4096, q_gain=1.0, sample=None, seed
         n_top = max(max(c) for c in chunk_counts)
         ws = torch.empty(cache.prefill_workspace_bytes(n_top, n_top * wl.batch), dtype=torch.uint8,
                          device="cuda")
-    for counts in chunk_counts:
+    for call, counts in enumerate(chunk_counts):
         total = sum(counts)
+        if last_grid is not None and call == len(chunk_counts) - 1:
+            held = [c + sum(x[b] for x in chunk_counts[:call]) for b, c in enumerate(wl.ctx_lens)]
+            kept = [n for row in cache.stats(with_kept_len=True)[1] for n in row]
+            got = record(dict(batch=wl.batch, n_q_heads=wl.n_q_heads, n_kv_heads=wl.n_kv_heads,
+                              head_dim=wl.head_dim, window=wl.window),
+                         [["append", held], ["lengths", kept], ["stats"], ["prefill", counts]])[-1]
+            assert [g for n, (g, _), _ in got.launches if "prefill_attend" in n] == [last_grid]
         k, v, f, cu = stream.next_tokens(counts)
         q = stream.next_query(rows=total)
         res = cache.prefill_attention(k, v, f, q, cu, workspace=ws, want_lse=True)
@@ -145,32 +154,31 @@ def test_prefill_one_workspace_for_every_chunk_length(Hq, Hkv, D):
     _run_prefill(wl, [[n, max(1, n // 3)] for n in lens], sample=24, seed=Hq, shared_workspace=True)
 
 
-@pytest.mark.parametrize("B,Hkv,G,D,top,n", [
-    (1, 1, 4, 128, 3000, 16),      # one pair: the cap of ranges per pair; four waves
-    (65, 1, 4, 64, 1500, 8),       # a lane with two pairs; two waves
-    (113, 3, 4, 64, 700, 16),      # 339 pairs: almost every slot taken by a first range
-    (171, 2, 4, 64, 500, 16),      # 342 pairs: not cut
-    (5, 13, 3, 128, 2000, 40),     # two column groups; a group that does not divide 16
-    (2, 8, 4, 128, 17000, 16),     # lists of more than half the last-level cache
+@pytest.mark.parametrize("B,Hkv,G,D,top,n,grid", [
+    (1, 1, 4, 128, 3000, 16, 24),        # one pair: ranges of its own; four waves
+    (1, 1, 4, 128, 42000, 16, 512),      # one pair, the cap of equal ranges per pair
+    (65, 1, 4, 64, 4000, 8, 512),        # a lane with two pairs; two waves
+    (65, 1, 4, 64, 1500, 8, 65 * 8),
+    (113, 3, 4, 64, 700, 16, 512),       # 339 pairs: almost every slot taken by a first range
+    (113, 3, 4, 64, 100, 16, 339),       # nothing worth cutting
+    (171, 2, 4, 64, 500, 16, 342),       # 342 pairs: not cut
+    (5, 13, 3, 128, 2000, 40, 512),      # two column groups; a group that does not divide 16
+    (7, 3, 3, 64, 1200, 40, 21 * 9),     # the same in ranges of every pair
+    (4, 8, 4, 128, 17000, 16, 512),      # lists of more than half the last-level cache
+    (2, 8, 4, 128, 17000, 16, 16 * 32),  # the same, alike: ranges of every pair
 ])
-def test_prefill_short_chunks_in_ranges_of_equal_length(B, Hkv, G, D, top, n):
-    """Few query columns per pair: the tiles of all pairs are cut into ranges of about equal
-    length.  Lengths from empty to long, keep rates from none to all, and sequences without
-    a token in the call."""
+def test_prefill_short_chunks_in_ranges_of_equal_length(B, Hkv, G, D, top, n, grid):
+    """Few query columns per pair: the tiles of every pair, or of all pairs together, are cut into
+    ranges of about equal length.  Lengths from empty to long, keep rates from none to all, and
+    sequences without a token in the call.  The second call finds its lengths known (check_state
+    reads them) and has the workgroups of the case."""
     rng = np.random.default_rng(B)
-    ctx = [top if B <= 2 else (0 if b % 7 == 3 else int(rng.integers(1, top))) for b in range(B)]
+    ctx = [top if B <= 4 else (0 if b % 7 == 3 else int(rng.integers(1, top))) for b in range(B)]
     kinds = np.array([1.0, 1.0, 0.0, 0.3]) if B > 2 else np.array([1.0])
     keep = kinds[np.arange(B * Hkv) % len(kinds)].reshape(B, Hkv)
     wl = small_workload("ranges", B, Hkv * G, Hkv, D, ctx, keep, window=64, seed=B)
     counts = [0 if b % 5 == 4 else (n if b % 3 == 0 else int(rng.integers(1, n + 1))) for b in range(B)]
-    _run_prefill(wl, [counts, [n] * B], sample=200)
-
-
-def test_prefill_calls_with_the_shortest_chunks():
-    """One token for every sequence (handed to the fused decode step), one or two tokens for
-    some (the multi-token step), then lengths just above the hand-over."""
-    wl = small_workload("ptiny", 3, 8, 2, 128, [300, 40, 0], 0.5, seed=23)
-    _run_prefill(wl, [[1, 1, 1], [1, 0, 2], [1, 1, 1], [4, 3, 1], [5, 4, 4], [1, 1, 1]])
+    _run_prefill(wl, [counts, [n] * B], sample=200, last_grid=grid)
 
 
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 8, 2), (64, 6, 2)])

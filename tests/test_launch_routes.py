@@ -58,3 +58,37 @@ def test_reset_is_one_launch():
     were a fifth of the time of feeding 4096 tokens."""
     got = record(dict(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=64), [["append", [4096]], ["reset"]])[1]
     assert got.rc == 0 and [name for name, _, _ in got.launches] == ["spkv_reset"]
+
+
+# ------------------------------------------------------------------ short chunks
+def _chunk_grid(call):
+    (got,) = [grid[0] for name, grid, _ in call.launches if name.startswith("spkv_prefill_attend")]
+    return got
+
+
+@pytest.mark.parametrize("batch,tokens,kept,grid", [
+    (8, 2000, [60 + p % 8 * 70 for p in range(64)], 64 * 5),       # short lists: ranges of every pair
+    (1, 2000, [300] * 8, 8 * 3),
+    (16, 400, [10] * 128, 128),                                    # nothing worth cutting
+    (16, 32768, [3300 + 7600 * (p % 8) // 7 for p in range(128)], 512),    # heads of unlike lists
+    (4, 131072, [2600 + 17000 * (p % 8) // 7 for p in range(32)], 512),
+    (8, 32768, [30000 if p == 5 else 500 for p in range(64)], 512),        # one dense head
+    (64, 8000, [900] * 512, 512)])                                 # more pairs than are cut
+def test_short_chunk_ranges(batch, tokens, kept, grid):
+    """Ranges of equal length over all pairs cost every workgroup a search: only where the lists are
+    long and unlike enough; and the lengths count, not the bound that a prompt has left (all its
+    tokens kept), as soon as a copy of them has arrived."""
+    chunk = ["chunk", [16] * batch]
+    script = [["append", [tokens] * batch], ["lengths", kept], chunk, chunk, chunk]
+    calls = record(dict(batch=batch), script)
+    assert _chunk_grid(calls[3]) == grid
+    copies = [sum(name == "copy" for name, _, _ in c.launches) for c in calls]
+    assert copies == [0, 0, 1, 0]                  # a single chunk after a prompt is not charged for one
+
+
+@pytest.mark.parametrize("batch,tokens,pairs_grid", [(8, 2000, 64 * 8), (1, 500, 8 * 4), (64, 4000, 512)])
+def test_short_chunk_right_after_a_prompt(batch, tokens, pairs_grid):
+    """The bound alone (nothing copied yet) takes the equal ranges for long lists only."""
+    got = record(dict(batch=batch), [["append", [tokens] * batch], ["event_ready", 0], ["chunk", [16] * batch]])[1]
+    assert _chunk_grid(got) == pairs_grid
+
