@@ -1029,10 +1029,8 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
     if (short_chunk) {
         slots = ks > 1 ? spkv_prefill_slots(c->carve.n_pairs, sh, c->cfg.head_dim, part_bytes) : 0;
         if (slots > 0 && !ranges_over_all_pairs(ks, spans, slots, known_longest, all, c->lists_known)) slots = 0;
-        if (slots > 0) ks = 1;      // (ranges cut on the device)
-        int64_t bound = 0;
-        for (int p = 0; p < c->carve.n_pairs; ++p) bound += c->L_ub[p];
-        once = bound * (4 * c->cfg.head_dim) > kOnceBytes;
+        if (slots > 0) ks = 1;      // (ranges cut on the device, which also decides `once` then)
+        once = c->lists_known && all * (int64_t)(kHalfTokens * 4 * c->cfg.head_dim) > kOnceBytes;
     }
     if (spkv_launch_prefill(c->view, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
                             util_logits, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),

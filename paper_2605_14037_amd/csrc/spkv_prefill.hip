@@ -35,7 +35,7 @@ struct SpkvPrefill {
     int32_t   ks;        // workgroups per span, its tiles are cut into ks ranges (split-K)
     int32_t   slots;     // > 0 (fewer than eight waves): ranges of about equal length over all pairs
                          // instead, at most this many in all
-    int32_t   once;      // fewer than eight waves: the lists pass the caches by (kOnceBytes)
+    int32_t   once;      // fewer than eight waves, slots = 0: the lists pass the caches by (kOnceBytes)
     float*    part;      // partial (acc, m, l) of every (range, column); slots > 0: then [n_pairs] int2
                          // (first range, ranges) of every pair
 };
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kHalfElems];
     // One span holds a whole chunk here, so a workgroup is a (pair, tile range of its list).
     int pair, kr, ranges;
-    const bool once = pf.once != 0;
+    bool once = pf.once != 0;
     if (pf.slots == 0) {
         pair = blockIdx.x / pf.ks;
         kr = (int)blockIdx.x - pair * pf.ks;
@@ -352,6 +352,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         int first, all;
         if (!locate_range(v, cu, pf.slots, blockIdx.x, pair, first, ranges, all)) return;
         kr = (int)blockIdx.x - first;
+        once = (int64_t)all * (2 * kHalfElems) > kOnceBytes;
         if (kr == 0 && threadIdx.x == 0)
             reinterpret_cast<int2*>(pf.part + (size_t)pf.slots * (NW * NQ * 16) * (D + 2))[pair] =
                 make_int2(first, ranges);

@@ -92,3 +92,15 @@ def test_short_chunk_right_after_a_prompt(batch, tokens, pairs_grid):
     got = record(dict(batch=batch), [["append", [tokens] * batch], ["event_ready", 0], ["chunk", [16] * batch]])[1]
     assert _chunk_grid(got) == pairs_grid
 
+
+@pytest.mark.parametrize("kept,once", [(100, 0), (340, 0), (400, 1), (3000, 1)])
+def test_short_chunk_reads_past_the_caches_by_the_kept_bytes(kept, once):
+    """512 pairs of 8000 tokens: 128 MB are 8192 tiles of 32 keys, 16 per pair, five of them the
+    window's.  The bound after the prompt (2 GB) must not decide."""
+    at_ks, at_once = 52, 60                                        # bytes of SpkvPrefill, argument 5
+    for at, want in ((at_ks, [1, 1, 1]), (at_once, [0, 0, once])):
+        chunk = ["chunk", [16] * 64]
+        script = [["append", [8000] * 64], ["lengths", [kept] * 512], ["watch", "spkv_prefill_attend", 5, at],
+                  chunk, chunk, chunk]
+        calls = record(dict(batch=64), script)[1:]
+        assert [x for c in calls for n, (x, _), _ in c.launches if n == "watched"] == want
