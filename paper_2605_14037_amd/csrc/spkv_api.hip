@@ -384,6 +384,27 @@ bool worth_gapless(const spkv_cache* c, const SpkvSplit& plain, int64_t items) {
     for (int p = 0; p < n; ++p) keys += c->L_ub[p];
     return keys >= (int64_t)n * kGapMeanKeys;
 }
+// The same for a multi-token step of one column group, whose gapless items are fewer (four per
+// compute unit) and up to five half-pages long a chain that short lists have no use for: not below
+// 24 half-pages a pair on average, and not between few pairs (whose many partial results of the
+// plain numbering cost more to merge) and five half-pages an item unless the lists are uneven.  Plain
+// / gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7; 48 x 8 of 500-1000 34 / 37; 48 x 3
+// of 2k-4k 26 / 28; but 8 heads of 40k 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of 4k-16k 73 / 69, 16 x 8 of
+// 1k-4k with dense and local-only heads 38 / 35, 32 x 8 of 8k-32k so 275 / 189.
+constexpr int kGapFewChunkPairs = 32, kGapChunkPairHps = 24, kGapChunkItemHps = 5;
+bool worth_gapless_chunk(const spkv_cache* c, int items) {
+    const int n = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
+    if (n > kCompactChunkPairs) return false;
+    int64_t sum = 0, longest = 0;                          // half-pages
+    for (int p = 0; p < n; ++p) {
+        const int Tw = std::min(c->T[p / Hkv], c->cfg.window);
+        const int64_t hp = (c->L_ub[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
+        sum += hp;
+        longest = std::max(longest, hp);
+    }
+    if (sum < (int64_t)n * kGapChunkPairHps) return false;
+    return n <= kGapFewChunkPairs || sum >= (int64_t)items * kGapChunkItemHps || longest * n >= sum * kGapRatio;
+}
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap,
                        bool gapless = true) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
@@ -908,12 +929,11 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     // With two or four column groups a wave needs most of the register file and only one or
     // two fit a SIMD; one resident round of such items then reads too little at a time, and
     // about 1 800 items (two rounds of the widest kernel) measured 12-15 % faster.
-    // One column group takes the gapless numbering with few items (spkv_chunk_split_compact) while
-    // a pair has several of them on average (4 tokens: 48 sequences x 8 heads of 2k-4k
-    // 57.7 -> 56.7 us, 64 x 8 of 1k-30k 185.7 -> 186.8, 128 x 8 of 0.5k-16k 233 -> 275).
-    const bool compact = groups == 1 && c->carve.n_pairs <= kCompactChunkPairs && c->item_target <= 0;
+    // One column group may take the gapless numbering with few items (spkv_chunk_split_compact).
+    const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
+    const bool compact = groups == 1 && c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
     int64_t items = 0;
-    c->split = choose_split_mw(c, compact ? c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu : std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
+    c->split = choose_split_mw(c, compact ? chunk_items : std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
                                slot_cap, 1, &items);
     if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
     room_to_grow(c, s);

@@ -22,6 +22,21 @@ def test_unanswered_capture_query_leaves_no_error_behind(call):
     assert "compact" in got.launches[0][0]           # the route that asks
 
 
+@pytest.mark.parametrize("batch,kept,gapless", [
+    (48, [150] * 384, False),                        # short lists
+    (24, [700] * 192, False),                        # 26 half-pages a pair, under five an item
+    (24, [900] * 192, True),
+    (24, [5000 if p % 8 == 0 else 100 for p in range(192)], True),     # uneven
+    (4, [800] * 32, True),                           # few pairs
+    (4, [600] * 32, False),
+    (49, [4000] * 392, False)])                      # more pairs than it pays for
+def test_gapless_numbering_of_drafts(batch, kept, gapless):
+    """Few items per compute unit make long chains of short lists (192 pairs of 300 keys: 25 us plain,
+    28 gapless)."""
+    got = record(dict(batch=batch), [["append", [8192] * batch], ["lengths", kept], ["score", [4] * batch]])[-1]
+    assert got.rc == 0 and got.launches[0][0].startswith("spkv_chunk_split_compact" if gapless else "spkv_chunk_split<")
+
+
 # ------------------------------------------------------------------ utility predictor
 @pytest.mark.parametrize("tokens,d_model,d_hidden,kernel", [
     (4096, 4096, 16, "spkv_predictor_hidden"), (4096, 4096, 48, "spkv_predictor_hidden"),
