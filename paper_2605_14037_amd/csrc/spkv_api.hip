@@ -388,10 +388,11 @@ bool worth_gapless(const spkv_cache* c, const SpkvSplit& plain, int64_t items) {
 // compute unit) and up to five half-pages long a chain that short lists have no use for: not below
 // 24 half-pages a pair on average, and not between few pairs (whose many partial results of the
 // plain numbering cost more to merge) and five half-pages an item unless the lists are uneven.  Plain
-// / gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7; 48 x 8 of 500-1000 34 / 37; 48 x 3
-// of 2k-4k 26 / 28; but 8 heads of 40k 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of 4k-16k 73 / 69, 16 x 8 of
-// 1k-4k with dense and local-only heads 38 / 35, 32 x 8 of 8k-32k so 275 / 189.
-constexpr int kGapFewChunkPairs = 32, kGapChunkPairHps = 24, kGapChunkItemHps = 5;
+// / gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7; 48 x 8 of 500-1000 34 / 37;
+// 48 x 3 of 2k-4k 26 / 28; 24 x 2 heads of 64, 8k-16k 23 / 25; but 8 x 8 of 4k 28 / 26, 8 heads of 40k
+// 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of 4k-16k 73 / 69, 16 x 8 of 1k-4k with dense and
+// local-only heads 38 / 35, 32 x 8 of 8k-32k so 275 / 189.
+constexpr int kGapFewChunkPairs = 64, kGapChunkPairHps = 24, kGapChunkItemHps = 5;     // (32 with head_dim 64)
 bool worth_gapless_chunk(const spkv_cache* c, int items) {
     const int n = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
     if (n > kCompactChunkPairs) return false;
@@ -403,7 +404,8 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
         longest = std::max(longest, hp);
     }
     if (sum < (int64_t)n * kGapChunkPairHps) return false;
-    return n <= kGapFewChunkPairs || sum >= (int64_t)items * kGapChunkItemHps || longest * n >= sum * kGapRatio;
+    return n * 128 <= kGapFewChunkPairs * c->cfg.head_dim || sum >= (int64_t)items * kGapChunkItemHps ||
+           longest * n >= sum * kGapRatio;
 }
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap,
                        bool gapless = true) {
@@ -929,7 +931,7 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     // With two or four column groups a wave needs most of the register file and only one or
     // two fit a SIMD; one resident round of such items then reads too little at a time, and
     // about 1 800 items (two rounds of the widest kernel) measured 12-15 % faster.
-    // One column group may take the gapless numbering with few items (spkv_chunk_split_compact).
+    // One column group may take the gapless numbering with few items (spkv_chunk_split<D, 1, true>).
     const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
     const bool compact = groups == 1 && c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
     int64_t items = 0;

@@ -742,151 +742,148 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
 // indicator 0 <= t - s < w with t = T + i); otherwise it counts only if its logit passes the
 // gate (Eq. 3-4).  The chunk's own keys (causal, always inside the window because the
 // chunk is not longer than the window) are added by spkv_chunk_combine.
-template <int D, int NQ>
-__device__ __forceinline__ void chunk_item(const SpkvView& v, const uint16_t* __restrict__ q,
-                                           float scale_log2e, SpkvSplit sp, const SpkvCu& cu,
-                                           const PairSplit& ps, int pair, int j) {
-    constexpr int NS = D / 32, NB = D / 16;
-    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
-    const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
-    if (n_tok == 0) return;
-    const int cols = n_tok * v.G;
-    const int hbase = ps.nhp / ps.items, hrem = ps.nhp - hbase * ps.items;
-    const int hp0 = j * hbase + min(j, hrem);
-    const int hp1 = hp0 + hbase + (j < hrem ? 1 : 0);
-    const int lane = threadIdx.x & 63, kc = lane >> 4, n = lane & 15;
-
-    bf16x8 qb[NQ][NS];
-    int tok_of_col[NQ];
-#pragma unroll
-    for (int c = 0; c < NQ; ++c) {
-        const int col = c * 16 + n;
-        const int i = col / v.G, g = col - i * v.G;
-        tok_of_col[c] = i;
-        const uint16_t* qrow = q + ((size_t)(row0 + i) * v.Hq + (size_t)h * v.G + g) * D + kc * 8;
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl) {
-            uint4 raw = {0u, 0u, 0u, 0u};
-            if (col < cols) raw = *reinterpret_cast<const uint4*>(qrow + sl * 32);
-            qb[c][sl] = __builtin_bit_cast(bf16x8, raw);
-        }
-    }
-    f32x4 acc[NQ][NB];
-    float m[NQ], l[NQ];
-#pragma unroll
-    for (int c = 0; c < NQ; ++c) {
-        m[c] = SPKV_NEG_INF;
-        l[c] = 0.f;
-#pragma unroll
-        for (int i = 0; i < NB; ++i) acc[c][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    }
-    const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
-    const float* rl = v.ring_logit + (size_t)pair * v.w;
-    const int t_mod = ps.T % v.w;
-
-    int hp = hp0;
-    while (hp < hp1) {
-        const int pbase = hp >> 1;
-        const int my_page = pt[min(pbase + lane, v.pt_cap - 1)];
-        const int hp_end = min(hp1, (pbase + 64) << 1);
-        for (; hp < hp_end; ++hp) {
-            const uint16_t* base;
-            int nvalid;
-            const bool ring = hp >= ps.ghp;
-            if (!ring) {
-                const int page = __builtin_amdgcn_readlane(my_page, (hp >> 1) - pbase);
-                base = pool_page(v, page) + (hp & 1) * (2 * kHalfTokens * D);
-                nvalid = min(kHalfTokens, ps.L - hp * kHalfTokens);
-            } else {
-                const int r = hp - ps.ghp;
-                base = ring_page(v, pair, r >> 1) + (r & 1) * (2 * kHalfTokens * D);
-                nvalid = min(kHalfTokens, ps.Tw - r * kHalfTokens);
-            }
-            // keys past the valid length (same for every column)
-            unsigned kill_len = 0u;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (kc * 8 + e >= nvalid) kill_len |= 1u << e;
-            // ring keys: age and gate of this lane's eight keys
-            int age[8];
-            unsigned gate_ok = 0u;
-            if (ring) {
-                const int x0 = (hp - ps.ghp) * kHalfTokens + kc * 8;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int x = x0 + e;
-                    age[e] = ps.T >= v.w ? (x - t_mod + v.w) % v.w : x + v.w - ps.T;
-                    if (kc * 8 + e < nvalid && gate_passes(v, rl[x], ps.T - v.w + age[e])) gate_ok |= 1u << e;
-                }
-            }
-            const uint16_t* kp = base + lane * 8;
-            const uint16_t* vp = base + kHalfTokens * D + lane * 8;
-            bf16x8 ka[2][NS], va[NB];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int sl = 0; sl < NS; ++sl)
-                    ka[t][sl] = load_stream_b128(kp + (t * (D / 8) + sl * 4) * 128);
-#pragma unroll
-            for (int db = 0; db < NB; ++db) va[db] = load_stream_b128(vp + db * 512);
-
-#pragma unroll
-            for (int c = 0; c < NQ; ++c) {
-                unsigned kill = kill_len;
-                if (ring) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (!(age[e] > tok_of_col[c] || ((gate_ok >> e) & 1u))) kill |= 1u << e;
-                }
-                attend_half_page<D>(ka, va, qb[c], kill, ring || nvalid < kHalfTokens, scale_log2e,
-                                    acc[c], m[c], l[c]);
-            }
-        }
-    }
-
-    const size_t slot = (size_t)pair * sp.slots + j;
-#pragma unroll
-    for (int c = 0; c < NQ; ++c) {
-        float lc = l[c];
-        lc += __shfl_xor(lc, 16);
-        lc += __shfl_xor(lc, 32);
-        const int col = c * 16 + n;
-        if (col < cols) {
-            float* pa = v.part_acc + ((slot * (NQ * 16) + col) * D) + kc * 4;
-#pragma unroll
-            for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(pa + db * 16) = acc[c][db];
-            if (kc == 0) {
-                float* pm = v.part_ml + (slot * (NQ * 16) + col) * 2;
-                pm[0] = m[c];
-                pm[1] = lc;
-            }
-        }
-    }
-}
-
-template <int D, int NQ>
-__global__ __launch_bounds__(64) void spkv_chunk_split(SpkvView v, const uint16_t* __restrict__ q,
-                                                       float scale_log2e, SpkvSplit sp, SpkvCu cu) {
-    const int pair = blockIdx.x / sp.slots;
-    const int j = blockIdx.x - pair * sp.slots;
-    const PairSplit ps = pair_split(v, pair, sp);
-    if (j == 0 && threadIdx.x == 0) v.pair_items[pair] = ps.items;
-    if (j < ps.items) chunk_item<D, NQ>(v, q, scale_log2e, sp, cu, ps, pair, j);
-}
-
-// One column group, workgroups numbered without gaps (see decode_split_compact), four waves per
-// compute unit: a partial result has 16 columns here, four times a decode item's, so fewer items
-// pay (16 sequences of 32k, 4 drafts: 103 us plain with 1960 items, 101.6 / 99.4 / 97.4 / 96.7 with
-// 1792 / 1536 / 1280 / 1024 without gaps; 40 of 2k-20k mixed 146 -> 133; 4 of 128k 56 -> 52).
-template <int D>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_chunk_split_compact(
+//
+// GAPLESS (one column group only): workgroups numbered without gaps (see decode_split_compact), four
+// waves per compute unit: a partial result has 16 columns here, four times a decode item's, so fewer
+// items pay (16 sequences of 32k, 4 drafts: 103 us plain with 1960 items, 101.6 / 99.4 / 97.4 / 96.7
+// with 1792 / 1536 / 1280 / 1024 without gaps; 40 of 2k-20k mixed 146 -> 133; 4 of 128k 56 -> 52).
+// (One body for both, in the kernel itself: as a function that the two numberings call it is
+// scheduled differently, 2 to 4 % slower with four column groups.)
+template <int D, int NQ, bool GAPLESS>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GAPLESS ? 2 : 1, GAPLESS ? 2 : 10))) void spkv_chunk_split(
     SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp, SpkvCu cu) {
-    int id = blockIdx.x, total, pair, j;
+    constexpr int NS = D / 32, NB = D / 16;
+    int id = blockIdx.x, total = 0;
     do {
-        if (!locate_item<true>(v, sp, id, total, pair, j)) return;
-        chunk_item<D, 1>(v, q, scale_log2e, sp, cu, pair_split(v, pair, sp), pair, j);
+        int pair, j;
+        if constexpr (GAPLESS) {
+            if (!locate_item<true>(v, sp, id, total, pair, j)) return;
+        } else {
+            pair = blockIdx.x / sp.slots;
+            j = blockIdx.x - pair * sp.slots;
+        }
+        const PairSplit ps = pair_split(v, pair, sp);
+        if (!GAPLESS) {
+            if (j == 0 && threadIdx.x == 0) v.pair_items[pair] = ps.items;
+            if (j >= ps.items) return;
+        }
+        const int b = pair / v.Hkv, h = pair - b * v.Hkv;
+        const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
+        if (n_tok == 0) { if (!GAPLESS) return; id += (int)gridDim.x; continue; }
+        const int cols = n_tok * v.G;
+        const int hbase = ps.nhp / ps.items, hrem = ps.nhp - hbase * ps.items;
+        const int hp0 = j * hbase + min(j, hrem);
+        const int hp1 = hp0 + hbase + (j < hrem ? 1 : 0);
+        const int lane = GAPLESS ? threadIdx.x & 63 : threadIdx.x, kc = lane >> 4, n = lane & 15;
+
+        bf16x8 qb[NQ][NS];
+        int tok_of_col[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) {
+            const int col = c * 16 + n;
+            const int i = col / v.G, g = col - i * v.G;
+            tok_of_col[c] = i;
+            const uint16_t* qrow = q + ((size_t)(row0 + i) * v.Hq + (size_t)h * v.G + g) * D + kc * 8;
+#pragma unroll
+            for (int sl = 0; sl < NS; ++sl) {
+                uint4 raw = {0u, 0u, 0u, 0u};
+                if (col < cols) raw = *reinterpret_cast<const uint4*>(qrow + sl * 32);
+                qb[c][sl] = __builtin_bit_cast(bf16x8, raw);
+            }
+        }
+        f32x4 acc[NQ][NB];
+        float m[NQ], l[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) {
+            m[c] = SPKV_NEG_INF;
+            l[c] = 0.f;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) acc[c][i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
+        const float* rl = v.ring_logit + (size_t)pair * v.w;
+        const int t_mod = ps.T % v.w;
+
+        int hp = hp0;
+        while (hp < hp1) {
+            const int pbase = hp >> 1;
+            const int my_page = pt[min(pbase + lane, v.pt_cap - 1)];
+            const int hp_end = min(hp1, (pbase + 64) << 1);
+            for (; hp < hp_end; ++hp) {
+                const uint16_t* base;
+                int nvalid;
+                const bool ring = hp >= ps.ghp;
+                if (!ring) {
+                    const int page = __builtin_amdgcn_readlane(my_page, (hp >> 1) - pbase);
+                    base = pool_page(v, page) + (hp & 1) * (2 * kHalfTokens * D);
+                    nvalid = min(kHalfTokens, ps.L - hp * kHalfTokens);
+                } else {
+                    const int r = hp - ps.ghp;
+                    base = ring_page(v, pair, r >> 1) + (r & 1) * (2 * kHalfTokens * D);
+                    nvalid = min(kHalfTokens, ps.Tw - r * kHalfTokens);
+                }
+                // keys past the valid length (same for every column)
+                unsigned kill_len = 0u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (kc * 8 + e >= nvalid) kill_len |= 1u << e;
+                // ring keys: age and gate of this lane's eight keys
+                int age[8];
+                unsigned gate_ok = 0u;
+                if (ring) {
+                    const int x0 = (hp - ps.ghp) * kHalfTokens + kc * 8;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int x = x0 + e;
+                        age[e] = ps.T >= v.w ? (x - t_mod + v.w) % v.w : x + v.w - ps.T;
+                        if (kc * 8 + e < nvalid && gate_passes(v, rl[x], ps.T - v.w + age[e])) gate_ok |= 1u << e;
+                    }
+                }
+                const uint16_t* kp = base + lane * 8;
+                const uint16_t* vp = base + kHalfTokens * D + lane * 8;
+                bf16x8 ka[2][NS], va[NB];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int sl = 0; sl < NS; ++sl)
+                        ka[t][sl] = load_stream_b128(kp + (t * (D / 8) + sl * 4) * 128);
+#pragma unroll
+                for (int db = 0; db < NB; ++db) va[db] = load_stream_b128(vp + db * 512);
+
+#pragma unroll
+                for (int c = 0; c < NQ; ++c) {
+                    unsigned kill = kill_len;
+                    if (ring) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (!(age[e] > tok_of_col[c] || ((gate_ok >> e) & 1u))) kill |= 1u << e;
+                    }
+                    attend_half_page<D>(ka, va, qb[c], kill, ring || nvalid < kHalfTokens, scale_log2e,
+                                        acc[c], m[c], l[c]);
+                }
+            }
+        }
+
+        const size_t slot = (size_t)pair * sp.slots + j;
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) {
+            float lc = l[c];
+            lc += __shfl_xor(lc, 16);
+            lc += __shfl_xor(lc, 32);
+            const int col = c * 16 + n;
+            if (col < cols) {
+                float* pa = v.part_acc + ((slot * (NQ * 16) + col) * D) + kc * 4;
+#pragma unroll
+                for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(pa + db * 16) = acc[c][db];
+                if (kc == 0) {
+                    float* pm = v.part_ml + (slot * (NQ * 16) + col) * 2;
+                    pm[0] = m[c];
+                    pm[1] = lc;
+                }
+            }
+        }
         id += (int)gridDim.x;
-    } while (id < total);
+    } while (GAPLESS && id < total);
 }
 
 // Merge for one (pair, column = token i, head g): the split-K partials plus one term per
@@ -983,8 +980,8 @@ static hipError_t launch_chunk(const SpkvView& v, const uint16_t* k, const uint1
                                const uint16_t* q, uint16_t* out, float* lse, float scale_log2e,
                                SpkvSplit sp, const SpkvCu& cu, hipStream_t s) {
     const unsigned grid = (unsigned)v.n_pairs * (unsigned)sp.slots;
-    if (NQ == 1 && sp.compact > 0) spkv_chunk_split_compact<D><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
-    else spkv_chunk_split<D, NQ><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    if (NQ == 1 && sp.compact > 0) spkv_chunk_split<D, 1, true><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    else spkv_chunk_split<D, NQ, false><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
     spkv_chunk_combine<D><<<dim3(v.n_pairs * NQ * 16), dim3(256), 0, s>>>(
         v, q, k, vv, out, lse, scale_log2e, sp, cu, NQ * 16);
     return hipGetLastError();
@@ -1010,13 +1007,13 @@ int spkv_chunk_resident_items(int head_dim, int col_groups) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     hipError_t e;
     if (head_dim == 128) {
-        if (col_groups <= 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 1>, 64, 0);
-        else if (col_groups == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 2>, 64, 0);
-        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 4>, 64, 0);
+        if (col_groups <= 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 1, false>, 64, 0);
+        else if (col_groups == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 2, false>, 64, 0);
+        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 4, false>, 64, 0);
     } else {
-        if (col_groups <= 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 1>, 64, 0);
-        else if (col_groups == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 2>, 64, 0);
-        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 4>, 64, 0);
+        if (col_groups <= 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 1, false>, 64, 0);
+        else if (col_groups == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 2, false>, 64, 0);
+        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 4, false>, 64, 0);
     }
     if (e != hipSuccess || per_cu <= 0 || cus <= 0) return 0;
     return per_cu * cus;

@@ -19,7 +19,8 @@ def test_unanswered_capture_query_leaves_no_error_behind(call):
     setup = [["append", [8192] * 16], ["lengths", _uneven(128, 6000)], ["attend"], ["capture", 0, 906]]
     got = record(dict(batch=16), setup + [call])[-1]
     assert got.rc == 0
-    assert "compact" in got.launches[0][0]           # the route that asks
+    assert got.launches[0][0] in ("spkv_decode_split_compact<128, 1>", "spkv_decode_split_compact<128, 0>",
+                                  "spkv_chunk_split<128, 1, 1>")     # the routes that ask
 
 
 @pytest.mark.parametrize("batch,kept,gapless", [
@@ -27,14 +28,14 @@ def test_unanswered_capture_query_leaves_no_error_behind(call):
     (24, [700] * 192, False),                        # 26 half-pages a pair, under five an item
     (24, [900] * 192, True),
     (24, [5000 if p % 8 == 0 else 100 for p in range(192)], True),     # uneven
-    (4, [800] * 32, True),                           # few pairs
-    (4, [600] * 32, False),
+    (8, [800] * 64, True),                           # few pairs
+    (8, [600] * 64, False),
     (49, [4000] * 392, False)])                      # more pairs than it pays for
 def test_gapless_numbering_of_drafts(batch, kept, gapless):
     """Few items per compute unit make long chains of short lists (192 pairs of 300 keys: 25 us plain,
     28 gapless)."""
     got = record(dict(batch=batch), [["append", [8192] * batch], ["lengths", kept], ["score", [4] * batch]])[-1]
-    assert got.rc == 0 and got.launches[0][0].startswith("spkv_chunk_split_compact" if gapless else "spkv_chunk_split<")
+    assert got.rc == 0 and got.launches[0][0] == f"spkv_chunk_split<128, 1, {int(gapless)}>"
 
 
 # ------------------------------------------------------------------ utility predictor
