@@ -769,7 +769,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GAPLESS ? 2 
         }
         const int b = pair / v.Hkv, h = pair - b * v.Hkv;
         const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
-        if (n_tok == 0) { if (!GAPLESS) return; id += (int)gridDim.x; continue; }
+        if (n_tok == 0) {
+            if (!GAPLESS) return;
+            id += (int)gridDim.x;
+            continue;
+        }
         const int cols = n_tok * v.G;
         const int hbase = ps.nhp / ps.items, hrem = ps.nhp - hbase * ps.items;
         const int hp0 = j * hbase + min(j, hrem);

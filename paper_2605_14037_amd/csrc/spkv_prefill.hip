@@ -891,6 +891,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const float* b0 = &s_bias[SOFT ? buf : 0][wb][0];
         const float* b1 = &s_bias[SOFT ? nb : 0][wb][0];
         unit(s0, s1, x, t0, b0, t0 + kHalfElems, t1, b1, [&]() { stage_step(x + 6, (buf + 3) & 3); });
+        if (x + 1 >= x_end) break;               // (an odd last half-page: nothing left to read or wait for)
         unit(s1, s0, x + 1, t0 + kHalfElems, b0 + b32, t1, t1 + kHalfElems, b1 + b32, [&]() {});
         wait_loads_but<kCopies>();               // all but the newest: the step after next has landed
         __syncthreads();
