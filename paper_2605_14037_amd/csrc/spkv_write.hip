@@ -399,14 +399,16 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
     if (any_bad) return;
     const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
 
-    // (d) move the kept ring rows, 256 ring positions at a time
+    // (d) move the kept ring rows, 256 ring positions at a time; without MOVE only their ranks are
+    //     wanted, for the prefix counts
+    if (!MOVE && prefix == nullptr) return;
     int done = 0;
     for (int base = 0; base < nr; base += 256) {
         const int idx = base + tid;
         const bool flag = idx < nr && gate_passes(v, base == 0 ? rl_first : rl[(r0 + idx) % v.w], r0 + idx);
         int tot;
         const int rank = block_excl_scan(flag ? 1 : 0, s_w, tot);
-        if (flag) s_list[rank] = (uint16_t)tid;
+        if (MOVE && flag) s_list[rank] = (uint16_t)tid;
         if (prefix != nullptr && idx < nr) {
             const int i = r0 + idx + v.w - T_old;      // the new token whose t - w is this position
             prefix[((size_t)cu.v[b] + i) * v.Hkv + (pair - b * v.Hkv)] = L_old + done + rank + (flag ? 1 : 0);
