@@ -361,17 +361,17 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // Caches of more pairs take one item per workgroup, and where their lists are uneven
 // (worth_gapless) the gapless numbering (spkv_decode_split_compact) with seven items per
 // compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
-// one-launch step keep the plain numbering, and so does the step with the predictor (gapless =
-// false): its workgroups come first in the launch and shift the items' start, and the gapless
-// numbering gave 82.6 us against 84.4 on 16 sequences of 32k but 64.2 against 62.9 on 32 of 16k
-// and 121.5 against 116.3 on 64 of 1k-30k.
+// one-launch step keep the plain numbering.
 constexpr int kMergePairs = 32, kCompactItemsPerCu = 7, kCompactChunkItemsPerCu = 4,
               kCompactChunkPairs = 384;
 // Where the gapless numbering is worth its search and its longer items: at least three slots to
-// an item.  Step, plain -> gapless: dense, sparse and local-only heads mixed, 64 sequences of
-// 1k-64k 604 -> 500 us, 40 of 2k-20k 131 -> 110, 24 of 1k-30k 116 -> 96, 16 of 4k-8k 36 -> 33; but
-// with less between the lists, equal ones of 32 sequences of 16k (one slot to an item)
-// 63.2 -> 65.8, 64 of 1k-30k 117 -> 123 and 163 -> 169, 128 of 0.5k-16k 195 -> 207.
+// an item.  Step, plain -> gapless, us: dense, sparse and local-only heads mixed (four to five slots an
+// item), 64 sequences of 1k-64k 604 -> 500, 40 of 2k-20k 131 -> 110, 24 of 1k-30k 116 -> 96, 16 of 4k-8k
+// 36 -> 33, and with the predictor inside 641 -> 512, 128 -> 114, 103 -> 98, 37 -> 34.  Sparse heads
+// alone (one to 2.7 slots an item) gain or lose a few percent in no order that slots, lengths or the
+// share per XCD would tell apart, and stay plain: 16 of 32k 82.6 -> 81.3 (all kept 322 -> 313), 40 of 16k
+// 104.7 -> 104.5, 24 of 20k 77.8 -> 77.1, but 32 of 16k 61.1 -> 63.3, 64 of 1k-30k 158 -> 163, 128 of
+// 0.5k-16k 195 -> 207.
 // The search costs more with more lengths per lane: above 384 pairs the lists must be worth it (64
 // sequences x 8 heads mixed, 300-3000 tokens, 400 keys a pair: 45 -> 51; 100 x 8 of 1k-12k,
 // 2300 keys: 201 -> 181).
@@ -407,8 +407,7 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
     return n * 128 <= kGapFewChunkPairs * c->cfg.head_dim || sum >= (int64_t)items * kGapChunkItemHps ||
            longest * n >= sum * kGapRatio;
 }
-SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap,
-                       bool gapless = true) {
+SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     int64_t items_one = 0;
     const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
@@ -421,7 +420,7 @@ SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_t
         }
         return one;
     }
-    if (!gapless || c->item_target > 0 || c->step_launches == 1 || !worth_gapless(c, one, items_one))
+    if (c->item_target > 0 || c->step_launches == 1 || !worth_gapless(c, one, items_one))
         return one;
     SpkvSplit sp = choose_split_mw(c, c->compact_items, slots_total_cap, 1, &items_one);
     sp.compact = (int32_t)std::max<int64_t>(1, items_one);
@@ -430,8 +429,8 @@ SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_t
 
 // A captured launch is replayed while the lists grow: until every pair has gained a whole item,
 // one workgroup more per pair has a place for every item.  Without them a replay gives some
-// workgroups a second item and waits for those (33 replays of a step at 16 sequences of 32k:
-// 89 us per step against 77 eager).  Eager launches take none: the host's bound is never short.
+// workgroups a second item and waits for those.  Eager launches take none: the host's bound is never
+// short.
 void room_to_grow(spkv_cache* c, hipStream_t s) {
     if (c->split.compact == 0) return;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -770,7 +769,8 @@ int spkv_decode_step_predict(spkv_cache_t* c, const void* hidden, const void* w1
     // the predictor's workgroups share the launch: leave them room in the resident round
     const int n_pred = spkv_predict_blocks(c->cfg.batch, d_hidden);
     c->split = choose_split(c, std::max(c->carve.n_pairs, c->one_round_items - n_pred),
-                            c->carve.max_items, false);
+                            c->carve.max_items);
+    room_to_grow(c, s);
     SpkvPredict pr = {};
     pr.x = static_cast<const uint16_t*>(hidden);
     pr.w1 = static_cast<const uint16_t*>(w1);

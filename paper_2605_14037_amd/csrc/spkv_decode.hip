@@ -425,14 +425,9 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split(SpkvView v, const u
 // items depends on the pattern of the lengths; the compute unit (or die) that gets the most sets
 // the time.  Without gaps the items spread evenly whatever the lengths are, and fewer of them
 // do: seven waves per compute unit (1792 items) keep enough bytes in flight, store fewer partials
-// and leave room for a compute unit that is handed one more.  Measured, plain with 2944 items
-// against this with 1792 (step time, us): 64 sequences of 1k-64k tokens with a quarter of the heads
-// dense and a quarter local (3.0 GB) 535 -> 466; the same with sparse heads only (1.6 GB) 263 -> 266;
-// 24 of 1k-40k mixed 139 -> 118; 40 of 16k 101 -> 88; 16 of 32k 83.3 -> 81.5; 16 dense of 32k
-// 322 -> 313; head_dim 64, 60 of 1k-64k mixed 100 -> 90.  1300 items: 2 to 19 % more than 1792;
-// 2944: 1 to 4 % more.  The prefix sum costs about 1 us of every wave's start.
-// Even lists gain or lose a few percent either way, so the host takes this numbering for uneven
-// ones only (worth_gapless).
+// and leave room for a compute unit that is handed one more (1300 items: 2 to 19 % longer; 2944: 1 to
+// 4 %).  The prefix sum costs about 1 us of every wave's start.  The host takes this numbering for
+// uneven lists only (worth_gapless, with the times of both).
 // n_wg comes from the host's bound of the lengths, with a workgroup more per pair in a captured
 // launch; when a replayed graph has outgrown that, workgroups take a second item.
 // Item `id` of all pairs' items in order: its pair and its index there; false past the last one.
@@ -530,6 +525,18 @@ __global__ __launch_bounds__(64 * MW) void spkv_decode_split_predict(SpkvView v,
     }
     const int unit = (int)blockIdx.x * MW + ((int)threadIdx.x >> 6);
     if (unit < pr.n_blocks) predict_hidden_part(v, pr, unit);
+}
+
+// The same under the gapless numbering.
+template <int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void spkv_decode_split_predict_compact(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp, SpkvPredict pr) {
+    if ((int)blockIdx.x < pr.n_blocks) {
+        predict_hidden_part(v, pr, blockIdx.x);
+        return;
+    }
+    decode_split_compact<D, true>(v, q, scale_log2e, sp, (int)blockIdx.x - pr.n_blocks,
+                                  (int)gridDim.x - pr.n_blocks);
 }
 
 // One wave folds the partials of one (pair, head) into a running (max, sum, acc) triple:
@@ -1041,6 +1048,10 @@ static void launch_split(const SpkvView& v, const uint16_t* q, float scale_log2e
 template <int D>
 static void launch_split_predict(const SpkvView& v, const uint16_t* q, float scale_log2e,
                                  SpkvSplit sp, const SpkvPredict& pr, hipStream_t s) {
+    if (sp.compact > 0) {
+        spkv_decode_split_predict_compact<D><<<dim3(pr.n_blocks + sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, pr);
+        return;
+    }
     const dim3 grid((unsigned)((pr.n_blocks + sp.mw - 1) / sp.mw) + (unsigned)v.n_pairs * (unsigned)sp.slots);
     const size_t lds = split_lds_bytes(sp.mw, v.G, D);
     if (sp.mw == 4) spkv_decode_split_predict<D, 4><<<grid, dim3(256), lds, s>>>(v, q, scale_log2e, sp, pr);

@@ -11,7 +11,7 @@ def _uneven(pairs, long):
 
 
 # ------------------------------------------------------------------ gapless numbering
-@pytest.mark.parametrize("call", [["step"], ["attend"], ["static"], ["score", [4] * 16]])
+@pytest.mark.parametrize("call", [["step"], ["attend"], ["static"], ["score", [4] * 16], ["predict", 4096, 256]])
 def test_unanswered_capture_query_leaves_no_error_behind(call):
     """The runtime may refuse to say whether a stream is being captured (the legacy stream while
     another one is: error 906).  The call must go on, and must not find that error when it asks
@@ -20,7 +20,21 @@ def test_unanswered_capture_query_leaves_no_error_behind(call):
     got = record(dict(batch=16), setup + [call])[-1]
     assert got.rc == 0
     assert got.launches[0][0] in ("spkv_decode_split_compact<128, 1>", "spkv_decode_split_compact<128, 0>",
-                                  "spkv_chunk_split<128, 1, 1>")     # the routes that ask
+                                  "spkv_chunk_split<128, 1, 1>",     # the routes that ask
+                                  "spkv_decode_split_predict_compact<128>")
+
+
+@pytest.mark.parametrize("batch,kept,gapless", [
+    (16, _uneven(128, 6000), True), (16, [1500] * 128, False), (4, _uneven(32, 6000), False),
+    (128, _uneven(1024, 9000), True), (128, _uneven(1024, 5000), False), (129, _uneven(1032, 9000), False)])
+def test_gapless_numbering_of_steps(batch, kept, gapless):
+    """Uneven lists take it in every single-token call alike, the step with the predictor inside too
+    (64 sequences of 1k-64k with dense and local-only heads: 641 us plain, 512 gapless)."""
+    calls = [["step"], ["attend"], ["predict", 4096, 256]]
+    got = record(dict(batch=batch, max_total_kept_tokens=1 << 26), [["append", [16384] * batch], ["lengths", kept]] + calls)[1:]
+    want = ["spkv_decode_split_compact<128, 1>", "spkv_decode_split_compact<128, 0>", "spkv_decode_split_predict_compact<128>"]
+    assert [c.rc for c in got] == [0, 0, 0]
+    assert [c.launches[0][0] == w for c, w in zip(got, want)] == [gapless] * 3
 
 
 @pytest.mark.parametrize("batch,kept,gapless", [
