@@ -11,6 +11,7 @@ import paper_2605_14037_amd as spkv
 from oracle.spkv_oracle import SPKVOracle, threshold_logit
 from paper_2605_14037_amd.inputs import (TokenStream, small_workload, to_numpy_f32, workload)
 from tests import harness as H
+from tests.recorder import record
 
 pytestmark = pytest.mark.gpu
 
@@ -1129,11 +1130,20 @@ def test_sink_tokens_every_entry_point(n_sink, w):
 
 
 # ------------------------------------------------------------- replay from a HIP graph
-@pytest.mark.parametrize("B,Hk,G,D", [(33, 1, 4, 128), (13, 5, 3, 64), (64, 1, 16, 64), (512, 2, 1, 64),
-                                      (205, 5, 2, 64), (49, 8, 1, 64)])
-def test_gapless_numbering_of_ragged_batches(B, Hk, G, D):
-    """Pair counts on both sides of a lane's share of the prefix sum (64, 128, 1024 pairs and one
-    more; more than 384 with short and with long lists), lengths from empty to long in one batch, keep rates from none to all; fused steps,
+def _first_kernel(cache, wl, held, call):
+    """The kernel that `call` starts with on a cache in this state (tests/recorder)."""
+    kept = [n for row in cache.stats(with_kept_len=True)[1] for n in row]
+    got = record(dict(batch=wl.batch, n_q_heads=wl.n_q_heads, n_kv_heads=wl.n_kv_heads, head_dim=wl.head_dim,
+                      window=wl.window), [["append", list(held)], ["lengths", kept], ["stats"], call])[-1]
+    assert got.rc == 0
+    return [name for name, _, _ in got.launches if name != "copy"][0]
+
+
+@pytest.mark.parametrize("B,Hk,G,D,gapless", [(33, 1, 4, 128, True), (13, 5, 3, 64, True), (64, 1, 16, 64, True),
+                                              (512, 2, 1, 64, False), (205, 5, 2, 64, False), (49, 8, 1, 64, False)])
+def test_gapless_numbering_of_ragged_batches(B, Hk, G, D, gapless):
+    """Pair counts around one per lane of the prefix sum, and more than 384 pairs whose lists are too
+    short for it; lengths from empty to long in one batch, keep rates from none to all; fused steps,
     the two-call step and the static variant."""
     rng = np.random.default_rng(B)
     top = 6000 if Hk == 8 else 900 if B < 200 else 150
@@ -1146,6 +1156,7 @@ def test_gapless_numbering_of_ragged_batches(B, Hk, G, D):
     for step in range(3):
         k, v, f, cu = stream.next_tokens([1] * B)
         q = stream.next_query()
+        assert ("compact" in _first_kernel(cache, wl, [c + step for c in ctx], ["step"])) == gapless
         if step < 2:
             out, lse = cache.decode_step(k, v, f, q, want_lse=True)
             oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
@@ -1162,6 +1173,85 @@ def test_gapless_numbering_of_ragged_batches(B, Hk, G, D):
     cache.close()
 
 
+@pytest.mark.parametrize("B,Hk,long,drafts", [(16, 8, 6000, True), (48, 8, 6000, True), (55, 7, 6200, False),
+                                              (256, 4, 3900, False)])
+def test_gapless_numbering_of_many_pairs(B, Hk, long, drafts):
+    """128, 384, 385 and 1024 pairs, two to sixteen per lane of the prefix sum: step, step with the
+    predictor, attention of its own and draft scoring against the plain numbering on a second cache
+    (forced by its merge width), whose kernels the oracle tests cover, and the first and last
+    sequence against the oracle."""
+    D, w, few = 64, 32, sorted({0, B // 2, B - 1})
+    keep = np.full((B, Hk), 0.05)
+    keep[:, 0], keep[:, 1] = 1.0, 0.0
+    ctx = [long - 7 * (b % 9) for b in range(B)]
+    wl = small_workload("manypairs", B, Hk, Hk, D, ctx, keep, window=w, decode_steps=40, seed=B)
+    sub = small_workload("manypairs", len(few), Hk, Hk, D, [ctx[b] for b in few], keep[few], window=w, decode_steps=40)
+    stream, oracle = TokenStream(wl, device="cuda"), H.make_oracle(sub)
+    caches = [H.make_cache(wl, extra_context=40) for _ in range(2)]
+    caches[1].set_option(spkv.OPT_MERGE_WAVES, 1)
+
+    def rows(t, cu):
+        return to_numpy_f32(torch.cat([t[cu[b]:cu[b + 1]] for b in few]))
+
+    def mirror(k, v, f, cu):
+        part = [0]
+        for b in few:
+            part.append(part[-1] + cu[b + 1] - cu[b])
+        oracle.append(rows(k, cu), rows(v, cu), rows(f, cu), part)
+
+    def both(call, kernel, held, script):
+        assert _first_kernel(caches[0], wl, held, script) == kernel
+        outs = [call(c)[0] for c in caches]
+        H.check_output(outs[0], to_numpy_f32(outs[1]), kernel)      # each is 2.2e-3 off (2-norm), bound 6e-3
+        return outs[0]
+
+    k, v, f, cu = stream.next_tokens(ctx)
+    for c in caches:
+        c.append(k, v, f, cu)
+    mirror(k, v, f, cu)
+    held = list(ctx)
+    one = [1] * B
+
+    k, v, f, cu = stream.next_tokens(one)
+    q = stream.next_query()
+    out = both(lambda c: c.decode_step(k, v, f, q, want_lse=True), "spkv_decode_split_compact<64, 1>", held, ["step"])
+    mirror(k, v, f, cu)
+    held = [n + 1 for n in held]
+    H.check_output(out[few], oracle.decode(to_numpy_f32(q[few]))[0], "step")
+
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn(B, 256, generator=g, device="cuda").to(torch.bfloat16)
+    w1 = (torch.randn(64, 256, generator=g, device="cuda") / 16).to(torch.bfloat16)
+    w2 = (torch.randn(Hk, 64, generator=g, device="cuda") / 4).to(torch.bfloat16)
+    k, v, _, cu = stream.next_tokens(one)
+    q = stream.next_query()
+    logits = []
+
+    def predict(c):
+        o, f = c.decode_step_predict(x, w1, None, w2, None, k, v, q)
+        logits.append(f)
+        return o, f
+    out = both(predict, "spkv_decode_split_predict_compact<64>", held, ["predict", 256, 64])
+    assert torch.equal(logits[0], logits[1])
+    mirror(k, v, logits[0], cu)
+    held = [n + 1 for n in held]
+    H.check_output(out[few], oracle.decode(to_numpy_f32(q[few]))[0], "step with the predictor")
+
+    q = stream.next_query()
+    out = both(lambda c: c.decode_attention(q, want_lse=True), "spkv_decode_split_compact<64, 0>", held, ["attend"])
+    H.check_output(out[few], oracle.decode(to_numpy_f32(q[few]))[0], "attention")
+
+    if drafts:
+        counts = [b % 4 if b % 5 else 4 for b in range(B)]          # some sequences bring none
+        k, v, f, cu = stream.next_tokens(counts)
+        q = stream.next_query(rows=sum(counts))
+        caches[1].set_option(spkv.OPT_ITEM_TARGET, 2000)            # the plain numbering of this call
+        both(lambda c: c.score_chunk(k, v, q, cu, want_lse=True), "spkv_chunk_split<64, 1, 1>", held, ["score", counts])
+    for c in caches:
+        assert [c.stats(with_kept_len=True)[1][b] for b in few] == oracle.kept_len().tolist()
+        c.close()
+
+
 def test_gapless_numbering_in_a_graph_that_its_lists_outgrow():
     """A step captured while the lists are a few keys long and replayed until they need more
     work items than the captured launch has workgroups: the workgroups take second items."""
@@ -1176,6 +1266,7 @@ def test_gapless_numbering_in_a_graph_that_its_lists_outgrow():
     cache.decode_step(k, v, f, q)                     # one eager step: tightens the host's bound
     oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
     assert cache.safe_steps() >= n
+    assert "compact" in _first_kernel(cache, wl, [n_old + 1 for n_old in wl.ctx_lens], ["step"])
     ks, vs, fs, qs, out = (torch.empty_like(t) for t in (k, v, f, q, q))
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
