@@ -183,10 +183,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // against 64 bits is 5.7e-8 (one chain over d_model: 1.55e-7) for 2 us.
 constexpr int kGemmK = 64;           // elements of d_model per stage
 constexpr int kGemmBufs = 3;         // stages in LDS: one in use, two on their way
-#ifndef FLUSH
-#define FLUSH 8
-#endif
-constexpr int kGemmFlush = FLUSH;        // stages summed in the MFMA accumulators before they are added up
+constexpr int kGemmFlush = 8;        // stages summed in the MFMA accumulators before they are added up
 constexpr int kGemmHeads = 32;       // KV heads per pass of the output layer
 
 template <int NHW, int TT>

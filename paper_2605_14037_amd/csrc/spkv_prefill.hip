@@ -14,10 +14,10 @@
 //      list lies at least w behind it (see spkv_bulk_ring).
 //   3. spkv_prefill_attend32 (long chunks) or spkv_prefill_attend: one wave per block of
 //      tb = 32 / G consecutive tokens of one (sequence, KV head) -- 32 MFMA columns (token,
-//      head), in two groups of 16 or, for the shortest chunks, one of 16 in the latter -- walks the long-term prefix and then the staging rows of
-//      the block's windows, one online softmax per column, and writes the normalised bf16
-//      rows (or, when a span's keys are cut into ranges, partial results that
-//      spkv_prefill_combine merges).
+//      head), in the latter in two groups of 16 or, for the shortest chunks, one -- walks the
+//      long-term prefix and then the staging rows of the block's windows, one online softmax per
+//      column, and writes the normalised bf16 rows (or, when a span's keys are cut into ranges,
+//      partial results that spkv_prefill_combine merges).
 // Window keys and long-term entries are disjoint (positions > t - w against <= t - w), so
 // every available key is counted once.
 
@@ -320,14 +320,13 @@ __device__ __forceinline__ bool locate_range(const SpkvView& v, const SpkvCu& cu
     return true;
 }
 
-// Short chunks (long ones: spkv_prefill_attend32 below).  One workgroup of NW (4 or 2) waves per
-// span of NW * tb consecutive tokens of one (sequence, KV head); wave wv owns tokens i0 = span start + wv * tb .. + tb - 1 as its
-// 16 NQ MFMA columns (tb = 16 NQ / G tokens times G heads; NQ = 2 groups of 16, one for the
-// shortest chunks).  The waves walk the
-// same half-pages, so each 16 KB tile is fetched from memory once per workgroup into a ring
-// of LDS buffers (every wave copies its share of a tile straight from memory into LDS, two
-// tiles ahead of the one all waves consume) and each wave reads its MFMA A operands from LDS
-// with conflict-free 16-byte reads.
+// Short chunks (long ones: spkv_prefill_attend32 below).  One workgroup of NW (4 or 2) waves per (sequence,
+// KV head) and tile range, which holds the whole chunk: wave wv owns tokens i0 = wv tb .. + tb - 1 as
+// its 16 NQ MFMA columns (tb = 16 NQ / G tokens times G heads; NQ = 2 groups of 16, one for the
+// shortest chunks).  The waves walk the same half-pages, so each 16 KB tile is fetched from memory
+// once per workgroup into a ring of LDS buffers (every wave copies its share of a tile straight from
+// memory into LDS, two tiles ahead of the one all waves consume) and each wave reads its MFMA A
+// operands from LDS with conflict-free 16-byte reads.
 template <int D, int NW, int NQ>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_prefill_attend(SpkvView v, const uint16_t* __restrict__ q,
                                                            uint16_t* __restrict__ out,
@@ -341,7 +340,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // chunks and for the two-wave workgroups of short ones alike).
     constexpr int kAhead = 2, kBufs = kAhead + 1;
     __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kHalfElems];
-    // One span holds a whole chunk here, so a workgroup is a (pair, tile range of its list).
     int pair, kr, ranges;
     bool once = pf.once != 0;
     if (pf.slots == 0) {
@@ -357,17 +355,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             reinterpret_cast<int2*>(pf.part + (size_t)pf.slots * (NW * NQ * 16) * (D + 2))[pair] =
                 make_int2(first, ranges);
     }
-    constexpr int qblk = 0;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
-    const int span0 = qblk * NW * pf.tb;
-    if (span0 >= n_tok) return;
-    const int span_last = min(span0 + NW * pf.tb, n_tok) - 1;
+    if (n_tok <= 0) return;
+    const int last_tok = n_tok - 1;
     const int tid = threadIdx.x, lane = tid & 63, kc = lane >> 4, n = lane & 15;
     // wave index as a scalar: everything derived from it (token range, loop bounds, the
     // branches on them) then stays in scalar registers and scalar branches
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i0 = span0 + wv * pf.tb;
+    const int i0 = wv * pf.tb;
     const int tbv = max(0, min(pf.tb, n_tok - i0)), i_last = i0 + tbv - 1, cols = tbv * v.G;
     const bool active = tbv > 0;
     // the cache is in the state after the append
@@ -396,15 +392,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             qb[c][sl] = __builtin_bit_cast(bf16x8, raw);
         }
     }
-    // long-term half-pages: the workgroup visits those some token of the span can see; this
+    // long-term half-pages: the workgroup visits those some token of the chunk can see; this
     // wave computes on those below its own last count, unmasked below its first count
-    const int nA = (prefix_of(span_last) + kHalfTokens - 1) >> 5;
+    const int nA = (prefix_of(last_tok) + kHalfTokens - 1) >> 5;
     const int nA_wave = active ? (prefix_of(i_last) + kHalfTokens - 1) >> 5 : 0;
     const int fullA = active ? prefix_of(i0) >> 5 : 0;
-    // staging half-pages: rows (span0, span_last + w] that hold a position; this wave's
-    // windows cover rows [lo_w, hi_w]
-    const int sB0 = max(span0 + 1, u_min) >> 5;
-    const int nB = ((span_last + v.w) >> 5) - sB0 + 1;
+    // staging half-pages: rows [1, last_tok + w] that hold a position; this wave's windows
+    // cover rows [lo_w, hi_w]
+    const int sB0 = max(1, u_min) >> 5;
+    const int nB = ((last_tok + v.w) >> 5) - sB0 + 1;
     const int lo_w = max(i0 + 1, u_min), hi_w = i_last + v.w;
     const int n_hp = nA + nB, last = n_hp - 1;
     // split-K: this workgroup takes tiles [x_begin, x_end) of the span's n_hp
@@ -608,7 +604,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(16))) float s_zero[32];
     if (SOFT && threadIdx.x < 32) s_zero[threadIdx.x] = 0.f;      // (the barrier before the loop)
     int pair, qblk, kr;      // (sequence, KV head), span, tile range of the span
-    if (pf.pin_xcd) {        // see spkv_prefill_attend
+    if (pf.pin_xcd) {
+        // workgroups go round-robin to the 8 XCDs: id % 8 picks the XCD, and every pair lives on one
+        // XCD, so its list is fetched into one L2 and re-read there; rotated inside every full group
+        // of 8 pairs by the group index: with 8 KV heads a plain pair % 8 would give each XCD one
+        // head of every sequence, and heads differ several-fold in kept length
         const int local = blockIdx.x >> 3, lp = local / (pf.nblk * pf.ks);
         const int rem = local - lp * pf.nblk * pf.ks;
         qblk = rem / pf.ks;
