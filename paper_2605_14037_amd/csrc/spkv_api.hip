@@ -365,15 +365,16 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 constexpr int kMergePairs = 32, kCompactItemsPerCu = 7, kCompactChunkItemsPerCu = 4,
               kCompactChunkPairs = 384;
 // Where the gapless numbering is worth its search and its longer items: at least three slots to
-// an item.  Step, plain -> gapless, us: dense, sparse and local-only heads mixed (four to five slots an
-// item), 64 sequences of 1k-64k 604 -> 500, 40 of 2k-20k 131 -> 110, 24 of 1k-30k 116 -> 96, 16 of 4k-8k
-// 36 -> 33, and with the predictor inside 641 -> 512, 128 -> 114, 103 -> 98, 37 -> 34.  Sparse heads
-// alone (one to 2.7 slots an item) gain or lose a few percent in no order that slots, lengths or the
-// share per XCD would tell apart, and stay plain: 16 of 32k 82.6 -> 81.3 (all kept 322 -> 313), 40 of 16k
-// 104.7 -> 104.5, 24 of 20k 77.8 -> 77.1, but 32 of 16k 61.1 -> 63.3, 64 of 1k-30k 158 -> 163, 128 of
-// 0.5k-16k 195 -> 207.
-// The search costs more with more lengths per lane: above 384 pairs the lists must be worth it (64
-// sequences x 8 heads mixed, 300-3000 tokens, 400 keys a pair: 45 -> 51; 100 x 8 of 1k-12k,
+// an item.  Step, plain -> gapless, us: a quarter of the heads keep all, a quarter nothing but
+// the window, the rest 0.10-0.33 (four to five slots an item), 64 sequences of 1k-64k 604 -> 500
+// (0.05-0.30: 536 -> 471), 40 of 2k-20k 131 -> 110, 24 of 1k-30k 116 -> 96, 16 of 4k-8k
+// 36 -> 33, with the predictor inside 641 -> 512, 128 -> 114, 103 -> 98, 37 -> 34.  Sparse heads
+// alone (one to 2.7 slots an item) gain or lose a few percent in no order that slots, lengths or the share per XCD would
+// tell apart, and stay plain: 16 of 32k 82.6 -> 81.3 (all kept 322 -> 313), 40 of 16k
+// 104.7 -> 104.5, 24 of 20k 77.8 -> 77.1, but 32 of 16k 61.1 -> 63.3, 64 of 1k-30k 158 -> 163,
+// 128 of 0.5k-16k 195 -> 207.
+// The search costs more with more lengths per lane: above 384 pairs the lists must be worth it
+// (64 sequences x 8 heads mixed, 300-3000 tokens, 400 keys a pair: 45 -> 51; 100 x 8 of 1k-12k,
 // 2300 keys: 201 -> 181).
 constexpr int kGapRatio = 3, kGapFewPairs = 384, kGapMeanKeys = 1024;
 bool worth_gapless(const spkv_cache* c, const SpkvSplit& plain, int64_t items) {
@@ -385,14 +386,14 @@ bool worth_gapless(const spkv_cache* c, const SpkvSplit& plain, int64_t items) {
     return keys >= (int64_t)n * kGapMeanKeys;
 }
 // The same for a multi-token step of one column group, whose gapless items are fewer (four per
-// compute unit) and up to five half-pages long a chain that short lists have no use for: not below
-// 24 half-pages a pair on average, and not between few pairs (whose many partial results of the
-// plain numbering cost more to merge) and five half-pages an item unless the lists are uneven.  Plain
-// / gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7; 48 x 8 of 500-1000 34 / 37;
-// 48 x 3 of 2k-4k 26 / 28; 24 x 2 heads of 64, 8k-16k 23 / 25; but 8 x 8 of 4k 28 / 26, 8 heads of 40k
-// 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of 4k-16k 73 / 69, 16 x 8 of 1k-4k with dense and
-// local-only heads 38 / 35, 32 x 8 of 8k-32k so 275 / 189.
-constexpr int kGapFewChunkPairs = 64, kGapChunkPairHps = 24, kGapChunkItemHps = 5;     // (32 with head_dim 64)
+// compute unit) and longer, which short lists have no use for: not below 24 half-pages a pair
+// on average; and from there on for few pairs (up to 64, 32 with head_dim 64: the plain
+// numbering's many partial results cost more to merge), for items of at least five half-pages, or
+// for uneven lists.  Plain / gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7;
+// 48 x 8 of 500-1000 34 / 37; 48 x 3 of 2k-4k 26 / 28; 24 x 2 heads of 64, 8k-16k 23 / 25; but
+// 8 x 8 of 4k 28 / 26, 8 heads of 40k 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of 4k-16k
+// 73 / 69, 16 x 8 of 1k-4k with dense and local-only heads 38 / 35, 32 x 8 of 8k-32k so 275 / 189.
+constexpr int kGapFewChunkPairs = 64, kGapChunkPairHps = 24, kGapChunkItemHps = 5;
 bool worth_gapless_chunk(const spkv_cache* c, int items) {
     const int n = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
     if (n > kCompactChunkPairs) return false;
@@ -451,7 +452,9 @@ SpkvSplit choose_split(const spkv_cache* c) {
 // K/V bytes): one launch 22.3 / 36.8 / 54.6 / 87.3 at 51 / 115 / 222 / 436 MB, two launches
 // 17.6 / 28.0 / 45.0 / 78.5 -- the tickets (an atomic per workgroup on one address per pair,
 // served one after the other) and the merge's dependent round trips inside the launch cost
-// more than a second launch does, at every size tried.  Two launches unless the caller asks.
+// more than a second launch does.  At the smallest sizes the kernels say the same (one sequence
+// of 2k, 0.25 MB, replayed from a graph: 8.1 one launch, 6.9 two), but a step issued by itself is
+// as long as the host takes to issue it (10.7 one, 14.1 two).  Two launches unless the caller asks.
 bool one_launch(const spkv_cache* c, hipStream_t) {
     return c->step_launches == 1;
 }

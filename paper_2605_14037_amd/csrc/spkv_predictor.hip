@@ -169,16 +169,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // four MFMA 32x32x16 accumulators.  Blocks of 64 elements of d_model -- 128 bytes of every W1
 // row and token row -- are copied straight into LDS, eight lanes per row, two blocks ahead of
 // the one in use (ring of three), and a wave waits only for its own copies of the next block,
-// not for the newest.  The token rows are copied non-temporal: kept in the L2 they pushed W1
-// out of it (35 % more traffic behind the L2 by counters, 2 % of the time).  Chunk c (16 bytes)
-// of row r lies at position c ^ ((r >> 1) & 7) of the row: the sixteen rows an operand read
-// touches at a time then cover all 64 banks once.
-// What bounds it, 32 768 tokens of 4096 -> 256 -> 8: the compute side of a stage alone takes
-// 0.7 us, the copies alone 1.0 (per compute unit one 1 KB copy of eight rows takes about 30
-// clocks of the address unit), both together 1.2; 118 us with 64-token workgroups, two stages
-// in LDS and 16x16x32 products, 82 us now.  Stages half as wide and five ahead: 100 us (the
-// copies are bound by rows, not by latency).  The epilogue's loads go out together: one by one,
-// behind a branch each, they were 9 us of every call.
+// not for the newest.  The token rows are copied non-temporal, so that they do not push W1 out of
+// the L2 (292 MB come from behind it, of which the tokens are 268; worth 2 % of the time).
+// Chunk c (16 bytes) of row r lies at position c ^ ((r >> 1) & 7) of the row: the sixteen rows
+// an operand read touches at a time then cover all 64 banks once.
+// What bounds it, 32 768 tokens of 4096 -> 256 -> 8: the rows' way into LDS beside the products
+// (by counters the matrix units are busy 48 % of the SIMD time; waves wait 26 % of their time for
+// copies and the barrier and 44 % for an issue slot).  115 us with 64-token workgroups, two
+// stages in LDS and 16x16x32 products, 78 us now.  Stages half as wide and five ahead: 100 us
+// (the copies are bound by rows, not by latency).  The epilogue's loads go out together: one by
+// one, behind a branch each, they were 9 us of every call.
 // Sums of kGemmFlush stages are added up outside the MFMA accumulators: the relative error
 // against 64 bits is 5.7e-8 (one chain over d_model: 1.55e-7) for 2 us.
 constexpr int kGemmK = 64;           // elements of d_model per stage
@@ -382,16 +382,18 @@ hipError_t spkv_launch_predictor(const uint16_t* x, const uint16_t* w1, const fl
     // The staged kernel takes about the same time for any number of tokens up to a workgroup per
     // compute unit (d_model 1024: 18 us, 4096: 42, 50 with 256 units), the pair of launches below
     // grows with tokens x (units + what reading a token and storing its heads costs, which weighs
-    // the more the shorter the rows are).  Pair / staged on either side of the line, us, 8 heads: 4096
-    // tokens of 4096, 16 / 48 units 19 / 33 against 42, 96 units 55 / 42; 6000 of 4096, 32 units 36 / 42,
-    // 48 units 51 / 42; 4096 of 1024, 32 units 15 / 18, 64 units 20 / 18; 6000 of 1024, 16 units 18 / 17;
-    // one head: 12 000 of 4096, 16 units 29 / 40, 32 units 50 / 41.  Up to 512 elements per row one
-    // launch is faster because it is one (11 us against 13).
+    // the more the shorter the rows are).  Pair / staged on either side of the line, us, 8 heads:
+    // 4096 tokens of 4096, 16 / 48 units 19 / 33 against 42, 96 units 55 / 42; 6000 of 4096, 32
+    // units 36 / 42, 48 units 51 / 42; 4096 of 1024, 32 units 15 / 18, 64 units 20 / 18; 6000 of
+    // 1024, 16 units 18 / 17; one head: 12 000 of 4096, 16 units 29 / 40, 32 units 50 / 41.  Up to
+    // 512 elements per row one launch is faster because it is one (11 us against 13).
     // 128 tokens per workgroup halve the fetches of W1 once 64 would need a second round (16 384
     // tokens: 58 us with 64 each; 20 000: 65 us with 128, 100 with 64).
     const int64_t units = (int64_t)n_tokens * d_hidden;
     const bool staged = units >= 350000 ||
-                        (n_tokens >= 4096 && (d_model <= 512 || units * d_model + n_tokens * (4000 + 4500LL * n_kv_heads) >= 300000LL * d_model));
+                        (n_tokens >= 4096 &&
+                         (d_model <= 512 ||
+                          units * d_model + n_tokens * (4000 + 4500LL * n_kv_heads) >= 300000LL * d_model));
     if (staged && d_hidden <= 256) {
         const bool wide = n_tokens > 16384;
         if (d_hidden <= 64) return wide ? launch_predictor_gemm<1, 128>(x, w1, b1, w2, b2, logits, n_tokens, d_model, d_hidden, n_kv_heads, s)

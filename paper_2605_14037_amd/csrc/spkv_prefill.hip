@@ -584,12 +584,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // barrier per step.  One code path for all half-pages: masks are a branch around the scores
 // alone, and a wave that sees no key of a half-page skips the product with V.
 // Soft gating: the bias log2 u of a key, in units of a score, is what its products start from.
-// 4 sequences of 16 384 tokens, 32 query / 8 KV heads of 128 (8.5 TFLOP): 9.33 -> 7.92 ms =
-// 1.09 PFLOP/s (two groups of 16 columns, reads and products of a tile one after the other,
-// before; a large matrix product reaches 1.35 here); prompts of 3 to 19.5 thousand tokens, keep rates 0.1 to
-// 0.33, 4 sequences: 2.27 -> 1.91 ms.  What is left: the matrix units are busy 53 % of the
-// cycles, the vector units beside them, 27 % of the wave time is the barrier; the clock falls
-// as the load rises (2.0 GHz).
+// 4 sequences of 16 384 tokens, 32 query / 8 KV heads of 128 (8.8 TFLOP): 9.37 -> 7.87 ms =
+// 1.12 PFLOP/s (two groups of 16 columns, reads and products of a tile one after the other,
+// before; a large matrix product reaches 1.35 here); prompts of 3 to 19.5 thousand tokens, keep
+// rates 0.1 to 0.33, 4 sequences: 2.26 -> 1.90 ms.  What is left, by counters: the matrix units are
+// busy 56 % of the SIMD time, with 5.6 vector instructions beside each product; waves wait 27 %
+// of their time (copies and the barrier) and 33 % for an issue slot; the clock falls as the
+// load rises (1.85 GHz; 1.7 on the last chunks of a 32k prompt).
 template <int D, bool SOFT>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_prefill_attend32(
     SpkvView v, const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float* __restrict__ lse,
