@@ -159,8 +159,9 @@ struct spkv_cache {
     // exact; past 1/16 of the bound the lengths are copied to pinned host memory behind the
     // step just issued (no wait) and adopted by the first later call that finds the copy done.
     int64_t slack;
-    int32_t* snap_host;           // pinned, [n_pairs]; null if the allocation failed
-    hipEvent_t snap_event;
+    int32_t* snap_host;           // pinned, [n_pairs] and a ticket; null if the allocation failed
+    int32_t snap_ticket;          // the ticket that comes with the copy enqueued last
+    hipEvent_t snap_event;        // behind it (awaited before the buffer is freed)
     bool snap_pending;
     std::vector<int32_t> snap_ev; // per sequence: pairs pushed out of the window since the copy
     // What is known of the lengths themselves: L_ub less what `since_exact` (per sequence) added to
@@ -258,8 +259,7 @@ void tighten_bound(spkv_cache* c, hipStream_t s, int share = 16) {
     if (c->snap_host == nullptr) return;
     const int n_pairs = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
     if (c->snap_pending) {
-        const hipError_t q = hipEventQuery(c->snap_event);
-        if (q == hipSuccess) {
+        if (__atomic_load_n(c->snap_host + n_pairs, __ATOMIC_ACQUIRE) == c->snap_ticket) {
             int64_t pages = 0, slack = 0;
             for (int p = 0; p < n_pairs; ++p) {
                 const int64_t L = (int64_t)c->snap_host[p] + c->snap_ev[p / Hkv];
@@ -273,7 +273,6 @@ void tighten_bound(spkv_cache* c, hipStream_t s, int share = 16) {
             if (c->snap_covers) c->lists_known = true;
             c->snap_pending = false;
         } else {
-            (void)hipGetLastError();      // "not ready" is not an error of the next launch
             return;
         }
     }
@@ -285,8 +284,8 @@ void tighten_bound(spkv_cache* c, hipStream_t s, int share = 16) {
         (void)hipGetLastError();
         return;
     }
-    if (hipMemcpyAsync(c->snap_host, c->view.kept_len, (size_t)n_pairs * 4, hipMemcpyDeviceToHost, s) !=
-            hipSuccess ||
+    c->snap_ticket += 1;
+    if (spkv_launch_copy_lengths(c->view, c->snap_host, c->snap_ticket, s) != hipSuccess ||
         hipEventRecord(c->snap_event, s) != hipSuccess) {
         (void)hipGetLastError();
         return;
@@ -546,6 +545,7 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     c->slack = 0;
     c->snap_host = nullptr;
     c->snap_event = nullptr;
+    c->snap_ticket = 0;
     c->snap_pending = false;
     c->snap_ev.assign(cfg->batch, 0);
     c->since_exact.assign(cfg->batch, 0);
@@ -579,9 +579,10 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     // pinned host buffer for the length snapshots (see tighten_bound); the cache works
     // without it, with a coarser partition on very long generations
     void* pinned = nullptr;
-    if (hipHostMalloc(&pinned, (size_t)k.n_pairs * 4, hipHostMallocDefault) == hipSuccess &&
+    if (hipHostMalloc(&pinned, (size_t)(k.n_pairs + 1) * 4, hipHostMallocCoherent) == hipSuccess &&
         hipEventCreateWithFlags(&c->snap_event, hipEventDisableTiming) == hipSuccess) {
         c->snap_host = static_cast<int32_t*>(pinned);
+        c->snap_host[k.n_pairs] = 0;
     } else {
         if (pinned != nullptr) (void)hipHostFree(pinned);
         c->snap_event = nullptr;

@@ -65,6 +65,8 @@ hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // `tail`; `counter` is where v.pool_next lies.  Bytes from the arena's start.
 hipError_t spkv_launch_reset(const SpkvView& v, void* arena, size_t counter, size_t pool, size_t tail,
                              size_t tail_bytes, hipStream_t s);
+// Copies the n kept lengths to pinned host memory, then stores `ticket` behind them (to_host[n]).
+hipError_t spkv_launch_copy_lengths(const SpkvView& v, int32_t* to_host, int32_t ticket, hipStream_t s);
 hipError_t spkv_launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // Streaming read of n_runs runs (chunks_per_run chunks of 16 KB each) of a region of
 // total_runs runs by n_workgroups one-wave workgroups; sink: n_workgroups KB.

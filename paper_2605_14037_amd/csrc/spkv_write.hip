@@ -66,6 +66,23 @@ hipError_t spkv_launch_reset(const SpkvView& v, void* arena, size_t counter, siz
     return hipGetLastError();
 }
 
+// --------------------------------------------------------------- lengths to the host
+// The ticket tells the host that the lengths have arrived without an event: asking an event while
+// any stream of the process is being captured ends that capture.  One workgroup; every thread's
+// lengths are out at system scope before the barrier, the ticket after it.
+__global__ __launch_bounds__(256) void spkv_copy_lengths(const int32_t* __restrict__ len, int n, int32_t* to_host,
+                                                         int32_t ticket) {
+    for (int p = threadIdx.x; p < n; p += blockDim.x) to_host[p] = len[p];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(to_host + n, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t spkv_launch_copy_lengths(const SpkvView& v, int32_t* to_host, int32_t ticket, hipStream_t s) {
+    spkv_copy_lengths<<<dim3(1), dim3(256), 0, s>>>(v.kept_len, v.n_pairs, to_host, ticket);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------- plain copy (reference)
 __global__ __launch_bounds__(256) void spkv_plain_copy(uint4* __restrict__ d,
                                                        const uint4* __restrict__ s, size_t n16) {

@@ -22,6 +22,11 @@ static int g_watch_arg, g_watch_at;                       // ... the int at this
 static Dim3 g_grid, g_block;
 static size_t g_shared;
 static void* g_stream;
+static int deliver(void* dst, size_t n) {
+    memset(dst, 0, n);
+    memcpy(dst, g_device_bytes.data(), n < g_device_bytes.size() ? n : g_device_bytes.size());
+    return 0;
+}
 
 extern "C" {
 
@@ -65,6 +70,12 @@ int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void** args, size_t
         int v;
         memcpy(&v, static_cast<char*>(args[g_watch_arg]) + g_watch_at, 4);
         g_log.push_back("watched " + std::to_string(v) + " 0 0");
+    }
+    if (g_kernel[host].find("spkv_copy_lengths") != std::string::npos && g_event_ready) {
+        const int n = *static_cast<int*>(args[1]);         // (lengths, n, where to, ticket)
+        int* to = *static_cast<int**>(args[2]);
+        deliver(to, 4 * (size_t)n);
+        to[n] = *static_cast<int*>(args[3]);
     }
     g_log.push_back(g_kernel[host] + " " + std::to_string(grid.x) + " " + std::to_string(grid.y) + " " + std::to_string(block.x));
     return 0;
@@ -113,11 +124,6 @@ int hipHostFree(void* p) {
     free(p);
     return 0;
 }
-static int deliver(void* dst, size_t n) {
-    memset(dst, 0, n);
-    memcpy(dst, g_device_bytes.data(), n < g_device_bytes.size() ? n : g_device_bytes.size());
-    return 0;
-}
 int hipMemcpy(void* dst, const void*, size_t n, int) { return deliver(dst, n); }
 int hipMemcpyAsync(void* dst, const void*, size_t n, int, void*) {
     g_log.push_back("copy " + std::to_string(n) + " 0 0");
@@ -138,6 +144,7 @@ int hipEventElapsedTime(float* ms, void*, void*) {
     return 0;
 }
 int hipEventQuery(void*) {
+    g_log.push_back("event_query 0 0 0");
     if (g_event_ready) return 0;
     return g_last_error = 600;                             // hipErrorNotReady
 }

@@ -181,6 +181,43 @@ def test_prefill_short_chunks_in_ranges_of_equal_length(B, Hkv, G, D, top, n, gr
     _run_prefill(wl, [counts, [n] * B], sample=200, last_grid=grid)
 
 
+@pytest.mark.parametrize("kind", ["chunk", "step"])
+def test_call_captured_while_lengths_are_on_their_way(kind):
+    """The second short chunk after a prompt sends the kept lengths to the host, and so does the
+    sixth step of a cache that holds little more than its window; the next call finds them.  That
+    call may be one that is captured into a graph (where an event must not be asked), and its
+    replay gives the oracle's result."""
+    B, n, eager, keep = (2, 16, 2, [[0.9, 0.05]]) if kind == "chunk" else (2, 1, 6, [[0.0, 0.0]])
+    wl = small_workload("onway", B, 8, 2, 128, [700, 300], keep, window=64, seed=23)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl, pool_tokens=8000, extra_context=64), H.make_oracle(wl)
+    H.prefill(cache, oracle, stream, wl, 4096)
+
+    def tokens(count):
+        k, v, f, cu = stream.next_tokens([count] * B)
+        oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+        return k, v, f, stream.next_query(rows=B * count), cu
+
+    def call(k, v, f, q, cu, **kw):
+        return cache.prefill_attention(k, v, f, q, cu, **kw) if kind == "chunk" else cache.decode_step(k, v, f, q, **kw)
+
+    for i in range(eager):
+        k, v, f, q, cu = tokens(n)
+        H.check_output(call(k, v, f, q, cu), oracle.decode_chunk(to_numpy_f32(q), [n] * B)[0], f"call {i}")
+    k, v, f, q, cu = tokens(n)
+    out = torch.zeros_like(q)
+    ws = torch.empty(cache.prefill_workspace_bytes(n, n * B), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):                     # records the launches; runs nothing
+        call(k, v, f, q, cu, out=out, **(dict(workspace=ws) if kind == "chunk" else {}))
+    graph.replay()
+    torch.cuda.synchronize()
+    H.check_output(out, oracle.decode_chunk(to_numpy_f32(q), [n] * B)[0], "replay")
+    H.check_state(cache, oracle, wl)
+    cache.close()
+
+
 @pytest.mark.parametrize("D,Hq,Hkv", [(128, 8, 2), (64, 6, 2)])
 def test_prefill_tokens_ahead_of_an_infinite_value_are_untouched(D, Hq, Hkv):
     """A workgroup fetches keys that only some of its waves see.  An infinite value at the end of

@@ -112,8 +112,21 @@ def test_short_chunk_ranges(batch, tokens, kept, grid):
     script = [["append", [tokens] * batch], ["lengths", kept], chunk, chunk, chunk]
     calls = record(dict(batch=batch), script)
     assert _chunk_grid(calls[3]) == grid
-    copies = [sum(name == "copy" for name, _, _ in c.launches) for c in calls]
+    copies = [sum(name in ("copy", "spkv_copy_lengths") for name, _, _ in c.launches) for c in calls]
     assert copies == [0, 0, 1, 0]                  # a single chunk after a prompt is not charged for one
+
+
+@pytest.mark.parametrize("call", [["chunk", [16] * 16], ["chunk", [4] * 16], ["step"], ["attend"], ["prefill", [16] * 16]])
+def test_lengths_on_their_way_are_not_asked_for_by_event(call):
+    """A query of an event is refused while a stream of the process is being captured (error 907) and
+    ends that capture: a call that finds a copy of the lengths on its way must be able to go into
+    a graph, and beside one."""
+    chunk = ["chunk", [16] * 16]
+    script = [["append", [32768] * 16], ["lengths", _uneven(128, 20000)], chunk, chunk]
+    for capturing in (0, 1):
+        got = record(dict(batch=16), script + [["capture", capturing, 0], call])
+        assert any("copy" in name for name, _, _ in got[2].launches)        # it is on its way
+        assert got[3].rc == 0 and not [n for n, _, _ in got[3].launches if n == "event_query"]
 
 
 @pytest.mark.parametrize("batch,tokens,pairs_grid", [(8, 2000, 64 * 8), (1, 500, 8 * 4), (64, 4000, 512)])
