@@ -169,7 +169,7 @@ struct spkv_cache {
     // tokens and short chunks only (lists_known), or by a prompt as well.
     std::vector<int32_t> since_exact;
     bool lists_known, snap_covers;    // snap_covers: no prompt since the copy was enqueued
-    bool chunk_since_prompt;          // a copy costs a call some 25 us: not for a single short chunk
+    bool chunk_since_prompt;          // a copy costs a call some 8 us: not for a single short chunk
     int item_target;
     int merge_waves;              // SPKV_OPT_MERGE_WAVES (0 = per call)
     int step_launches;            // SPKV_OPT_STEP_LAUNCHES (0 = per call)
