@@ -385,14 +385,18 @@ bool worth_gapless(const spkv_cache* c, const SpkvSplit& plain, int64_t items) {
     return keys >= (int64_t)n * kGapMeanKeys;
 }
 // The same for a multi-token step of one column group, whose gapless items are fewer (four per
-// compute unit) and longer, which short lists have no use for: not below 24 half-pages a pair
-// on average; and from there on for few pairs (up to 64, 32 with head_dim 64: the plain
+// compute unit) and longer, which short lists have no use for: not where the longest is below 40
+// half-pages; and from there on for few pairs (up to 64, 32 with head_dim 64: the plain
 // numbering's many partial results cost more to merge), for items of at least five half-pages, or
-// for uneven lists.  Plain / gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7;
-// 48 x 8 of 500-1000 34 / 37; 48 x 3 of 2k-4k 26 / 28; 24 x 2 heads of 64, 8k-16k 23 / 25; but
-// 8 x 8 of 4k 28 / 26, 8 heads of 40k 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of 4k-16k
-// 73 / 69, 16 x 8 of 1k-4k with dense and local-only heads 38 / 35, 32 x 8 of 8k-32k so 275 / 189.
-constexpr int kGapFewChunkPairs = 64, kGapChunkPairHps = 24, kGapChunkItemHps = 5;
+// for uneven lists (the longest half as long again as the mean, twice with head_dim 64).  Plain /
+// gapless, us: 64 x 3 heads of 64, 1k-2k tokens, 2 drafts 24.6 / 27.7; 48 x 8 of 500-1000 34 / 37;
+// 48 x 3 of 2k-4k 26 / 28; but 8 heads of 40k 26 / 23, 3 heads of 64, 100k 30 / 24, 24 x 8 of
+// 4k-16k 73 / 69, 10 x 8 of 4k-12k 26.5 / 24.8, 16 x 8 of 1k-4k with dense and local-only heads
+// 38 / 35, 32 x 8 of 8k-32k so 275 / 189.  Over 9900 caches of up to 384 pairs, of all kinds,
+// drawn at random: always plain 5.1 % slower on average than the faster of the two, always
+// gapless 1.2 %, by this rule 0.8 %; what is left is even lists, up to 10 % either way (20 % with
+// head_dim 64) by how the plain numbering happens to fall on the compute units.
+constexpr int kGapFewChunkPairs = 64, kGapChunkLongestHps = 40, kGapChunkItemHps = 5;
 bool worth_gapless_chunk(const spkv_cache* c, int items) {
     const int n = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
     if (n > kCompactChunkPairs) return false;
@@ -403,9 +407,9 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
         sum += hp;
         longest = std::max(longest, hp);
     }
-    if (sum < (int64_t)n * kGapChunkPairHps) return false;
+    if (longest < kGapChunkLongestHps) return false;
     return n * 128 <= kGapFewChunkPairs * c->cfg.head_dim || sum >= (int64_t)items * kGapChunkItemHps ||
-           longest * n >= sum * kGapRatio;
+           2 * longest * n >= sum * (c->cfg.head_dim == 128 ? 3 : 4);
 }
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
