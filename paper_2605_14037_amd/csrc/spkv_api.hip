@@ -462,6 +462,36 @@ bool one_launch(const spkv_cache* c, hipStream_t) {
     return c->step_launches == 1;
 }
 
+// Short lists: one workgroup per pair does the whole call (spkv_decode_short) in place of a split and
+// a merge launch.  What limits it is one compute unit's share of a pair: 16 half-pages with
+// head_dim 128 (two rounds of eight waves; 8 for groups of more than eight heads, whose merge is
+// longer), 24 with 64.  Longer lists only where there are pairs for most compute units and the lists are
+// alike, so that no unit works on alone.  Step replayed from a graph, two launches / this, us:
+// 2 pairs of 64, 4 half-pages 6.6 / 4.9, 24 6.8 / 6.2, 48 7.0 / 8.0; 8 pairs of 128, 4 half-pages
+// 8.6 / 5.4, 16 8.3 / 7.2, 32 8.4 / 9.0; 4 pairs of 16 heads, 8 half-pages 9.3 / 9.0, 16 9.4 / 10.2;
+// 128 pairs of 128, 16 half-pages 15.3 / 10.7; 256 pairs, 16 22 / 15, 64 52 / 44; 512 pairs, 4 23 / 15, 64
+// 94 / 88; but 300 pairs, 64 the longest and 16 the mean, 1.3 times as long.  (Issued call by call,
+// short steps take what the host takes: 13 / 10.)  Over 500 caches of up to 512 pairs drawn at random
+// this takes 0.80 of the time on those it is chosen for, 1.01 at most.
+constexpr int kShortHps = 16, kShortHpsWideGroup = 8, kShortHps64 = 24, kShortEvenPairs = 192, kShortEvenHps = 64;
+bool short_lists(const spkv_cache* c) {
+    if (c->item_target > 0 || c->merge_waves > 0 || c->step_launches > 0) return false;
+    const int n = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
+    int64_t longest = 0, sum = 0;                          // half-pages
+    for (int p = 0; p < n; ++p) {
+        const int Tw = std::min(c->T[p / Hkv], c->cfg.window);
+        const int64_t hp = (c->L_ub[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
+        longest = std::max(longest, hp);
+        sum += hp;
+    }
+    if (longest <= (c->cfg.head_dim == 64 ? kShortHps64 : c->carve.G > 8 ? kShortHpsWideGroup : kShortHps)) return true;
+    return n >= kShortEvenPairs && longest <= kShortEvenHps && 2 * longest * n <= 3 * sum;
+}
+// The partition reported for such a call: one workgroup per pair.
+SpkvSplit short_split(const spkv_cache* c) {
+    return SpkvSplit{1 << 16, 1, spkv_short_waves(c->cfg.head_dim), 0};
+}
+
 // Tokens sequence b receives in a call: from cu_seqlens, or one each (cu == nullptr).
 int tokens_for(const int32_t* cu, int b) { return cu == nullptr ? 1 : cu[b + 1] - cu[b]; }
 
@@ -733,6 +763,15 @@ int spkv_decode_step(spkv_cache_t* c, const void* k, const void* v, const float*
     tighten_bound(c, s);
     const int rc = reserve_capacity(c, nullptr, s);
     if (rc != SPKV_OK) return rc;
+    if (short_lists(c)) {
+        const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, static_cast<const uint16_t*>(k),
+                               static_cast<const uint16_t*>(v), util_logits};
+        c->split = short_split(c);
+        if (spkv_launch_decode_short(c->view, static_cast<const uint16_t*>(q), sm_scale, io, s) != hipSuccess)
+            return SPKV_E_HIP;
+        commit_lengths(c, nullptr);
+        return SPKV_OK;
+    }
     c->split = choose_split(c);          // partition of the state BEFORE the append
     room_to_grow(c, s);
     if (spkv_launch_decode_step(c->view, static_cast<const uint16_t*>(k),
@@ -811,6 +850,13 @@ int spkv_decode_attention(spkv_cache_t* c, const void* q, void* out, float* lse,
         if (rc != SPKV_OK) return rc;
     }
     tighten_bound(c, s);
+    if (!c->timing && !c->split_only && short_lists(c)) {
+        const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, nullptr, nullptr, nullptr};
+        c->split = short_split(c);
+        return spkv_launch_decode_short(c->view, static_cast<const uint16_t*>(q), sm_scale, io, s) == hipSuccess
+                   ? SPKV_OK
+                   : SPKV_E_HIP;
+    }
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (c->timing && c->n_timed < kMaxTimedLaunches) {
         if ((size_t)(2 * c->n_timed + 2) > c->events.size()) {
@@ -853,6 +899,14 @@ int spkv_decode_attention_static(spkv_cache_t* c, const void* q, void* out, floa
     v.part_acc = reinterpret_cast<float*>(base);
     v.part_ml = reinterpret_cast<float*>(base + align_up((size_t)cap * G * D * sizeof(float)));
     v.max_items = (int32_t)std::min<int64_t>(cap, INT32_MAX);
+    if (short_lists(c)) {                            // no partial results at all
+        const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, nullptr, nullptr, nullptr};
+        c->split = short_split(c);
+        return spkv_launch_decode_short(c->view, static_cast<const uint16_t*>(q), sm_scale, io,
+                                        static_cast<hipStream_t>(stream)) == hipSuccess
+                   ? SPKV_OK
+                   : SPKV_E_HIP;
+    }
     c->split = choose_split(c, c->one_round_items, cap);
     room_to_grow(c, static_cast<hipStream_t>(stream));
     if ((int64_t)c->carve.n_pairs * c->split.slots > cap) return SPKV_E_CAPACITY;
@@ -1293,7 +1347,7 @@ int spkv_cache_stats(spkv_cache_t* c, spkv_stats_t* st, int32_t* kept_len, void*
     st->pool_pages_total = c->carve.n_pages;
     st->arena_bytes = (int64_t)c->arena_bytes;
     st->device_error = err;
-    const SpkvSplit sp = choose_split(c);   // the partition the next decode call would use
+    const SpkvSplit sp = short_lists(c) ? short_split(c) : choose_split(c);   // of the next decode call
     int64_t n_items = 0;
     for (int p = 0; p < n_pairs; ++p) {
         const int Tw = std::min(c->T[p / Hkv], w);

@@ -219,15 +219,6 @@ __device__ __forceinline__ void split_compute(const SpkvView& v, const uint16_t*
     }
 }
 
-// Inputs and outputs of the merging workgroup (modes with a ticket).
-struct SpkvStepIO {
-    uint16_t* out;            // [B][Hq][D]
-    float* lse;               // [B][Hq] or null
-    const uint16_t* k_new;    // fused step: the new token's pair and logits
-    const uint16_t* v_new;
-    const float* f_new;
-};
-
 // Ticket and merge.  Every workgroup of the pair calls this once, after its partial (if it
 // had work) has been stored.  In the merging workgroup a thread owns eight consecutive
 // floats of the pair's G x D outputs (a "unit": two float4 of one head); the waves share the

@@ -95,6 +95,18 @@ struct SpkvSplit {
                           // gaps (spkv_decode_split_compact), this many of them
 };
 
+// Inputs and outputs of the single-token kernels that finish a pair themselves.
+struct SpkvStepIO {
+    uint16_t* out;            // [B][Hq][D]
+    float* lse;               // [B][Hq] or null
+    const uint16_t* k_new;    // fused step: the new token's pair and logits (else null)
+    const uint16_t* v_new;
+    const float* f_new;
+};
+// Short lists: one workgroup per pair, one launch, no partial results (the fused step if io.k_new is set).
+hipError_t spkv_launch_decode_short(const SpkvView& v, const uint16_t* q, float sm_scale, const SpkvStepIO& io,
+                                    hipStream_t s);
+int spkv_short_waves(int head_dim);       // waves of such a workgroup
 // one_launch: the last workgroup of every pair merges (and, in the step, appends) inside the
 // split launch; otherwise a second launch does.
 hipError_t spkv_launch_decode(const SpkvView& v, const uint16_t* q, uint16_t* out, float* lse,

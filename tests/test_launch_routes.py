@@ -10,6 +10,30 @@ def _uneven(pairs, long):
     return [long if p % 8 == 0 else long // 20 for p in range(pairs)]
 
 
+# ------------------------------------------------------------------ short lists
+# (a window of 128 tokens is four half-pages, a list of 32 n keys n more; the step may add a key)
+@pytest.mark.parametrize("cfg,kept,short", [
+    (dict(batch=4), [12 * 32 - 1] * 32, True), (dict(batch=4), [12 * 32] * 31 + [12 * 32 + 1], False),
+    (dict(batch=3, n_q_heads=24, n_kv_heads=3, head_dim=64), [20 * 32 - 1] * 9, True),
+    (dict(batch=3, n_q_heads=24, n_kv_heads=3, head_dim=64), [20 * 32 + 1] + [0] * 8, False),
+    (dict(batch=2, n_q_heads=16, n_kv_heads=1), [4 * 32 - 1] * 2, True), (dict(batch=2, n_q_heads=16, n_kv_heads=1), [129, 0], False),
+    (dict(batch=23), [300] * 184, True), (dict(batch=23), [60 * 32] * 184, False),
+    (dict(batch=24), [60 * 32 - 1] * 192, True), (dict(batch=24), [60 * 32 + 1] * 192, False),
+    (dict(batch=24), [60 * 32 - 1] * 96 + [25 * 32 - 1] * 96, True), (dict(batch=24), [60 * 32] * 96 + [16 * 32] * 96, False)])
+def test_short_lists_are_one_launch(cfg, kept, short):
+    """Every single-token call alike; an explicit partition, launch count or timing keeps the split kernel."""
+    calls = [["step"], ["attend"], ["static"]]
+    fill = [["append", [8192] * cfg["batch"]], ["lengths", kept], ["stats"]]
+    got = record(cfg, fill + calls)[2:]
+    assert [c.rc for c in got] == [0] * 3
+    for c in got:
+        names = [n for n, _, _ in c.launches if "copy" not in n]
+        assert (len(names) == 1 and names[0].startswith("spkv_decode_short<")) == short, names
+    for option in ([1, 64], [5, 1], [5, 4], [6, 2], [6, 1]):
+        names = [n for c in record(cfg, fill + [["option"] + option] + calls)[3:] for n, _, _ in c.launches]
+        assert names and not any("short" in n for n in names)
+
+
 # ------------------------------------------------------------------ gapless numbering
 @pytest.mark.parametrize("call", [["step"], ["attend"], ["static"], ["score", [4] * 16], ["predict", 4096, 256]])
 def test_unanswered_capture_query_leaves_no_error_behind(call):
