@@ -25,8 +25,8 @@ struct Carve {
     size_t ring, ring_logit, t_pair, kept_len, gate_on, pool_next, free_top, free_pages, err_flag,
         page_table, pool,
         pos_pool, logit_pool, seg_count, seg_on, bulk_info, part_acc, part_ml, pair_items,
-        pair_ticket, pos_scratch, chunk_stage, chunk_prefix, total;
-    int n_pairs, G, n_ring_pages, pt_cap, n_pages, n_seg_cap, max_items, chunk_shp;
+        pair_ticket, pos_scratch, total;
+    int n_pairs, G, n_ring_pages, pt_cap, n_pages, n_seg_cap, max_items;
 };
 
 bool config_ok(const spkv_config_t* c) {
@@ -91,12 +91,6 @@ bool carve(const spkv_config_t* c, Carve* out) {
     k.pair_items = take((size_t)k.n_pairs * 4);
     k.pair_ticket = take((size_t)k.n_pairs * 4);
     k.pos_scratch = take((size_t)k.pt_cap * kPageTokens * 4);
-    // multi-token steps (spkv_decode_chunk) wider than one group of 16 query columns run on the
-    // prefill kernels: staging half-pages for the window plus 16 new rows per pair, and the
-    // per-token prefix counts
-    k.chunk_shp = (int)(((int64_t)c->window + SPKV_MAX_CHUNK_TOKENS + kHalfTokens - 1) / kHalfTokens);
-    k.chunk_stage = take((size_t)k.n_pairs * k.chunk_shp * ((size_t)2 * kHalfTokens * c->head_dim * 2));
-    k.chunk_prefix = take((size_t)c->batch * SPKV_MAX_CHUNK_TOKENS * c->n_kv_heads * 4);
     k.total = off;
     *out = k;
     return true;
@@ -176,7 +170,7 @@ struct spkv_cache {
     int n_sink;                   // always-kept first positions (SPKV_OPT_SINK_TOKENS)
     int one_round_items;          // items the chip runs in one resident round, with a margin
     int compact_items;            // item target under the gapless numbering
-    int chunk_round_items[3];     // the same for the chunk kernel with 1, 2, 4 column groups
+    int chunk_round_items;        // as one_round_items, for the chunk kernel
     SpkvSplit split;              // partition used by the last decode call
     bool timing;
     bool split_only;
@@ -597,7 +591,7 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
         c->one_round_items = resident > 0 ? resident - resident / 24 : kFallbackItems;
         const int cus = spkv_compute_units();
         c->compact_items = kCompactItemsPerCu * (cus > 0 ? cus : 256);
-        c->chunk_round_items[0] = c->chunk_round_items[1] = c->chunk_round_items[2] = 0;
+        c->chunk_round_items = 0;
     }
     c->split = SpkvSplit{1, 1, 1, 0};
     c->timing = false;
@@ -960,17 +954,15 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
         !aligned16(out) || (lse != nullptr && !aligned16(lse)))
         return SPKV_E_INVAL;
     if (!(sm_scale > 0.f)) sm_scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
-    const int cols = n_max * G;
-    const int groups = cols <= 16 ? 1 : (cols <= 32 ? 2 : 4);
-    if (append && groups > 1) {
-        // More than one group of 16 query columns: the prefill kernels (tiles shared by a
-        // workgroup through LDS) are the faster way to the same result; their staging rows and
-        // prefix counts live in the cache's arena, the split-K partials in its partial buffers.
-        return prefill_core(c, k, v, util_logits, q, cu_seqlens, n_max, out, lse, sm_scale,
-                            reinterpret_cast<uint16_t*>(c->arena + c->carve.chunk_stage),
-                            reinterpret_cast<int32_t*>(c->arena + c->carve.chunk_prefix),
-                            c->carve.chunk_shp, c->view.part_acc,
-                            (size_t)c->carve.max_items * G * c->cfg.head_dim * sizeof(float), false, s);
+    if (n_max * G > 16) {
+        if (!append && c->bound_is_loose) {
+            const int rc = refresh_bound(c, s, nullptr);
+            if (rc != SPKV_OK) return rc;
+        }
+        // More than one group of 16 query columns: the prefill kernels (each tile serves all
+        // columns of a workgroup); their split-K partials live in the cache's partial buffers.
+        return prefill_core(c, k, v, util_logits, q, cu_seqlens, n_max, out, lse, sm_scale, nullptr, nullptr, 0,
+                            c->view.part_acc, (size_t)c->carve.max_items * G * c->cfg.head_dim * sizeof(float), false, s);
     }
     if (c->bound_is_loose) {       // the split-K partition below wants the exact lengths
         const int rc = refresh_bound(c, s, nullptr);
@@ -983,28 +975,23 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
         if (rc != SPKV_OK) return rc;
     }
 
-    const int gi = groups == 1 ? 0 : (groups == 2 ? 1 : 2);
-    if (c->chunk_round_items[gi] == 0) {
-        const int resident = spkv_chunk_resident_items(c->cfg.head_dim, groups);
-        c->chunk_round_items[gi] = resident > 0 ? resident - resident / 24 : 960;
+    if (c->chunk_round_items == 0) {
+        const int resident = spkv_chunk_resident_items(c->cfg.head_dim);
+        c->chunk_round_items = resident > 0 ? resident - resident / 24 : 960;
     }
-    // every slot holds groups * 16 columns of partials instead of G
-    const int64_t slot_cap = (int64_t)c->carve.max_items * G / (groups * 16);
-    // With two or four column groups a wave needs most of the register file and only one or
-    // two fit a SIMD; one resident round of such items then reads too little at a time, and
-    // about 1 800 items (two rounds of the widest kernel) measured 12-15 % faster.
-    // One column group may take the gapless numbering with few items (spkv_chunk_split<D, 1, true>).
+    // every slot holds 16 columns of partials instead of G
+    const int64_t slot_cap = (int64_t)c->carve.max_items * G / 16;
+    // May take the gapless numbering with few items (spkv_chunk_split<D, 1, true>).
     const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
-    const bool compact = groups == 1 && c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
+    const bool compact = c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
     int64_t items = 0;
-    c->split = choose_split_mw(c, compact ? chunk_items : std::max(c->chunk_round_items[gi], groups > 1 ? c->one_round_items * 5 / 8 : 0),
-                               slot_cap, 1, &items);
+    c->split = choose_split_mw(c, compact ? chunk_items : c->chunk_round_items, slot_cap, 1, &items);
     if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
     room_to_grow(c, s);
 
     // every slot the launch may write must lie inside the partial buffers (they are sized
     // for this at create; checked again here because an overrun would be a wild device write)
-    if ((int64_t)c->carve.n_pairs * c->split.slots * groups * 16 > (int64_t)c->carve.max_items * G)
+    if ((int64_t)c->carve.n_pairs * c->split.slots * 16 > (int64_t)c->carve.max_items * G)
         return SPKV_E_CAPACITY;
 
     SpkvCu cu;
@@ -1012,15 +999,10 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
     if (spkv_launch_decode_chunk(c->view, kk, vv, static_cast<const uint16_t*>(q),
-                                 static_cast<uint16_t*>(out), lse, sm_scale, c->split, cu, groups,
-                                 s) != hipSuccess)
+                                 static_cast<uint16_t*>(out), lse, sm_scale, c->split, cu,
+                                 append ? util_logits : nullptr, s) != hipSuccess)
         return SPKV_E_HIP;
-    if (!append) return SPKV_OK;
-    const hipError_t e = (n_max == 1)
-                             ? spkv_launch_append_step(c->view, kk, vv, util_logits, cu, s)
-                             : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, s);
-    if (e != hipSuccess) return SPKV_E_HIP;
-    commit_lengths(c, cu_seqlens);
+    if (append) commit_lengths(c, cu_seqlens);
     return SPKV_OK;
 }
 }  // namespace
@@ -1074,15 +1056,18 @@ size_t spkv_prefill_workspace_bytes(const spkv_cache_t* c, int32_t max_tokens_pe
 
 namespace {
 // Prefill attention + append of a call whose arguments have been checked: staging rows,
-// prefix counts and split-K partials in the buffers given (part_bytes: what `part` holds; the
-// number of key ranges per span is cut down to what fits).  exact_fit: fail instead.
+// prefix counts (neither for spkv_prefill_direct chunks) and split-K partials in the buffers given
+// (part_bytes: what `part` holds; the number of key ranges per span is cut down to what fits).
+// exact_fit: fail instead.  util_logits = null: attention alone (spkv_prefill_direct chunks).
 int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* util_logits,
                  const void* q, const int32_t* cu_seqlens, int n_max, void* out, float* lse,
                  float sm_scale, uint16_t* stage, int32_t* prefix, int shp, float* part,
                  size_t part_bytes, bool exact_fit, hipStream_t s) {
     const int B = c->cfg.batch;
-    const int rc = reserve_capacity(c, cu_seqlens, s);
-    if (rc != SPKV_OK) return rc;
+    if (util_logits != nullptr) {
+        const int rc = reserve_capacity(c, cu_seqlens, s);
+        if (rc != SPKV_OK) return rc;
+    }
     SpkvCu cu;
     std::memcpy(cu.v, cu_seqlens, (size_t)(B + 1) * 4);
     // split-K over every span's tiles when the spans alone would not fill the chip; each
@@ -1120,6 +1105,7 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
                             util_logits, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),
                             lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, once, part, s) != hipSuccess)
         return SPKV_E_HIP;
+    if (util_logits == nullptr) return SPKV_OK;
     commit_lengths(c, cu_seqlens);
     if (n_max > SPKV_MAX_CHUNK_TOKENS) {          // shorter ones: see tighten_bound
         if (short_chunk) c->bound_is_loose = true;

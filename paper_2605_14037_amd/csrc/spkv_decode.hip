@@ -732,8 +732,9 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
 
 // ------------------------------------------------------- multi-token step (chunk)
 // Up to 16 new tokens per sequence attend in one pass (speculative-decoding verification,
-// prompt feed in 16-token chunks): the MFMA columns are (token i, head g) pairs, col =
-// i G + g, in NQ groups of 16, so every K/V tile is still read once per (sequence, KV head).
+// prompt feed in short chunks) if they fit the 16 MFMA columns: (token i, head g) pairs, col =
+// i G + g, so every K/V tile is still read once per (sequence, KV head).  (Wider chunks:
+// spkv_prefill_attend_direct.)
 // The cache is in the state before the chunk's append.  Long-term keys are available to
 // every token of the chunk (they are at least w + 1 positions behind).  A ring key of age
 // a (0 = oldest, position T - w) is inside the window of chunk token i iff a > i (the window
@@ -741,12 +742,10 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
 // gate (Eq. 3-4).  The chunk's own keys (causal, always inside the window because the
 // chunk is not longer than the window) are added by spkv_chunk_combine.
 //
-// GAPLESS (one column group only): workgroups numbered without gaps (see decode_split_compact), four
+// GAPLESS: workgroups numbered without gaps (see decode_split_compact), four
 // waves per compute unit: a partial result has 16 columns here, four times a decode item's, so fewer
 // items pay (16 sequences of 32k, 4 drafts: 103 us plain with 1960 items, 101.6 / 99.4 / 97.4 / 96.7
 // with 1792 / 1536 / 1280 / 1024 without gaps; 40 of 2k-20k mixed 146 -> 133; 4 of 128k 56 -> 52).
-// (One body for both, in the kernel itself: as a function that the two numberings call it is
-// scheduled differently, 2 to 4 % slower with four column groups.)
 template <int D, int NQ, bool GAPLESS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GAPLESS ? 2 : 1, GAPLESS ? 2 : 10))) void spkv_chunk_split(
     SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvSplit sp, SpkvCu cu) {
@@ -891,16 +890,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GAPLESS ? 2 
 // Merge for one (pair, column = token i, head g): the split-K partials plus one term per
 // chunk token j <= i taken from the caller's k / v rows (score q_i . k_j in fp32, sum 1,
 // value v_j); bf16 output row cu[b] + i.  The waves share the partials and the chunk
-// tokens round-robin and meet in LDS, as in spkv_decode_combine.
+// tokens round-robin and meet in LDS, as in spkv_decode_combine.  With f set the first n_pairs
+// workgroups append the chunk meanwhile: the merge reads the caller's rows and the partials only.
 template <int D>
 __global__ __launch_bounds__(256) void spkv_chunk_combine(SpkvView v, const uint16_t* __restrict__ q,
                                                           const uint16_t* __restrict__ k_new,
                                                           const uint16_t* __restrict__ v_new,
                                                           uint16_t* __restrict__ out,
                                                           float* __restrict__ lse, float scale_log2e,
-                                                          SpkvSplit sp, SpkvCu cu, int cstride) {
-    constexpr int E = D / 64;
-    const int pair = blockIdx.x / cstride, col = blockIdx.x - pair * cstride;
+                                                          SpkvSplit sp, SpkvCu cu, const float* __restrict__ f) {
+    constexpr int E = D / 64, cstride = 16;
+    const int n_append = f != nullptr ? v.n_pairs : 0;
+    if ((int)blockIdx.x < n_append) {
+        append_few<D>(v, blockIdx.x, k_new, v_new, f, cu);
+        return;
+    }
+    const int at = (int)blockIdx.x - n_append, pair = at / cstride, col = at - pair * cstride;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
     if (col >= n_tok * v.G) return;
@@ -977,46 +982,33 @@ __global__ __launch_bounds__(256) void spkv_chunk_combine(SpkvView v, const uint
     }
 }
 
-template <int D, int NQ>
+template <int D>
 static hipError_t launch_chunk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const uint16_t* q, uint16_t* out, float* lse, float scale_log2e,
-                               SpkvSplit sp, const SpkvCu& cu, hipStream_t s) {
+                               SpkvSplit sp, const SpkvCu& cu, const float* f, hipStream_t s) {
     const unsigned grid = (unsigned)v.n_pairs * (unsigned)sp.slots;
-    if (NQ == 1 && sp.compact > 0) spkv_chunk_split<D, 1, true><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
-    else spkv_chunk_split<D, NQ, false><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
-    spkv_chunk_combine<D><<<dim3(v.n_pairs * NQ * 16), dim3(256), 0, s>>>(
-        v, q, k, vv, out, lse, scale_log2e, sp, cu, NQ * 16);
+    if (sp.compact > 0) spkv_chunk_split<D, 1, true><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    else spkv_chunk_split<D, 1, false><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    spkv_chunk_combine<D><<<dim3((f != nullptr ? v.n_pairs : 0) + v.n_pairs * 16), dim3(256), 0, s>>>(
+        v, q, k, vv, out, lse, scale_log2e, sp, cu, f);
     return hipGetLastError();
 }
 
 hipError_t spkv_launch_decode_chunk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                     const uint16_t* q, uint16_t* out, float* lse, float sm_scale,
-                                    SpkvSplit sp, const SpkvCu& cu, int col_groups, hipStream_t s) {
+                                    SpkvSplit sp, const SpkvCu& cu, const float* f, hipStream_t s) {
     const float sl = sm_scale * 1.4426950408889634f;
-    if (v.D == 128) {
-        if (col_groups <= 1) return launch_chunk<128, 1>(v, k, vv, q, out, lse, sl, sp, cu, s);
-        if (col_groups == 2) return launch_chunk<128, 2>(v, k, vv, q, out, lse, sl, sp, cu, s);
-        return launch_chunk<128, 4>(v, k, vv, q, out, lse, sl, sp, cu, s);
-    }
-    if (col_groups <= 1) return launch_chunk<64, 1>(v, k, vv, q, out, lse, sl, sp, cu, s);
-    if (col_groups == 2) return launch_chunk<64, 2>(v, k, vv, q, out, lse, sl, sp, cu, s);
-    return launch_chunk<64, 4>(v, k, vv, q, out, lse, sl, sp, cu, s);
+    return v.D == 128 ? launch_chunk<128>(v, k, vv, q, out, lse, sl, sp, cu, f, s)
+                      : launch_chunk<64>(v, k, vv, q, out, lse, sl, sp, cu, f, s);
 }
 
-int spkv_chunk_resident_items(int head_dim, int col_groups) {
+int spkv_chunk_resident_items(int head_dim) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    hipError_t e;
-    if (head_dim == 128) {
-        if (col_groups <= 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 1, false>, 64, 0);
-        else if (col_groups == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 2, false>, 64, 0);
-        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 4, false>, 64, 0);
-    } else {
-        if (col_groups <= 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 1, false>, 64, 0);
-        else if (col_groups == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 2, false>, 64, 0);
-        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 4, false>, 64, 0);
-    }
+    const hipError_t e =
+        head_dim == 128 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<128, 1, false>, 64, 0)
+                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spkv_chunk_split<64, 1, false>, 64, 0);
     if (e != hipSuccess || per_cu <= 0 || cus <= 0) return 0;
     return per_cu * cus;
 }

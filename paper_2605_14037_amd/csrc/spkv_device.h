@@ -144,12 +144,28 @@ __device__ __forceinline__ void load_row_to_lds(const char* base, unsigned voff,
                  : "m0");
 }
 
+__device__ __forceinline__ void load_row_to_lds_once(const char* base, unsigned voff, unsigned lds_row) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                 :
+                 : "v"(voff), "s"(base), "s"(lds_row)
+                 : "m0");
+}
+
 // Waits until at most N of this wave's vector memory loads are still in flight (they
 // complete in the order issued).
 template <int N>
 __device__ __forceinline__ void wait_loads_but() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N));
 }
+
+// The same where no barrier follows (LDS that only this wave copies to and reads): nor may the
+// compiler move a read of LDS across it.
+template <int N>
+__device__ __forceinline__ void wait_copies_but() {
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+// Every LDS read of this wave has returned (before a copy may overwrite what it read).
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
 
 // ------------------------------------------------------------------ utility predictor
 // Hidden layer of the predictor (Eq. 1) for 16 hidden units x 16 tokens over kq (a multiple
@@ -286,6 +302,89 @@ __device__ __forceinline__ void append_store(const SpkvView& v, int pair, int T,
         v.ring_logit[(size_t)pair * v.w + slot] = r.f_new;
         v.t_pair[pair] = T + 1;
         if (gate_passes(v, r.f_new, T)) v.gate_on[pair] += 1;
+    }
+}
+
+// Lane (r = lane / 16, c = lane % 16) moves chunk c of one row into row dk of page dp.
+template <int D>
+__device__ __forceinline__ void store_row_chunk(uint16_t* dp, int dk, int c, uint4 kk, uint4 vv) {
+    *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk, c * 8)) = kk;
+    uint16_t* vd = dp + spkv_v_off(D, dk, c * 8);      // element e of the chunk is 8 e further
+    const unsigned w[4] = {vv.x, vv.y, vv.z, vv.w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vd[e * 8] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
+}
+
+// Append of up to kFewTokens tokens (and at most w, so that none enters and leaves the window within
+// the call) to one (sequence, head) by a workgroup of 256 threads: chunk c = tid % 16 of leaving row and
+// of new row tid / 16.  Every wave judges all leaving rows for itself, so the only barriers are the one
+// between reading the ring and writing it and the one that hands out a page.  Bound by dependent round
+// trips, three of them: counters (the new rows travel beside), ring rows, logits and page id, stores.
+constexpr int kFewTokens = 16;
+template <int D>
+__device__ __forceinline__ void append_few(const SpkvView& v, int pair, const uint16_t* __restrict__ k,
+                                           const uint16_t* __restrict__ vv, const float* __restrict__ f,
+                                           const SpkvCu& cu) {
+    const int b = pair / v.Hkv, h = pair - b * v.Hkv, row0 = cu.v[b], n = cu.v[b + 1] - row0;
+    if (n == 0) return;
+    __shared__ int s_few_page;
+    const int tid = threadIdx.x, lane = tid & 63, r = tid >> 4, c = tid & 15;
+    const int T = v.t_pair[pair], L = v.kept_len[pair];
+    const bool mover = c < D / 8;
+    uint4 k_new = {0u, 0u, 0u, 0u}, v_new = k_new, k_old = k_new, v_old = k_new;
+    if (r < n && mover) {
+        const size_t src = ((size_t)(row0 + r) * v.Hkv + h) * D + c * 8;
+        k_new = *reinterpret_cast<const uint4*>(k + src);
+        v_new = *reinterpret_cast<const uint4*>(vv + src);
+    }
+    const float f_new = lane < n ? f[((size_t)row0 + lane) * v.Hkv + h] : 0.f;      // lane j: token j
+    const int r0 = max(0, T - v.w), nr = max(0, min(T, max(0, T + n - v.w)) - r0);
+    const float f_old = lane < nr ? v.ring_logit[(size_t)pair * v.w + (r0 + lane) % v.w] : 0.f;
+    const int lp = L >> 6, gk = L & 63;
+    int page = gk != 0 && lp < v.pt_cap ? v.page_table[(size_t)pair * v.pt_cap + lp] : -1;
+    if (r < nr && mover) {
+        const int slot = (r0 + r) % v.w, sk = slot & 63;
+        const uint16_t* sp = ring_page(v, pair, slot >> 6);
+        const uint16_t* vs = sp + spkv_v_off(D, sk, c * 8);
+        k_old = *reinterpret_cast<const uint4*>(sp + spkv_k_off(D, sk, c * 8));
+        v_old.x = (unsigned)vs[0] | ((unsigned)vs[8] << 16);
+        v_old.y = (unsigned)vs[16] | ((unsigned)vs[24] << 16);
+        v_old.z = (unsigned)vs[32] | ((unsigned)vs[40] << 16);
+        v_old.w = (unsigned)vs[48] | ((unsigned)vs[56] << 16);
+    }
+    const unsigned long long mask = __ballot(lane < nr && gate_passes(v, f_old, r0 + lane));
+    const int kept = __popcll(mask), on = __popcll(__ballot(lane < n && gate_passes(v, f_new, T + lane)));
+    const int first = (L + kPageTokens - 1) / kPageTokens, last = (L + kept + kPageTokens - 1) / kPageTokens;
+    if (last > first) {                                  // at most one page (kept <= 16)
+        if (tid == 0) {
+            const int np = first < v.pt_cap ? alloc_page(v) : -1;
+            if (np >= 0) v.page_table[(size_t)pair * v.pt_cap + first] = np;
+            else *v.err_flag = 1;
+            s_few_page = np;
+        }
+    }
+    __syncthreads();                                     // the leaving rows have been read
+    const int new_page = last > first ? s_few_page : 0;
+    if (tid == 0) {
+        if (new_page >= 0) v.kept_len[pair] = L + kept;
+        v.t_pair[pair] = T + n;
+        v.gate_on[pair] += on;
+    }
+    if (new_page < 0) return;
+    const float lg_old = __shfl(f_old, r), lg_new = __shfl(f_new, r);      // (all lanes here)
+    if (r < nr && ((mask >> r) & 1ull)) {
+        const int gi = L + __popcll(mask & ((1ull << r) - 1)), dk = gi & 63;
+        if ((gi >> 6) >= first) page = new_page;
+        if (mover) store_row_chunk<D>(pool_page(v, page), dk, c, k_old, v_old);
+        if (c == 0) {
+            v.pos_pool[(size_t)page * kPageTokens + dk] = r0 + r;
+            v.logit_pool[(size_t)page * kPageTokens + dk] = lg_old;
+        }
+    }
+    if (r < n) {
+        const int slot = (T + r) % v.w;
+        if (mover) store_row_chunk<D>(ring_page(v, pair, slot >> 6), slot & 63, c, k_new, v_new);
+        if (c == 0) v.ring_logit[(size_t)pair * v.w + slot] = lg_new;
     }
 }
 

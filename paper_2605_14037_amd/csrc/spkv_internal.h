@@ -134,14 +134,16 @@ hipError_t spkv_launch_decode_step_predict(const SpkvView& v, const uint16_t* k,
                                            const uint16_t* q, uint16_t* out, float* lse,
                                            float sm_scale, SpkvSplit split, SpkvPredict pr,
                                            hipStream_t s);
+// At most 16 columns (token, head).  f: the new tokens' logits, which are then appended in the second
+// launch; null: attention alone.
 hipError_t spkv_launch_decode_chunk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                     const uint16_t* q, uint16_t* out, float* lse, float sm_scale,
-                                    SpkvSplit split, const SpkvCu& cu, int col_groups, hipStream_t s);
+                                    SpkvSplit split, const SpkvCu& cu, const float* f, hipStream_t s);
 hipError_t spkv_launch_soft_gated(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                   const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                   float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
                                   float* bias, int shp, hipStream_t s);
-int spkv_chunk_resident_items(int head_dim, int col_groups);
+int spkv_chunk_resident_items(int head_dim);
 // Prefill attention of n <= n_max new tokens per sequence plus their append.  stage:
 // n_pairs * shp staging half-pages (shp >= ceil((w + n_max) / 32)); prefix: one int32 per
 // (new token, KV head).
@@ -154,6 +156,10 @@ hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint1
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
                                int32_t* prefix, int shp, int ks, int slots, bool once, float* part, hipStream_t s);
+// Chunks that are attended from the lists and the ring as they are, before their append (by
+// spkv_launch_prefill, which then needs no staging rows and no prefix counts and takes f = null for
+// "append nothing").
+bool spkv_prefill_direct(const SpkvView& v, int n_max);
 // Workgroups (spans of tokens per (sequence, KV head)) of a prefill call, and the bytes of
 // split-K partials for them.
 struct SpkvPrefillShape {

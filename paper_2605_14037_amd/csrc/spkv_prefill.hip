@@ -18,6 +18,8 @@
 //      long-term prefix and then the staging rows of the block's windows, one online softmax per
 //      column, and writes the normalised bf16 rows (or, when a span's keys are cut into ranges,
 //      partial results that spkv_prefill_combine merges).
+// Chunks of at most kFewTokens tokens skip the first two steps and are appended beside the merge
+// (DIRECT below).
 // Window keys and long-term entries are disjoint (positions > t - w against <= t - w), so
 // every available key is counted once.
 
@@ -327,11 +329,24 @@ __device__ __forceinline__ bool locate_range(const SpkvView& v, const SpkvCu& cu
 // once per workgroup into a ring of LDS buffers (every wave copies its share of a tile straight from
 // memory into LDS, two tiles ahead of the one all waves consume) and each wave reads its MFMA A
 // operands from LDS with conflict-free 16-byte reads.
-template <int D, int NW, int NQ>
+// DIRECT (at most kFewTokens tokens, no more than the window): attended BEFORE the append, without the
+// staging rows and prefix counts of the longer chunks, two launches less.  The tiles are the whole list, the ring's
+// half-pages as they lie -- a ring key counts for the tokens that still have it in their window, and
+// for all if it passes the gate -- and, for the last range of a pair, the chunk's own rows, which its waves
+// lay out in LDS themselves.  16 tokens, 16 sequences of 32k: stage 11, append 7.5, attention 95.6
+// and merge 7.5 us as four launches; attention 93.6 and merge with the append beside it 9.1 as two
+// (118 -> 100 us a call; one of 4 x 2k 31 -> 19.5).  What is left is the read at 5 TB/s: ranges up to a
+// tenth longer than their mean (a pair has a whole number of them), about 4 us of search.  Tried and
+// slower: tiles in registers, a wave per 32 columns and tile (115 us: two waves load a tile, half the
+// bytes in flight); a ring of LDS per wave, all columns in one wave, no barrier (102 us, and 8 us more
+// for short lists, where one wave's products are the longest chain).
+template <int D, int NW, int NQ, bool DIRECT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_prefill_attend(SpkvView v, const uint16_t* __restrict__ q,
                                                            uint16_t* __restrict__ out,
                                                            float* __restrict__ lse, float scale_log2e,
-                                                           SpkvPrefill pf, SpkvCu cu) {
+                                                           SpkvPrefill pf, SpkvCu cu,
+                                                           const uint16_t* __restrict__ k_new,
+                                                           const uint16_t* __restrict__ v_new) {
     constexpr int NS = D / 32, NB = D / 16;
     constexpr int kHalfElems = 2 * kHalfTokens * D;
     constexpr int kRows = kHalfElems / 512;     // 1 KB rows of a tile
@@ -339,7 +354,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // Tiles in flight ahead of the one in use (three measured no faster than two, for long
     // chunks and for the two-wave workgroups of short ones alike).
     constexpr int kAhead = 2, kBufs = kAhead + 1;
-    __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs][kHalfElems];
+    __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs + (DIRECT ? 1 : 0)][kHalfElems];
+    constexpr int kGateSlots = 1024;
+    __shared__ unsigned long long s_gate[DIRECT ? kGateSlots / 64 : 1];       // gate of the ring's first slots
     int pair, kr, ranges;
     bool once = pf.once != 0;
     if (pf.slots == 0) {
@@ -366,11 +383,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int i0 = wv * pf.tb;
     const int tbv = max(0, min(pf.tb, n_tok - i0)), i_last = i0 + tbv - 1, cols = tbv * v.G;
     const bool active = tbv > 0;
-    // the cache is in the state after the append
-    const int T0 = v.t_pair[pair] - n_tok, L = v.kept_len[pair];
+    // the cache is in the state after the append (DIRECT: before it)
+    const int T0 = v.t_pair[pair] - (DIRECT ? 0 : n_tok), L = v.kept_len[pair];
     const int u_min = max(0, v.w - T0);     // first staging row that holds a position
 
     auto prefix_of = [&](int i) -> int {   // long-term entries at least w behind token i
+        if (DIRECT) return L;
         if (T0 + i - v.w < 0) return 0;
         return min(max(pf.prefix[((size_t)row0 + i) * v.Hkv + h], 0), L);
     };
@@ -399,13 +417,47 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int fullA = active ? prefix_of(i0) >> 5 : 0;
     // staging half-pages: rows [1, last_tok + w] that hold a position; this wave's windows
     // cover rows [lo_w, hi_w]
-    const int sB0 = max(1, u_min) >> 5;
-    const int nB = ((last_tok + v.w) >> 5) - sB0 + 1;
+    // (DIRECT: ring half-pages that hold a key, and one tile more, which the loop does not reach)
+    const int sB0 = DIRECT ? 0 : max(1, u_min) >> 5, held = min(T0, v.w);
+    const int nB = DIRECT ? (held + kHalfTokens - 1) >> 5 : ((last_tok + v.w) >> 5) - sB0 + 1;
     const int lo_w = max(i0 + 1, u_min), hi_w = i_last + v.w;
-    const int n_hp = nA + nB, last = n_hp - 1;
-    // split-K: this workgroup takes tiles [x_begin, x_end) of the span's n_hp
+    const int n_loop = nA + nB, n_hp = n_loop + (DIRECT ? 1 : 0), last = max(n_loop - 1, 0);
+    // split-K: this workgroup takes tiles [x_begin, x_stop) of the span's n_hp
     const int x_begin = (int)(((long long)kr * n_hp) / ranges);
-    const int x_end = (int)(((long long)(kr + 1) * n_hp) / ranges);
+    const int x_stop = (int)(((long long)(kr + 1) * n_hp) / ranges), x_end = min(x_stop, n_loop);
+    // DIRECT: age of a ring slot's key, 0 = the position w behind the first new token; does it pass the gate?
+    const int slot0 = T0 >= v.w ? T0 % v.w : T0 - v.w;
+    auto age_of = [&](int at) -> int { return at - slot0 + (at < slot0 ? v.w : 0); };
+    auto ring_gate = [&](int at) -> bool {
+        return gate_passes(v, v.ring_logit[(size_t)pair * v.w + at], T0 - v.w + age_of(at));
+    };
+    if (DIRECT && x_end > nA)               // this workgroup reaches into the ring
+        for (int at = wv * 64; at < min(held, kGateSlots); at += 64 * NW) {
+            const unsigned long long gates = __ballot(ring_gate(min(at + lane, held - 1)));
+            if (lane == 0) s_gate[at >> 6] = gates;
+        }
+    if (DIRECT && x_stop > n_loop) {        // the chunk's own rows as a tile: key j is token j, then zeros
+        uint16_t* tile = s_tile[kBufs];
+#pragma unroll 2
+        for (int e = tid; e < kHalfElems / 16; e += 64 * NW) {          // 16-byte units of K, then of V
+            const int mm = e & 15, chunk = (e >> 4) % (D / 8), t = (e >> 4) / (D / 8);
+            const int key = 8 * (mm >> 2) + 4 * t + (mm & 3);
+            uint4 kk = {0u, 0u, 0u, 0u};
+            if (key < n_tok) kk = *reinterpret_cast<const uint4*>(k_new + ((size_t)(row0 + key) * v.Hkv + h) * D + chunk * 8);
+            const int d = (e >> 6) * 16 + (e & 15), key0 = 8 * ((e >> 4) & 3);
+            unsigned w[4] = {0u, 0u, 0u, 0u};
+            if (key0 < n_tok) {
+                unsigned x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[j] = v_new[((size_t)(row0 + min(key0 + j, last_tok)) * v.Hkv + h) * D + d];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (key0 + j < n_tok) w[j >> 1] |= x[j] << (16 * (j & 1));
+            }
+            *reinterpret_cast<uint4*>(tile + (size_t)e * 8) = kk;
+            *reinterpret_cast<uint4*>(tile + kHalfTokens * D + (size_t)e * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
 
     const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
     const uint16_t* stage = pf.stage + (size_t)pair * pf.shp * (size_t)kHalfElems;
@@ -427,6 +479,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             const int page = min(max(page_of(min(x >> 1, v.pt_cap - 1)), 0), v.n_pages - 1);
             return pool_page(v, page) + (x & 1) * kHalfElems;
         }
+        if (DIRECT) return ring_page(v, pair, (x - nA) >> 1) + ((x - nA) & 1) * kHalfElems;
         return stage + (size_t)min(sB0 + x - nA, pf.shp - 1) * kHalfElems;
     };
 
@@ -486,6 +539,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 // the tile after next (past the last one: the last tile again, never used)
                 stage_tile(p_next, buf >= 1 ? buf - 1 : kBufs - 1);
                 p_next = base_of(x + kAhead + 1);
+                if (DIRECT && x == n_loop - 1 && (held & 31) != 0) {
+                    // slots of a ring that is not full yet: whatever lies there must not meet a weight of 0
+                    uint16_t* vt = s_tile[buf] + kHalfTokens * D;
+                    for (int e = tid; e < kHalfElems / 2; e += 64 * NW)       // element e: key 8 ((e >> 7) & 3) + (e & 7)
+                        if (8 * ((e >> 7) & 3) + (e & 7) >= (held & 31)) vt[e] = 0;
+                    __syncthreads();
+                }
             }
             resume = false;
             const uint16_t* tile = s_tile[buf];
@@ -495,7 +555,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 mine = x < nA_wave;
             } else {
                 u_tile = (sB0 + x - nA) * kHalfTokens;
-                mine = active && u_tile <= hi_w && u_tile + kHalfTokens > lo_w;
+                mine = active && (DIRECT || (u_tile <= hi_w && u_tile + kHalfTokens > lo_w));
             }
             if (mine) {
                 // per column group: which of this lane's eight keys are excluded
@@ -507,6 +567,23 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                         const int k0 = x * kHalfTokens + kc * 8;   // list index of this lane's first key
 #pragma unroll
                         for (int c = 0; c < NQ; ++c) kill[c] = bit_range8(0, cnt[c] - k0 - 1) ^ 0xffu;
+                    }
+                } else if (DIRECT) {
+                    const int u0 = u_tile + kc * 8;
+                    unsigned gate = 0u;
+                    if (u_tile < kGateSlots) {
+                        gate = (unsigned)(s_gate[u_tile >> 6] >> (u0 & 63));
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (ring_gate(min(u0 + e, held - 1))) gate |= 1u << e;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int at = u0 + e, age = age_of(at);
+#pragma unroll
+                        for (int c = 0; c < NQ; ++c)       // in token i's window iff its age is above i
+                            if (at >= held || !(((gate >> e) & 1u) || age > tok[c])) kill[c] |= 1u << e;
                     }
                 } else {
                     const int u0 = u_tile + kc * 8;
@@ -534,6 +611,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         }
     }
     wait_loads_but<0>();
+    if (DIRECT && x_stop > n_loop && active) {
+        unsigned kill[NQ];
+#pragma unroll
+        for (int c = 0; c < NQ; ++c) kill[c] = bit_range8(0, tok[c] - kc * 8) ^ 0xffu;
+        tile_scores<D, NQ>(s_tile[kBufs], lane, qb, kill, true, xs);
+        f32x8 pw[NQ];
+        float psum[NQ];
+        if (tile_weights<NQ>(xs, scale_log2e, m, pw, psum)) {
+            rescale_columns<D, NQ>(xs, scale_log2e, acc, m, l);
+            (void)tile_weights<NQ>(xs, scale_log2e, m, pw, psum);
+        }
+        tile_accumulate<D, NQ>(s_tile[kBufs], lane, pw, psum, acc, l);
+    }
 
 #pragma unroll
     for (int c = 0; c < NQ; ++c) {
@@ -938,15 +1028,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Merge of the tile ranges of one (span, column): out = sum_r 2^(m_r - M) acc_r /
 // sum_r 2^(m_r - M) l_r.  A workgroup of 256 threads takes 256 / (D / 4) consecutive columns
 // of a span's workgroup; a thread owns four consecutive output elements of one column.
+// With f set (chunks attended before their append) the first n_pairs workgroups append the chunk
+// meanwhile: the merge reads nothing of the cache.
 template <int D>
 __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t* __restrict__ out,
                                                             float* __restrict__ lse, SpkvPrefill pf,
-                                                            SpkvCu cu) {
+                                                            SpkvCu cu, const uint16_t* __restrict__ k,
+                                                            const uint16_t* __restrict__ vv,
+                                                            const float* __restrict__ f) {
+    const int n_append = f != nullptr ? v.n_pairs : 0;
+    if ((int)blockIdx.x < n_append) {
+        append_few<D>(v, blockIdx.x, k, vv, f, cu);
+        return;
+    }
     constexpr int TPC = D / 4, CPB = 256 / TPC;          // threads per column, columns per block
     const int kCols = pf.nw * pf.nq * 16;               // a multiple of CPB (of 16)
     const int blocks_per_span = kCols / CPB;
-    const int span = blockIdx.x / blocks_per_span;
-    const int cs = (blockIdx.x - span * blocks_per_span) * CPB + (int)threadIdx.x / TPC;
+    const int id = (int)blockIdx.x - n_append, span = id / blocks_per_span;
+    const int cs = (id - span * blocks_per_span) * CPB + (int)threadIdx.x / TPC;
     const int d = ((int)threadIdx.x % TPC) * 4;
     const int pair = span / pf.nblk, qblk = span - pair * pf.nblk;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
@@ -961,18 +1060,34 @@ __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t
     if (pf.slots > 0) cut = reinterpret_cast<const int2*>(pf.part + n_cols * (D + 2))[pair];
     const size_t pc0 = (size_t)cut.x * kCols + cs;             // range r: pc0 + r * kCols
     const float* ml = pf.part + n_cols * D;
-    // (unrolled: the loads of several ranges in flight together)
-    float M = SPKV_NEG_INF;
-#pragma unroll 8
-    for (int r = 0; r < cut.y; ++r) M = fmaxf(M, ml[(pc0 + (size_t)r * kCols) * 2]);
+    // Ranges kFold at a time, all their loads in flight together; only the rescaling is chained.
+    constexpr int kFold = 8;
+    float M = SPKV_NEG_INF, den = 0.f;
     f32x4 num = {0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-#pragma unroll 4
-    for (int r = 0; r < cut.y; ++r) {
-        const size_t pc = pc0 + (size_t)r * kCols;
-        const float sc = __builtin_amdgcn_exp2f(ml[pc * 2] - M);      // 0 for a range without keys
-        num += *reinterpret_cast<const f32x4*>(pf.part + pc * D + d) * sc;
-        den += ml[pc * 2 + 1] * sc;
+    for (int r0 = 0; r0 < cut.y; r0 += kFold) {
+        float2 x[kFold];
+        f32x4 a[kFold];
+#pragma unroll
+        for (int u = 0; u < kFold; ++u) {
+            const size_t pc = pc0 + (size_t)min(r0 + u, cut.y - 1) * kCols;      // past the end: re-read, ignored
+            x[u] = *reinterpret_cast<const float2*>(ml + pc * 2);
+            a[u] = *reinterpret_cast<const f32x4*>(pf.part + pc * D + d);
+        }
+        float m_new = M;
+#pragma unroll
+        for (int u = 0; u < kFold; ++u)
+            if (r0 + u < cut.y) m_new = fmaxf(m_new, x[u].x);
+        const float m_ref = m_new == SPKV_NEG_INF ? 0.f : m_new, so = __builtin_amdgcn_exp2f(M - m_ref);
+        den *= so;
+        num *= so;
+#pragma unroll
+        for (int u = 0; u < kFold; ++u)
+            if (r0 + u < cut.y) {
+                const float sc = __builtin_amdgcn_exp2f(x[u].x - m_ref);         // 0 for a range without keys
+                num += a[u] * sc;
+                den += x[u].y * sc;
+            }
+        M = m_new;
     }
     const size_t o = (size_t)(row0 + i) * v.Hq + (size_t)h * v.G + g;
     const float inv = 1.0f / den;
@@ -1035,17 +1150,47 @@ size_t spkv_prefill_partial_bytes(int spans, int ks, SpkvPrefillShape sh, int he
 }
 
 // The attention launch of the shape chosen for the call.
-template <int D>
+template <int D, bool DIRECT>
 static void launch_attend(const SpkvView& v, const uint16_t* q, uint16_t* out, float* lse, float sl,
-                          const SpkvPrefill& pf, const SpkvCu& cu, unsigned grid, hipStream_t s) {
+                          const SpkvPrefill& pf, const SpkvCu& cu, const uint16_t* k, const uint16_t* vv,
+                          hipStream_t s) {
+    const dim3 grid(prefill_grid(v, pf));
     if (pf.nw == 8)
-        spkv_prefill_attend32<D, false><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend32<D, false><<<grid, dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     else if (pf.nq == 2)
-        spkv_prefill_attend<D, 4, 2><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend<D, 4, 2, DIRECT><<<grid, dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu, k, vv);
     else if (pf.nw == 4)
-        spkv_prefill_attend<D, 4, 1><<<dim3(grid), dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend<D, 4, 1, DIRECT><<<grid, dim3(256), 0, s>>>(v, q, out, lse, sl, pf, cu, k, vv);
     else
-        spkv_prefill_attend<D, 2, 1><<<dim3(grid), dim3(128), 0, s>>>(v, q, out, lse, sl, pf, cu);
+        spkv_prefill_attend<D, 2, 1, DIRECT><<<grid, dim3(128), 0, s>>>(v, q, out, lse, sl, pf, cu, k, vv);
+}
+
+bool spkv_prefill_direct(const SpkvView& v, int n_max) {
+    return n_max <= kFewTokens && n_max <= v.w && prefill_shape(v.G, n_max).nw != 8;
+}
+
+template <int D>
+static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv, const float* f,
+                                 const uint16_t* q, uint16_t* out, float* lse, float sl, const SpkvCu& cu, int n_max,
+                                 const SpkvPrefill& pf, hipStream_t s) {
+    const bool direct = spkv_prefill_direct(v, n_max), merge = pf.ks > 1 || pf.slots > 0;
+    if (direct) {
+        launch_attend<D, true>(v, q, out, lse, sl, pf, cu, k, vv, s);
+    } else {
+        const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
+        spkv_prefill_stage<D><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
+        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, s);
+        if (e != hipSuccess) return e;
+        launch_attend<D, false>(v, q, out, lse, sl, pf, cu, nullptr, nullptr, s);
+    }
+    if (merge) {
+        const float* fa = direct ? f : nullptr;
+        const int blocks = v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / (256 / (D / 4));
+        spkv_prefill_combine<D><<<dim3((fa != nullptr ? v.n_pairs : 0) + blocks), dim3(256), 0, s>>>(v, out, lse, pf, cu, k, vv, fa);
+    } else if (direct && f != nullptr) {
+        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, s);
+    }
+    return hipGetLastError();
 }
 
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
@@ -1054,23 +1199,8 @@ hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint1
                                int32_t* prefix, int shp, int ks, int slots, bool once, float* part, hipStream_t s) {
     const SpkvPrefill pf = prefill_params(v, n_max, stage, prefix, nullptr, shp, ks, part, slots, once);
     const float sl = sm_scale * 1.4426950408889634f;
-    const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
-    const unsigned grid = prefill_grid(v, pf);
-    hipError_t e;
-    if (v.D == 128) {
-        spkv_prefill_stage<128><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
-        if ((e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, prefix, s)) != hipSuccess) return e;
-        launch_attend<128>(v, q, out, lse, sl, pf, cu, grid, s);
-        if (ks > 1 || slots > 0)
-            spkv_prefill_combine<128><<<dim3(v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / 8), dim3(256), 0, s>>>(v, out, lse, pf, cu);
-    } else {
-        spkv_prefill_stage<64><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
-        if ((e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, prefix, s)) != hipSuccess) return e;
-        launch_attend<64>(v, q, out, lse, sl, pf, cu, grid, s);
-        if (ks > 1 || slots > 0)
-            spkv_prefill_combine<64><<<dim3(v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / 16), dim3(256), 0, s>>>(v, out, lse, pf, cu);
-    }
-    return hipGetLastError();
+    return v.D == 128 ? launch_prefill<128>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, s)
+                      : launch_prefill<64>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, s);
 }
 
 // Soft-gated attention of whole sequences (no cache): the same staging and the same tile

@@ -208,16 +208,6 @@ struct BulkInfo {
     int32_t pad[5];
 };
 
-// Lane (r = lane / 16, c = lane % 16) moves chunk c of one row into row dk of page dp.
-template <int D>
-__device__ __forceinline__ void store_row_chunk(uint16_t* dp, int dk, int c, uint4 kk, uint4 vv) {
-    *reinterpret_cast<uint4*>(dp + spkv_k_off(D, dk, c * 8)) = kk;
-    uint16_t* vd = dp + spkv_v_off(D, dk, c * 8);      // element e of the chunk is 8 e further
-    const unsigned w[4] = {vv.x, vv.y, vv.z, vv.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) vd[e * 8] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
-}
-
 // Stage 1: per (segment, pair): how many of the segment's new tokens pass the gate, and how
 // many of those also leave the window within this call (j < n - w).
 __global__ __launch_bounds__(256) void spkv_bulk_count(SpkvView v, const float* __restrict__ f,
@@ -750,9 +740,21 @@ static bool ring_in_one_workgroup(const SpkvView& v, int n_max) {
     return v.w <= 64 || (n_max > kScatterThreads && (v.w <= 128 || v.n_pairs >= 64));
 }
 
+template <int D>
+__global__ __launch_bounds__(256) void spkv_append_few(SpkvView v, const uint16_t* __restrict__ k,
+                                                       const uint16_t* __restrict__ vv,
+                                                       const float* __restrict__ f, SpkvCu cu) {
+    append_few<D>(v, blockIdx.x, k, vv, f, cu);
+}
+
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
                                    hipStream_t s) {
+    if (n_max <= kFewTokens && n_max <= v.w && prefix == nullptr) {
+        if (v.D == 128) spkv_append_few<128><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
+        else spkv_append_few<64><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
+        return hipGetLastError();
+    }
     if (n_max <= v.w && n_max <= kSegTokens) {      // short chunks: one launch
         if (v.D == 128) spkv_bulk_ring<128, true, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
         else spkv_bulk_ring<64, true, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);

@@ -143,6 +143,22 @@ def test_short_chunk_ranges(batch, tokens, kept, grid):
     assert copies == [0, 0, 1, 0]                  # a single chunk after a prompt is not charged for one
 
 
+@pytest.mark.parametrize("tokens,attend,merge", [
+    (4, "spkv_chunk_split<128, 1, 1>", "spkv_chunk_combine<128>"), (8, "spkv_prefill_attend<128, 2, 1, 1>", "spkv_prefill_combine<128>"),
+    (16, "spkv_prefill_attend<128, 4, 1, 1>", "spkv_prefill_combine<128>")])
+def test_chunks_are_two_launches(tokens, attend, merge):
+    """Attention from the cache as it is, then the merge with the append beside it: staging rows and an
+    append of its own were 18 of the 118 us of a 16-token chunk.  Drafts the same without the append."""
+    counts = [tokens] * 16
+    fill = [["append", [32768] * 16], ["lengths", _uneven(128, 20000)], ["stats"]]
+    for call, more in ((["chunk", counts], 128), (["score", counts], 0)):
+        names = [(n, grid[0]) for n, grid, _ in record(dict(batch=16), fill + [call])[-1].launches if "copy" not in n]
+        assert [n for n, _ in names] == [attend, merge]
+        assert names[1][1] == more + 128 * (16 if tokens == 4 else tokens * 4 // 8)
+    few = record(dict(batch=16), fill + [["append", counts]])[-1].launches
+    assert [n for n, _, _ in few] == ["spkv_append_few<128>"]
+
+
 @pytest.mark.parametrize("call", [["chunk", [16] * 16], ["chunk", [4] * 16], ["step"], ["attend"], ["prefill", [16] * 16]])
 def test_lengths_on_their_way_are_not_asked_for_by_event(call):
     """A query of an event is refused while a stream of the process is being captured (error 907) and
