@@ -128,7 +128,7 @@ typedef struct spkv_stats {
 size_t spkv_cache_required_bytes(const spkv_config_t* cfg);
 
 /* Create a cache inside `dev_arena` (device, 256-byte aligned, >= required bytes) and
- * enqueue on `stream` the fill that zeroes it.  The arena stays owned by the caller and
+ * enqueue on `stream` the fill that clears its counters, tables and ring.  The arena stays owned by the caller and
  * must outlive the cache.  *out receives the handle.  (Sec. 2.1; appendix "Inference
  * Kernels": window ring + per-head long-term pages.) */
 int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_bytes,
@@ -151,7 +151,8 @@ int spkv_cache_destroy(spkv_cache_t* cache);
 int spkv_cache_grow(spkv_cache_t* cache, const spkv_config_t* new_cfg, void* new_dev_arena,
                     size_t new_arena_bytes, void* stream);
 
-/* Forget every token (all sequences back to length 0); enqueues the zero fill. */
+/* Forget every token (all sequences back to length 0); one kernel is enqueued.  Pages of the
+ * long-term cache keep their bytes until they are written again; nothing of them is attended to. */
 int spkv_cache_reset(spkv_cache_t* cache, void* stream);
 
 /* Write path (Eq. 1-2; appendix "Inference Kernels").  Appends, for each sequence b,
@@ -318,9 +319,7 @@ int spkv_soft_gated_attention(const void* q, const void* k, const void* v, const
  * holds an empty sequence that can be appended to again.  (The paper's cache manager grows
  * and shares one page pool across requests, appendix "Inference Kernels"; giving pages
  * back is the counterpart a serving loop needs.)  Synchronises `stream` once to read the
- * exact lengths, then enqueues the release.  A recycled page keeps its old bytes beyond the
- * new owner's length; they are masked in attention, which is exact as long as the old
- * values were finite. */
+ * exact lengths, then enqueues the release. */
 int spkv_cache_release_sequence(spkv_cache_t* cache, int32_t b, void* stream);
 
 /* Utility predictor (Eq. 1; the listing's UtilityPredictor: Linear(d_model, d_hidden), SiLU,

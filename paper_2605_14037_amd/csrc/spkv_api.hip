@@ -75,7 +75,7 @@ bool carve(const spkv_config_t* c, Carve* out) {
     k.t_pair = take((size_t)k.n_pairs * 4);
     k.kept_len = take((size_t)k.n_pairs * 4);
     k.gate_on = take((size_t)k.n_pairs * 4);
-    k.pool_next = take(8);
+    k.pool_next = take(4);
     k.free_top = take(4);
     k.free_pages = take((size_t)k.n_pages * 4);
     k.err_flag = take(4);
@@ -221,6 +221,13 @@ void bind_view(spkv_cache* c) {
     v.pair_items = reinterpret_cast<int32_t*>(a + k.pair_items);
     v.pair_ticket = reinterpret_cast<int32_t*>(a + k.pair_ticket);
     v.pos_scratch = reinterpret_cast<int32_t*>(a + k.pos_scratch);
+}
+
+// What an empty cache needs cleared: everything up to the pool (ring, counters, tables) and the
+// counters behind it.  Pages keep what they hold: whoever begins a half-page clears the values behind
+// the list's end (clear_list_end).  Nothing else is read before it is written.
+hipError_t clear_arena(char* arena, const Carve& k, hipStream_t s) {
+    return spkv_launch_reset(arena, k.pool, k.pair_items, k.pos_scratch - k.pair_items, s);
 }
 
 // Read the exact long-term lengths back and tighten the host's bound.  Synchronises.
@@ -598,8 +605,7 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     c->split_only = false;
     c->n_timed = 0;
     bind_view(c);
-    if (spkv_launch_fill_zero(c->arena, c->arena_bytes, static_cast<hipStream_t>(stream)) !=
-        hipSuccess) {
+    if (clear_arena(c->arena, k, static_cast<hipStream_t>(stream)) != hipSuccess) {
         delete c;
         return SPKV_E_HIP;
     }
@@ -639,7 +645,7 @@ int spkv_cache_grow(spkv_cache_t* c, const spkv_config_t* cfg, void* dev_arena, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Carve& q = c->carve;
     const size_t page_bytes = (size_t)spkv_page_elems(o.head_dim) * 2;
-    if (spkv_launch_fill_zero(na, k.total, s) != hipSuccess) return SPKV_E_HIP;
+    if (clear_arena(na, k, s) != hipSuccess) return SPKV_E_HIP;
     struct Region { size_t to, from, bytes; };
     const Region regions[] = {
         {k.ring, q.ring, (size_t)q.n_pairs * q.n_ring_pages * page_bytes},
@@ -647,7 +653,7 @@ int spkv_cache_grow(spkv_cache_t* c, const spkv_config_t* cfg, void* dev_arena, 
         {k.t_pair, q.t_pair, (size_t)q.n_pairs * 4},
         {k.kept_len, q.kept_len, (size_t)q.n_pairs * 4},
         {k.gate_on, q.gate_on, (size_t)q.n_pairs * 4},
-        {k.pool_next, q.pool_next, 8},
+        {k.pool_next, q.pool_next, 4},
         {k.free_top, q.free_top, 4},
         {k.free_pages, q.free_pages, (size_t)q.n_pages * 4},
         {k.err_flag, q.err_flag, 4},
@@ -690,14 +696,7 @@ int spkv_cache_destroy(spkv_cache_t* c) {
 int spkv_cache_reset(spkv_cache_t* c, void* stream) {
     if (c == nullptr) return SPKV_E_INVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // Everything up to the pool (counters, ring, tables) is cleared; of the pool the pages that
-    // were ever handed out -- the others are zero since create, nothing else writes there; then
-    // the counters behind the pool.  What is left holds nothing that is read before it is written:
-    // positions and logits of entries, scratch, partial results.
-    const Carve& k = c->carve;
-    if (spkv_launch_reset(c->view, c->arena, k.pool_next, k.pool, k.pair_items, k.pos_scratch - k.pair_items,
-                          s) != hipSuccess)
-        return SPKV_E_HIP;
+    if (clear_arena(c->arena, c->carve, s) != hipSuccess) return SPKV_E_HIP;
     std::fill(c->T.begin(), c->T.end(), 0);
     std::fill(c->L_ub.begin(), c->L_ub.end(), 0);
     c->pages_ub = 0;

@@ -105,6 +105,22 @@ __device__ __forceinline__ int batch_page(const SpkvView& v, const PageBatch& pb
     return page < v.n_pages ? page : -1;
 }
 
+// The half-page in which a list ends is read whole: its keys past the end are masked, but a weight of
+// zero would still turn an infinite value into a NaN.  Whoever lengthens a list from `from` to `to`
+// entries therefore clears the values behind its end if this call began that half-page (page: the one it
+// lies in) -- bytes that no row of the call touches, so in any order with the rows.  Pages then need no
+// clearing when they are handed out again, whatever they held.  nt threads, this one tid.
+__device__ __forceinline__ bool ends_in_new_half_page(int from, int to) {
+    return to > from && (to & (kHalfTokens - 1)) != 0 && (to & ~(kHalfTokens - 1)) >= from;
+}
+template <int D>
+__device__ __forceinline__ void clear_list_end(uint16_t* page, int to, int tid, int nt) {
+    const int a = to & (kPageTokens - 1), end = (a | (kHalfTokens - 1)) + 1, whole = (a + 7) & ~7;
+    for (int i = tid; i < (whole - a) * D; i += nt) page[spkv_v_off(D, a + i / D, i % D)] = 0;
+    for (int i = tid; i < (end - whole) / 8 * D; i += nt)
+        *reinterpret_cast<uint4*>(page + spkv_v_off(D, whole + i / D * 8, i % D)) = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // ------------------------------------------------------------------ memory -> LDS copies
 // One wave-wide 16-byte load from global memory straight into LDS: lane i's 16 bytes at
 // `src` land at LDS byte address lds_row + 16 i (lds_row wave-uniform).  The load counts
@@ -285,6 +301,7 @@ __device__ __forceinline__ void append_store(const SpkvView& v, int pair, int T,
                 if (d < D) gp[spkv_v_off(D, gk, d)] = r.v_old[j];
             }
             if (kmover) *reinterpret_cast<uint4*>(gp + spkv_k_off(D, gk, tid * 8)) = r.k_old;
+            if (tid < NT && ends_in_new_half_page(L, L + 1)) clear_list_end<D>(gp, L + 1, tid, NT);
             if (tid == 0) {
                 v.pos_pool[(size_t)page * kPageTokens + gk] = T - v.w;
                 v.logit_pool[(size_t)page * kPageTokens + gk] = r.f_old;
@@ -371,6 +388,8 @@ __device__ __forceinline__ void append_few(const SpkvView& v, int pair, const ui
         v.gate_on[pair] += on;
     }
     if (new_page < 0) return;
+    if (ends_in_new_half_page(L, L + kept))
+        clear_list_end<D>(pool_page(v, (L + kept) >> 6 >= first ? new_page : page), L + kept, tid, 256);
     const float lg_old = __shfl(f_old, r), lg_new = __shfl(f_new, r);      // (all lanes here)
     if (r < nr && ((mask >> r) & 1ull)) {
         const int gi = L + __popcll(mask & ((1ull << r) - 1)), dk = gi & 63;

@@ -37,7 +37,7 @@ struct SpkvView {
     int32_t*  t_pair;       // [n_pairs] tokens appended so far (same for all heads of a seq)
     int32_t*  kept_len;     // [n_pairs] long-term length L
     int32_t*  gate_on;      // [n_pairs] count of appended tokens with gate on
-    int32_t*  pool_next;    // [2] next never-used pool page (bump allocator); ticket of spkv_reset
+    int32_t*  pool_next;    // [1] next never-used pool page (bump allocator)
     int32_t*  free_top;     // [1] entries on the stack of recycled pages
     int32_t*  free_pages;   // [n_pages] stack of pages given back by released sequences
     int32_t*  err_flag;     // [1] set by kernels on an impossible state
@@ -61,10 +61,8 @@ struct SpkvCu {
 };
 
 hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s);
-// Zeroes [0, pool), the pool pages handed out since the pool was last all zero, and tail_bytes at
-// `tail`; `counter` is where v.pool_next lies.  Bytes from the arena's start.
-hipError_t spkv_launch_reset(const SpkvView& v, void* arena, size_t counter, size_t pool, size_t tail,
-                             size_t tail_bytes, hipStream_t s);
+// Zeroes [0, pool) and tail_bytes at `tail`.  Bytes from the arena's start.
+hipError_t spkv_launch_reset(void* arena, size_t pool, size_t tail, size_t tail_bytes, hipStream_t s);
 // Copies the n kept lengths to pinned host memory, then stores `ticket` behind them (to_host[n]).
 hipError_t spkv_launch_copy_lengths(const SpkvView& v, int32_t* to_host, int32_t ticket, hipStream_t s);
 hipError_t spkv_launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);

@@ -24,45 +24,20 @@ hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Back to the empty cache in one launch: everything before the pool (counters, ring, tables), the
-// pool pages that were ever handed out -- those below the bump counter, which a failed allocation can
-// leave past the pool's end -- and `tail` (the counters behind the pool).  The counter itself is read
-// by every workgroup, so it goes last: by the workgroup that draws the last ticket, which sits in the
-// next word of the counter's line.  A workgroup per compute unit, because tickets are served one after
-// the other: 16 sequences of 32k tokens, half of a 0.9 GB arena in use, 71 us, 84 with 1024 workgroups
-// of 512 threads (three launches: 71; all of the arena: 159); one sequence of 4k, 2 heads of 64, 10 us
-// (three launches 19, all of the arena 13).
-constexpr int kResetBlocks = 256;
-__global__ __launch_bounds__(1024) void spkv_reset(SpkvView v, uint4* arena, size_t counter16, size_t pool16,
-                                                   size_t tail16, size_t tail_n16) {
-    __shared__ int s_pages;
-    if (threadIdx.x == 0) {
-        const int handed_out = *v.pool_next;
-        asm volatile("" : : "v"(handed_out) : "memory");   // arrived before the ticket is drawn
-        s_pages = min(max(handed_out, 0), v.n_pages);
-        if (atomicAdd(v.pool_next + 1, 1) == (int)gridDim.x - 1) {
-            v.pool_next[0] = 0;
-            v.pool_next[1] = 0;
-        }
-    }
-    __syncthreads();
+// Back to the empty cache in one launch: everything before the pool (counters, ring, tables) and the
+// counters behind it.  The pages keep what they held (clear_list_end): 16 sequences of 32k tokens, half
+// of a 0.9 GB arena in use, 64 us with the pages cleared, 6 without.
+__global__ __launch_bounds__(256) void spkv_reset(uint4* arena, size_t n16, size_t tail16, size_t tail_n16) {
     const uint4 z = {0u, 0u, 0u, 0u};
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
-    constexpr size_t kLine16 = 16;                         // the counter's 256 bytes
-    for (size_t i = i0; i < pool16 - kLine16; i += step) arena[i < counter16 ? i : i + kLine16] = z;
+    for (size_t i = i0; i < n16; i += step) arena[i] = z;
     for (size_t i = i0; i < tail_n16; i += step) arena[tail16 + i] = z;
-    uint4* pool = reinterpret_cast<uint4*>(v.pool);
-    const size_t n16 = (size_t)s_pages * (spkv_page_elems(v.D) / 8);
-    for (size_t i = i0; i < n16; i += step) pool[i] = z;
 }
 
 // Offsets and sizes in bytes, multiples of 256.
-hipError_t spkv_launch_reset(const SpkvView& v, void* arena, size_t counter, size_t pool, size_t tail,
-                             size_t tail_bytes, hipStream_t s) {
-    const size_t most16 = (pool + tail_bytes) / 16 + (size_t)v.n_pages * (spkv_page_elems(v.D) / 8);
-    const unsigned blocks = (unsigned)std::min<size_t>((most16 + 1023) / 1024, kResetBlocks);
-    spkv_reset<<<dim3(blocks), dim3(1024), 0, s>>>(v, static_cast<uint4*>(arena), counter / 16, pool / 16,
-                                                   tail / 16, tail_bytes / 16);
+hipError_t spkv_launch_reset(void* arena, size_t pool, size_t tail, size_t tail_bytes, hipStream_t s) {
+    const unsigned blocks = (unsigned)std::min<size_t>((std::max(pool, tail_bytes) / 16 + 255) / 256, 256 * 8);
+    spkv_reset<<<dim3(blocks), dim3(256), 0, s>>>(static_cast<uint4*>(arena), pool / 16, tail / 16, tail_bytes / 16);
     return hipGetLastError();
 }
 
@@ -405,6 +380,8 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
     __syncthreads();
     if (any_bad) return;
     const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
+    if (ends_in_new_half_page(L_old, L_old + total_new))
+        clear_list_end<D>(pool_page(v, pt[(L_old + total_new) >> 6]), L_old + total_new, tid, 256);
 
     // (d) move the kept ring rows, 256 ring positions at a time; without MOVE only their ranks are
     //     wanted, for the prefix counts
