@@ -167,8 +167,8 @@ int spkv_cache_reset(spkv_cache_t* cache, void* stream);
  * Larger calls take a bulk path (ballot/prefix-sum stream compaction, stable order).
  * Errors: SPKV_E_CAPACITY if any sequence would exceed max_context, or if the pool could
  * overflow even when every pushed-out pair were kept, judged after refreshing the host's
- * bound from the device counters (synchronises only in that case); then nothing is
- * written.  Feed long prompts in chunks so that this worst case fits. */
+ * bound from the device counters (only in that case the call waits until earlier calls have
+ * settled the kept lengths); then nothing is written.  Feed long prompts in chunks so that this worst case fits. */
 int spkv_append(spkv_cache_t* cache, const void* k, const void* v, const float* util_logits,
                 const int32_t* cu_seqlens, void* stream);
 
@@ -179,8 +179,8 @@ int spkv_append(spkv_cache_t* cache, const void* k, const void* v, const float* 
  *   lse  device fp32 [batch, n_q_heads] or NULL: log sum_s exp(sm_scale * <q, k_s>)
  *   sm_scale <= 0 selects 1 / sqrt(head_dim)
  * Call after spkv_append of the same step, so that the query's own key is in the window.
- * The first call after a multi-token append synchronises `stream` once to read the kept
- * lengths back (they size the split-K grid); decode steps in steady state never wait.
+ * The first call after a multi-token append waits once for the kept lengths it leaves (they
+ * size the split-K grid); decode steps in steady state never wait.
  * Errors: SPKV_E_STATE if some sequence holds no token. */
 int spkv_decode_attention(spkv_cache_t* cache, const void* q, void* out, float* lse,
                           float sm_scale, void* stream);

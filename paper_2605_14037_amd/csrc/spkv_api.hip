@@ -3,6 +3,7 @@
 // Kernels": capacity is checked on the host without reading the device until a worst-case
 // bound trips), and kernel launches.  See include/spkv.h for the contract.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -153,11 +154,15 @@ struct spkv_cache {
     // exact; past 1/16 of the bound the lengths are copied to pinned host memory behind the
     // step just issued (no wait) and adopted by the first later call that finds the copy done.
     int64_t slack;
-    int32_t* snap_host;           // pinned, [n_pairs] and a ticket; null if the allocation failed
+    int32_t* snap_host;           // pinned, twice [n_pairs] and a ticket; null if the allocation failed
     int32_t snap_ticket;          // the ticket that comes with the copy enqueued last
     hipEvent_t snap_event;        // behind it (awaited before the buffer is freed)
     bool snap_pending;
     std::vector<int32_t> snap_ev; // per sequence: pairs pushed out of the window since the copy
+    // Lengths that a prompt append sent by itself (second half of the buffer): current while no call
+    // has changed any since.
+    int32_t sent_ticket;
+    bool sent;
     // What is known of the lengths themselves: L_ub less what `since_exact` (per sequence) added to
     // it is the length when the bound was last exact -- from which the lists have grown by single
     // tokens and short chunks only (lists_known), or by a prompt as well.
@@ -230,12 +235,8 @@ hipError_t clear_arena(char* arena, const Carve& k, hipStream_t s) {
     return spkv_launch_reset(arena, k.pool, k.pair_items, k.pos_scratch - k.pair_items, s);
 }
 
-// Read the exact long-term lengths back and tighten the host's bound.  Synchronises.
-int refresh_bound(spkv_cache* c, hipStream_t s, int32_t* kept_len_out) {
-    std::vector<int32_t> len(c->carve.n_pairs);
-    if (hipStreamSynchronize(s) != hipSuccess) return SPKV_E_HIP;
-    if (hipMemcpy(len.data(), c->view.kept_len, len.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
-        return SPKV_E_HIP;
+// The host's bound from the exact lengths.
+void adopt_lengths(spkv_cache* c, const int32_t* len) {
     int64_t pages = 0;
     for (int p = 0; p < c->carve.n_pairs; ++p) {
         c->L_ub[p] = len[p];
@@ -246,8 +247,53 @@ int refresh_bound(spkv_cache* c, hipStream_t s, int32_t* kept_len_out) {
     c->slack = 0;
     std::fill(c->since_exact.begin(), c->since_exact.end(), 0);
     c->lists_known = true;
-    c->snap_pending = false;      // a copy still on its way is older than what was just read
+    c->snap_pending = c->sent = false;
+}
+
+// Read the exact long-term lengths back and tighten the host's bound.  Synchronises.
+int refresh_bound(spkv_cache* c, hipStream_t s, int32_t* kept_len_out) {
+    std::vector<int32_t> len(c->carve.n_pairs);
+    if (hipStreamSynchronize(s) != hipSuccess) return SPKV_E_HIP;
+    if (hipMemcpy(len.data(), c->view.kept_len, len.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
+        return SPKV_E_HIP;
+    adopt_lengths(c, len.data());      // a copy still on its way is older than what was just read
     if (kept_len_out != nullptr) std::memcpy(kept_len_out, len.data(), len.size() * 4);
+    return SPKV_OK;
+}
+
+bool being_captured(hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();          // no answer: not an error of the next launch
+    return true;
+}
+
+// A prompt append sends the lengths it leaves to the host by itself (spkv_bulk_scatter).  Not under
+// capture: a replay would send them again, with an old ticket.
+SpkvLengthCopy prompt_length_copy(spkv_cache* c, int n_max, hipStream_t s) {
+    if (c->snap_host == nullptr || !spkv_append_copies_lengths(c->view, n_max) || being_captured(s))
+        return SpkvLengthCopy{nullptr, 0};
+    return SpkvLengthCopy{c->snap_host + c->carve.n_pairs + 1, ++c->sent_ticket};
+}
+// ... once it has been launched and its tokens are counted.
+void prompt_copy_enqueued(spkv_cache* c, const SpkvLengthCopy& to, hipStream_t s) {
+    c->sent = to.host != nullptr && hipEventRecord(c->snap_event, s) == hipSuccess;
+    if (to.host != nullptr && !c->sent) (void)hipGetLastError();
+}
+
+// The exact lengths, where a call cannot go on without them: those that the last call sent, as soon as
+// they are there -- the stream goes on meanwhile -- else read back.  (A prompt of 16 sequences in 8
+// pieces of 4096 tokens: five read-backs, each of which drained the stream, were 84 us of 642.)
+// The wait is bounded: past it the stream is waited for.
+constexpr auto kLengthsPatience = std::chrono::milliseconds(20);
+int exact_lengths(spkv_cache* c, hipStream_t s) {
+    if (!c->sent) return refresh_bound(c, s, nullptr);
+    const int n_pairs = c->carve.n_pairs;
+    const int32_t* len = c->snap_host + n_pairs + 1;
+    const auto until = std::chrono::steady_clock::now() + kLengthsPatience;
+    while (__atomic_load_n(len + n_pairs, __ATOMIC_ACQUIRE) != c->sent_ticket)
+        if (std::chrono::steady_clock::now() > until) return refresh_bound(c, s, nullptr);
+    adopt_lengths(c, len);
     return SPKV_OK;
 }
 
@@ -280,13 +326,9 @@ void tighten_bound(spkv_cache* c, hipStream_t s, int share = 16) {
     int64_t sum = 0;
     for (int p = 0; p < n_pairs; ++p) sum += c->L_ub[p] + std::min(c->T[p / Hkv], c->cfg.window);
     if (c->slack * share <= sum) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return;
-    }
+    if (being_captured(s)) return;
     c->snap_ticket += 1;
-    if (spkv_launch_copy_lengths(c->view, c->snap_host, c->snap_ticket, s) != hipSuccess ||
+    if (spkv_launch_copy_lengths(c->view, SpkvLengthCopy{c->snap_host, c->snap_ticket}, s) != hipSuccess ||
         hipEventRecord(c->snap_event, s) != hipSuccess) {
         (void)hipGetLastError();
         return;
@@ -437,13 +479,7 @@ SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_t
 // workgroups a second item and waits for those.  Eager launches take none: the host's bound is never
 // short.
 void room_to_grow(spkv_cache* c, hipStream_t s) {
-    if (c->split.compact == 0) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-        (void)hipGetLastError();      // no answer is not an error of the next launch
-        cap = hipStreamCaptureStatusActive;
-    }
-    if (cap != hipStreamCaptureStatusNone) c->split.compact += c->carve.n_pairs;
+    if (c->split.compact > 0 && being_captured(s)) c->split.compact += c->carve.n_pairs;
 }
 
 SpkvSplit choose_split(const spkv_cache* c) {
@@ -517,7 +553,7 @@ int reserve_capacity(spkv_cache* c, const int32_t* cu, hipStream_t s) {
         }
         if (pages <= c->carve.n_pages) return SPKV_OK;
         if (attempt == 1) return SPKV_E_CAPACITY;
-        const int rc = refresh_bound(c, s, nullptr);
+        const int rc = exact_lengths(c, s);
         if (rc != SPKV_OK) return rc;
     }
 }
@@ -531,6 +567,7 @@ void prompt_appended(spkv_cache* c) {
 // Host bookkeeping after the launch: exact token counts, upper bounds of the lengths.
 void commit_lengths(spkv_cache* c, const int32_t* cu) {
     const int B = c->cfg.batch, Hkv = c->cfg.n_kv_heads, w = c->cfg.window;
+    c->sent = false;
     for (int b = 0; b < B; ++b) {
         const int n = tokens_for(cu, b);
         const int64_t ev = std::max<int64_t>(0, (int64_t)c->T[b] + n - w) -
@@ -582,6 +619,8 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     c->snap_event = nullptr;
     c->snap_ticket = 0;
     c->snap_pending = false;
+    c->sent_ticket = 0;
+    c->sent = false;
     c->snap_ev.assign(cfg->batch, 0);
     c->since_exact.assign(cfg->batch, 0);
     c->lists_known = true;
@@ -613,10 +652,10 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     // pinned host buffer for the length snapshots (see tighten_bound); the cache works
     // without it, with a coarser partition on very long generations
     void* pinned = nullptr;
-    if (hipHostMalloc(&pinned, (size_t)(k.n_pairs + 1) * 4, hipHostMallocCoherent) == hipSuccess &&
+    if (hipHostMalloc(&pinned, (size_t)(k.n_pairs + 1) * 8, hipHostMallocCoherent) == hipSuccess &&
         hipEventCreateWithFlags(&c->snap_event, hipEventDisableTiming) == hipSuccess) {
         c->snap_host = static_cast<int32_t*>(pinned);
-        c->snap_host[k.n_pairs] = 0;
+        c->snap_host[k.n_pairs] = c->snap_host[2 * k.n_pairs + 1] = 0;
     } else {
         if (pinned != nullptr) (void)hipHostFree(pinned);
         c->snap_event = nullptr;
@@ -704,7 +743,7 @@ int spkv_cache_reset(spkv_cache_t* c, void* stream) {
     c->slack = 0;
     std::fill(c->since_exact.begin(), c->since_exact.end(), 0);
     c->lists_known = true;
-    c->snap_pending = false;
+    c->snap_pending = c->sent = false;
     return SPKV_OK;
 }
 
@@ -730,12 +769,14 @@ int spkv_append(spkv_cache_t* c, const void* k, const void* v, const float* util
     std::memcpy(cu.v, cu_seqlens, (size_t)(B + 1) * 4);
     const uint16_t* kk = static_cast<const uint16_t*>(k);
     const uint16_t* vv = static_cast<const uint16_t*>(v);
+    const SpkvLengthCopy to = prompt_length_copy(c, n_max, s);
     hipError_t e = (n_max == 1)
                        ? spkv_launch_append_step(c->view, kk, vv, util_logits, cu, s)
-                       : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, s);
+                       : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, to, s);
     if (e != hipSuccess) return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
     if (n_max > SPKV_MAX_CHUNK_TOKENS) prompt_appended(c);         // short chunks: see tighten_bound
+    prompt_copy_enqueued(c, to, s);
     return SPKV_OK;
 }
 
@@ -750,7 +791,7 @@ int spkv_decode_step(spkv_cache_t* c, const void* k, const void* v, const float*
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (!(sm_scale > 0.f)) sm_scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
     if (c->bound_is_loose) {
-        const int rc = refresh_bound(c, s, nullptr);
+        const int rc = exact_lengths(c, s);
         if (rc != SPKV_OK) return rc;
     }
     tighten_bound(c, s);
@@ -800,7 +841,7 @@ int spkv_decode_step_predict(spkv_cache_t* c, const void* hidden, const void* w1
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (!(sm_scale > 0.f)) sm_scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
     if (c->bound_is_loose) {
-        const int rc = refresh_bound(c, s, nullptr);
+        const int rc = exact_lengths(c, s);
         if (rc != SPKV_OK) return rc;
     }
     tighten_bound(c, s);
@@ -839,7 +880,7 @@ int spkv_decode_attention(spkv_cache_t* c, const void* q, void* out, float* lse,
     if (!(sm_scale > 0.f)) sm_scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (c->bound_is_loose) {   // first decode after a bulk append: one read-back of the lengths
-        const int rc = refresh_bound(c, s, nullptr);
+        const int rc = exact_lengths(c, s);
         if (rc != SPKV_OK) return rc;
     }
     tighten_bound(c, s);
@@ -955,7 +996,7 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     if (!(sm_scale > 0.f)) sm_scale = 1.0f / std::sqrt((float)c->cfg.head_dim);
     if (n_max * G > 16) {
         if (!append && c->bound_is_loose) {
-            const int rc = refresh_bound(c, s, nullptr);
+            const int rc = exact_lengths(c, s);
             if (rc != SPKV_OK) return rc;
         }
         // More than one group of 16 query columns: the prefill kernels (each tile serves all
@@ -964,7 +1005,7 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
                             c->view.part_acc, (size_t)c->carve.max_items * G * c->cfg.head_dim * sizeof(float), false, s);
     }
     if (c->bound_is_loose) {       // the split-K partition below wants the exact lengths
-        const int rc = refresh_bound(c, s, nullptr);
+        const int rc = exact_lengths(c, s);
         if (rc != SPKV_OK) return rc;
     } else {
         tighten_bound(c, s);
@@ -1100,9 +1141,10 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
         if (slots > 0) ks = 1;      // (ranges cut on the device, which also decides `once` then)
         once = c->lists_known && all * (int64_t)(kHalfTokens * 4 * c->cfg.head_dim) > kOnceBytes;
     }
+    const SpkvLengthCopy to = prompt_length_copy(c, n_max, s);
     if (spkv_launch_prefill(c->view, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
                             util_logits, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),
-                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, once, part, s) != hipSuccess)
+                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, once, part, to, s) != hipSuccess)
         return SPKV_E_HIP;
     if (util_logits == nullptr) return SPKV_OK;
     commit_lengths(c, cu_seqlens);
@@ -1110,6 +1152,7 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
         if (short_chunk) c->bound_is_loose = true;
         else prompt_appended(c);
     }
+    prompt_copy_enqueued(c, to, s);
     return SPKV_OK;
 }
 }  // namespace
@@ -1284,6 +1327,7 @@ int spkv_cache_advance(spkv_cache_t* c, int64_t n_steps) {
         if ((int64_t)c->T[b] + n_steps > c->cfg.max_context) return SPKV_E_CAPACITY;
     if (pages_after_steps(c, n_steps) > c->carve.n_pages) return SPKV_E_CAPACITY;
     const int B = c->cfg.batch, Hkv = c->cfg.n_kv_heads, w = c->cfg.window;
+    c->sent = false;
     for (int b = 0; b < B; ++b) {
         const int64_t ev = std::max<int64_t>(0, (int64_t)c->T[b] + n_steps - w) -
                            std::max<int64_t>(0, (int64_t)c->T[b] - w);

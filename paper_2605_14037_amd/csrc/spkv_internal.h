@@ -63,8 +63,12 @@ struct SpkvCu {
 hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // Zeroes [0, pool) and tail_bytes at `tail`.  Bytes from the arena's start.
 hipError_t spkv_launch_reset(void* arena, size_t pool, size_t tail, size_t tail_bytes, hipStream_t s);
-// Copies the n kept lengths to pinned host memory, then stores `ticket` behind them (to_host[n]).
-hipError_t spkv_launch_copy_lengths(const SpkvView& v, int32_t* to_host, int32_t ticket, hipStream_t s);
+// Where the kept lengths go: pinned host memory, [n_pairs] and then `ticket` behind them; null: nowhere.
+struct SpkvLengthCopy {
+    int32_t* host;
+    int32_t ticket;
+};
+hipError_t spkv_launch_copy_lengths(const SpkvView& v, SpkvLengthCopy to, hipStream_t s);
 hipError_t spkv_launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // Streaming read of n_runs runs (chunks_per_run chunks of 16 KB each) of a region of
 // total_runs runs by n_workgroups one-wave workgroups; sink: n_workgroups KB.
@@ -77,9 +81,11 @@ hipError_t spkv_launch_copy_rows(int32_t* dst, const int32_t* src, int rows, int
 hipError_t spkv_launch_append_step(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, hipStream_t s);
 // prefix: null, or where the prefill attention wants the per-token long-term prefix counts.
+// to: where to send the lengths as they are after the append, if spkv_append_copies_lengths.
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
-                                   hipStream_t s);
+                                   SpkvLengthCopy to, hipStream_t s);
+bool spkv_append_copies_lengths(const SpkvView& v, int n_max);
 // Split of every (seq, head) list into work items, chosen by the host per decode call:
 // a pair with n half-pages (32 keys each) is cut evenly into min(ceil(n / hp_per_item),
 // slots) items; item j of pair p owns partial slot p * slots + j.  In the single-token
@@ -153,7 +159,8 @@ int spkv_chunk_resident_items(int head_dim);
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
-                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part, hipStream_t s);
+                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part,
+                               SpkvLengthCopy to, hipStream_t s);
 // Chunks that are attended from the lists and the ring as they are, before their append (by
 // spkv_launch_prefill, which then needs no staging rows and no prefix counts and takes f = null for
 // "append nothing").

@@ -1172,14 +1172,14 @@ bool spkv_prefill_direct(const SpkvView& v, int n_max) {
 template <int D>
 static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv, const float* f,
                                  const uint16_t* q, uint16_t* out, float* lse, float sl, const SpkvCu& cu, int n_max,
-                                 const SpkvPrefill& pf, hipStream_t s) {
+                                 const SpkvPrefill& pf, SpkvLengthCopy to, hipStream_t s) {
     const bool direct = spkv_prefill_direct(v, n_max), merge = pf.ks > 1 || pf.slots > 0;
     if (direct) {
         launch_attend<D, true>(v, q, out, lse, sl, pf, cu, k, vv, s);
     } else {
         const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
         spkv_prefill_stage<D><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
-        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, s);
+        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, to, s);
         if (e != hipSuccess) return e;
         launch_attend<D, false>(v, q, out, lse, sl, pf, cu, nullptr, nullptr, s);
     }
@@ -1188,7 +1188,7 @@ static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uin
         const int blocks = v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / (256 / (D / 4));
         spkv_prefill_combine<D><<<dim3((fa != nullptr ? v.n_pairs : 0) + blocks), dim3(256), 0, s>>>(v, out, lse, pf, cu, k, vv, fa);
     } else if (direct && f != nullptr) {
-        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, s);
+        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, to, s);
     }
     return hipGetLastError();
 }
@@ -1196,11 +1196,12 @@ static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uin
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
-                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part, hipStream_t s) {
+                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part,
+                               SpkvLengthCopy to, hipStream_t s) {
     const SpkvPrefill pf = prefill_params(v, n_max, stage, prefix, nullptr, shp, ks, part, slots, once);
     const float sl = sm_scale * 1.4426950408889634f;
-    return v.D == 128 ? launch_prefill<128>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, s)
-                      : launch_prefill<64>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, s);
+    return v.D == 128 ? launch_prefill<128>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, to, s)
+                      : launch_prefill<64>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, to, s);
 }
 
 // Soft-gated attention of whole sequences (no cache): the same staging and the same tile

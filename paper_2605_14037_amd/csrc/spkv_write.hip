@@ -45,16 +45,19 @@ hipError_t spkv_launch_reset(void* arena, size_t pool, size_t tail, size_t tail_
 // The ticket tells the host that the lengths have arrived without an event: asking an event while
 // any stream of the process is being captured ends that capture.  One workgroup; every thread's
 // lengths are out at system scope before the barrier, the ticket after it.
-__global__ __launch_bounds__(256) void spkv_copy_lengths(const int32_t* __restrict__ len, int n, int32_t* to_host,
-                                                         int32_t ticket) {
-    for (int p = threadIdx.x; p < n; p += blockDim.x) to_host[p] = len[p];
+__device__ __forceinline__ void copy_lengths(const int32_t* __restrict__ len, int n, const SpkvLengthCopy& to) {
+    for (int p = threadIdx.x; p < n; p += blockDim.x) to.host[p] = len[p];
     __threadfence_system();
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(to_host + n, ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x == 0) __hip_atomic_store(to.host + n, to.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ __launch_bounds__(256) void spkv_copy_lengths(const int32_t* __restrict__ len, int n, int32_t* to_host,
+                                                         int32_t ticket) {
+    copy_lengths(len, n, SpkvLengthCopy{to_host, ticket});
 }
 
-hipError_t spkv_launch_copy_lengths(const SpkvView& v, int32_t* to_host, int32_t ticket, hipStream_t s) {
-    spkv_copy_lengths<<<dim3(1), dim3(256), 0, s>>>(v.kept_len, v.n_pairs, to_host, ticket);
+hipError_t spkv_launch_copy_lengths(const SpkvView& v, SpkvLengthCopy to, hipStream_t s) {
+    spkv_copy_lengths<<<dim3(1), dim3(256), 0, s>>>(v.kept_len, v.n_pairs, to.host, to.ticket);
     return hipGetLastError();
 }
 
@@ -547,7 +550,9 @@ __device__ __forceinline__ void store_ring_unit(const SpkvView& v, const RingUni
 // pair (ring_here) moves the kept rows that leave the ring in the
 // same way and then writes the last min(n, w) tokens of the call into the ring, two units' loads
 // at a time; without it (ring_in_one_workgroup) workgroups of their own write the slots, eight per
-// wave, and stage 2 has moved the rows.
+// wave, and stage 2 has moved the rows.  The first workgroup sends the lengths, which stage 2 has
+// settled, to the host (`to`) before its own work: the host has them while this launch runs and need
+// not wait for the stream to know what the next call may take.
 // Bound by the requests in flight of a few dependent rounds (logits, rows, stores) more than by
 // bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
 // written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
@@ -559,8 +564,10 @@ template <int D>
 __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v, const uint16_t* __restrict__ k,
                                                                      const uint16_t* __restrict__ vv,
                                                                      const float* __restrict__ f, SpkvCu cu,
-                                                                     int32_t* prefix, int quads, int ring_here) {
+                                                                     int32_t* prefix, int quads, int ring_here,
+                                                                     SpkvLengthCopy to) {
     constexpr int NW = kScatterThreads / 64;
+    if (to.host != nullptr && blockIdx.x == 0 && blockIdx.y == 0) copy_lengths(v.kept_len, v.n_pairs, to);
     const int pair = blockIdx.y, quad = blockIdx.x;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b];
@@ -717,6 +724,8 @@ static bool ring_in_one_workgroup(const SpkvView& v, int n_max) {
     return v.w <= 64 || (n_max > kScatterThreads && (v.w <= 128 || v.n_pairs >= 64));
 }
 
+bool spkv_append_copies_lengths(const SpkvView& v, int n_max) { return n_max > v.w || n_max > kSegTokens; }
+
 template <int D>
 __global__ __launch_bounds__(256) void spkv_append_few(SpkvView v, const uint16_t* __restrict__ k,
                                                        const uint16_t* __restrict__ vv,
@@ -726,13 +735,13 @@ __global__ __launch_bounds__(256) void spkv_append_few(SpkvView v, const uint16_
 
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
-                                   hipStream_t s) {
+                                   SpkvLengthCopy to, hipStream_t s) {
     if (n_max <= kFewTokens && n_max <= v.w && prefix == nullptr) {
         if (v.D == 128) spkv_append_few<128><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
         else spkv_append_few<64><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
         return hipGetLastError();
     }
-    if (n_max <= v.w && n_max <= kSegTokens) {      // short chunks: one launch
+    if (!spkv_append_copies_lengths(v, n_max)) {    // short chunks: one launch
         if (v.D == 128) spkv_bulk_ring<128, true, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
         else spkv_bulk_ring<64, true, false, true><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f);
         return hipGetLastError();
@@ -747,11 +756,11 @@ hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const u
     if (v.D == 128) {
         if (fold) ring_here ? stage2(spkv_bulk_ring<128, false, true, false>) : stage2(spkv_bulk_ring<128, false, true, true>);
         else ring_here ? stage2(spkv_bulk_ring<128, false, false, false>) : stage2(spkv_bulk_ring<128, false, false, true>);
-        spkv_bulk_scatter<128><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here);
+        spkv_bulk_scatter<128><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, to);
     } else {
         if (fold) ring_here ? stage2(spkv_bulk_ring<64, false, true, false>) : stage2(spkv_bulk_ring<64, false, true, true>);
         else ring_here ? stage2(spkv_bulk_ring<64, false, false, false>) : stage2(spkv_bulk_ring<64, false, false, true>);
-        spkv_bulk_scatter<64><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here);
+        spkv_bulk_scatter<64><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, to);
     }
     return hipGetLastError();
 }
