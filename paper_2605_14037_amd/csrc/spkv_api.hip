@@ -772,7 +772,7 @@ int spkv_append(spkv_cache_t* c, const void* k, const void* v, const float* util
     const SpkvLengthCopy to = prompt_length_copy(c, n_max, s);
     hipError_t e = (n_max == 1)
                        ? spkv_launch_append_step(c->view, kk, vv, util_logits, cu, s)
-                       : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, to, s);
+                       : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, SpanCut{0, 1}, to, s);
     if (e != hipSuccess) return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
     if (n_max > SPKV_MAX_CHUNK_TOKENS) prompt_appended(c);         // short chunks: see tighten_bound
@@ -1052,7 +1052,7 @@ namespace {
 // walks a whole list: cut every span's tiles into ranges so that the launch has about as
 // many workgroups as the chip holds at once -- one eight-wave workgroup per compute unit,
 // two of four or two waves; more ranges than that only add partial results to write and merge.
-constexpr int kPrefillResident8 = 256, kPrefillResident = 512;
+constexpr int kPrefillResident = 512;
 int prefill_split_cap(int spans, int nw) {
     const int resident = nw == 8 ? kPrefillResident8 : kPrefillResident;
     if (spans <= 0) return 1;
@@ -1116,7 +1116,6 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
     const bool short_chunk = sh.nw != 8;
     if (short_chunk && (c->lists_known || c->chunk_since_prompt)) tighten_bound(c, s, 4);
     c->chunk_since_prompt = short_chunk;
-    const int spans = spkv_prefill_spans(c->carve.n_pairs, c->carve.G, n_max);
     const int64_t window_tiles = c->cfg.window / kHalfTokens + 1;
     int64_t longest = 0, known_longest = 0, all = 0;               // in tiles; known_longest and all:
     for (int p = 0; p < c->carve.n_pairs; ++p) {                   // of the lengths rather than the bound
@@ -1126,8 +1125,16 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
         known_longest = std::max(known_longest, known / kHalfTokens + window_tiles);
         all += known / kHalfTokens + window_tiles;
     }
+    const bool ordered = spkv_prefill_ordered(c->view, n_max, longest == 0);
+    const int spans = spkv_prefill_spans(c->view, cu, n_max, ordered);
     const int64_t tiles = longest + (c->cfg.window + 64) / kHalfTokens;
     int ks = (int)std::max<int64_t>(1, std::min<int64_t>(prefill_split_cap(spans, sh.nw), tiles / 4));
+    // Long chunks: not for less than it costs to merge (a tile takes about 1 us, writing and merging 250
+    // partial results 14), and not into a second round of workgroups that are over soon.  us, two
+    // sequences of 1.7k in pieces of 500, a last piece of 56 spans in 5 ranges 29, in 4 20; four of 700-3000,
+    // last piece whole 35, in 2 ranges 28 and the merge 11.
+    if (!short_chunk && spans * ks > kPrefillResident8 && tiles / ks < 24) ks = std::max(1, kPrefillResident8 / spans);
+    if (!short_chunk && tiles * (ks - 1) < 40 * ks) ks = 1;
     // exactly what this call writes must fit
     while (spkv_prefill_partial_bytes(spans, ks, sh, c->cfg.head_dim) > part_bytes) {
         if (exact_fit) return SPKV_E_INVAL;
@@ -1144,7 +1151,7 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
     const SpkvLengthCopy to = prompt_length_copy(c, n_max, s);
     if (spkv_launch_prefill(c->view, static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v),
                             util_logits, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out),
-                            lse, sm_scale, cu, n_max, stage, prefix, shp, ks, slots, once, part, to, s) != hipSuccess)
+                            lse, sm_scale, cu, n_max, stage, prefix, shp, ordered, ks, slots, once, part, to, s) != hipSuccess)
         return SPKV_E_HIP;
     if (util_logits == nullptr) return SPKV_OK;
     commit_lengths(c, cu_seqlens);

@@ -9,6 +9,17 @@
 
 constexpr int kSegTokens = 256;       // bulk append: tokens per compaction segment (one per thread)
 constexpr int kMaxItemTarget = 32768;
+// Order of the spans of a long prefill call (spkv_prefill_attend32): the pairs of a group by length, longest
+// first, and each pair's spans from its last one.  One entry per pair in the append's scratch
+// (bulk_info), the entries of a group together and in order: the spans of the group before the pair, and
+// pair | group << 16.
+struct SpanOrder {
+    int32_t before, pair_group;
+};
+constexpr int kSpanOrderPairs = 64, kSpanOrderAt = 4, kSpanOrderStride = 8;
+struct SpanCut {
+    int32_t tokens, groups;           // tokens of a span (0: no order wanted), groups of pairs (a divisor of H_kv)
+};
 constexpr int kCompactPairs = 1024;   // most (sequence, head) pairs the gapless numbering serves
 
 // A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)
@@ -83,7 +94,7 @@ hipError_t spkv_launch_append_step(const SpkvView& v, const uint16_t* k, const u
 // prefix: null, or where the prefill attention wants the per-token long-term prefix counts.
 // to: where to send the lengths as they are after the append, if spkv_append_copies_lengths.
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
-                                   const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
+                                   const float* f, const SpkvCu& cu, int n_max, int32_t* prefix, SpanCut cut,
                                    SpkvLengthCopy to, hipStream_t s);
 bool spkv_append_copies_lengths(const SpkvView& v, int n_max);
 // Split of every (seq, head) list into work items, chosen by the host per decode call:
@@ -159,19 +170,22 @@ int spkv_chunk_resident_items(int head_dim);
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
-                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part,
-                               SpkvLengthCopy to, hipStream_t s);
+                               int32_t* prefix, int shp, bool ordered, int ks, int slots, bool once,
+                               float* part, SpkvLengthCopy to, hipStream_t s);
 // Chunks that are attended from the lists and the ring as they are, before their append (by
 // spkv_launch_prefill, which then needs no staging rows and no prefix counts and takes f = null for
 // "append nothing").
 bool spkv_prefill_direct(const SpkvView& v, int n_max);
 // Workgroups (spans of tokens per (sequence, KV head)) of a prefill call, and the bytes of
 // split-K partials for them.
+constexpr int kPrefillResident8 = 256;        // eight-wave workgroups that the chip holds at once
 struct SpkvPrefillShape {
     int nq, nw, tb;       // column groups of 16 per wave, waves per workgroup, tokens per wave
 };
 SpkvPrefillShape spkv_prefill_shape(int group, int n_max);   // for chunks of at most n_max tokens
-int spkv_prefill_spans(int n_pairs, int group, int n_max);
+int spkv_prefill_spans(const SpkvView& v, const SpkvCu& cu, int n_max, bool ordered);
+// Are the spans of a call taken in order (SpanOrder)?  from_empty: no sequence has a list yet.
+bool spkv_prefill_ordered(const SpkvView& v, int n_max, bool from_empty);
 // Ranges of about equal length that `part_bytes` hold, at most what the device takes at once;
 // 0: not for this shape, or not more than one per pair.
 int spkv_prefill_slots(int n_pairs, SpkvPrefillShape sh, int head_dim, size_t part_bytes);

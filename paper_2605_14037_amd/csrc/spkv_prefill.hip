@@ -40,6 +40,10 @@ struct SpkvPrefill {
     int32_t   once;      // fewer than eight waves, slots = 0: the lists pass the caches by (kOnceBytes)
     float*    part;      // partial (acc, m, l) of every (range, column); slots > 0: then [n_pairs] int2
                          // (first range, ranges) of every pair
+    const int32_t* order;    // not null: the spans in the order that the append leaves here (SpanOrder)
+    int32_t   groups;    // with `order`: groups of pairs, 8 / groups XCDs each (1, 2, 4 or 8; ks > 1: 1)
+    int32_t   steps;     // with `order`: workgroups per XCD
+    int32_t   spans;     // spans in all: n_pairs nblk; with `order` those that hold a token
 };
 
 // One workgroup per (staging half-page, pair): wave wv fills rows 8 wv .. 8 wv + 7.  Rows
@@ -662,6 +666,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 }
 
+// Span `id` of a group of pairs in the order that the append has left (SpanOrder): its pair, and its index
+// among the pair's spans, counted from the last one.  Where the group has none: -1.  Past its last one: an
+// index past the pair's spans.  e: the entry of this lane.
+__device__ __forceinline__ SpanOrder span_entry(const int32_t* __restrict__ order, int n_pairs) {
+    const int lane = threadIdx.x & 63;
+    return *reinterpret_cast<const SpanOrder*>(order + (size_t)min(lane, n_pairs - 1) * kSpanOrderStride);
+}
+__device__ __forceinline__ void find_span(SpanOrder e, int n_pairs, int group, int id, int& pair, int& at) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long m = __ballot(lane < n_pairs && e.pair_group >> 16 == group && e.before <= id);
+    const int r = m != 0ull ? 63 - __builtin_clzll(m) : 0;
+    pair = min(__builtin_amdgcn_readlane(e.pair_group, r) & 0xffff, n_pairs - 1);
+    at = m != 0ull ? id - __builtin_amdgcn_readlane(e.before, r) : -1;
+}
+
 // Long chunks and the soft-gated forward: one workgroup of eight waves per span of 8 tb tokens,
 // each wave with 32 columns (token, head) as ONE group of MFMA 32x32x16, so that 256 query columns
 // share one tile fetch.  Half the matrix instructions of two groups of 16x16x32 for the same
@@ -694,8 +713,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(16))) float s_bias[SOFT ? kBufs : 1][SOFT ? NW : 1][SOFT ? 64 : 4];
     __shared__ __attribute__((aligned(16))) float s_zero[32];
     if (SOFT && threadIdx.x < 32) s_zero[threadIdx.x] = 0.f;      // (the barrier before the loop)
-    int pair, qblk, kr;      // (sequence, KV head), span, tile range of the span
-    if (pf.pin_xcd) {
+    int pair, qblk, kr, id = 0;      // (sequence, KV head), span, tile range of the span
+    if (pf.order != nullptr) {
+        // `share` XCDs for a group; two neighbours of a pair at a time on one (they share most of their windows)
+        const int share = 8 / pf.groups, xcd = blockIdx.x & 7, group = xcd / share, at = blockIdx.x >> 3;
+        const int j = ((at >> 1) * share + xcd - group * share) * 2 + (at & 1);
+        id = j / pf.ks;
+        kr = j - id * pf.ks;
+        find_span(span_entry(pf.order, v.n_pairs), v.n_pairs, group, id, pair, qblk);
+    } else if (pf.pin_xcd) {
         // workgroups go round-robin to the 8 XCDs: id % 8 picks the XCD, and every pair lives on one
         // XCD, so its list is fetched into one L2 and re-read there; rotated inside every full group
         // of 8 pairs by the group index: with 8 KV heads a plain pair % 8 would give each XCD one
@@ -713,11 +739,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         qblk = rem / pf.ks;
         kr = rem - qblk * pf.ks;
     }
-    qblk = pf.nblk - 1 - qblk;            // longest prefixes first
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
+    // longest prefixes first
+    qblk = (pf.order != nullptr ? (n_tok + NW * pf.tb - 1) / (NW * pf.tb) : pf.nblk) - 1 - qblk;
     const int span0 = qblk * NW * pf.tb;
-    if (span0 >= n_tok) return;
+    if (span0 < 0 || span0 >= n_tok) return;
     const int span_last = min(span0 + NW * pf.tb, n_tok) - 1;
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -993,8 +1020,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     l += __shfl_xor(l, 32);
     if (!valid) return;
     if (pf.ks > 1) {
-        const size_t n_cols = (size_t)v.n_pairs * pf.nblk * pf.ks * (NW * 32);
-        const size_t pc = (((size_t)pair * pf.nblk + qblk) * pf.ks + kr) * (NW * 32) + wv * 32 + col;
+        const size_t n_cols = (size_t)pf.spans * pf.ks * (NW * 32);
+        const size_t range = pf.order != nullptr ? (size_t)id * pf.ks + kr : ((size_t)pair * pf.nblk + qblk) * pf.ks + kr;
+        const size_t pc = range * (NW * 32) + wv * 32 + col;
         float* pa = pf.part + pc * D + half * 4;
 #pragma unroll
         for (int db = 0; db < NB; ++db)
@@ -1047,15 +1075,24 @@ __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t
     const int id = (int)blockIdx.x - n_append, span = id / blocks_per_span;
     const int cs = (id - span * blocks_per_span) * CPB + (int)threadIdx.x / TPC;
     const int d = ((int)threadIdx.x % TPC) * 4;
-    const int pair = span / pf.nblk, qblk = span - pair * pf.nblk;
-    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
-    const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
-    const int wv = cs / (pf.nq * 16), col = cs - wv * (pf.nq * 16);
-    const int i0 = qblk * pf.nw * pf.tb + wv * pf.tb;
-    const int tbv = max(0, min(pf.tb, n_tok - i0));
-    if (col >= tbv * v.G) return;
-    const int i = i0 + col / v.G, g = col - (col / v.G) * v.G;
-    const size_t n_cols = (size_t)(pf.slots > 0 ? pf.slots : v.n_pairs * pf.nblk * pf.ks) * kCols;
+    int pair = span / pf.nblk, qblk = span - pair * pf.nblk;
+    size_t o = 0;
+    auto holds_token = [&]() -> bool {                         // o: its output row
+        const int b = pair / v.Hkv, h = pair - b * v.Hkv;
+        const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
+        if (pf.order != nullptr) qblk = (n_tok + pf.nw * pf.tb - 1) / (pf.nw * pf.tb) - 1 - qblk;
+        const int wv = cs / (pf.nq * 16), col = cs - wv * (pf.nq * 16);
+        const int i0 = qblk * pf.nw * pf.tb + wv * pf.tb;
+        const int tbv = max(0, min(pf.tb, n_tok - i0));
+        const int i = i0 + col / v.G, g = col - (col / v.G) * v.G;
+        o = (size_t)(row0 + i) * v.Hq + (size_t)h * v.G + g;
+        return col < tbv * v.G;
+    };
+    // in order, the pair is looked up beside the merge: columns without a token merge what nobody wrote
+    SpanOrder e = {0, 0};
+    if (pf.order != nullptr) e = span_entry(pf.order, v.n_pairs);
+    else if (!holds_token()) return;
+    const size_t n_cols = (size_t)(pf.slots > 0 ? pf.slots : pf.spans * pf.ks) * kCols;
     int2 cut = make_int2(span * pf.ks, pf.ks);                 // first range, ranges
     if (pf.slots > 0) cut = reinterpret_cast<const int2*>(pf.part + n_cols * (D + 2))[pair];
     const size_t pc0 = (size_t)cut.x * kCols + cs;             // range r: pc0 + r * kCols
@@ -1089,7 +1126,10 @@ __global__ __launch_bounds__(256) void spkv_prefill_combine(SpkvView v, uint16_t
             }
         M = m_new;
     }
-    const size_t o = (size_t)(row0 + i) * v.Hq + (size_t)h * v.G + g;
+    if (pf.order != nullptr) {
+        find_span(e, v.n_pairs, 0, span, pair, qblk);
+        if (!holds_token()) return;
+    }
     const float inv = 1.0f / den;
     uint2 packed;
     packed.x = (unsigned)__builtin_bit_cast(uint16_t, (__bf16)(num[0] * inv)) |
@@ -1119,21 +1159,62 @@ static SpkvPrefill prefill_params(const SpkvView& v, int n_max, uint16_t* stage,
     pf.nw = sh.nw;
     pf.nq = sh.nq;
     pf.nblk = (n_max + pf.nw * pf.tb - 1) / (pf.nw * pf.tb);   // spans of one workgroup
+    pf.spans = v.n_pairs * pf.nblk;
+    pf.order = nullptr;
+    pf.groups = 1;
+    pf.steps = 0;
     pf.pin_xcd = (pf.nw == 8 && v.n_pairs >= 8 && pf.nblk * pf.ks >= 4) ? 1 : 0;
     return pf;
 }
 
 static unsigned prefill_grid(const SpkvView& v, const SpkvPrefill& pf) {
     if (pf.slots > 0) return (unsigned)pf.slots;
+    if (pf.order != nullptr) return 8u * (unsigned)pf.steps;
     return pf.pin_xcd ? 8u * (unsigned)((v.n_pairs + 7) / 8) * (unsigned)(pf.nblk * pf.ks)
                       : (unsigned)v.n_pairs * (unsigned)(pf.nblk * pf.ks);
 }
 
 SpkvPrefillShape spkv_prefill_shape(int group, int n_max) { return prefill_shape(group, n_max); }
 
-int spkv_prefill_spans(int n_pairs, int group, int n_max) {
-    const SpkvPrefillShape sh = prefill_shape(group, n_max);
-    return n_pairs * ((n_max + sh.nw * sh.tb - 1) / (sh.nw * sh.tb));
+// Spans in order (SpanOrder) for few pairs.  With each pair on an XCD of its own, pairs in turn (below,
+// as from 65 pairs on), the XCD with the densest heads finishes last, and sequences that have ended
+// leave theirs idle.  us for prompts in pieces of 4096 tokens, keep rates 0.1 to 0.33, pairs in turn / in
+// order: one sequence of 16k 832 / 698, two 1400 / 1214, four 2500 / 2295, eight 4478 / 4428, four of
+// 3k-19k 1872 / 1630; three of
+// 3k-19k with 3 KV heads of 64 1520 / 807; one of 128k 35.0 / 26.9 ms.  Pairs share the XCDs in groups, so that a list is
+// fetched into few L2s and neighbours find their windows there: all pairs on all XCDs took 2409
+// (four) and 4825 us (eight), 112 against 105 ms for four of 128k; neighbours on different XCDs
+// 2332 (four), but one whole prompt of 16k 700 instead of 728.
+// Not where the spans run in one round, which the order cannot even out, nor for pieces that begin
+// prompts (no list yet), whose spans differ by their own place more than by their pair's list: 4096
+// tokens of one sequence 72 / 78.
+bool spkv_prefill_ordered(const SpkvView& v, int n_max, bool from_empty) {
+    const SpkvPrefillShape sh = prefill_shape(v.G, n_max);
+    const int spans = v.n_pairs * ((n_max + sh.nw * sh.tb - 1) / (sh.nw * sh.tb));
+    return sh.nw == 8 && v.n_pairs <= kSpanOrderPairs && spans > kPrefillResident8 &&
+           !(from_empty && n_max <= 4096 && v.n_pairs % 8 == 0) && spkv_append_copies_lengths(v, n_max);
+}
+static void order_params(const SpkvView& v, const SpkvCu& cu, int n_max, SpkvPrefill& pf) {
+    const int span = pf.nw * pf.tb;
+    pf.order = v.bulk_info + kSpanOrderAt;
+    pf.spans = spkv_prefill_spans(v, cu, n_max, true);
+    pf.pin_xcd = 0;
+    const int64_t pairs = (int64_t)cu.v[v.B] * v.Hkv / n_max;       // as many as would bring n_max tokens each
+    // at least eight such pairs to a group: their unlike lengths even out
+    pf.groups = 1;
+    while (pf.ks == 1 && pairs >= 16 * pf.groups && v.Hkv % (2 * pf.groups) == 0 && pf.groups < 8) pf.groups *= 2;
+    const int each = pf.spans / pf.groups * pf.ks;                  // a group has as many heads of every sequence
+    const int run = 2 * (8 / pf.groups);
+    pf.steps = (each + run - 1) / run * 2;
+}
+
+int spkv_prefill_spans(const SpkvView& v, const SpkvCu& cu, int n_max, bool ordered) {
+    const SpkvPrefillShape sh = prefill_shape(v.G, n_max);
+    const int span = sh.nw * sh.tb;
+    if (!ordered) return v.n_pairs * ((n_max + span - 1) / span);
+    int n = 0;
+    for (int b = 0; b < v.B; ++b) n += (cu.v[b + 1] - cu.v[b] + span - 1) / span;
+    return n * v.Hkv;
 }
 
 int spkv_prefill_slots(int n_pairs, SpkvPrefillShape sh, int head_dim, size_t part_bytes) {
@@ -1179,16 +1260,17 @@ static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uin
     } else {
         const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
         spkv_prefill_stage<D><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
-        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, to, s);
+        const SpanCut cut = {pf.order != nullptr ? pf.nw * pf.tb : 0, pf.groups};
+        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, cut, to, s);
         if (e != hipSuccess) return e;
         launch_attend<D, false>(v, q, out, lse, sl, pf, cu, nullptr, nullptr, s);
     }
     if (merge) {
         const float* fa = direct ? f : nullptr;
-        const int blocks = v.n_pairs * pf.nblk * pf.nw * pf.nq * 16 / (256 / (D / 4));
+        const int blocks = pf.spans * (pf.nw * pf.nq * 16 / (256 / (D / 4)));
         spkv_prefill_combine<D><<<dim3((fa != nullptr ? v.n_pairs : 0) + blocks), dim3(256), 0, s>>>(v, out, lse, pf, cu, k, vv, fa);
     } else if (direct && f != nullptr) {
-        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, to, s);
+        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, SpanCut{0, 1}, to, s);
     }
     return hipGetLastError();
 }
@@ -1196,9 +1278,10 @@ static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uin
 hipError_t spkv_launch_prefill(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                const float* f, const uint16_t* q, uint16_t* out, float* lse,
                                float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
-                               int32_t* prefix, int shp, int ks, int slots, bool once, float* part,
-                               SpkvLengthCopy to, hipStream_t s) {
-    const SpkvPrefill pf = prefill_params(v, n_max, stage, prefix, nullptr, shp, ks, part, slots, once);
+                               int32_t* prefix, int shp, bool ordered, int ks, int slots, bool once,
+                               float* part, SpkvLengthCopy to, hipStream_t s) {
+    SpkvPrefill pf = prefill_params(v, n_max, stage, prefix, nullptr, shp, ks, part, slots, once);
+    if (ordered) order_params(v, cu, n_max, pf);
     const float sl = sm_scale * 1.4426950408889634f;
     return v.D == 128 ? launch_prefill<128>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, to, s)
                       : launch_prefill<64>(v, k, vv, f, q, out, lse, sl, cu, n_max, pf, to, s);

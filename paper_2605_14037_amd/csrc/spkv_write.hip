@@ -183,8 +183,11 @@ struct BulkInfo {
     int32_t T_old;        // tokens held before this call
     int32_t new_base;     // long-term index of the first kept NEW token (after ring-evicted ones)
     int32_t ok;           // 0: capacity error, the call writes nothing more for this pair
-    int32_t pad[5];
+    int32_t pad;
+    SpanOrder order;      // entry `pair` of the order of the attention's spans, written by spkv_bulk_scatter
+    int32_t pad2[2];
 };
+static_assert(sizeof(BulkInfo) == kSpanOrderStride * 4, "order entries lie in the scratch of the pairs");
 
 // Stage 1: per (segment, pair): how many of the segment's new tokens pass the gate, and how
 // many of those also leave the window within this call (j < n - w).
@@ -553,11 +556,38 @@ __device__ __forceinline__ void store_ring_unit(const SpkvView& v, const RingUni
 // wave, and stage 2 has moved the rows.  The first workgroup sends the lengths, which stage 2 has
 // settled, to the host (`to`) before its own work: the host has them while this launch runs and need
 // not wait for the stream to know what the next call may take.
+// cut.tokens > 0: one row of workgroups more, of which the first leaves the order of the attention's spans.
 // Bound by the requests in flight of a few dependent rounds (logits, rows, stores) more than by
 // bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
 // written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
 // pairs; 46 us now with the leaving ring rows, whose move took 7 of the 18 us of stage 2.
 // 256 tokens per workgroup 52 us, 1024 tokens 49.
+// One wave, a lane per pair: its group, rank by length in the group, and the spans of the group before it.
+// The heads of a sequence are dealt to the groups by length, back and forth.
+__device__ __forceinline__ void order_spans(const SpkvView& v, const SpkvCu& cu, SpanCut cut) {
+    const int p = threadIdx.x, b = min(p, v.n_pairs - 1) / v.Hkv;
+    const int len = p < v.n_pairs ? v.kept_len[p] : -1;
+    const int spans = p < v.n_pairs ? (cu.v[b + 1] - cu.v[b] + cut.tokens - 1) / cut.tokens : 0;
+    int rank = 0;
+    for (int o = 0; o < v.n_pairs; ++o) {
+        const int l = __builtin_amdgcn_readlane(len, o);
+        rank += o >= b * v.Hkv && o < (b + 1) * v.Hkv && (l > len || (l == len && o < p)) ? 1 : 0;
+    }
+    const int round = rank / cut.groups, at = rank - round * cut.groups;
+    const int group = ((round + b) & 1) != 0 ? cut.groups - 1 - at : at;
+    int entry = 0, before = 0;
+    for (int o = 0; o < v.n_pairs; ++o) {
+        const int l = __builtin_amdgcn_readlane(len, o), n = __builtin_amdgcn_readlane(spans, o);
+        const int g = __builtin_amdgcn_readlane(group, o);
+        const bool ahead = g == group && (l > len || (l == len && o < p));
+        entry += g < group || ahead ? 1 : 0;
+        before += ahead ? n : 0;
+    }
+    if (p < v.n_pairs)
+        *reinterpret_cast<SpanOrder*>(v.bulk_info + kSpanOrderAt + (size_t)entry * kSpanOrderStride) =
+            SpanOrder{before, p | group << 16};
+}
+
 constexpr int kScatterSegs = 2, kScatterThreads = kScatterSegs * kSegTokens;
 
 template <int D>
@@ -565,8 +595,12 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
                                                                      const uint16_t* __restrict__ vv,
                                                                      const float* __restrict__ f, SpkvCu cu,
                                                                      int32_t* prefix, int quads, int ring_here,
-                                                                     SpkvLengthCopy to) {
+                                                                     SpanCut cut, SpkvLengthCopy to) {
     constexpr int NW = kScatterThreads / 64;
+    if ((int)blockIdx.y == v.n_pairs) {
+        if (blockIdx.x == 0 && threadIdx.x < 64) order_spans(v, cu, cut);
+        return;
+    }
     if (to.host != nullptr && blockIdx.x == 0 && blockIdx.y == 0) copy_lengths(v.kept_len, v.n_pairs, to);
     const int pair = blockIdx.y, quad = blockIdx.x;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
@@ -735,7 +769,7 @@ __global__ __launch_bounds__(256) void spkv_append_few(SpkvView v, const uint16_
 
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
-                                   SpkvLengthCopy to, hipStream_t s) {
+                                   SpanCut cut, SpkvLengthCopy to, hipStream_t s) {
     if (n_max <= kFewTokens && n_max <= v.w && prefix == nullptr) {
         if (v.D == 128) spkv_append_few<128><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
         else spkv_append_few<64><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
@@ -749,18 +783,18 @@ hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const u
     const int segs_all = (n_max + kSegTokens - 1) / kSegTokens;
     const int quads = (n_max + kScatterThreads - 1) / kScatterThreads;
     const bool ring_here = ring_in_one_workgroup(v, n_max);
-    const dim3 grid3(quads + (ring_here ? 1 : (v.w + kScatterThreads / 8 - 1) / (kScatterThreads / 8)), v.n_pairs);
+    const dim3 grid3(quads + (ring_here ? 1 : (v.w + kScatterThreads / 8 - 1) / (kScatterThreads / 8)), v.n_pairs + (cut.tokens > 0 ? 1 : 0));
     const bool fold = segs_all <= kCountSegs;       // the per-pair launch counts for itself
     if (!fold) spkv_bulk_count<<<dim3(segs_all, v.n_pairs), dim3(256), 0, s>>>(v, f, cu);
     auto stage2 = [&](auto kernel) { kernel<<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f); };
     if (v.D == 128) {
         if (fold) ring_here ? stage2(spkv_bulk_ring<128, false, true, false>) : stage2(spkv_bulk_ring<128, false, true, true>);
         else ring_here ? stage2(spkv_bulk_ring<128, false, false, false>) : stage2(spkv_bulk_ring<128, false, false, true>);
-        spkv_bulk_scatter<128><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, to);
+        spkv_bulk_scatter<128><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, cut, to);
     } else {
         if (fold) ring_here ? stage2(spkv_bulk_ring<64, false, true, false>) : stage2(spkv_bulk_ring<64, false, true, true>);
         else ring_here ? stage2(spkv_bulk_ring<64, false, false, false>) : stage2(spkv_bulk_ring<64, false, false, true>);
-        spkv_bulk_scatter<64><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, to);
+        spkv_bulk_scatter<64><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, cut, to);
     }
     return hipGetLastError();
 }
