@@ -772,7 +772,7 @@ int spkv_append(spkv_cache_t* c, const void* k, const void* v, const float* util
     const SpkvLengthCopy to = prompt_length_copy(c, n_max, s);
     hipError_t e = (n_max == 1)
                        ? spkv_launch_append_step(c->view, kk, vv, util_logits, cu, s)
-                       : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, SpanCut{0, 1}, to, s);
+                       : spkv_launch_append_bulk(c->view, kk, vv, util_logits, cu, n_max, nullptr, SpanCut{0, 1}, SpkvStage{}, to, s);
     if (e != hipSuccess) return SPKV_E_HIP;
     commit_lengths(c, cu_seqlens);
     if (n_max > SPKV_MAX_CHUNK_TOKENS) prompt_appended(c);         // short chunks: see tighten_bound

@@ -515,3 +515,67 @@ __device__ __forceinline__ void store_v_units(uint16_t* dp, int dk0, const uint1
         *reinterpret_cast<uint4*>(dp + spkv_v_off(D, dk0, d)) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
+
+// ----------------------------------------------------------- staging rows of a prefill call
+// One workgroup of 256 threads per (staging half-page sh, pair): wave wv fills rows 8 wv .. 8 wv + 7.  Rows
+// without a position (before the sequence start, past the chunk) are zero, so that a
+// masked key never meets a non-finite V element.  Reads the ring and the token count as they were before
+// the append: at most beside the launch of it that leaves both alone (spkv_stage_ring).
+// With st.bias set (soft gating) it also stores log2 u = log2 sigmoid(f) of every new row,
+// divided by the score scale.
+template <int D>
+__device__ __forceinline__ void stage_half_page(const SpkvView& v, const uint16_t* __restrict__ k,
+                                                const uint16_t* __restrict__ vv, const float* __restrict__ f,
+                                                const SpkvCu& cu, const SpkvStage& st, int pair, int sh) {
+    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
+    const int row0 = cu.v[b], n = cu.v[b + 1] - row0;
+    if (n == 0 || sh * kHalfTokens >= v.w + n) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15;
+    const int T0 = v.t_pair[pair];
+    __shared__ __attribute__((aligned(16))) uint16_t s_v[4][8][D];
+    uint16_t* dp = st.stage + ((size_t)pair * st.shp + sh) * (size_t)(2 * kHalfTokens * D);
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        const int row = pass * 4 + (lane >> 4);
+        const int u = sh * kHalfTokens + wave * 8 + row;
+        if (c < D / 8) {
+            uint4 kk = {0u, 0u, 0u, 0u}, vl = {0u, 0u, 0u, 0u};
+            if (u >= v.w) {
+                const int j = u - v.w;
+                if (j < n) {
+                    const size_t src = ((size_t)(row0 + j) * v.Hkv + h) * D + c * 8;
+                    kk = *reinterpret_cast<const uint4*>(k + src);
+                    vl = *reinterpret_cast<const uint4*>(vv + src);
+                }
+            } else {
+                const int s = T0 - v.w + u;
+                if (s >= 0) {
+                    const int slot = s % v.w;
+                    const uint16_t* sp = ring_page(v, pair, slot >> 6);
+                    const int sk = slot & 63;
+                    kk = *reinterpret_cast<const uint4*>(sp + spkv_k_off(D, sk, c * 8));
+                    const uint16_t* vs = sp + spkv_v_off(D, sk, c * 8);
+                    unsigned wd[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        wd[e] = (unsigned)vs[(2 * e) * 8] | ((unsigned)vs[(2 * e + 1) * 8] << 16);
+                    vl = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+                }
+            }
+            *reinterpret_cast<uint4*>(dp + spkv_k_off(D, wave * 8 + row, c * 8)) = kk;
+            *reinterpret_cast<uint4*>(&s_v[wave][row][c * 8]) = vl;
+        }
+        if (st.bias != nullptr && c == 0) {
+            float lb = 0.f;
+            if (u >= v.w && u - v.w < n) {
+                // log u = log sigmoid(f) = -softplus(-f) (Eq. 1 and the soft gate), in log2
+                const float x = f[((size_t)row0 + (u - v.w)) * v.Hkv + h];
+                const float ls = x < -20.f ? x : -log1pf(__expf(-x));
+                lb = ls * 1.4426950408889634f * st.bias_unit;
+            }
+            st.bias[((size_t)pair * st.shp + sh) * kHalfTokens + wave * 8 + row] = lb;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    store_v_units<D>(dp, wave * 8, s_v[wave], lane);
+}

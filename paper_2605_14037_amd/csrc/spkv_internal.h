@@ -71,6 +71,14 @@ struct SpkvCu {
     int32_t v[SPKV_MAX_BATCH + 1];
 };
 
+// Staging half-pages of a prefill call (spkv_prefill.hip).
+struct SpkvStage {
+    uint16_t* stage;     // [n_pairs][shp] half-pages; null: none
+    float*    bias;      // soft gating only: [n_pairs][shp][32] log2 u of every staging row, in units of a score
+    float     bias_unit; // soft gating only: 1 / (sm_scale log2 e)
+    int32_t   shp;       // staging half-pages per pair
+    int32_t   hps;       // of them in use at most: ceil((w + n_max) / 32)
+};
 hipError_t spkv_launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // Zeroes [0, pool) and tail_bytes at `tail`.  Bytes from the arena's start.
 hipError_t spkv_launch_reset(void* arena, size_t pool, size_t tail, size_t tail_bytes, hipStream_t s);
@@ -91,12 +99,15 @@ hipError_t spkv_launch_copy_rows(int32_t* dst, const int32_t* src, int rows, int
                                  int dst_width, hipStream_t s);
 hipError_t spkv_launch_append_step(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, hipStream_t s);
+// st.stage not null: the staging rows of the prefill attention as well, in the append's first launch; only
+// where spkv_append_stages says so.
 // prefix: null, or where the prefill attention wants the per-token long-term prefix counts.
 // to: where to send the lengths as they are after the append, if spkv_append_copies_lengths.
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
-                                   const float* f, const SpkvCu& cu, int n_max, int32_t* prefix, SpanCut cut,
+                                   const float* f, const SpkvCu& cu, int n_max, int32_t* prefix, SpanCut cut, const SpkvStage& st,
                                    SpkvLengthCopy to, hipStream_t s);
 bool spkv_append_copies_lengths(const SpkvView& v, int n_max);
+bool spkv_append_stages(const SpkvView& v, int n_max);
 // Split of every (seq, head) list into work items, chosen by the host per decode call:
 // a pair with n half-pages (32 keys each) is cut evenly into min(ceil(n / hp_per_item),
 // slots) items; item j of pair p owns partial slot p * slots + j.  In the single-token

@@ -6,11 +6,11 @@
 // ------------------------------------------------- prefill attention (any chunk length)
 // n new tokens per sequence attend causally with the availability rule of Eq. 3-4 and are
 // appended, in four steps:
-//   1. spkv_prefill_stage copies the window as it stands (ring, un-rotated into position
+//   1. spkv_stage_ring (or spkv_prefill_stage) copies the window as it stands (ring, un-rotated into position
 //      order) and the n new K/V rows into staging half-pages in the page layout: staging
 //      row u holds position T_old - w + u, so query i (position T_old + i) has exactly the
 //      rows i < u <= i + w in its window.
-//   2. the bulk append runs and records, per new token, how long a prefix of the long-term
+//   2. the bulk append runs, its first launch beside step 1, and records, per new token, how long a prefix of the long-term
 //      list lies at least w behind it (see spkv_bulk_ring).
 //   3. spkv_prefill_attend32 (long chunks) or spkv_prefill_attend: one wave per block of
 //      tb = 32 / G consecutive tokens of one (sequence, KV head) -- 32 MFMA columns (token,
@@ -46,69 +46,13 @@ struct SpkvPrefill {
     int32_t   spans;     // spans in all: n_pairs nblk; with `order` those that hold a token
 };
 
-// One workgroup per (staging half-page, pair): wave wv fills rows 8 wv .. 8 wv + 7.  Rows
-// without a position (before the sequence start, past the chunk) are zero, so that a
-// masked key never meets a non-finite V element.  Runs BEFORE the append (reads the ring
-// and the token count as they were).
-// With pf.bias set (soft gating) it also stores log2 u = log2 sigmoid(f) of every new row,
-// divided by the score scale.
+// A workgroup per (staging half-page, pair), in a launch of its own: soft gating, and chunks whose append
+// writes the ring in its first launch.
 template <int D>
 __global__ __launch_bounds__(256) void spkv_prefill_stage(SpkvView v, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ vv,
-                                                          const float* __restrict__ f, SpkvCu cu,
-                                                          SpkvPrefill pf) {
-    const int pair = blockIdx.y, sh = blockIdx.x;
-    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
-    const int row0 = cu.v[b], n = cu.v[b + 1] - row0;
-    if (n == 0 || sh * kHalfTokens >= v.w + n) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15;
-    const int T0 = v.t_pair[pair];
-    __shared__ __attribute__((aligned(16))) uint16_t s_v[4][8][D];
-    uint16_t* dp = pf.stage + ((size_t)pair * pf.shp + sh) * (size_t)(2 * kHalfTokens * D);
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        const int row = pass * 4 + (lane >> 4);
-        const int u = sh * kHalfTokens + wave * 8 + row;
-        if (c < D / 8) {
-            uint4 kk = {0u, 0u, 0u, 0u}, vl = {0u, 0u, 0u, 0u};
-            if (u >= v.w) {
-                const int j = u - v.w;
-                if (j < n) {
-                    const size_t src = ((size_t)(row0 + j) * v.Hkv + h) * D + c * 8;
-                    kk = *reinterpret_cast<const uint4*>(k + src);
-                    vl = *reinterpret_cast<const uint4*>(vv + src);
-                }
-            } else {
-                const int s = T0 - v.w + u;
-                if (s >= 0) {
-                    const int slot = s % v.w;
-                    const uint16_t* sp = ring_page(v, pair, slot >> 6);
-                    const int sk = slot & 63;
-                    kk = *reinterpret_cast<const uint4*>(sp + spkv_k_off(D, sk, c * 8));
-                    const uint16_t* vs = sp + spkv_v_off(D, sk, c * 8);
-                    unsigned wd[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        wd[e] = (unsigned)vs[(2 * e) * 8] | ((unsigned)vs[(2 * e + 1) * 8] << 16);
-                    vl = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-                }
-            }
-            *reinterpret_cast<uint4*>(dp + spkv_k_off(D, wave * 8 + row, c * 8)) = kk;
-            *reinterpret_cast<uint4*>(&s_v[wave][row][c * 8]) = vl;
-        }
-        if (pf.bias != nullptr && c == 0) {
-            float lb = 0.f;
-            if (u >= v.w && u - v.w < n) {
-                // log u = log sigmoid(f) = -softplus(-f) (Eq. 1 and the soft gate), in log2
-                const float x = f[((size_t)row0 + (u - v.w)) * v.Hkv + h];
-                const float ls = x < -20.f ? x : -log1pf(__expf(-x));
-                lb = ls * 1.4426950408889634f * pf.bias_unit;
-            }
-            pf.bias[((size_t)pair * pf.shp + sh) * kHalfTokens + wave * 8 + row] = lb;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    store_v_units<D>(dp, wave * 8, s_v[wave], lane);
+                                                          const float* __restrict__ f, SpkvCu cu, SpkvStage st) {
+    stage_half_page<D>(v, k, vv, f, cu, st, blockIdx.y, blockIdx.x);
 }
 
 // Bits e = 0..7 set for a <= e <= b (empty if the range misses 0..7); branch-free.
@@ -1259,9 +1203,13 @@ static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uin
         launch_attend<D, true>(v, q, out, lse, sl, pf, cu, k, vv, s);
     } else {
         const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
-        spkv_prefill_stage<D><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
+        SpkvStage st = {pf.stage, pf.bias, pf.bias_unit, pf.shp, stage_hps};
+        if (!spkv_append_stages(v, n_max)) {
+            spkv_prefill_stage<D><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, st);
+            st.stage = nullptr;
+        }
         const SpanCut cut = {pf.order != nullptr ? pf.nw * pf.tb : 0, pf.groups};
-        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, cut, to, s);
+        const hipError_t e = spkv_launch_append_bulk(v, k, vv, f, cu, n_max, pf.prefix, cut, st, to, s);
         if (e != hipSuccess) return e;
         launch_attend<D, false>(v, q, out, lse, sl, pf, cu, nullptr, nullptr, s);
     }
@@ -1270,7 +1218,7 @@ static hipError_t launch_prefill(const SpkvView& v, const uint16_t* k, const uin
         const int blocks = pf.spans * (pf.nw * pf.nq * 16 / (256 / (D / 4)));
         spkv_prefill_combine<D><<<dim3((fa != nullptr ? v.n_pairs : 0) + blocks), dim3(256), 0, s>>>(v, out, lse, pf, cu, k, vv, fa);
     } else if (direct && f != nullptr) {
-        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, SpanCut{0, 1}, to, s);
+        return spkv_launch_append_bulk(v, k, vv, f, cu, n_max, nullptr, SpanCut{0, 1}, SpkvStage{}, to, s);
     }
     return hipGetLastError();
 }
@@ -1301,11 +1249,12 @@ hipError_t spkv_launch_soft_gated(const SpkvView& v, const uint16_t* k, const ui
     pf.bias_unit = 1.0f / sl;
     const int stage_hps = (v.w + n_max + kHalfTokens - 1) / kHalfTokens;
     const unsigned grid = prefill_grid(v, pf);
+    const SpkvStage st = {pf.stage, pf.bias, pf.bias_unit, pf.shp, stage_hps};
     if (v.D == 128) {
-        spkv_prefill_stage<128><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
+        spkv_prefill_stage<128><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, st);
         spkv_prefill_attend32<128, true><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     } else {
-        spkv_prefill_stage<64><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, pf);
+        spkv_prefill_stage<64><<<dim3(stage_hps, v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu, st);
         spkv_prefill_attend32<64, true><<<dim3(grid), dim3(512), 0, s>>>(v, q, out, lse, sl, pf, cu);
     }
     return hipGetLastError();

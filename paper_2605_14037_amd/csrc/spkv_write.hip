@@ -259,12 +259,11 @@ __device__ __forceinline__ int block_excl_scan(int x, int* s_w, int& total) {
 constexpr int kCountSegs = 16;
 //
 // MOVE = false: the kept ring rows are moved by stage 3 (ring_in_one_workgroup).
+// SMALL = false leaves the ring and the token counts alone (stage 3 writes both).
 template <int D, bool SMALL, bool COUNT, bool MOVE>
-__global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int32_t* prefix,
-                                                      const uint16_t* __restrict__ k,
-                                                      const uint16_t* __restrict__ vv,
-                                                      const float* __restrict__ f) {
-    const int pair = blockIdx.x;
+__device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, int32_t* prefix,
+                                          const uint16_t* __restrict__ k, const uint16_t* __restrict__ vv,
+                                          const float* __restrict__ f, int pair) {
     const int b = pair / v.Hkv;
     const int n = cu.v[b + 1] - cu.v[b];
     if (n == 0) return;
@@ -380,7 +379,7 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
         s_bi.ok = any_bad ? 0 : 1;
         *reinterpret_cast<BulkInfo*>(v.bulk_info + (size_t)pair * 8) = s_bi;
         if (!any_bad) v.kept_len[pair] = L_old + total_new;
-        v.t_pair[pair] = T_new;
+        if (SMALL) v.t_pair[pair] = T_new;
     }
     __threadfence_block();
     __syncthreads();
@@ -464,6 +463,31 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
                     v.ring_logit[(size_t)pair * v.w + slot] = f[((size_t)row0 + jj) * v.Hkv + h];
             }
         }
+    }
+}
+
+template <int D, bool SMALL, bool COUNT, bool MOVE>
+__global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int32_t* prefix,
+                                                      const uint16_t* __restrict__ k,
+                                                      const uint16_t* __restrict__ vv,
+                                                      const float* __restrict__ f) {
+    bulk_ring<D, SMALL, COUNT, MOVE>(v, cu, prefix, k, vv, f, blockIdx.x);
+}
+// Stage 2 of a prefill call and, in further workgroups, its staging rows: neither writes what the other
+// reads (ring, ring logits, token counts; lists and tables).  Both wait for memory most of their time.
+// Two launches / one, us a prompt with its attention: one sequence of 1000 tokens in pieces of 270
+// 193 / 173, two of 600 48 / 44, one of 16k in pieces of 4096 720 / 693, four of 3k-19k 1660 / 1621.
+template <int D, bool COUNT, bool MOVE>
+__global__ __launch_bounds__(256) void spkv_stage_ring(SpkvView v, SpkvCu cu, int32_t* prefix,
+                                                       const uint16_t* __restrict__ k,
+                                                       const uint16_t* __restrict__ vv,
+                                                       const float* __restrict__ f, SpkvStage st) {
+    const int id = (int)blockIdx.x - v.n_pairs;
+    if (id < 0) {
+        bulk_ring<D, false, COUNT, MOVE>(v, cu, prefix, k, vv, f, blockIdx.x);
+    } else {
+        const int pair = id / st.hps;
+        stage_half_page<D>(v, k, vv, f, cu, st, pair, id - pair * st.hps);
     }
 }
 
@@ -615,6 +639,7 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
     const float fj = (quad < quads && j < n) ? f[((size_t)row0 + j) * v.Hkv + h] : 0.f;
     const int seg_off = (quad < quads && j0 < n_ev) ? v.seg_count[(size_t)pair * v.n_seg_cap + quad * kScatterSegs] : 0;
     const BulkInfo bi = *reinterpret_cast<const BulkInfo*>(v.bulk_info + (size_t)pair * 8);
+    if (quad == 0 && tid == 0) v.t_pair[pair] = bi.T_old + n;
     if (bi.ok == 0) return;
     __shared__ int s_cnt[2][NW];
     __shared__ uint16_t s_list[2 * kScatterThreads];
@@ -758,6 +783,10 @@ static bool ring_in_one_workgroup(const SpkvView& v, int n_max) {
     return v.w <= 64 || (n_max > kScatterThreads && (v.w <= 128 || v.n_pairs >= 64));
 }
 
+bool spkv_append_stages(const SpkvView& v, int n_max) {        // (a launch counts its threads in 32 bits)
+    return spkv_append_copies_lengths(v, n_max) &&
+           (int64_t)v.n_pairs * (1 + ((int64_t)v.w + n_max + kHalfTokens - 1) / kHalfTokens) <= INT32_MAX / 256;
+}
 bool spkv_append_copies_lengths(const SpkvView& v, int n_max) { return n_max > v.w || n_max > kSegTokens; }
 
 template <int D>
@@ -769,7 +798,7 @@ __global__ __launch_bounds__(256) void spkv_append_few(SpkvView v, const uint16_
 
 hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const uint16_t* vv,
                                    const float* f, const SpkvCu& cu, int n_max, int32_t* prefix,
-                                   SpanCut cut, SpkvLengthCopy to, hipStream_t s) {
+                                   SpanCut cut, const SpkvStage& st, SpkvLengthCopy to, hipStream_t s) {
     if (n_max <= kFewTokens && n_max <= v.w && prefix == nullptr) {
         if (v.D == 128) spkv_append_few<128><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
         else spkv_append_few<64><<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, k, vv, f, cu);
@@ -787,12 +816,18 @@ hipError_t spkv_launch_append_bulk(const SpkvView& v, const uint16_t* k, const u
     const bool fold = segs_all <= kCountSegs;       // the per-pair launch counts for itself
     if (!fold) spkv_bulk_count<<<dim3(segs_all, v.n_pairs), dim3(256), 0, s>>>(v, f, cu);
     auto stage2 = [&](auto kernel) { kernel<<<dim3(v.n_pairs), dim3(256), 0, s>>>(v, cu, prefix, k, vv, f); };
+    const dim3 grid2((unsigned)v.n_pairs * (unsigned)(1 + st.hps));
+    auto staged = [&](auto kernel) { kernel<<<grid2, dim3(256), 0, s>>>(v, cu, prefix, k, vv, f, st); };
     if (v.D == 128) {
-        if (fold) ring_here ? stage2(spkv_bulk_ring<128, false, true, false>) : stage2(spkv_bulk_ring<128, false, true, true>);
+        if (st.stage != nullptr && fold) ring_here ? staged(spkv_stage_ring<128, true, false>) : staged(spkv_stage_ring<128, true, true>);
+        else if (st.stage != nullptr) ring_here ? staged(spkv_stage_ring<128, false, false>) : staged(spkv_stage_ring<128, false, true>);
+        else if (fold) ring_here ? stage2(spkv_bulk_ring<128, false, true, false>) : stage2(spkv_bulk_ring<128, false, true, true>);
         else ring_here ? stage2(spkv_bulk_ring<128, false, false, false>) : stage2(spkv_bulk_ring<128, false, false, true>);
         spkv_bulk_scatter<128><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, cut, to);
     } else {
-        if (fold) ring_here ? stage2(spkv_bulk_ring<64, false, true, false>) : stage2(spkv_bulk_ring<64, false, true, true>);
+        if (st.stage != nullptr && fold) ring_here ? staged(spkv_stage_ring<64, true, false>) : staged(spkv_stage_ring<64, true, true>);
+        else if (st.stage != nullptr) ring_here ? staged(spkv_stage_ring<64, false, false>) : staged(spkv_stage_ring<64, false, true>);
+        else if (fold) ring_here ? stage2(spkv_bulk_ring<64, false, true, false>) : stage2(spkv_bulk_ring<64, false, true, true>);
         else ring_here ? stage2(spkv_bulk_ring<64, false, false, false>) : stage2(spkv_bulk_ring<64, false, false, true>);
         spkv_bulk_scatter<64><<<grid3, dim3(kScatterThreads), 0, s>>>(v, k, vv, f, cu, prefix, quads, ring_here, cut, to);
     }

@@ -33,3 +33,13 @@ def test_prefill_spans_in_order(B, Hkv, ctx, counts, ranges, groups):
         each = sum(-(-n // span) for n in counts) * Hkv * ranges // groups       # workgroups of a group
         grid = 8 * 2 * -(-each // (2 * (8 // groups)))                           # two at a time per XCD
     _run_prefill(wl, [counts], sample=120, last_grid=grid, decode_after=1)
+
+
+@pytest.mark.parametrize("D,window,ctx,n", [(64, 64, 500, 4099), (128, 600, 700, 4099), (128, 600, 40, 4097),
+                                            (64, 100, 0, 513), (128, 64, 90, 65), (64, 600, 2000, 601)])
+def test_prefill_rows_staged_beside_the_append(D, window, ctx, n):
+    """The window is staged while the append counts: chunks whose segments are counted before it (above
+    4096 tokens) or by it, leaving ring rows moved by it (long windows) or later, windows that hold
+    nothing or a part, chunks of one token more than the window, and decode steps on what is left."""
+    wl = small_workload("staged", 2, 4, 2, D, [ctx, ctx // 2], [[0.4, 0.1]], window=window, seed=D + n)
+    _run_prefill(wl, [[n, n // 3]], sample=60, decode_after=2)
