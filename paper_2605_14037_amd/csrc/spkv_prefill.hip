@@ -677,6 +677,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int rot = (lp * 8 + 8 <= v.n_pairs) ? lp : 0;
         pair = lp * 8 + (((blockIdx.x & 7) + rot) & 7);
         if (pair >= v.n_pairs) return;
+    } else if (SOFT) {                    // the last, longest spans of all pairs first
+        qblk = (int)blockIdx.x / v.n_pairs;
+        pair = (int)blockIdx.x - qblk * v.n_pairs;
+        kr = 0;
     } else {
         pair = blockIdx.x / (pf.nblk * pf.ks);
         const int rem = blockIdx.x - pair * pf.nblk * pf.ks;
@@ -1244,6 +1248,12 @@ hipError_t spkv_launch_soft_gated(const SpkvView& v, const uint16_t* k, const ui
                                   float sm_scale, const SpkvCu& cu, int n_max, uint16_t* stage,
                                   float* bias, int shp, hipStream_t s) {
     SpkvPrefill pf = prefill_params(v, n_max, stage, nullptr, bias, shp);
+    // A pair to an XCD leaves some XCDs more pairs than others where their number is no multiple of eight:
+    // then all pairs on all XCDs, unless the spans run in one round, whose tiles come sooner from one L2.
+    // us, pairs of an XCD / all: 9 pairs of 700 tokens (99 spans) 37.3 / 39.2, of 2000 91 / 75, of 8000
+    // 913 / 611, with head_dim 64 and groups of 8 1303 / 770; 12 of those 1347 / 1009; 20 pairs of 8000 834 / 700,
+    // 30 2053 / 1953, 36 2552 / 2330.
+    if (v.n_pairs % 8 != 0 && pf.spans > kPrefillResident8) pf.pin_xcd = 0;
     // (below 1e-30 a score no longer shows beside the biases: keeps bias / scale finite)
     const float sl = std::max(sm_scale * 1.4426950408889634f, 1e-30f);
     pf.bias_unit = 1.0f / sl;
