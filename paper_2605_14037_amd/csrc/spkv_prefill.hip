@@ -658,7 +658,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(16))) float s_zero[32];
     if (SOFT && threadIdx.x < 32) s_zero[threadIdx.x] = 0.f;      // (the barrier before the loop)
     int pair, qblk, kr, id = 0;      // (sequence, KV head), span, tile range of the span
-    if (pf.order != nullptr) {
+    if (!SOFT && pf.order != nullptr) {
         // `share` XCDs for a group; two neighbours of a pair at a time on one (they share most of their windows)
         const int share = 8 / pf.groups, xcd = blockIdx.x & 7, group = xcd / share, at = blockIdx.x >> 3;
         const int j = ((at >> 1) * share + xcd - group * share) * 2 + (at & 1);
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b], n_tok = cu.v[b + 1] - row0;
     // longest prefixes first
-    qblk = (pf.order != nullptr ? (n_tok + NW * pf.tb - 1) / (NW * pf.tb) : pf.nblk) - 1 - qblk;
+    qblk = (!SOFT && pf.order != nullptr ? (n_tok + NW * pf.tb - 1) / (NW * pf.tb) : pf.nblk) - 1 - qblk;
     const int span0 = qblk * NW * pf.tb;
     if (span0 < 0 || span0 >= n_tok) return;
     const int span_last = min(span0 + NW * pf.tb, n_tok) - 1;
@@ -969,7 +969,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (!valid) return;
     if (pf.ks > 1) {
         const size_t n_cols = (size_t)pf.spans * pf.ks * (NW * 32);
-        const size_t range = pf.order != nullptr ? (size_t)id * pf.ks + kr : ((size_t)pair * pf.nblk + qblk) * pf.ks + kr;
+        const size_t range = !SOFT && pf.order != nullptr ? (size_t)id * pf.ks + kr : ((size_t)pair * pf.nblk + qblk) * pf.ks + kr;
         const size_t pc = range * (NW * 32) + wv * 32 + col;
         float* pa = pf.part + pc * D + half * 4;
 #pragma unroll
