@@ -677,6 +677,7 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
             f_tok = f_new[(size_t)b * v.Hkv + h];
         }
         const AppendRegs<D> ar = append_load<D>(v, pair, h, b, T, L, k_new, v_new, f_tok, threadIdx.x);
+        __syncthreads();
         append_store<D>(v, pair, T, L, ar, threadIdx.x, &s_page);
         return;
     }

@@ -223,6 +223,8 @@ __device__ __forceinline__ f32x4 predictor_contract(const uint16_t* __restrict__
 // pair's counters as read by every thread before any of them is updated.
 // NT = threads that take part (a multiple of 64); thread tid moves V elements tid,
 // tid + NT, ... (one per thread when NT >= D).
+// Between the halves lies a barrier of the workgroup (the caller's): the second one changes the
+// counters, the ring's row and its logit, which a late wave of the first must not find changed.
 template <int D, int NT = D>
 struct AppendRegs {
     static constexpr int VPT = (D + NT - 1) / NT;
