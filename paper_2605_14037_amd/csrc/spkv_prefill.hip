@@ -938,6 +938,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // its head makes the first operand wait of every pass wait for all LDS reads).
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
     asm volatile("" : : "s"(scale_log2e));
+    // Soft gating: where the loop lies against the 32-byte lines that instructions are fetched in counts,
+    // with the same instructions: 4 sequences of 16k at the eight places 8275 (this one) to 8351 us, head_dim 64
+    // 1333 (this one) to 1352.  (Moved by anything between here and the loop.)
+    if (SOFT && D == 128) asm volatile(".p2align 5\n\t.rept 5\n\ts_nop 0\n\t.endr");
+    if (SOFT && D != 128) asm volatile(".p2align 5\n\t.rept 7\n\ts_nop 0\n\t.endr");
     stage_step(x_begin, 0);
     stage_step(x_begin + 2, 1);
     stage_step(x_begin + 4, 2);

@@ -82,3 +82,14 @@ def test_single_token_append_stores_after_every_wave_has_read(code, kernel):
     for body in bodies:
         assert any(op == "s_barrier" for op, _, _ in body.values())
         assert _first_stores(body) == []
+
+
+@pytest.mark.parametrize("head_dim,place", [(128, 24), (64, 8)])
+def test_soft_gated_loop_lies_where_it_was_measured(code, head_dim, place):
+    """The same instructions took up to 1 % longer at other places in a 32-byte line of instructions."""
+    (body,) = [b for name, b in code.items() if f"spkv_prefill_attend32ILi{head_dim}ELb1E" in name]
+    loops = [(sum(to <= a <= at and "mfma" in body[a][0] for a in body), to - at, to)
+             for at, (_, to, _) in body.items() if to is not None and to <= at]
+    products, _, head = max(loops)
+    assert products >= 16
+    assert head % 32 == place
