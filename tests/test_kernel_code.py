@@ -84,12 +84,11 @@ def test_single_token_append_stores_after_every_wave_has_read(code, kernel):
         assert _first_stores(body) == []
 
 
-@pytest.mark.parametrize("head_dim,place", [(128, 24), (64, 8)])
-def test_soft_gated_loop_lies_where_it_was_measured(code, head_dim, place):
-    """The same instructions took up to 1 % longer at other places in a 32-byte line of instructions."""
+@pytest.mark.parametrize("head_dim", [128, 64])
+def test_soft_gated_loop_lies_where_it_was_measured(code, head_dim):
+    """The same instructions took up to 1 % longer at other places in a 32-byte line of instructions.  The
+    loop is the one of two half-pages' products."""
     (body,) = [b for name, b in code.items() if f"spkv_prefill_attend32ILi{head_dim}ELb1E" in name]
-    loops = [(sum(to <= a <= at and "mfma" in body[a][0] for a in body), to - at, to)
-             for at, (_, to, _) in body.items() if to is not None and to <= at]
-    products, _, head = max(loops)
-    assert products >= 16
-    assert head % 32 == place
+    heads = {to for at, (_, to, _) in body.items() if to is not None and to <= at
+             and sum(to <= a <= at and "mfma" in body[a][0] for a in body) == head_dim // 4}
+    assert len(heads) == 1 and heads.pop() % 32 == 16
