@@ -319,7 +319,8 @@ int spkv_soft_gated_attention(const void* q, const void* k, const void* v, const
  * holds an empty sequence that can be appended to again.  (The paper's cache manager grows
  * and shares one page pool across requests, appendix "Inference Kernels"; giving pages
  * back is the counterpart a serving loop needs.)  Synchronises `stream` once to read the
- * exact lengths, then enqueues the release. */
+ * exact lengths, then enqueues the release.  What the pages and the window held does not show in
+ * the next owner's attention, infinities and NaN included. */
 int spkv_cache_release_sequence(spkv_cache_t* cache, int32_t b, void* stream);
 
 /* Utility predictor (Eq. 1; the listing's UtilityPredictor: Linear(d_model, d_hidden), SiLU,

@@ -487,13 +487,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 // the tile after next (past the last one: the last tile again, never used)
                 stage_tile(p_next, buf >= 1 ? buf - 1 : kBufs - 1);
                 p_next = base_of(x + kAhead + 1);
-                if (DIRECT && x == n_loop - 1 && (held & 31) != 0) {
-                    // slots of a ring that is not full yet: whatever lies there must not meet a weight of 0
-                    uint16_t* vt = s_tile[buf] + kHalfTokens * D;
-                    for (int e = tid; e < kHalfElems / 2; e += 64 * NW)       // element e: key 8 ((e >> 7) & 3) + (e & 7)
-                        if (8 * ((e >> 7) & 3) + (e & 7) >= (held & 31)) vt[e] = 0;
-                    __syncthreads();
-                }
             }
             resume = false;
             const uint16_t* tile = s_tile[buf];

@@ -903,6 +903,8 @@ __global__ __launch_bounds__(256) void spkv_prune(SpkvView v) {
     if (tid == 0) s_base = n_free > 0 ? atomicAdd(v.free_top, n_free) : 0;
     __syncthreads();
     for (int i = tid; i < n_free; i += 256) v.free_pages[s_base + i] = pt[np_new + i];
+    if (out < L && (out & (kHalfTokens - 1)) != 0)         // dropped rows behind the new end (every row has moved)
+        clear_list_end<D>(pool_page(v, pt[out >> 6]), out, tid, 256);
     if (tid == 0) v.kept_len[pair] = out;
 }
 
@@ -914,10 +916,20 @@ hipError_t spkv_launch_prune(const SpkvView& v, hipStream_t s) {
 
 // ---------------------------------------------------------------- release a sequence
 // One workgroup per KV head of the sequence: its pages go onto the stack of recycled pages
-// and its counters back to zero (the ring needs no clearing: with T = 0 no slot is valid).
+// and its counters back to zero.  Further ones clear the values of its ring: while the next
+// owner's window fills, the half-page that ends it is read whole, and a weight of zero would turn an
+// infinity among the old ones into a NaN (keys are masked by selection).
+__host__ __device__ __forceinline__ int ring_half_pages(const SpkvView& v) { return (v.w + kHalfTokens - 1) / kHalfTokens; }
 __global__ __launch_bounds__(256) void spkv_release_sequence(SpkvView v, int b) {
     const int pair = b * v.Hkv + blockIdx.x;
     const int tid = threadIdx.x;
+    if (blockIdx.y > 0) {
+        for (int hp = blockIdx.y - 1; hp < ring_half_pages(v); hp += gridDim.y - 1) {
+            uint4* values = reinterpret_cast<uint4*>(ring_page(v, pair, hp >> 1) + ((hp & 1) * 2 + 1) * kHalfTokens * v.D);
+            for (int i = tid; i < kHalfTokens * v.D / 8; i += 256) values[i] = make_uint4(0u, 0u, 0u, 0u);
+        }
+        return;
+    }
     const int np = (v.kept_len[pair] + kPageTokens - 1) / kPageTokens;
     __shared__ int s_base;
     if (tid == 0) s_base = np > 0 ? atomicAdd(v.free_top, np) : 0;
@@ -932,7 +944,7 @@ __global__ __launch_bounds__(256) void spkv_release_sequence(SpkvView v, int b) 
 }
 
 hipError_t spkv_launch_release_sequence(const SpkvView& v, int b, hipStream_t s) {
-    spkv_release_sequence<<<dim3(v.Hkv), dim3(256), 0, s>>>(v, b);
+    spkv_release_sequence<<<dim3(v.Hkv, 1 + std::min(ring_half_pages(v), 256)), dim3(256), 0, s>>>(v, b);
     return hipGetLastError();
 }
 
