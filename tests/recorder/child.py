@@ -82,6 +82,8 @@ def main():
             rc = lib.spkv_cache_stats(handle, C.create_string_buffer(4096), None, None)
         elif op == "reset":
             rc = lib.spkv_cache_reset(handle, None)
+        elif op == "destroy":                             # last of a script
+            rc = lib.spkv_cache_destroy(handle)
         elif op == "advance":
             rc = lib.spkv_cache_advance(handle, C.c_int64(a[0]))
         elif op == "option":

@@ -121,6 +121,7 @@ int hipHostMalloc(void** p, size_t n, unsigned) {
     return 0;
 }
 int hipHostFree(void* p) {
+    g_log.push_back("host_free 0 0 0");
     free(p);
     return 0;
 }
@@ -148,6 +149,13 @@ int hipEventQuery(void*) {
     if (g_event_ready) return 0;
     return g_last_error = 600;                             // hipErrorNotReady
 }
-int hipEventRecord(void*, void*) { return 0; }
+int hipEventRecord(void*, void*) {
+    g_log.push_back("event_record 0 0 0");
+    return 0;
+}
+int hipDeviceSynchronize() {
+    g_log.push_back("device_sync 0 0 0");
+    return 0;
+}
 int hipEventSynchronize(void*) { return 0; }
 }

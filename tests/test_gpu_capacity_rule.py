@@ -1,7 +1,10 @@
 """Calls are refused by the exact lengths, whichever way the host has learnt them."""
 
+import ctypes
+
 import numpy as np
 import pytest
+import torch
 
 import paper_2605_14037_amd as spkv
 from paper_2605_14037_amd.inputs import TokenStream, small_workload, to_numpy_f32
@@ -66,3 +69,22 @@ def test_refusals_follow_the_exact_lengths(seed):
     if all(oracle.seq_len(b) for b in range(B)):
         H.check_output(cache.decode_attention(q), oracle.decode(to_numpy_f32(q))[0])
     cache.close()
+
+
+def test_destroyed_right_behind_a_prompt():
+    """The lengths that a prompt sends to the host go into pinned memory of the cache: destroyed while the
+    launches are still on their way, it frees that memory only when they have come."""
+    hold = torch.randn(4096, 4096, device="cuda")
+    held = []
+    for r in range(8):
+        cache = spkv.SPKVCache(4, 8, 2, 64, max_context=8192, max_total_kept_tokens=65536, window=64, tau=0.5)
+        k = torch.zeros(4 * 700, 2, 64, dtype=torch.bfloat16, device="cuda")
+        f = torch.ones(4 * 700, 2, device="cuda")
+        for _ in range(r):
+            hold = hold @ hold * 1e-3                     # so that the append starts late
+        cache.append(k, k, f, [0, 700, 1400, 2100, 2800])
+        assert cache.lib.spkv_cache_destroy(cache.handle) == 0       # (close() would wait by itself)
+        cache.handle = ctypes.c_void_p()
+        held.append((cache.arena, torch.full((1024,), -7, dtype=torch.int32, pin_memory=True)))
+    torch.cuda.synchronize()
+    assert all(bool((p == -7).all()) for _, p in held)

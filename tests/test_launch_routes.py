@@ -110,6 +110,23 @@ def test_bulk_append_who_writes_the_ring(batch, window, piece, ring_workgroups, 
     assert grid == (-(-piece // 512) + ring_workgroups, batch * 8)
 
 
+@pytest.mark.parametrize("call", [["append", [4096] * 16], ["prefill", [4096] * 16], ["chunk", [16] * 16]])
+def test_lengths_are_sent_without_an_event(call):
+    """The launch after an event starts 5 to 6 us late, which every append of a prompt would pay for."""
+    script = [["append", [4096] * 16], ["lengths", _uneven(128, 4000)], ["chunk", [16] * 16], call]
+    for got in record(dict(batch=16), script):
+        assert got.rc == 0 and got.launches and not [n for n, _, _ in got.launches if "event" in n]
+
+
+def test_a_cache_is_destroyed_after_its_copies():
+    """The pinned buffer is freed when nothing can write it any more: at once where every copy has arrived,
+    behind the device where one has not (here the prompt's, which this runtime never delivers)."""
+    def end(script):
+        return [n for n, _, _ in record(dict(batch=16), script + [["destroy"]])[-1].launches]
+    assert end([]) == ["host_free"]
+    assert end([["append", [4096] * 16]]) == ["device_sync", "host_free"]
+
+
 def test_reset_is_one_launch():
     """A prompt of a small model is fed in two or three launches a piece: three more for the reset
     were a fifth of the time of feeding 4096 tokens."""
