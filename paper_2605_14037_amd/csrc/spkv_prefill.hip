@@ -563,7 +563,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
             rescale_columns<D, NQ>(xs, scale_log2e, acc, m, l);
             (void)tile_weights<NQ>(xs, scale_log2e, m, pw, psum);
         }
-        tile_accumulate<D, NQ>(s_tile[kBufs], lane, pw, psum, acc, l);
+        // these weights stay in 32 bits, as in spkv_chunk_combine: three bf16 parts hold all 24 of one
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+            tile_accumulate<D, NQ>(s_tile[kBufs], lane, pw, psum, acc, l);
+#pragma unroll
+            for (int c = 0; c < NQ; ++c) {
+                psum[c] = 0.f;
+                pw[c] -= __builtin_convertvector(__builtin_convertvector(pw[c], bf16x8), f32x8);
+            }
+        }
     }
 
 #pragma unroll

@@ -111,3 +111,22 @@ def test_few_tokens_appended_over_page_boundaries(D, w, sinks, keep):
     H.check_output(out, oracle.decode(to_numpy_f32(q))[0], "decode of what was appended")
     H.check_state(cache, oracle, wl)
     cache.close()
+
+
+@pytest.mark.parametrize("Hk,G,D,n", [(2, 4, 128, 16), (2, 4, 64, 16), (3, 8, 64, 7), (1, 16, 128, 4), (2, 4, 128, 4)])
+def test_weights_of_the_chunk_itself_are_32_bit(Hk, G, D, n):
+    """Drafts on an empty cache see nothing but each other: with weights and sums in 32 bits an output is the
+    64-bit one rounded to bf16, but for those within some 2^-20 of the middle between two (fewer than one
+    in 500); with weights of 8 bits one in five is another one."""
+    wl = small_workload("own", 4, Hk * G, Hk, D, [0] * 4, 0.5, window=64, seed=D + n)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl, extra_context=100), H.make_oracle(wl)
+    counts = [n, n, 1, n - 1]
+    k, v, f, cu = stream.next_tokens(counts)
+    q = stream.next_query(rows=sum(counts))
+    oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+    ref = torch.from_numpy(oracle.decode_chunk(to_numpy_f32(q), counts)[0])
+    for out in (cache.score_chunk(k, v, q, cu), cache.decode_chunk(k, v, f, q, cu)):
+        other = float((out.cpu() != ref.to(torch.bfloat16)).double().mean())
+        assert other < 0.01, other
+    cache.close()
