@@ -303,8 +303,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // chunks and for the two-wave workgroups of short ones alike).
     constexpr int kAhead = 2, kBufs = kAhead + 1;
     __shared__ __attribute__((aligned(16))) uint16_t s_tile[kBufs + (DIRECT ? 1 : 0)][kHalfElems];
-    constexpr int kGateSlots = 1024;
-    __shared__ unsigned long long s_gate[DIRECT ? kGateSlots / 64 : 1];       // gate of the ring's first slots
+    constexpr int kGateTiles = 256;
+    __shared__ unsigned s_gate[DIRECT ? kGateTiles : 1];       // gates of the first ring tiles of this workgroup
     int pair, kr, ranges;
     bool once = pf.once != 0;
     if (pf.slots == 0) {
@@ -379,11 +379,23 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     auto ring_gate = [&](int at) -> bool {
         return gate_passes(v, v.ring_logit[(size_t)pair * v.w + at], T0 - v.w + age_of(at));
     };
-    if (DIRECT && x_end > nA)               // this workgroup reaches into the ring
-        for (int at = wv * 64; at < min(held, kGateSlots); at += 64 * NW) {
-            const unsigned long long gates = __ballot(ring_gate(min(at + lane, held - 1)));
-            if (lane == 0) s_gate[at >> 6] = gates;
+    const int ring0 = max(x_begin - nA, 0);     // DIRECT: this workgroup's first ring tile
+    if (DIRECT) {
+        // two tiles' gates per wave and pass, the loads of four passes together
+        const int tiles = min(x_end - nA - ring0, kGateTiles);
+        for (int t0 = wv * 2; t0 < tiles; t0 += 4 * 2 * NW) {
+            bool on[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                on[u] = ring_gate(min((ring0 + t0 + u * 2 * NW) * kHalfTokens + lane, held - 1));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long gates = __ballot(on[u]);
+                const int t = t0 + u * 2 * NW + lane;
+                if (lane < 2 && t < tiles) s_gate[t] = (unsigned)(gates >> (32 * lane));
+            }
         }
+    }
     if (DIRECT && x_stop > n_loop) {        // the chunk's own rows as a tile: key j is token j, then zeros
         uint16_t* tile = s_tile[kBufs];
 #pragma unroll 2
@@ -512,8 +524,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
                 } else if (DIRECT) {
                     const int u0 = u_tile + kc * 8;
                     unsigned gate = 0u;
-                    if (u_tile < kGateSlots) {
-                        gate = (unsigned)(s_gate[u_tile >> 6] >> (u0 & 63));
+                    if (x - nA - ring0 < kGateTiles) {
+                        gate = s_gate[x - nA - ring0] >> (kc * 8);
                     } else {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)

@@ -57,6 +57,26 @@ def test_chunks_attended_before_their_append(Hk, G, D, w, ctx, n, kernel):
     cache.close()
 
 
+def test_wide_window_in_one_workgroup():
+    """512 pairs are not cut into ranges: the workgroup of the one that holds a sequence meets more ring tiles
+    than it keeps gates of."""
+    B, w, n = 64, 8300, 10
+    wl = small_workload("wide", B, 16, 8, 64, [w + 150] + [0] * (B - 1), 0.4, window=w, seed=9)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl, extra_context=100, pool_tokens=8 * 400), H.make_oracle(wl)
+    H.prefill(cache, oracle, stream, wl, 4096)
+    counts = [n] + [0] * (B - 1)
+    k, v, f, cu = stream.next_tokens(counts)
+    q = stream.next_query(rows=n)
+    assert _first_kernel(cache, wl, list(wl.ctx_lens), ["chunk", counts]) == "spkv_prefill_attend<64, 2, 1, 1>"
+    scored = cache.score_chunk(k, v, q, cu)
+    out = cache.decode_chunk(k, v, f, q, cu)
+    assert torch.equal(scored, out)
+    oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+    H.check_output(out, oracle.decode_chunk(to_numpy_f32(q), counts)[0], "wide window")
+    cache.close()
+
+
 def test_stale_ring_slots_do_not_show():
     """A released sequence leaves its rows in the ring; infinite ones must not show in the chunks of the
     sequence that takes its place while its own ring is filling."""
