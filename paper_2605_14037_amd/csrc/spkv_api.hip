@@ -520,8 +520,14 @@ bool one_launch(const spkv_cache* c, hipStream_t) {
 // 94 / 88; but 300 pairs, 64 the longest and 16 the mean, 1.3 times as long.  (Issued call by call,
 // short steps take what the host takes: 13 / 10.)  Over 500 caches of up to 512 pairs drawn at random
 // this takes 0.80 of the time on those it is chosen for, 1.01 at most.
+// A captured launch is replayed on lists of any length: it is one only of lists so short that the split
+// kernel, frozen with as few workgroups, is never the faster one.  us a replay, split / this, captured at
+// 4 half-pages: 2 pairs of 64 at 4 5.8 / 3.3, at 64 14.0 / 7.7, at 1024 273 / 150; 8 of 128 at 64 20 / 15, at 1024
+// 547 / 283; 128 at 64 40 / 28, at 1024 504 / 364.  Captured at 5 already, 8 of 128 at 64 13 / 17, at 1024 189 / 285;
+// 2 of 64 captured at 24, at 48 6.3 / 6.5, at 384 18 / 54.
 constexpr int kShortHps = 16, kShortHpsWideGroup = 8, kShortHps64 = 24, kShortEvenPairs = 192, kShortEvenHps = 64;
-bool short_lists(const spkv_cache* c) {
+constexpr int kShortHpsCaptured = 4;
+bool short_lists(const spkv_cache* c, hipStream_t s) {
     if (c->item_target > 0 || c->merge_waves > 0 || c->step_launches > 0) return false;
     const int n = c->carve.n_pairs, Hkv = c->cfg.n_kv_heads;
     int64_t longest = 0, sum = 0;                          // half-pages
@@ -531,8 +537,10 @@ bool short_lists(const spkv_cache* c) {
         longest = std::max(longest, hp);
         sum += hp;
     }
-    if (longest <= (c->cfg.head_dim == 64 ? kShortHps64 : c->carve.G > 8 ? kShortHpsWideGroup : kShortHps)) return true;
-    return n >= kShortEvenPairs && longest <= kShortEvenHps && 2 * longest * n <= 3 * sum;
+    if (longest <= kShortHpsCaptured) return true;
+    const bool few = longest <= (c->cfg.head_dim == 64 ? kShortHps64 : c->carve.G > 8 ? kShortHpsWideGroup : kShortHps);
+    const bool even = n >= kShortEvenPairs && longest <= kShortEvenHps && 2 * longest * n <= 3 * sum;
+    return (few || even) && !being_captured(s);
 }
 // The partition reported for such a call: one workgroup per pair.
 SpkvSplit short_split(const spkv_cache* c) {
@@ -802,7 +810,7 @@ int spkv_decode_step(spkv_cache_t* c, const void* k, const void* v, const float*
     tighten_bound(c, s);
     const int rc = reserve_capacity(c, nullptr, s);
     if (rc != SPKV_OK) return rc;
-    if (short_lists(c)) {
+    if (short_lists(c, s)) {
         const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, static_cast<const uint16_t*>(k),
                                static_cast<const uint16_t*>(v), util_logits};
         c->split = short_split(c);
@@ -889,7 +897,7 @@ int spkv_decode_attention(spkv_cache_t* c, const void* q, void* out, float* lse,
         if (rc != SPKV_OK) return rc;
     }
     tighten_bound(c, s);
-    if (!c->timing && !c->split_only && short_lists(c)) {
+    if (!c->timing && !c->split_only && short_lists(c, s)) {
         const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, nullptr, nullptr, nullptr};
         c->split = short_split(c);
         return spkv_launch_decode_short(c->view, static_cast<const uint16_t*>(q), sm_scale, io, s) == hipSuccess
@@ -938,7 +946,7 @@ int spkv_decode_attention_static(spkv_cache_t* c, const void* q, void* out, floa
     v.part_acc = reinterpret_cast<float*>(base);
     v.part_ml = reinterpret_cast<float*>(base + align_up((size_t)cap * G * D * sizeof(float)));
     v.max_items = (int32_t)std::min<int64_t>(cap, INT32_MAX);
-    if (short_lists(c)) {                            // no partial results at all
+    if (short_lists(c, static_cast<hipStream_t>(stream))) {      // no partial results at all
         const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, nullptr, nullptr, nullptr};
         c->split = short_split(c);
         return spkv_launch_decode_short(c->view, static_cast<const uint16_t*>(q), sm_scale, io,
@@ -1388,7 +1396,7 @@ int spkv_cache_stats(spkv_cache_t* c, spkv_stats_t* st, int32_t* kept_len, void*
     st->pool_pages_total = c->carve.n_pages;
     st->arena_bytes = (int64_t)c->arena_bytes;
     st->device_error = err;
-    const SpkvSplit sp = short_lists(c) ? short_split(c) : choose_split(c);   // of the next decode call
+    const SpkvSplit sp = short_lists(c, s) ? short_split(c) : choose_split(c);   // of the next decode call
     int64_t n_items = 0;
     for (int p = 0; p < n_pairs; ++p) {
         const int Tw = std::min(c->T[p / Hkv], w);

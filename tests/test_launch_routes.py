@@ -34,6 +34,21 @@ def test_short_lists_are_one_launch(cfg, kept, short):
         assert names and not any("short" in n for n in names)
 
 
+@pytest.mark.parametrize("call", [["step"], ["attend"], ["static"]])
+@pytest.mark.parametrize("cfg,kept,short,captured", [
+    (dict(batch=1), [8 * 32] * 8, True, False), (dict(batch=24), [60 * 32 - 1] * 192, True, False),
+    (dict(batch=1, n_q_heads=8, n_kv_heads=2, head_dim=64), [10, 10], True, False),
+    (dict(batch=1, window=64), [2 * 32 - 1] * 8, True, True), (dict(batch=1, window=64), [2 * 32 + 1] * 8, True, False)])
+def test_captured_short_lists(cfg, kept, short, captured, call):
+    """A captured step is replayed on lists that grow: 2 pairs of 64 captured at 24 half-pages took 54 us in one
+    workgroup each at 384, 18 split."""
+    for capture, want in (([0, 0], short), ([1, 0], captured), ([0, 906], captured)):
+        script = [["append", [8192] * cfg["batch"]], ["lengths", kept], ["stats"], ["capture"] + capture, call]
+        got = record(cfg, script)[-1]
+        names = [n for n, _, _ in got.launches if "copy" not in n]
+        assert got.rc == 0 and names[0].startswith("spkv_decode_short<") == want, names
+
+
 # ------------------------------------------------------------------ gapless numbering
 @pytest.mark.parametrize("call", [["step"], ["attend"], ["static"], ["score", [4] * 16], ["predict", 4096, 256]])
 def test_unanswered_capture_query_leaves_no_error_behind(call):
