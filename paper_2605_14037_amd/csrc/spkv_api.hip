@@ -284,7 +284,11 @@ void prompt_copy_enqueued(spkv_cache* c, const SpkvLengthCopy& to) { c->sent = t
 // The wait is bounded: past it the stream is waited for.
 constexpr auto kLengthsPatience = std::chrono::milliseconds(20);
 int exact_lengths(spkv_cache* c, hipStream_t s) {
-    if (!c->sent) return refresh_bound(c, s, nullptr);
+    // Under capture never from the copy: whether a call can be captured would depend on whether the prompt
+    // before it has run yet.  Refused as ever by the read-back.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->sent && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    if (!c->sent || cap == hipStreamCaptureStatusActive) return refresh_bound(c, s, nullptr);
     const int n_pairs = c->carve.n_pairs;
     const int32_t* len = c->snap_host + n_pairs + 1;
     const auto until = std::chrono::steady_clock::now() + kLengthsPatience;

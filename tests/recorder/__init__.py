@@ -8,6 +8,8 @@ Script entries: ["append" | "chunk" | "score" | "prefill", tokens per sequence],
 ["static"], ["predict", d_model, d_hidden], ["stats"], ["reset"], ["logits", tokens, d_model, d_hidden, heads],
 ["soft", tokens per sequence], ["advance", n], ["option", id, value], ["destroy"] (last); and what the runtime answers from
 there on: ["lengths", per pair] (any read-back of device lengths), ["capture", status, error],
+["prompt_lengths", 0 | 1] (whether what a prompt sends to the host arrives: of lengths set before it),
+["sync_error", error] (of waiting for a stream),
 ["event_ready", 0 | 1] (whether what is enqueued has run when the call returns), ["watch", kernel, argument, byte] (an entry ("watched", (value, 0), 0) before
 every launch of that kernel: the int at that byte of that argument).
 """

@@ -50,7 +50,7 @@ def main():
         if op == "watch":
             rt.rec_watch(a[0].encode(), a[1], a[2])
             continue
-        if op in ("capture", "event_ready"):
+        if op in ("capture", "event_ready", "prompt_lengths", "sync_error"):
             getattr(rt, "rec_" + op)(*a)
             continue
         if op == "append":

@@ -16,6 +16,8 @@ struct Dim3 {
 static std::map<const void*, std::string> g_kernel;       // host stub -> mangled device name
 static std::vector<std::string> g_log;
 static std::vector<unsigned char> g_device_bytes;         // what copies to the host deliver
+static int g_sync_error = 0;                              // what waiting for a stream returns
+static int g_prompt_lengths = 0;                          // do the lengths that a prompt sends arrive?
 static int g_capture_status = 0, g_capture_error = 0, g_last_error = 0, g_event_ready = 1;
 static std::string g_watch;                               // kernels whose argument is read ...
 static int g_watch_arg, g_watch_at;                       // ... the int at this byte of this argument
@@ -36,6 +38,8 @@ void rec_device_bytes(const void* p, size_t n) {
 }
 void rec_capture(int status, int error) { g_capture_status = status, g_capture_error = error; }
 void rec_event_ready(int ready) { g_event_ready = ready; }
+void rec_prompt_lengths(int arrive) { g_prompt_lengths = arrive; }
+void rec_sync_error(int e) { g_sync_error = e; }
 void rec_watch(const char* kernel, int arg, int at) { g_watch = kernel, g_watch_arg = arg, g_watch_at = at; }
 int rec_take(char* buf, int cap) {                        // the oldest entry; -1: none
     if (g_log.empty()) return -1;
@@ -76,6 +80,13 @@ int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void** args, size_t
         int* to = *static_cast<int**>(args[2]);
         deliver(to, 4 * (size_t)n);
         to[n] = *static_cast<int*>(args[3]);
+    }
+    if (g_kernel[host].find("spkv_bulk_scatter") != std::string::npos && g_prompt_lengths) {
+        const int ordered = *static_cast<int*>(args[8]) > 0;   // (..., order of spans, {where to, ticket})
+        struct { int* to; int ticket; } copy;
+        memcpy(&copy, args[9], sizeof(copy));
+        const int n = (int)grid.y - ordered;
+        if (copy.to != nullptr) deliver(copy.to, 4 * (size_t)n), copy.to[n] = copy.ticket;
     }
     g_log.push_back(g_kernel[host] + " " + std::to_string(grid.x) + " " + std::to_string(grid.y) + " " + std::to_string(block.x));
     return 0;
@@ -130,7 +141,7 @@ int hipMemcpyAsync(void* dst, const void*, size_t n, int, void*) {
     g_log.push_back("copy " + std::to_string(n) + " 0 0");
     return deliver(dst, n);
 }
-int hipStreamSynchronize(void*) { return 0; }
+int hipStreamSynchronize(void*) { return g_sync_error; }
 int hipEventCreate(void** e) {
     *e = malloc(1);
     return 0;

@@ -133,13 +133,25 @@ def test_lengths_are_sent_without_an_event(call):
         assert got.rc == 0 and got.launches and not [n for n, _, _ in got.launches if "event" in n]
 
 
+@pytest.mark.parametrize("arrived", [0, 1])
+@pytest.mark.parametrize("call", [["step"], ["attend"], ["predict", 4096, 256], ["chunk", [4] * 16], ["score", [16] * 16]])
+def test_first_call_after_a_prompt_is_not_captured(call, arrived):
+    """It needs the lengths, and waits for the stream, which a capture refuses: always, not only while the
+    prompt still runs.  Outside a capture the lengths that have arrived will do."""
+    prompt = [["lengths", _uneven(128, 6000)], ["prompt_lengths", arrived], ["append", [8192] * 16]]
+    assert record(dict(batch=16), prompt + [["capture", 1, 0], ["sync_error", 900], call])[-1].rc != 0
+    assert record(dict(batch=16), prompt + [["capture", 0, 906], call])[-1].rc == 0
+    assert record(dict(batch=16), prompt + [call])[-1].rc == 0
+
+
 def test_a_cache_is_destroyed_after_its_copies():
     """The pinned buffer is freed when nothing can write it any more: at once where every copy has arrived,
-    behind the device where one has not (here the prompt's, which this runtime never delivers)."""
+    behind the device where one has not."""
     def end(script):
         return [n for n, _, _ in record(dict(batch=16), script + [["destroy"]])[-1].launches]
     assert end([]) == ["host_free"]
     assert end([["append", [4096] * 16]]) == ["device_sync", "host_free"]
+    assert end([["prompt_lengths", 1], ["append", [4096] * 16]]) == ["host_free"]
 
 
 def test_reset_is_one_launch():
