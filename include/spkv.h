@@ -84,7 +84,7 @@ typedef struct spkv_stats {
     int64_t pool_pages_total;
     int64_t arena_bytes;
     int32_t device_error;      /* nonzero if a kernel ever flagged an inconsistency         */
-    int32_t n_work_items;      /* split-K work items the next decode call would launch      */
+    int32_t n_work_items;      /* work items the next spkv_decode_attention would launch    */
     int32_t n_work_items_last_call; /* the same lists cut by the partition the most recent
                                   decode call used (it is chosen from the host's upper bound
                                   of the lengths; far fewer items than n_work_items would mean
@@ -98,7 +98,11 @@ typedef struct spkv_stats {
                                       come in workgroups of up to four (SPKV_OPT_MERGE_WAVES),
                                       so a call may use up to four per (sequence, KV head)
                                       even for a target of 1                                 */
-#define SPKV_OPT_KERNEL_TIMING  2  /* 1: bracket every split-K kernel launch with HIP events */
+#define SPKV_OPT_KERNEL_TIMING  2  /* 1: bracket every split-K kernel launch of
+                                      spkv_decode_attention with HIP events; like
+                                      SPKV_OPT_SPLIT_ONLY it has that call take the split-K
+                                      kernel also where the lists are so short that one launch
+                                      of another kernel does the whole call                */
 #define SPKV_OPT_SPLIT_ONLY     3  /* 1: spkv_decode_attention launches the split-K kernel
                                       only (no combine, `out` and `lse` left untouched):
                                       lets a harness time that kernel back to back        */

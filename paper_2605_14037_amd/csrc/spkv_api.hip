@@ -546,6 +546,8 @@ bool short_lists(const spkv_cache* c, hipStream_t s) {
     const bool even = n >= kShortEvenPairs && longest <= kShortEvenHps && 2 * longest * n <= 3 * sum;
     return (few || even) && !being_captured(s);
 }
+// spkv_decode_attention: what times or measures the split kernel alone is given that kernel.
+bool short_attention(const spkv_cache* c, hipStream_t s) { return !c->timing && !c->split_only && short_lists(c, s); }
 // The partition reported for such a call: one workgroup per pair.
 SpkvSplit short_split(const spkv_cache* c) {
     return SpkvSplit{1 << 16, 1, spkv_short_waves(c->cfg.head_dim), 0};
@@ -901,7 +903,7 @@ int spkv_decode_attention(spkv_cache_t* c, const void* q, void* out, float* lse,
         if (rc != SPKV_OK) return rc;
     }
     tighten_bound(c, s);
-    if (!c->timing && !c->split_only && short_lists(c, s)) {
+    if (short_attention(c, s)) {
         const SpkvStepIO io = {static_cast<uint16_t*>(out), lse, nullptr, nullptr, nullptr};
         c->split = short_split(c);
         return spkv_launch_decode_short(c->view, static_cast<const uint16_t*>(q), sm_scale, io, s) == hipSuccess
@@ -1400,7 +1402,7 @@ int spkv_cache_stats(spkv_cache_t* c, spkv_stats_t* st, int32_t* kept_len, void*
     st->pool_pages_total = c->carve.n_pages;
     st->arena_bytes = (int64_t)c->arena_bytes;
     st->device_error = err;
-    const SpkvSplit sp = short_lists(c, s) ? short_split(c) : choose_split(c);   // of the next decode call
+    const SpkvSplit sp = short_attention(c, s) ? short_split(c) : choose_split(c);   // of the next spkv_decode_attention
     int64_t n_items = 0;
     for (int p = 0; p < n_pairs; ++p) {
         const int Tw = std::min(c->T[p / Hkv], w);

@@ -5,6 +5,9 @@ import json
 import sys
 
 
+STATS_ITEMS = 100          # offset of n_work_items in spkv_stats_t: twelve 8-byte fields and device_error before it
+
+
 class Config(C.Structure):
     _fields_ = [("batch", C.c_int32), ("n_q_heads", C.c_int32), ("n_kv_heads", C.c_int32),
                 ("head_dim", C.c_int32), ("window", C.c_int32), ("page_tokens", C.c_int32),
@@ -79,7 +82,11 @@ def main():
         elif op == "logits":
             rc = lib.spkv_utility_logits(at, at, None, at, None, at, at, *a, None)
         elif op == "stats":
-            rc = lib.spkv_cache_stats(handle, C.create_string_buffer(4096), None, None)
+            buf = (C.c_byte * 4096)()
+            rc = lib.spkv_cache_stats(handle, buf, None, None)
+            items = C.c_int32.from_buffer(buf, STATS_ITEMS).value
+            calls.append([rc, [["items", items, 0, 0]] + taken()])
+            continue
         elif op == "reset":
             rc = lib.spkv_cache_reset(handle, None)
         elif op == "destroy":                             # last of a script

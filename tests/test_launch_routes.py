@@ -49,6 +49,19 @@ def test_captured_short_lists(cfg, kept, short, captured, call):
         assert got.rc == 0 and names[0].startswith("spkv_decode_short<") == want, names
 
 
+@pytest.mark.parametrize("option", [[2, 1], [3, 1]])
+def test_what_times_the_split_kernel_is_given_it(option):
+    """Timing and split-only take spkv_decode_attention to the split kernel on short lists too, and the work
+    items reported are of the kernel that the next such call takes."""
+    fill = [["append", [8192]], ["lengths", [300] * 8], ["stats"]]        # 10 half-pages and the window's 4
+    plain = record(dict(batch=1), fill + [["stats"], ["attend"], ["step"]])
+    other = record(dict(batch=1), fill + [["option"] + option, ["stats"], ["attend"], ["step"]])[1:]
+    assert plain[2].launches[0] == ("items", (8 * 8, 0), 0) and other[2].launches[0] == ("items", (8 * 14, 0), 0)
+    assert plain[3].launches[0][0].startswith("spkv_decode_short<")
+    assert [n for n, _, _ in other[3].launches if "event" not in n][0].startswith("spkv_decode_split<")
+    assert plain[4].launches == other[4].launches and plain[4].launches[0][0].startswith("spkv_decode_short<")
+
+
 # ------------------------------------------------------------------ gapless numbering
 @pytest.mark.parametrize("call", [["step"], ["attend"], ["static"], ["score", [4] * 16], ["predict", 4096, 256]])
 def test_unanswered_capture_query_leaves_no_error_behind(call):
