@@ -1123,6 +1123,9 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
                  float sm_scale, uint16_t* stage, int32_t* prefix, int shp, float* part,
                  size_t part_bytes, bool exact_fit, hipStream_t s) {
     const int B = c->cfg.batch;
+    // without staging rows, prefix counts or logits only what needs none of them
+    if ((stage == nullptr || prefix == nullptr || util_logits == nullptr) && !spkv_prefill_direct(c->view, n_max))
+        return SPKV_E_INVAL;
     if (util_logits != nullptr) {
         const int rc = reserve_capacity(c, cu_seqlens, s);
         if (rc != SPKV_OK) return rc;

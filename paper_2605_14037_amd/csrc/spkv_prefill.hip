@@ -1213,6 +1213,7 @@ static void launch_attend(const SpkvView& v, const uint16_t* q, uint16_t* out, f
         spkv_prefill_attend<D, 2, 1, DIRECT><<<grid, dim3(128), 0, s>>>(v, q, out, lse, sl, pf, cu, k, vv);
 }
 
+static_assert(SPKV_MAX_CHUNK_TOKENS <= kFewTokens, "spkv_decode_chunk and spkv_score_chunk have no staging rows");
 bool spkv_prefill_direct(const SpkvView& v, int n_max) {
     return n_max <= kFewTokens && n_max <= v.w && prefill_shape(v.G, n_max).nw != 8;
 }

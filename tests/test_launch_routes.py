@@ -216,6 +216,20 @@ def test_chunks_are_two_launches(tokens, attend, merge):
     assert [n for n, _, _ in few] == ["spkv_append_few<128>"]
 
 
+@pytest.mark.parametrize("group", [1, 2, 3, 5, 8, 16])
+def test_every_chunk_length_needs_no_staging_rows(group):
+    """spkv_decode_chunk and spkv_score_chunk bring none: all that they accept is attended before its append."""
+    cfg = dict(batch=2, n_q_heads=group, n_kv_heads=1, head_dim=64, window=16)
+    counts = [n for n in range(1, 18) if n <= 16 and n * group <= 64]
+    script = [[op, [n, 0]] for n in counts for op in ("score", "chunk")]
+    for (_, (n, _)), got in zip(script, record(cfg, [["append", [900, 900]], ["stats"]] + script)[2:]):
+        names = [x for x, _, _ in got.launches if "copy" not in x]
+        assert got.rc == 0 and names[0].startswith("spkv_prefill_attend<64," if n * group > 16 else "spkv_chunk_split<64")
+        assert n * group <= 16 or names[0].endswith(", 1>"), names
+        assert not [x for x in names if "stage" in x or "bulk" in x]
+    assert record(cfg, [["score", [17, 0]]])[0].rc != 0
+
+
 @pytest.mark.parametrize("call", [["chunk", [16] * 16], ["chunk", [4] * 16], ["step"], ["attend"], ["prefill", [16] * 16]])
 def test_lengths_on_their_way_are_not_asked_for_by_event(call):
     """A query of an event is refused while a stream of the process is being captured (error 907) and
