@@ -1157,9 +1157,10 @@ int prefill_core(spkv_cache_t* c, const void* k, const void* v, const float* uti
     // last piece whole 35, in 2 ranges 28 and the merge 11.
     if (!short_chunk && spans * ks > kPrefillResident8 && tiles / ks < 24) ks = std::max(1, kPrefillResident8 / spans);
     if (!short_chunk && tiles * (ks - 1) < 40 * ks) ks = 1;
-    // exactly what this call writes must fit
+    // exactly what this call writes must fit (spans in order are no reason to refuse: counted without the
+    // order, by n_max alone, they are too many to be cut into ranges)
     while (spkv_prefill_partial_bytes(spans, ks, sh, c->cfg.head_dim) > part_bytes) {
-        if (exact_fit) return SPKV_E_INVAL;
+        if (exact_fit && !ordered) return SPKV_E_INVAL;
         ks -= 1;                    // ks = 1 writes no partials
     }
     int slots = 0;

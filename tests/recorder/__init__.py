@@ -4,7 +4,7 @@ process of its own against hip_recorder.cpp, a HIP runtime that writes launches 
     calls = record(dict(batch=16, ...), [["append", [4096] * 16], ["lengths", [700] * 128], ["step"]])
     calls[-1].rc, calls[-1].launches      # [("spkv_decode_split<128, 1, 1>", (grid x, grid y), block), ...]
 
-Script entries: ["append" | "chunk" | "score" | "prefill", tokens per sequence], ["step"], ["attend"],
+Script entries: ["append" | "chunk" | "score" | "prefill", tokens per sequence] (prefill: and the workspace's bytes), ["step"], ["attend"],
 ["static"], ["predict", d_model, d_hidden], ["stats"], ["reset"], ["logits", tokens, d_model, d_hidden, heads],
 ["soft", tokens per sequence], ["advance", n], ["option", id, value], ["destroy"] (last; "stats" has an
 entry ("items", (n_work_items, 0), 0)); and what the runtime answers from

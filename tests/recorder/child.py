@@ -73,7 +73,7 @@ def main():
         elif op == "score":
             rc = lib.spkv_score_chunk(handle, at, at, at, cu(a[0]), at, None, zero, None)
         elif op == "prefill":
-            ws = lib.spkv_prefill_workspace_bytes(handle, max(a[0]), C.c_int64(sum(a[0])))
+            ws = a[1] if len(a) > 1 else lib.spkv_prefill_workspace_bytes(handle, max(a[0]), C.c_int64(sum(a[0])))
             rc = lib.spkv_prefill_attention(handle, at, at, at, at, cu(a[0]), at, None, zero, at, C.c_size_t(ws), None)
         elif op == "soft":
             ws = lib.spkv_soft_gated_workspace_bytes(cfg.batch, cfg.n_kv_heads, cfg.head_dim, cfg.window, max(a[0]))

@@ -243,6 +243,18 @@ def test_lengths_on_their_way_are_not_asked_for_by_event(call):
         assert got[3].rc == 0 and not [n for n, _, _ in got[3].launches if n == "event_query"]
 
 
+def test_ordered_spans_need_no_room_for_ranges():
+    """A ragged call whose longest piece alone counts too many spans to be cut took a workspace of staging rows
+    and prefix counts; the spans that hold a token are fewer, and are cut where there is room."""
+    counts, at_ks = [1024, 10, 10, 10], 52
+    rows = -(-sum(counts) * 8 * 4 // 256) * 256 + 32 * -(-(128 + 1024) // 32) * 32 * 128 * 4
+    fill = [["append", [30000] * 4], ["lengths", [6000] * 32], ["stats"], ["watch", "spkv_prefill_attend32", 5, at_ks]]
+    for more, ks in (([], 2), ([rows], 1)):
+        got = record(dict(batch=4), fill + [["prefill", counts] + more])[-1]
+        assert got.rc == 0 and [x for n, (x, _), _ in got.launches if n == "watched"] == [ks]
+    assert record(dict(batch=4), fill + [["prefill", counts, rows - 256]])[-1].rc != 0
+
+
 @pytest.mark.parametrize("batch,tokens,pairs_grid", [(8, 2000, 64 * 8), (1, 500, 8 * 4), (64, 4000, 512)])
 def test_short_chunk_right_after_a_prompt(batch, tokens, pairs_grid):
     """The bound alone (nothing copied yet) takes the equal ranges for long lists only."""
