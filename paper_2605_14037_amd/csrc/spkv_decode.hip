@@ -735,7 +735,7 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
 // Up to 16 new tokens per sequence attend in one pass (speculative-decoding verification,
 // prompt feed in short chunks) if they fit the 16 MFMA columns: (token i, head g) pairs, col =
 // i G + g, so every K/V tile is still read once per (sequence, KV head).  (Wider chunks:
-// spkv_prefill_attend_direct.)
+// spkv_prefill_attend<..., DIRECT>; NQ, the groups of 16 columns, is 1.)
 // The cache is in the state before the chunk's append.  Long-term keys are available to
 // every token of the chunk (they are at least w + 1 positions behind).  A ring key of age
 // a (0 = oldest, position T - w) is inside the window of chunk token i iff a > i (the window

@@ -160,28 +160,12 @@ __device__ __forceinline__ void load_row_to_lds(const char* base, unsigned voff,
                  : "m0");
 }
 
-__device__ __forceinline__ void load_row_to_lds_once(const char* base, unsigned voff, unsigned lds_row) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-                 :
-                 : "v"(voff), "s"(base), "s"(lds_row)
-                 : "m0");
-}
-
 // Waits until at most N of this wave's vector memory loads are still in flight (they
 // complete in the order issued).
 template <int N>
 __device__ __forceinline__ void wait_loads_but() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N));
 }
-
-// The same where no barrier follows (LDS that only this wave copies to and reads): nor may the
-// compiler move a read of LDS across it.
-template <int N>
-__device__ __forceinline__ void wait_copies_but() {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-// Every LDS read of this wave has returned (before a copy may overwrite what it read).
-__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
 
 // ------------------------------------------------------------------ utility predictor
 // Hidden layer of the predictor (Eq. 1) for 16 hidden units x 16 tokens over kq (a multiple

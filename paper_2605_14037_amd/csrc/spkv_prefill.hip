@@ -1162,7 +1162,6 @@ bool spkv_prefill_ordered(const SpkvView& v, int n_max, bool from_empty) {
            !(from_empty && n_max <= 4096 && v.n_pairs % 8 == 0) && spkv_append_copies_lengths(v, n_max);
 }
 static void order_params(const SpkvView& v, const SpkvCu& cu, int n_max, SpkvPrefill& pf) {
-    const int span = pf.nw * pf.tb;
     pf.order = v.bulk_info + kSpanOrderAt;
     pf.spans = spkv_prefill_spans(v, cu, n_max, true);
     pf.pin_xcd = 0;

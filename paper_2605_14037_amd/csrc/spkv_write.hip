@@ -569,24 +569,6 @@ __device__ __forceinline__ void store_ring_unit(const SpkvView& v, const RingUni
     }
 }
 
-// Stage 3: per (kScatterSegs segments = 512 tokens, pair).  Thread i owns token j0 + i: gate flag,
-// rank (mbcnt inside the wave + the popcounts of the lower waves + the offset from stage 2); the
-// kept tokens' indices are compacted into LDS and their rows moved in groups of eight consecutive
-// destination rows (whole 16-byte V units, transposed through LDS), two groups per wave at a
-// time so that all their loads are in flight together; rows before the first and after the
-// last whole group go one by one, their V elements as 2-byte stores.  The last workgroup of a
-// pair (ring_here) moves the kept rows that leave the ring in the
-// same way and then writes the last min(n, w) tokens of the call into the ring, two units' loads
-// at a time; without it (ring_in_one_workgroup) workgroups of their own write the slots, eight per
-// wave, and stage 2 has moved the rows.  The first workgroup sends the lengths, which stage 2 has
-// settled, to the host (`to`) before its own work: the host has them while this launch runs and need
-// not wait for the stream to know what the next call may take.
-// cut.tokens > 0: one row of workgroups more, of which the first leaves the order of the attention's spans.
-// Bound by the requests in flight of a few dependent rounds (logits, rows, stores) more than by
-// bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
-// written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
-// pairs; 46 us now with the leaving ring rows, whose move took 7 of the 18 us of stage 2.
-// 256 tokens per workgroup 52 us, 1024 tokens 49.
 // One wave, a lane per pair: its group, rank by length in the group, and the spans of the group before it.
 // The heads of a sequence are dealt to the groups by length, back and forth.
 __device__ __forceinline__ void order_spans(const SpkvView& v, const SpkvCu& cu, SpanCut cut) {
@@ -613,6 +595,24 @@ __device__ __forceinline__ void order_spans(const SpkvView& v, const SpkvCu& cu,
             SpanOrder{before, p | group << 16};
 }
 
+// Stage 3: per (kScatterSegs segments = 512 tokens, pair).  Thread i owns token j0 + i: gate flag,
+// rank (mbcnt inside the wave + the popcounts of the lower waves + the offset from stage 2); the
+// kept tokens' indices are compacted into LDS and their rows moved in groups of eight consecutive
+// destination rows (whole 16-byte V units, transposed through LDS), two groups per wave at a
+// time so that all their loads are in flight together; rows before the first and after the
+// last whole group go one by one, their V elements as 2-byte stores.  The last workgroup of a
+// pair (ring_here) moves the kept rows that leave the ring in the
+// same way and then writes the last min(n, w) tokens of the call into the ring, two units' loads
+// at a time; without it (ring_in_one_workgroup) workgroups of their own write the slots, eight per
+// wave, and stage 2 has moved the rows.  The first workgroup sends the lengths, which stage 2 has
+// settled, to the host (`to`) before its own work: the host has them while this launch runs and need
+// not wait for the stream to know what the next call may take.
+// cut.tokens > 0: one row of workgroups more, of which the first leaves the order of the attention's spans.
+// Bound by the requests in flight of a few dependent rounds (logits, rows, stores) more than by
+// bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
+// written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
+// pairs; 46 us now with the leaving ring rows, whose move took 7 of the 18 us of stage 2.
+// 256 tokens per workgroup 52 us, 1024 tokens 49.
 constexpr int kScatterSegs = 2, kScatterThreads = kScatterSegs * kSegTokens;
 
 template <int D>
