@@ -1082,9 +1082,9 @@ int prefill_split_cap(int spans, int nw) {
 // range, twice where the ranges do not fit the chip at once, and merge ks partial results; the equal
 // ranges cost every workgroup the search for its own (about five tiles) and are merged up to 64 per
 // pair.  ks ranges / equal ones, us per call of 16 tokens: heads of unlike lists, 16 sequences of 32k
-// 139 / 117, 4 of 128k 70 / 65, 40 of 2k-20k with dense and local-only heads 243 / 190; like or short
-// ones, 64 of 4k-8k with 2 heads of 64 36 / 39, one of 10k 29 / 33, one of 100k 44 / 48, 48 of 2k-4k
-// with 2 heads of 64 31 / 34, 16 of 250-500 36 / 39.  Before the lengths are known (after a prompt,
+// 109 / 101, 4 of 128k 56 / 54, 40 of 2k-20k with dense and local-only heads 257 / 159; like or short
+// ones, 64 of 4k-8k with 2 heads of 64 26 / 28, one of 10k 20 / 23, one of 100k 38 / 40, 48 of 2k-4k
+// with 2 heads of 64 19 / 23, 16 of 250-500 24 / 28.  Before the lengths are known (after a prompt,
 // until a copy of them has arrived) the bound says nothing about how unlike they are: equal
 // ranges only where it is far above what the search costs.
 bool ranges_over_all_pairs(int ks, int pairs, int slots, int64_t longest, int64_t all, bool known) {
@@ -1207,8 +1207,8 @@ int spkv_prefill_attention(spkv_cache_t* c, const void* k, const void* v, const 
         return spkv_decode_step(c, k, v, util_logits, q, out, lse, sm_scale, stream);
     // The shortest chunks go to the multi-token step: with one group of 16 query columns its
     // one-wave items read the lists at the decode step's rate, and it needs fewer launches
-    // (measured on 16 sequences of 32k tokens: 2 / 4 tokens there 94 / 97 us, 5 / 8 tokens here
-    // 113; on 4 sequences of 128k 51 / 52 there, 69 here).
+    // (2 and 4 tokens, there / here, us a call: 16 sequences of 32k 89 / 92, 91 / 92, 4 of 128k 45 / 48, 47 / 49,
+    // one of 8k 14 / 19, 15 / 18, 40 of 2k-20k with dense and local-only heads 124 / 151, 126 / 153).
     if (n_max <= SPKV_MAX_CHUNK_TOKENS && n_max <= c->cfg.window && n_max * c->carve.G <= 16)
         return spkv_decode_chunk(c, k, v, util_logits, q, cu_seqlens, out, lse, sm_scale, stream);
     if (k == nullptr || v == nullptr || util_logits == nullptr || q == nullptr || out == nullptr ||

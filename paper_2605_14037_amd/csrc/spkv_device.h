@@ -108,8 +108,8 @@ __device__ __forceinline__ int batch_page(const SpkvView& v, const PageBatch& pb
 // The half-page in which a list ends is read whole: its keys past the end are masked, but a weight of
 // zero would still turn an infinite value into a NaN.  Whoever lengthens a list from `from` to `to`
 // entries therefore clears the values behind its end if this call began that half-page (page: the one it
-// lies in) -- bytes that no row of the call touches, so in any order with the rows.  Pages then need no
-// clearing when they are handed out again, whatever they held.  nt threads, this one tid.
+// lies in) -- bytes that no row of the call touches, so in any order with the rows -- and a prune those behind
+// its new end.  Pages then need no clearing when they are handed out again, whatever they held.  nt threads, this one tid.
 __device__ __forceinline__ bool ends_in_new_half_page(int from, int to) {
     return to > from && (to & (kHalfTokens - 1)) != 0 && (to & ~(kHalfTokens - 1)) >= from;
 }

@@ -24,11 +24,12 @@ constexpr int kCompactPairs = 1024;   // most (sequence, head) pairs the gapless
 
 // A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)
 // do not survive in it from one layer's call to its next, and loads that allocate nothing there
-// are then ahead (16 tokens: 16 sequences of 32k, 460 MB, 132 -> 118 us; 4 of 128k, 190 MB,
-// 76 -> 73; 40 of 2k-20k 207 -> 191; 48 of 2k-4k, 155 MB, 80 -> 77); shorter lists may, and are read
-// as usual (12 of 20k-30k with head_dim 64, 50 MB: 43 against 45 us; one of 100k, 80 MB: 48 against
-// 51).  By the lengths, not by the host's bound, which counts a whole prompt as kept: on the device
-// where it adds the lengths up anyway, on the host once a copy of them has arrived.
+// are then ahead; shorter lists may, and are read as usual.  16 tokens, one cache called again and again,
+// past the caches / as usual, us: 16 sequences of 32k, 460 MB, 101 / 111; of 8k, 115 MB, 45 / 42.5; of 4k 36 / 32.5.
+// (Between half and all of that cache a lone cache does survive: 4 of 128k, 190 MB, 54 / 52, 16 of 10k, 145 MB,
+// 50 / 47; the line is drawn for one among others.)  By the lengths, not by the host's bound, which counts a
+// whole prompt as kept: on the device where it adds the lengths up anyway, on the host once a copy of them
+// has arrived.
 constexpr int64_t kOnceBytes = (int64_t)128 << 20;
 
 // Device-side view of one cache: plain pointers into the caller's arena.

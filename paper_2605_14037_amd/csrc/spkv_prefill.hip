@@ -200,8 +200,8 @@ __device__ __forceinline__ void rescale_columns(const float (&x)[NQ][8], float s
 // down to slots - pairs; the last one always fits), at least kRangeMinTiles.  Every wave works it out
 // from the lengths: a handful of loads per lane, nine wave sums and a prefix sum, 3 to 4 us.  Equal
 // pairs are cut alike.  512 slots are one round of two workgroups per compute unit (16 tokens, per
-// call: 16 sequences of 32k 118 us, 40 of 2k-20k with dense and local-only heads 191); 640 take 145
-// and 227.  Ranges below eight tiles cost more to merge than they hide.
+// call: 16 sequences of 32k 101 us, 40 of 2k-20k with dense and local-only heads 159); 640 take 124
+// and 187.  Ranges below eight tiles cost more to merge than they hide.
 constexpr int kRangePairsPerLane = 6, kRangeSlots = 512, kRangeMinTiles = 8, kRangeCap = 64;
 // Range `id` of all pairs' ranges in order: its pair, the id of the pair's first range and the
 // pair's number of ranges; false past the last one.  all: the tiles of all pairs.
@@ -283,7 +283,8 @@ __device__ __forceinline__ bool locate_range(const SpkvView& v, const SpkvCu& cu
 // for all if it passes the gate -- and, for the last range of a pair, the chunk's own rows, which its waves
 // lay out in LDS themselves.  16 tokens, 16 sequences of 32k: stage 11, append 7.5, attention 95.6
 // and merge 7.5 us as four launches; attention 93.6 and merge with the append beside it 9.1 as two
-// (118 -> 100 us a call; one of 4 x 2k 31 -> 19.5).  What is left is the read at 5 TB/s: ranges up to a
+// (118 -> 101 us a call; one of 4 x 2k 31 -> 19.5).  The gates of the ring tiles are looked up once, before the
+// loop: left to the tiles, each waited for its own (windows of 2048 / 4096, 104 / 145 us; 81 / 100 so).  What is left is the read at 5 TB/s: ranges up to a
 // tenth longer than their mean (a pair has a whole number of them), about 4 us of search.  Tried and
 // slower: tiles in registers, a wave per 32 columns and tile (115 us: two waves load a tile, half the
 // bytes in flight); a ring of LDS per wave, all columns in one wave, no barrier (102 us, and 8 us more
@@ -1152,9 +1153,11 @@ SpkvPrefillShape spkv_prefill_shape(int group, int n_max) { return prefill_shape
 // fetched into few L2s and neighbours find their windows there: all pairs on all XCDs took 2409
 // (four) and 4825 us (eight), 112 against 105 ms for four of 128k; neighbours on different XCDs
 // 2332 (four), but one whole prompt of 16k 700 instead of 728.
-// Not where the spans run in one round, which the order cannot even out, nor for pieces that begin
-// prompts (no list yet), whose spans differ by their own place more than by their pair's list: 4096
-// tokens of one sequence 72 / 78.
+// Not where the spans run in one round, which the order cannot even out, nor for pieces of up to 4096 tokens
+// that begin prompts (no list yet), whose spans differ by their own place more than by their pair's list:
+// us a call, one sequence of 2100 66 / 67, 4096 106 / 106; two of 1100 62 / 65, 2048 81 / 83, 4096 163 / 152; four of
+// 600 61 / 63, 4096 288 / 279; eight of 300 57 / 61, 2048 232 / 240, 4096 537 / 536.  Longer ones gain as others
+// do: one of 4500 123 / 108, 12 000 437 / 353, two of 5000 222 / 195, eight of 6000 870 / 873.
 bool spkv_prefill_ordered(const SpkvView& v, int n_max, bool from_empty) {
     const SpkvPrefillShape sh = prefill_shape(v.G, n_max);
     const int spans = v.n_pairs * ((n_max + sh.nw * sh.tb - 1) / (sh.nw * sh.tb));
