@@ -138,7 +138,8 @@ size_t spkv_cache_required_bytes(const spkv_config_t* cfg);
 int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_bytes,
                       void* stream, spkv_cache_t** out);
 
-/* Free the host object.  Synchronises nothing; the caller frees the arena afterwards. */
+/* Free the host object.  Waits only for what earlier calls still have to write into its pinned
+ * memory (the lengths they send); the caller frees the arena afterwards. */
 int spkv_cache_destroy(spkv_cache_t* cache);
 
 /* Capacity growth ("Inference Kernels" appendix: the cache is given headroom and grows when
