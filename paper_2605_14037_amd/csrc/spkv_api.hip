@@ -394,7 +394,7 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
     sp.hp_per_item = (int32_t)per;
     sp.slots = (int32_t)((max_hp + per * mw - 1) / (per * mw)) | 1;   // odd: see spkv_decode_split
     sp.mw = mw;
-    sp.compact = 0;
+    sp.compact = sp.runs = 0;
     if (n_items != nullptr) {
         *n_items = 0;
         for (int p = 0; p < n_pairs; ++p)
@@ -468,11 +468,64 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
     return n * 128 <= kGapFewChunkPairs * c->cfg.head_dim || sum >= (int64_t)items * kGapChunkItemHps ||
            2 * longest * n >= sum * (c->cfg.head_dim == 128 ? 3 : 4);
 }
+// Large caches in equal shares (spkv_decode_shares): two runs per compute unit, one where few pairs would have
+// many partial results each to merge.  From which size on, by what a wave with two half-pages in registers
+// costs at its start against what equal shares save; D = 64 has half the bytes to a half-page and the same
+// arithmetic.  Step replayed from a graph, items / shares, us: 8 heads of 128, 32 pairs of 18 MB 9.9 / 10.2, 26 MB
+// 11.3 / 10.3, 67 MB 16.6 / 15.6, 192 MB 38.0 / 33.1; 128 pairs of 49 MB 15.9 / 14.3, 266 MB 49.4 / 45.7; 512 pairs of
+// 193 MB 44.3 / 41.5, 988 MB 191 / 160; 8 pairs of 44 MB 13.6 / 14.4, 156 MB 31.4 / 29.8 (30.9 with two runs per
+// compute unit); head_dim 64: 128 pairs of 53 MB 14.6 / 16.3, 133 MB 27.6 / 27.4, 256 pairs of 265 MB 49.0 / 47.1, 105 MB
+// 24.0 / 24.4.  The multi-token step, whose partial results are four times as long, gains earlier: 4 drafts, 32
+// pairs of 26 MB 17.9 / 15.9, 67 MB 26.3 / 21.3, 256 pairs of 98 MB 37.4 / 28.8, 8 pairs of 18 MB 15.3 / 15.6; head_dim 64,
+// 128 pairs of 133 MB 36.5 / 32.3.  (Uneven lists too: 512 pairs, a quarter dense, a quarter local, 3.0 GB 468 / 455.)
+// Not where two sequences have the same lengths throughout: an item's place in its pair depends on the pair's
+// length and the call, a run's on the pairs before it as well, and copies of a sequence are given the same bits.
+constexpr int kShareFewPairs = 8;
+constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)96 << 20, kShareBytes64 = (int64_t)160 << 20;
+constexpr int64_t kShareBytesChunk = (int64_t)20 << 20, kShareBytesChunk64 = (int64_t)100 << 20;
+SpkvSplit share_split(const spkv_cache* c) {
+    const int n = c->carve.n_pairs, cus = c->compact_items / kCompactItemsPerCu;
+    const int runs = cus * (n <= kShareFewPairs && c->cfg.head_dim == 128 ? 1 : 2);
+    return SpkvSplit{1, runs + n, 1, 0, runs};
+}
+// Do two sequences have the same lengths in every head?  (Copies of a sequence do.)  Those of one half-page
+// a head do not count: it is never cut.
+bool sequences_alike(const spkv_cache* c) {
+    const int B = c->cfg.batch, Hkv = c->cfg.n_kv_heads;
+    std::vector<uint64_t> seen;
+    seen.reserve(B);
+    for (int b = 0; b < B; ++b) {
+        uint64_t x = (uint64_t)c->T[b] * 0x9e3779b97f4a7c15ull;
+        bool any = std::min(c->T[b], c->cfg.window) > kHalfTokens;
+        for (int h = 0; h < Hkv; ++h) {
+            const int32_t L = c->L_ub[b * Hkv + h];
+            x = (x ^ (uint32_t)L) * 0xff51afd7ed558ccdull;
+            x ^= x >> 32;
+            any = any || L > 0;
+        }
+        if (any) seen.push_back(x);
+    }
+    std::sort(seen.begin(), seen.end());
+    return std::adjacent_find(seen.begin(), seen.end()) != seen.end();
+}
+bool worth_shares(const spkv_cache* c, int64_t slots_total_cap, bool chunk) {
+    const int n = c->carve.n_pairs, D = c->cfg.head_dim;
+    if (n > kSharePairs || share_split(c).slots > slots_total_cap) return false;
+    int64_t hps = 0;
+    for (int p = 0; p < n; ++p) {
+        const int Tw = std::min(c->T[p / c->cfg.n_kv_heads], c->cfg.window);
+        hps += (c->L_ub[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
+    }
+    const int64_t least = D == 64 ? (chunk ? kShareBytesChunk64 : kShareBytes64)
+                                  : chunk ? kShareBytesChunk : n <= kShareFewPairs ? kShareBytesFewPairs : kShareBytes;
+    return hps * (kHalfTokens * 4 * D) >= least && !sequences_alike(c);
+}
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     int64_t items_one = 0;
     const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
     if (c->merge_waves == 1) return one;
+    if (c->item_target <= 0 && c->step_launches != 1 && worth_shares(c, slots_total_cap, false)) return share_split(c);
     if (c->carve.n_pairs <= kMergePairs) {
         for (int mw = 4; mw > 1; mw >>= 1) {
             int64_t items = 0;
@@ -486,6 +539,11 @@ SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_t
     SpkvSplit sp = choose_split_mw(c, c->compact_items, slots_total_cap, 1, &items_one);
     sp.compact = (int32_t)std::max<int64_t>(1, items_one);
     return sp;
+}
+
+// Slots of partial results that a launch may write.
+int64_t partial_slots(const spkv_cache* c, const SpkvSplit& sp) {
+    return sp.runs > 0 ? sp.slots : (int64_t)c->carve.n_pairs * sp.slots;
 }
 
 // A captured launch is replayed while the lists grow: until every pair has gained a whole item,
@@ -550,7 +608,7 @@ bool short_lists(const spkv_cache* c, hipStream_t s) {
 bool short_attention(const spkv_cache* c, hipStream_t s) { return !c->timing && !c->split_only && short_lists(c, s); }
 // The partition reported for such a call: one workgroup per pair.
 SpkvSplit short_split(const spkv_cache* c) {
-    return SpkvSplit{1 << 16, 1, spkv_short_waves(c->cfg.head_dim), 0};
+    return SpkvSplit{1 << 16, 1, spkv_short_waves(c->cfg.head_dim), 0, 0};
 }
 
 // Tokens sequence b receives in a call: from cu_seqlens, or one each (cu == nullptr).
@@ -662,7 +720,7 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
         c->compact_items = kCompactItemsPerCu * (cus > 0 ? cus : 256);
         c->chunk_round_items = 0;
     }
-    c->split = SpkvSplit{1, 1, 1, 0};
+    c->split = SpkvSplit{1, 1, 1, 0, 0};
     c->timing = false;
     c->split_only = false;
     c->n_timed = 0;
@@ -962,7 +1020,7 @@ int spkv_decode_attention_static(spkv_cache_t* c, const void* q, void* out, floa
     }
     c->split = choose_split(c, c->one_round_items, cap);
     room_to_grow(c, static_cast<hipStream_t>(stream));
-    if ((int64_t)c->carve.n_pairs * c->split.slots > cap) return SPKV_E_CAPACITY;
+    if (partial_slots(c, c->split) > cap) return SPKV_E_CAPACITY;
     if (spkv_launch_decode(v, static_cast<const uint16_t*>(q), static_cast<uint16_t*>(out), lse,
                            sm_scale, c->split, false, false, nullptr, nullptr,
                            static_cast<hipStream_t>(stream)) != hipSuccess)
@@ -1044,13 +1102,17 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
     const bool compact = c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
     int64_t items = 0;
-    c->split = choose_split_mw(c, compact ? chunk_items : c->chunk_round_items, slot_cap, 1, &items);
-    if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
+    if (c->item_target <= 0 && worth_shares(c, slot_cap, true)) {
+        c->split = share_split(c);
+    } else {
+        c->split = choose_split_mw(c, compact ? chunk_items : c->chunk_round_items, slot_cap, 1, &items);
+        if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
+    }
     room_to_grow(c, s);
 
     // every slot the launch may write must lie inside the partial buffers (they are sized
     // for this at create; checked again here because an overrun would be a wild device write)
-    if ((int64_t)c->carve.n_pairs * c->split.slots * 16 > (int64_t)c->carve.max_items * G)
+    if (partial_slots(c, c->split) * 16 > (int64_t)c->carve.max_items * G)
         return SPKV_E_CAPACITY;
 
     SpkvCu cu;
@@ -1406,26 +1468,18 @@ int spkv_cache_stats(spkv_cache_t* c, spkv_stats_t* st, int32_t* kept_len, void*
     st->pool_pages_total = c->carve.n_pages;
     st->arena_bytes = (int64_t)c->arena_bytes;
     st->device_error = err;
-    const SpkvSplit sp = short_attention(c, s) ? short_split(c) : choose_split(c);   // of the next spkv_decode_attention
-    int64_t n_items = 0;
-    for (int p = 0; p < n_pairs; ++p) {
-        const int Tw = std::min(c->T[p / Hkv], w);
-        const int64_t hp = (len[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
-        const int64_t per = (int64_t)sp.hp_per_item * sp.mw;
-        n_items += std::min<int64_t>(std::min<int64_t>((hp + per - 1) / per, sp.slots) * sp.mw, hp);
-    }
-    st->n_work_items = (int32_t)n_items;
-    {   // the same count under the partition the most recent decode call actually used
-        const SpkvSplit lp = c->split;
-        int64_t n_last = 0;
+    auto work_items = [&](const SpkvSplit& sp) -> int32_t {
+        int64_t n = 0;
         for (int p = 0; p < n_pairs; ++p) {
             const int Tw = std::min(c->T[p / Hkv], w);
             const int64_t hp = (len[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
-            const int64_t per = (int64_t)lp.hp_per_item * lp.mw;
-            n_last += std::min<int64_t>(std::min<int64_t>((hp + per - 1) / per, lp.slots) * lp.mw, hp);
+            const int64_t per = (int64_t)sp.hp_per_item * sp.mw;
+            n += sp.runs > 0 ? hp : std::min<int64_t>(std::min<int64_t>((hp + per - 1) / per, sp.slots) * sp.mw, hp);
         }
-        st->n_work_items_last_call = (int32_t)n_last;
-    }
+        return (int32_t)(sp.runs > 0 ? std::min<int64_t>(n, sp.runs) : n);
+    };
+    st->n_work_items = work_items(short_attention(c, s) ? short_split(c) : choose_split(c));   // of the next spkv_decode_attention
+    st->n_work_items_last_call = work_items(c->split);             // of the most recent decode call
     if (kept_len != nullptr) std::memcpy(kept_len, len.data(), (size_t)n_pairs * 4);
     return err ? SPKV_E_DEVICE : SPKV_OK;
 }

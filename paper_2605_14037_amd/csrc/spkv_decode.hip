@@ -1,7 +1,8 @@
 // Read path of the SP-KV cache on gfx950 (MI355X, wave64, MFMA):
 //   spkv_decode_split    split-K flash decoding, one wave per work item, K/V tiles consumed
 //                        as MFMA operands straight from the page layout
-//                        (.._split_compact: the same items, workgroups numbered without gaps)
+//                        (.._split_compact: the same items, workgroups numbered without gaps;
+//                        spkv_decode_shares: large caches in equal shares)
 //   spkv_decode_combine  log-sum-exp merge of the partials
 //   fused step           spkv_decode_split<.., true> + spkv_combine_append: append and decode
 //                        of one token per sequence in two launches instead of three; with
@@ -398,7 +399,7 @@ __device__ __forceinline__ void decode_split_item(const SpkvView& v, const uint1
 // 4 sequences of 128k with about 150 partials per pair: 1.1 us less per step; with 39 per
 // pair, 0.5 us more; with 512 merge workgroups, 3 us more).
 static bool wide_merge(const SpkvView& v, const SpkvSplit& sp) {
-    return sp.slots > 64 && v.n_pairs * v.G <= 256;
+    return (sp.runs > 0 ? sp.runs / v.n_pairs : sp.slots) > 64 && v.n_pairs * v.G <= 256;
 }
 
 template <int D, int MODE, int MW>
@@ -476,6 +477,290 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
     decode_split_compact<D, FUSED>(v, q, scale_log2e, sp, blockIdx.x, gridDim.x);
 }
 
+// ------------------------------------------------------------------ equal shares
+// Large caches (host: worth_shares): the half-pages of all pairs, in order, are cut into SpkvSplit.runs equal
+// runs, one per one-wave workgroup.  A run may begin in one pair and end in another and leaves a partial result
+// in each; run i and pair p share partial slot i + p (no two overlaps have the same sum).  Every wave finds its
+// run from the exact lengths, so the runs stay equal in a graph replayed on growing lists; one workgroup more
+// leaves the merge every pair's slots.
+// What bounds a step of this size is the rate of one compute unit, which little keeps up: a wave with one
+// half-page in work and the next in flight.  More waves queue up behind each other, leave more to merge, and
+// any that one compute unit has more than another work on alone at the end (hence whole multiples of the compute
+// units, and no rounding to whole items per pair).  The loads behind a run's end are issued against a buffer of no
+// bytes, so that what a half-page waits for is a constant number of loads in flight.
+// 16 sequences of 32k, 484 MB, us a step: 82.3 as items of one pair each (2880 waves), 78.0 with 512 runs, 78.2
+// with 256, 79.3 with 768, 80.3 with 1024, 81.9 with 640; three half-pages in registers 79.2.  A plain read
+// of the same bytes takes 71 with 1792 workgroups, 72.7 with 2880.
+constexpr int kPairUnits = 1;    // a pair's units: its half-pages and one for what beginning it costs
+__device__ __forceinline__ int list_half_pages(int n) { return (n + kHalfTokens - 1) >> 5; }
+// Sum over the lanes up to and including this one.
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return x;
+}
+struct RunStart {
+    int pair, L, T, hp, left;            // first half-page, its pair and lengths; units from there on
+};
+// All lengths in one round of loads, four pairs a lane.  run = n_runs: the workgroup of the merge's table, first
+// slot | number of partial results << 16 of every pair.  False: no half-page for this workgroup.
+// counts(pair): does the pair take part?
+template <class Counts>
+__device__ __forceinline__ bool find_run(const SpkvView& v, int run, int n_runs, RunStart& r, Counts counts) {
+    constexpr int kChunks = kSharePairs / 256;
+    const int lane = threadIdx.x & 63, last4 = (v.n_pairs - 1) & ~3;     // (both arrays are padded to 256 bytes)
+    int4 L[kChunks], T[kChunks];
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+        if (c * 256 < v.n_pairs) {
+            const int p = min(c * 256 + lane * 4, last4);
+            L[c] = *reinterpret_cast<const int4*>(v.kept_len + p);
+            T[c] = *reinterpret_cast<const int4*>(v.t_pair + p);
+        }
+    }
+    auto units = [&](int p, int l, int t) -> int {
+        const int n = p < v.n_pairs && counts(p) ? list_half_pages(l) + list_half_pages(min(t, v.w)) : 0;
+        return n > 0 ? n + kPairUnits : 0;
+    };
+    int n[kChunks][4], before[kChunks], total = 0;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+        if (c * 256 < v.n_pairs) {
+            const int p = c * 256 + lane * 4;
+            n[c][0] = units(p, L[c].x, T[c].x);
+            n[c][1] = units(p + 1, L[c].y, T[c].y);
+            n[c][2] = units(p + 2, L[c].z, T[c].z);
+            n[c][3] = units(p + 3, L[c].w, T[c].w);
+            const int sum = n[c][0] + n[c][1] + n[c][2] + n[c][3], incl = wave_scan(sum);
+            before[c] = total + incl - sum;
+            total += __builtin_amdgcn_readlane(incl, 63);
+        }
+    }
+    // run i begins at unit i * share + min(i, more)
+    const int share = total / n_runs, more = total - share * n_runs;
+    if (run == n_runs) {
+        const int longer = more * (share + 1);
+        auto run_of = [&](int x) -> int { return x < longer ? x / (share + 1) : more + (x - longer) / share; };
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) {
+            if (c * 256 < v.n_pairs) {
+                int at = before[c];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int p = c * 256 + lane * 4 + e;
+                    int packed = 0;
+                    if (n[c][e] > 0) {
+                        const int r0 = run_of(at + kPairUnits);
+                        packed = (run_of(at + n[c][e] - 1) - r0 + 1) << 16 | (r0 + p);
+                    }
+                    if (p < v.n_pairs) v.pair_items[p] = packed;
+                    at += n[c][e];
+                }
+            }
+        }
+        return false;
+    }
+    const int x = run * share + min(run, more), len = share + (run < more ? 1 : 0);
+    if (len == 0) return false;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+        if (c * 256 < v.n_pairs) {
+            int at = before[c], mine = -1, first = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (x >= at && x < at + n[c][e]) {
+                    mine = e;
+                    first = at;
+                }
+                at += n[c][e];
+            }
+            const unsigned long long m = __ballot(mine >= 0);
+            if (m != 0ull) {
+                const int src = __builtin_ctzll(m), e = __builtin_amdgcn_readlane(mine, src);
+                const int j = x - __builtin_amdgcn_readlane(first, src);
+                r.pair = c * 256 + src * 4 + e;
+                r.L = __builtin_amdgcn_readlane(e == 0 ? L[c].x : e == 1 ? L[c].y : e == 2 ? L[c].z : L[c].w, src);
+                r.T = __builtin_amdgcn_readlane(e == 0 ? T[c].x : e == 1 ? T[c].y : e == 2 ? T[c].z : T[c].w, src);
+                r.hp = max(0, j - kPairUnits);
+                r.left = len - max(0, kPairUnits - j);
+            }
+        }
+    }
+    return true;
+}
+
+template <int D>
+struct HalfPage {
+    bf16x8 k[2][D / 32], v[D / 16];
+};
+template <int D>
+__device__ __forceinline__ void load_half_page(HalfPage<D>& t, const uint16_t* base, bool wanted, int lane) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(base), 0, wanted ? 4 * kHalfTokens * D : 0, 0x00027000);
+    auto get = [&](int at) -> bf16x8 {                                   // non-temporal
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + (at & 4095), at & ~4095, 2));
+    };
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int sl = 0; sl < D / 32; ++sl) t.k[i][sl] = get((i * (D / 8) + sl * 4) * 256);
+#pragma unroll
+    for (int db = 0; db < D / 16; ++db) t.v[db] = get(2 * kHalfTokens * D + db * 1024);
+}
+
+// KIND: the state of the cache and the columns, as in the split kernel (kSplitPlain, kSplitFusedTwo) or in
+// the multi-token step (kSplitChunk: spkv_chunk_split; cu is looked at there alone).
+constexpr int kSplitChunk = 4;
+template <int D, int KIND>
+__device__ __forceinline__ void attend_run(const SpkvView& v, const uint16_t* __restrict__ q, float scale_log2e,
+                                           int run, int n_runs, const SpkvCu* cu) {
+    constexpr bool FUSED = KIND == kSplitFusedTwo, CHUNK = KIND == kSplitChunk;
+    constexpr int NS = D / 32, NB = D / 16, NT = D == 128 ? 2 : 4;
+    constexpr int kNoVmem = 0x0f70;                // s_waitcnt vmcnt(0)
+    const int lane = threadIdx.x & 63, kc = lane >> 4, n = lane & 15;
+    RunStart r;
+    if (!find_run(v, run, n_runs, r, [&](int p) -> bool {
+            if (!CHUNK) return true;
+            const int b = p / v.Hkv;
+            return cu->v[b + 1] > cu->v[b];
+        }))
+        return;
+    int pair = r.pair, L = r.L, T = r.T, left = r.left, hp0 = r.hp;
+    while (true) {                                 // the run's part of pair after pair
+        const int b = pair / v.Hkv, h = pair - b * v.Hkv;
+        const int row0 = CHUNK ? cu->v[b] : b, n_tok = CHUNK ? cu->v[b + 1] - row0 : 1;
+        const int Tw = min(T, v.w), ghp = list_half_pages(L), nhp = n_tok > 0 ? ghp + list_half_pages(Tw) : 0;
+        const int hp1 = min(nhp, hp0 + left);
+        if (hp1 > hp0) {
+            const int cols = n_tok * v.G;          // column n: token n / G, head n % G
+            const int tok = CHUNK ? n / v.G : 0;
+            const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
+            const float* rl = v.ring_logit + (size_t)pair * v.w;
+            int pbase = hp0 >> 1, my_page = pt[min(pbase + lane, v.pt_cap - 1)];     // 64 page ids, one per lane
+            bf16x8 qb[NS];
+            const uint16_t* qrow = q + ((size_t)(row0 + tok) * v.Hq + (size_t)h * v.G + (CHUNK ? n - tok * v.G : n)) * D + kc * 8;
+#pragma unroll
+            for (int sl = 0; sl < NS; ++sl) {
+                uint4 raw = {0u, 0u, 0u, 0u};
+                if (n < cols) raw = *reinterpret_cast<const uint4*>(qrow + sl * 32);
+                qb[sl] = __builtin_bit_cast(bf16x8, raw);
+            }
+            // Step: the ring key that leaves the window and fails the gate.
+            int drop_hp = -1, drop_r = -1;
+            if (FUSED && hp1 > ghp && T >= v.w) {
+                const int slot = T % v.w;
+                if (!gate_passes(v, rl[slot], T - v.w)) {
+                    drop_hp = ghp + (slot >> 5);
+                    drop_r = slot & 31;
+                }
+            }
+            // Chunk: the gates of 64 ring half-pages from g0 on, one per lane.
+            const int slot0 = T >= v.w ? T % v.w : T - v.w;                // slot of age 0
+            auto age_of = [&](int at) -> int { return at - slot0 + (at < slot0 ? v.w : 0); };
+            int g0 = 0;
+            unsigned gates = 0u;
+            auto load_gates = [&](int from) {
+                g0 = from;
+                for (int i = 0; i < min(hp1 - ghp - from, 64); i += 2) {
+                    const int at = min((from + i) * kHalfTokens + lane, Tw - 1);
+                    const unsigned long long on = __ballot(gate_passes(v, rl[at], T - v.w + age_of(at)));
+                    gates = lane == i ? (unsigned)on : lane == i + 1 ? (unsigned)(on >> 32) : gates;
+                }
+            };
+            if (CHUNK && hp1 > ghp) load_gates(max(0, hp0 - ghp));
+            f32x4 acc[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            float m = SPKV_NEG_INF, l = 0.f;
+            __builtin_amdgcn_s_waitcnt(kNoVmem);   // nothing of the above is waited for in the loop
+            auto load = [&](HalfPage<D>& t, int hp) {
+                const uint16_t* base;
+                if (hp < ghp) {
+                    if ((hp >> 1) >= pbase + 64) {
+                        pbase = hp >> 1;
+                        my_page = pt[min(pbase + lane, v.pt_cap - 1)];
+                        __builtin_amdgcn_s_waitcnt(kNoVmem);
+                    }
+                    base = pool_page(v, __builtin_amdgcn_readlane(my_page, (hp >> 1) - pbase)) + (hp & 1) * (2 * kHalfTokens * D);
+                } else {
+                    const int rp = hp - ghp;
+                    base = ring_page(v, pair, rp >> 1) + (rp & 1) * (2 * kHalfTokens * D);
+                }
+                load_half_page<D>(t, base, hp < hp1, lane);
+            };
+            auto attend = [&](const HalfPage<D>& t, int hp) {
+                const bool ring = hp >= ghp;
+                const int nvalid = !ring ? min(kHalfTokens, L - hp * kHalfTokens)
+                                         : min(kHalfTokens, Tw - (hp - ghp) * kHalfTokens);
+                const int masked_r = (FUSED && hp == drop_hp) ? drop_r : -1;
+                const bool any_kill = nvalid < kHalfTokens || masked_r >= 0 || (CHUNK && ring);
+                unsigned kill = 0u;
+                if (any_kill) {
+                    unsigned gate = 0u;
+                    if (CHUNK && ring) {
+                        if (hp - ghp >= g0 + 64) load_gates(hp - ghp);
+                        gate = __builtin_amdgcn_readlane(gates, hp - ghp - g0) >> (kc * 8);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        bool out = kc * 8 + e >= nvalid || kc * 8 + e == masked_r;
+                        // in the window of the chunk's token i iff its age is above i
+                        if (CHUNK && ring)
+                            out = out || !(((gate >> e) & 1u) || age_of((hp - ghp) * kHalfTokens + kc * 8 + e) > tok);
+                        if (out) kill |= 1u << e;
+                    }
+                }
+                attend_half_page<D>(t.k, t.v, qb, kill, any_kill, scale_log2e, acc, m, l);
+            };
+            HalfPage<D> t[NT];
+            int hp = hp0;
+            bool more = true;
+#pragma unroll
+            for (int i = 0; i < NT - 1; ++i) load(t[i], hp + i);
+            while (more) {
+#pragma unroll
+                for (int i = 0; i < NT; ++i) {
+                    if (more) {
+                        load(t[(i + NT - 1) % NT], hp + NT - 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        attend(t[i], hp);
+                        __builtin_amdgcn_sched_barrier(0);
+                        more = ++hp < hp1;
+                    }
+                }
+            }
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            if (n < cols) {
+                const size_t col = (size_t)(run + pair) * (CHUNK ? 16 : v.G) + n;
+                float* pa = v.part_acc + col * D + kc * 4;
+#pragma unroll
+                for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(pa + db * 16) = acc[db];
+                if (kc == 0) {
+                    v.part_ml[col * 2] = m;
+                    v.part_ml[col * 2 + 1] = l;
+                }
+            }
+        }
+        left -= max(0, hp1 - hp0);
+        if (left <= 0 || ++pair >= v.n_pairs) return;
+        L = v.kept_len[pair];
+        T = v.t_pair[pair];
+        hp0 = 0;
+        const int nb = pair / v.Hkv;
+        if (T > 0 && (!CHUNK || cu->v[nb + 1] > cu->v[nb])) left -= kPairUnits;
+    }
+}
+template <int D, bool FUSED>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_decode_shares(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e) {
+    attend_run<D, FUSED ? kSplitFusedTwo : kSplitPlain>(v, q, scale_log2e, blockIdx.x, (int)gridDim.x - 1, nullptr);
+}
+
 // Fused step with the utility predictor (Eq. 1; the appendix builds it as Linear - SiLU -
 // Linear per token): the hidden layer rides in the split launch, the output layer in the
 // append workgroups of the second launch, so the gate logits of the new tokens cost no
@@ -530,6 +815,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
                                   (int)gridDim.x - pr.n_blocks);
 }
 
+// The same with the lists in equal shares.
+template <int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_decode_shares_predict(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvPredict pr) {
+    if ((int)blockIdx.x < pr.n_blocks)
+        predict_hidden_part(v, pr, blockIdx.x);
+    else
+        attend_run<D, kSplitFusedTwo>(v, q, scale_log2e, (int)blockIdx.x - pr.n_blocks, (int)gridDim.x - pr.n_blocks - 1, nullptr);
+}
+
 // One wave folds the partials of one (pair, head) into a running (max, sum, acc) triple:
 // with M the running max,  acc = sum_i 2^(m_i - M) acc_i,  den = sum_i 2^(m_i - M) l_i.
 // The loads of successive items are independent; only the cheap rescaling is chained.
@@ -581,26 +876,39 @@ __device__ __forceinline__ void fold_items(const SpkvView& v, size_t slot0, int 
     }
 }
 
+// The partial results of a pair: the first slot, how many (`known`: pair_items of the split launch, which with
+// shares holds both), and the slots from the first one to the last that a load may touch.
+struct PartSlots {
+    size_t first;
+    int count, room;
+};
+template <bool SHARES>
+__device__ __forceinline__ PartSlots part_slots(const SpkvSplit& sp, int pair, int known) {
+    if (SHARES) return PartSlots{(size_t)(known & 0xffff), known >> 16, sp.slots - (known & 0xffff)};
+    return PartSlots{(size_t)pair * sp.slots, known, sp.slots};
+}
+
 // Merge the partials of one (sequence, query head):
 //   out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i,  lse = (M + log2(sum)) ln 2.
 // One workgroup of NWM waves per (pair, head): the waves take the items round-robin, each
 // lane owns D/64 output elements, and the wave results meet in LDS.  NWM = 4, or 16 (see
 // wide_merge) so that every wave still gets its items in one round of loads.
-template <int D, int NWM>
+// SHARES: the partial results are those of equal shares (their slots come from a load, which the first round
+// of the others need not wait for).
+template <int D, int NWM, bool SHARES>
 __global__ __launch_bounds__(64 * NWM) void spkv_decode_combine(SpkvView v, uint16_t* __restrict__ out,
                                                                 float* __restrict__ lse, SpkvSplit sp) {
     constexpr int E = D / 64;
     const int pair = blockIdx.x / v.G, g = blockIdx.x - pair * v.G;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int items = pair_split(v, pair, sp).groups;
-    const size_t slot0 = (size_t)pair * sp.slots;
+    const PartSlots ps = part_slots<SHARES>(sp, pair, SHARES ? v.pair_items[pair] : pair_split(v, pair, sp).groups);
     __shared__ float s_m[NWM];
     __shared__ float s_den[NWM];
     __shared__ float s_acc[NWM][D];
 
     float mw, den, num[E];
-    fold_items<D>(v, slot0, g, wave, NWM, sp.slots, items, lane, mw, den, num);
+    fold_items<D>(v, ps.first, g, wave, NWM, ps.room, ps.count, lane, mw, den, num);
 #pragma unroll
     for (int e = 0; e < E; ++e) s_acc[wave][lane * E + e] = num[e];
     if (lane == 0) {
@@ -639,7 +947,7 @@ __global__ __launch_bounds__(64 * NWM) void spkv_decode_combine(SpkvView v, uint
 // activations a_j = SiLU(b1_j + sum of the kPredictSplit partial sums the split launch left),
 // logit = b2_h + sum_j W2[h, j] a_j, all in fp32 -- stores the logit for the caller and
 // appends with it.
-template <int D, bool PRED, int NWM>
+template <int D, bool PRED, int NWM, bool SHARES>
 __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint16_t* __restrict__ out,
                                                            float* __restrict__ lse, SpkvSplit sp,
                                                            const uint16_t* __restrict__ k_new,
@@ -684,7 +992,7 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
     const int pair = blockIdx.x / v.G, g = blockIdx.x - pair * v.G;
     const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int items = v.pair_items[pair];
+    const PartSlots ps = part_slots<SHARES>(sp, pair, v.pair_items[pair]);
     const size_t kv_row = ((size_t)b * v.Hkv + h) * D;
     const size_t q_row = ((size_t)b * v.Hq + (size_t)h * v.G + g) * D;
     // score of the new token for this head (every wave computes it; 6 shuffles)
@@ -697,13 +1005,12 @@ __global__ __launch_bounds__(64 * NWM) void spkv_combine_append(SpkvView v, uint
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
     const float m_tok = dot * scale_log2e;
-    const size_t slot0 = (size_t)pair * sp.slots;
     __shared__ float s_m[NWM];
     __shared__ float s_den[NWM];
     __shared__ float s_acc[NWM][D];
 
     float mw, den, num[E];
-    fold_items<D>(v, slot0, g, wave, NWM, sp.slots, items, lane, mw, den, num);
+    fold_items<D>(v, ps.first, g, wave, NWM, ps.room, ps.count, lane, mw, den, num);
 #pragma unroll
     for (int e = 0; e < E; ++e) s_acc[wave][lane * E + e] = num[e];
     if (lane == 0) {
@@ -888,6 +1195,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(GAPLESS ? 2 
     } while (GAPLESS && id < total);
 }
 
+// The same with the lists in equal shares.
+template <int D>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void spkv_chunk_shares(
+    SpkvView v, const uint16_t* __restrict__ q, float scale_log2e, SpkvCu cu) {
+    attend_run<D, kSplitChunk>(v, q, scale_log2e, blockIdx.x, (int)gridDim.x - 1, &cu);
+}
+
 // Merge for one (pair, column = token i, head g): the split-K partials plus one term per
 // chunk token j <= i taken from the caller's k / v rows (score q_i . k_j in fp32, sum 1,
 // value v_j); bf16 output row cu[b] + i.  The waves share the partials and the chunk
@@ -912,8 +1226,8 @@ __global__ __launch_bounds__(256) void spkv_chunk_combine(SpkvView v, const uint
     if (col >= n_tok * v.G) return;
     const int i = col / v.G, g = col - i * v.G;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int items = v.pair_items[pair];
-    const size_t slot0 = (size_t)pair * sp.slots;
+    const int known = v.pair_items[pair];
+    const PartSlots ps = sp.runs > 0 ? part_slots<true>(sp, pair, known) : part_slots<false>(sp, pair, known);
     __shared__ float s_m[4];
     __shared__ float s_den[4];
     __shared__ float s_acc[4][D];
@@ -922,8 +1236,8 @@ __global__ __launch_bounds__(256) void spkv_chunk_combine(SpkvView v, const uint
 #pragma unroll
     for (int e = 0; e < E; ++e) num[e] = 0.f;
 #pragma unroll 8
-    for (int it = wave; it < items; it += 4) {
-        const size_t idx = (slot0 + it) * cstride + col;
+    for (int it = wave; it < ps.count; it += 4) {
+        const size_t idx = (ps.first + it) * cstride + col;
         const float mi = v.part_ml[idx * 2], li = v.part_ml[idx * 2 + 1];
         float a[E];
 #pragma unroll
@@ -988,7 +1302,8 @@ static hipError_t launch_chunk(const SpkvView& v, const uint16_t* k, const uint1
                                const uint16_t* q, uint16_t* out, float* lse, float scale_log2e,
                                SpkvSplit sp, const SpkvCu& cu, const float* f, hipStream_t s) {
     const unsigned grid = (unsigned)v.n_pairs * (unsigned)sp.slots;
-    if (sp.compact > 0) spkv_chunk_split<D, 1, true><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
+    if (sp.runs > 0) spkv_chunk_shares<D><<<dim3(sp.runs + 1), dim3(64), 0, s>>>(v, q, scale_log2e, cu);
+    else if (sp.compact > 0) spkv_chunk_split<D, 1, true><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
     else spkv_chunk_split<D, 1, false><<<dim3(grid), dim3(64), 0, s>>>(v, q, scale_log2e, sp, cu);
     spkv_chunk_combine<D><<<dim3((f != nullptr ? v.n_pairs : 0) + v.n_pairs * 16), dim3(256), 0, s>>>(
         v, q, k, vv, out, lse, scale_log2e, sp, cu, f);
@@ -1018,6 +1333,10 @@ int spkv_chunk_resident_items(int head_dim) {
 template <int D, int MODE>
 static void launch_split(const SpkvView& v, const uint16_t* q, float scale_log2e, SpkvSplit sp,
                          const SpkvStepIO& io, hipStream_t s) {
+    if (sp.runs > 0 && (MODE == kSplitPlain || MODE == kSplitFusedTwo)) {
+        spkv_decode_shares<D, MODE == kSplitFusedTwo><<<dim3(sp.runs + 1), dim3(64), 0, s>>>(v, q, scale_log2e);
+        return;
+    }
     if (sp.compact > 0 && (MODE == kSplitPlain || MODE == kSplitFusedTwo)) {
         spkv_decode_split_compact<D, MODE == kSplitFusedTwo><<<dim3(sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp);
         return;
@@ -1032,6 +1351,10 @@ static void launch_split(const SpkvView& v, const uint16_t* q, float scale_log2e
 template <int D>
 static void launch_split_predict(const SpkvView& v, const uint16_t* q, float scale_log2e,
                                  SpkvSplit sp, const SpkvPredict& pr, hipStream_t s) {
+    if (sp.runs > 0) {
+        spkv_decode_shares_predict<D><<<dim3(pr.n_blocks + sp.runs + 1), dim3(64), 0, s>>>(v, q, scale_log2e, pr);
+        return;
+    }
     if (sp.compact > 0) {
         spkv_decode_split_predict_compact<D><<<dim3(pr.n_blocks + sp.compact), dim3(64), 0, s>>>(v, q, scale_log2e, sp, pr);
         return;
@@ -1041,6 +1364,25 @@ static void launch_split_predict(const SpkvView& v, const uint16_t* q, float sca
     if (sp.mw == 4) spkv_decode_split_predict<D, 4><<<grid, dim3(256), lds, s>>>(v, q, scale_log2e, sp, pr);
     else if (sp.mw == 2) spkv_decode_split_predict<D, 2><<<grid, dim3(128), lds, s>>>(v, q, scale_log2e, sp, pr);
     else spkv_decode_split_predict<D, 1><<<grid, dim3(64), 0, s>>>(v, q, scale_log2e, sp, pr);
+}
+
+// The merge of spkv_decode_attention, and of the steps (pr: with the predictor).
+template <int D, int NWM>
+static void launch_merge(const SpkvView& v, uint16_t* out, float* lse, SpkvSplit sp, hipStream_t s) {
+    const dim3 grid(v.n_pairs * v.G), block(64 * NWM);
+    if (sp.runs > 0) spkv_decode_combine<D, NWM, true><<<grid, block, 0, s>>>(v, out, lse, sp);
+    else spkv_decode_combine<D, NWM, false><<<grid, block, 0, s>>>(v, out, lse, sp);
+}
+template <int D, bool PRED>
+static void launch_merge_append(const SpkvView& v, uint16_t* out, float* lse, SpkvSplit sp, const uint16_t* k,
+                                const uint16_t* vv, const float* f, const uint16_t* q, float scale_log2e,
+                                const SpkvPredict& pr, hipStream_t s) {
+    const dim3 grid(v.n_pairs * v.G + v.n_pairs);
+    const bool wide = wide_merge(v, sp), shares = sp.runs > 0;
+    if (wide && shares) spkv_combine_append<D, PRED, 16, true><<<grid, dim3(1024), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, pr);
+    else if (wide) spkv_combine_append<D, PRED, 16, false><<<grid, dim3(1024), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, pr);
+    else if (shares) spkv_combine_append<D, PRED, 4, true><<<grid, dim3(256), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, pr);
+    else spkv_combine_append<D, PRED, 4, false><<<grid, dim3(256), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, pr);
 }
 
 hipError_t spkv_launch_decode(const SpkvView& v, const uint16_t* q, uint16_t* out, float* lse,
@@ -1065,14 +1407,9 @@ hipError_t spkv_launch_decode(const SpkvView& v, const uint16_t* q, uint16_t* ou
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (ev1 != nullptr && (e = hipEventRecord(ev1, s)) != hipSuccess) return e;
     if (split_only) return hipSuccess;
-    const dim3 grid2(v.n_pairs * v.G);
-    if (wide_merge(v, sp)) {
-        if (v.D == 128) spkv_decode_combine<128, 16><<<grid2, dim3(1024), 0, s>>>(v, out, lse, sp);
-        else spkv_decode_combine<64, 16><<<grid2, dim3(1024), 0, s>>>(v, out, lse, sp);
-    } else {
-        if (v.D == 128) spkv_decode_combine<128, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp);
-        else spkv_decode_combine<64, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp);
-    }
+    const bool wide = wide_merge(v, sp);
+    if (v.D == 128) wide ? launch_merge<128, 16>(v, out, lse, sp, s) : launch_merge<128, 4>(v, out, lse, sp, s);
+    else wide ? launch_merge<64, 16>(v, out, lse, sp, s) : launch_merge<64, 4>(v, out, lse, sp, s);
     return hipGetLastError();
 }
 
@@ -1110,16 +1447,12 @@ hipError_t spkv_launch_decode_step(const SpkvView& v, const uint16_t* k, const u
     }
     const SpkvStepIO no_io = {};
     const SpkvPredict none = {};
-    const dim3 grid2(v.n_pairs * v.G + v.n_pairs);
-    const bool wide = wide_merge(v, sp);
     if (v.D == 128) {
         launch_split<128, kSplitFusedTwo>(v, q, scale_log2e, sp, no_io, s);
-        if (wide) spkv_combine_append<128, false, 16><<<grid2, dim3(1024), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, none);
-        else spkv_combine_append<128, false, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, none);
+        launch_merge_append<128, false>(v, out, lse, sp, k, vv, f, q, scale_log2e, none, s);
     } else {
         launch_split<64, kSplitFusedTwo>(v, q, scale_log2e, sp, no_io, s);
-        if (wide) spkv_combine_append<64, false, 16><<<grid2, dim3(1024), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, none);
-        else spkv_combine_append<64, false, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp, k, vv, f, q, scale_log2e, none);
+        launch_merge_append<64, false>(v, out, lse, sp, k, vv, f, q, scale_log2e, none, s);
     }
     return hipGetLastError();
 }
@@ -1135,16 +1468,12 @@ hipError_t spkv_launch_decode_step_predict(const SpkvView& v, const uint16_t* k,
     const float scale_log2e = sm_scale * 1.4426950408889634f;
     if (sp.mw != 1 && sp.mw != 2 && sp.mw != 4) return hipErrorInvalidValue;
     pr.n_blocks = spkv_predict_blocks(v.B, pr.d_hidden);
-    const dim3 grid2(v.n_pairs * v.G + v.n_pairs);
-    const bool wide = wide_merge(v, sp);
     if (v.D == 128) {
         launch_split_predict<128>(v, q, scale_log2e, sp, pr, s);
-        if (wide) spkv_combine_append<128, true, 16><<<grid2, dim3(1024), 0, s>>>(v, out, lse, sp, k, vv, nullptr, q, scale_log2e, pr);
-        else spkv_combine_append<128, true, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp, k, vv, nullptr, q, scale_log2e, pr);
+        launch_merge_append<128, true>(v, out, lse, sp, k, vv, nullptr, q, scale_log2e, pr, s);
     } else {
         launch_split_predict<64>(v, q, scale_log2e, sp, pr, s);
-        if (wide) spkv_combine_append<64, true, 16><<<grid2, dim3(1024), 0, s>>>(v, out, lse, sp, k, vv, nullptr, q, scale_log2e, pr);
-        else spkv_combine_append<64, true, 4><<<grid2, dim3(256), 0, s>>>(v, out, lse, sp, k, vv, nullptr, q, scale_log2e, pr);
+        launch_merge_append<64, true>(v, out, lse, sp, k, vv, nullptr, q, scale_log2e, pr, s);
     }
     return hipGetLastError();
 }

@@ -20,6 +20,7 @@ constexpr int kSpanOrderPairs = 64, kSpanOrderAt = 4, kSpanOrderStride = 8;
 struct SpanCut {
     int32_t tokens, groups;           // tokens of a span (0: no order wanted), groups of pairs (a divisor of H_kv)
 };
+constexpr int kSharePairs = 512;      // most (sequence, head) pairs that are cut into equal shares
 constexpr int kCompactPairs = 1024;   // most (sequence, head) pairs the gapless numbering serves
 
 // A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)
@@ -120,6 +121,7 @@ struct SpkvSplit {
     int32_t mw;
     int32_t compact;      // 0: workgroup id = pair * slots + item; else workgroups numbered without
                           // gaps (spkv_decode_split_compact), this many of them
+    int32_t runs;         // > 0: equal shares instead (spkv_decode_shares), this many; slots: all there are
 };
 
 // Inputs and outputs of the single-token kernels that finish a pair themselves.
