@@ -84,11 +84,12 @@ __device__ __forceinline__ int alloc_page(const SpkvView& v) {
 struct PageBatch {
     int stack_lo, from_stack, pool_base;
 };
-__device__ __forceinline__ PageBatch alloc_page_batch(const SpkvView& v, int need) {
+// recycled: the stack's entries as they were when the launch had begun.
+__device__ __forceinline__ PageBatch alloc_page_batch(const SpkvView& v, int need, int recycled) {
     PageBatch pb = {0, 0, 0};
     if (need <= 0) return pb;
     // no page is pushed in a launch that pops, so a stack seen empty stays empty
-    if (__hip_atomic_load(v.free_top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0) {
+    if (recycled > 0) {
         const int top = atomicSub(v.free_top, need);
         const int take = min(max(top, 0), need);
         if (take < need) atomicAdd(v.free_top, need - take);     // put back what was not there
@@ -98,6 +99,9 @@ __device__ __forceinline__ PageBatch alloc_page_batch(const SpkvView& v, int nee
     const int rest = need - pb.from_stack;
     if (rest > 0) pb.pool_base = atomicAdd(v.pool_next, rest);
     return pb;
+}
+__device__ __forceinline__ PageBatch alloc_page_batch(const SpkvView& v, int need) {
+    return alloc_page_batch(v, need, __hip_atomic_load(v.free_top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 __device__ __forceinline__ int batch_page(const SpkvView& v, const PageBatch& pb, int i) {
     if (i < pb.from_stack) return v.free_pages[pb.stack_lo + i];

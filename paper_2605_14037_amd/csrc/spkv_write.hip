@@ -190,6 +190,25 @@ struct BulkInfo {
 };
 static_assert(sizeof(BulkInfo) == kSpanOrderStride * 4, "order entries lie in the scratch of the pairs");
 
+// The heads of a sequence's tokens lie side by side, 4 bytes of logit each in 32 of a token (8 heads), so the
+// workgroups that look at the same tokens for different heads run on one XCD (ids go round-robin to
+// the eight): its L2 fetches the logits once, and what they write side by side leaves it as whole lines.  Workgroup
+// `id` of groups x heads: whole eights of groups, a group to an XCD; the rest, or less than eight groups where they
+// divide eight evenly, several XCDs to a group; else in turn.
+struct HeadOfGroup {
+    int group, head;
+};
+__device__ __forceinline__ HeadOfGroup head_of_group(int id, int groups, int heads) {
+    const int whole = groups & ~7, xcd = id & 7, k = id >> 3;
+    if (id < whole * heads) return HeadOfGroup{k / heads * 8 + xcd, k % heads};
+    const int rest = groups - whole, at = id - whole * heads;
+    if ((rest == 1 || rest == 2 || rest == 4) && heads % (8 / rest) == 0) {
+        const int each = heads * rest / 8;
+        return HeadOfGroup{whole + xcd % rest, xcd / rest * each + (at >> 3)};
+    }
+    return HeadOfGroup{whole + at / heads, at % heads};
+}
+
 // Stage 1: per (segment, pair): how many of the segment's new tokens pass the gate, and how
 // many of those also leave the window within this call (j < n - w).
 __global__ __launch_bounds__(256) void spkv_bulk_count(SpkvView v, const float* __restrict__ f,
@@ -256,7 +275,10 @@ __device__ __forceinline__ int block_excl_scan(int x, int* s_w, int& total) {
 //
 // COUNT: chunks of at most kCountSegs segments per sequence -- this launch also does stage 1's
 // job for its pair (the per-segment counts from the logits, every wave's popcounts parked in
-// LDS and summed after one barrier), so that the call is two launches instead of three.
+// LDS), so that the call is two launches instead of three.  Bound by dependent round trips, so only three are
+// left: logits, counters and the stack of pages together, ring logits, the pool's atomic; counts, offsets and
+// lengths go from one barrier's popcounts to every wave's registers.  16 sequences x 4096 tokens 11.3 -> 9.5 us
+// (counts and offsets through memory, the counters before the logits, six barriers more before).
 constexpr int kCountSegs = 16;
 //
 // MOVE = false: the kept ring rows are moved by stage 3 (ring_in_one_workgroup).
@@ -269,6 +291,22 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
     const int n = cu.v[b + 1] - cu.v[b];
     if (n == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hh = pair - b * v.Hkv, nseg_all = (n + kSegTokens - 1) / kSegTokens;
+    // COUNT: every segment's logit of this thread and what thread 0 needs to count and to take pages, before
+    // anything is waited for
+    float fv[COUNT ? kCountSegs : 1];
+    int on_before = 0, recycled = 0;
+    if (COUNT) {
+#pragma unroll
+        for (int sg = 0; sg < kCountSegs; ++sg) {
+            const int j = sg * kSegTokens + tid;
+            fv[sg] = (sg < nseg_all && j < n) ? f[((size_t)cu.v[b] + j) * v.Hkv + hh] : 0.f;
+        }
+        if (tid == 0) {
+            on_before = v.gate_on[pair];
+            recycled = __hip_atomic_load(v.free_top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
     const int T_old = v.t_pair[pair], T_new = T_old + n, L_old = v.kept_len[pair];
     const int r0 = max(0, T_old - v.w);
     const int r1 = min(T_old, max(0, T_new - v.w));
@@ -284,14 +322,8 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
 
     // the ring logits of the first 256 leaving positions travel with the segments' logits
     const float rl_first = tid < nr ? rl[(r0 + tid) % v.w] : 0.f;
+    const int end_page = (COUNT && (L_old & (kPageTokens - 1)) != 0) ? v.page_table[(size_t)pair * v.pt_cap + (L_old >> 6)] : -1;
     if (COUNT) {          // stage 1 for this pair: per segment and wave, kept-and-leaving / gate-on
-        const int hh = pair - b * v.Hkv, nseg_all = (n + kSegTokens - 1) / kSegTokens;
-        float fv[kCountSegs];           // every segment's logit of this thread, loads issued together
-#pragma unroll
-        for (int sg = 0; sg < kCountSegs; ++sg) {
-            const int j = sg * kSegTokens + tid;
-            fv[sg] = (sg < nseg_all && j < n) ? f[((size_t)cu.v[b] + j) * v.Hkv + hh] : 0.f;
-        }
 #pragma unroll
         for (int sg = 0; sg < kCountSegs; ++sg) {
             if (sg < nseg_all) {
@@ -305,14 +337,6 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
                 }
             }
         }
-        __syncthreads();
-        if (tid < nseg_all) {
-            sc[tid] = s_seg[tid][0][0] + s_seg[tid][1][0] + s_seg[tid][2][0] + s_seg[tid][3][0];
-            v.seg_on[(size_t)pair * v.n_seg_cap + tid] =
-                s_seg[tid][0][1] + s_seg[tid][1][1] + s_seg[tid][2][1] + s_seg[tid][3][1];
-        }
-        __threadfence_block();
-        __syncthreads();
     }
 
     // (a) how many ring pairs are kept
@@ -326,9 +350,23 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
     __syncthreads();
     const int ring_kept = s_w[0] + s_w[1] + s_w[2] + s_w[3];
 
-    // (b) segment counts -> exclusive offsets (in place)
+    // (b) segment counts -> exclusive offsets
     int carry = 0;
-    for (int base = 0; base < nseg; base += 256) {
+    if (COUNT) {          // by every wave, of (segment, wave) pairs, one a lane: nothing goes through memory
+        const bool counted = lane < 4 * nseg_all;
+        int incl = counted ? s_seg[lane >> 2][lane & 3][0] : 0, on = counted ? s_seg[lane >> 2][lane & 3][1] : 0;
+        const int mine = incl;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(incl, o);
+            if (lane >= o) incl += t;
+            on += __shfl_xor(on, o);
+        }
+        carry = __builtin_amdgcn_readlane(incl, 63);
+        if (wave == 0 && counted && (lane & 3) == 0) sc[lane >> 2] = incl - mine;
+        if (tid == 0) v.gate_on[pair] = on_before + on;
+    }
+    for (int base = 0; !COUNT && base < nseg; base += 256) {
         const int i = base + tid;
         const int c = i < nseg ? sc[i] : 0;
         int tot;
@@ -340,14 +378,12 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
 
     // gate-on count of the call (Eq. 8 numerator), summed here so that no kernel needs
     // same-address atomics
-    {
+    if (!COUNT) {
         int on = 0;
         if (SMALL) {
-            const bool flag = tid < n && gate_passes(v, f[((size_t)cu.v[b] + tid) * v.Hkv + (pair - b * v.Hkv)],
-                                                     T_old + tid);
+            const bool flag = tid < n && gate_passes(v, f[((size_t)cu.v[b] + tid) * v.Hkv + hh], T_old + tid);
             on = flag ? 1 : 0;
         } else {
-            const int nseg_all = (n + kSegTokens - 1) / kSegTokens;
             const int32_t* so = v.seg_on + (size_t)pair * v.n_seg_cap;
             for (int i = tid; i < nseg_all; i += 256) on += so[i];
         }
@@ -365,14 +401,16 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
     const int need = last <= v.pt_cap ? last - first : 0;
     int bad = last > v.pt_cap ? 1 : 0;
     __shared__ PageBatch s_pb;
-    if (tid == 0) s_pb = alloc_page_batch(v, need);
+    if (tid == 0) s_pb = COUNT ? alloc_page_batch(v, need, recycled) : alloc_page_batch(v, need);
     __syncthreads();
     for (int i = tid; i < need; i += 256) {
         const int page = batch_page(v, s_pb, i);
         if (page < 0) bad = 1;
         else v.page_table[(size_t)pair * v.pt_cap + first + i] = page;
     }
-    const int any_bad = __syncthreads_or(bad);
+    // (the bump allocator's pages ascend: the last one of the batch is past the pool if any is)
+    const int any_bad = COUNT ? (bad != 0 || (need > s_pb.from_stack && s_pb.pool_base + (need - s_pb.from_stack) > v.n_pages))
+                              : __syncthreads_or(bad);
     if (tid == 0) {
         if (any_bad) *v.err_flag = 1;
         s_bi.T_old = T_old;
@@ -382,12 +420,17 @@ __device__ __forceinline__ void bulk_ring(const SpkvView& v, const SpkvCu& cu, i
         if (!any_bad) v.kept_len[pair] = L_old + total_new;
         if (SMALL) v.t_pair[pair] = T_new;
     }
-    __threadfence_block();
-    __syncthreads();
+    if (!COUNT || MOVE) {
+        __threadfence_block();
+        __syncthreads();
+    }
     if (any_bad) return;
     const int32_t* pt = v.page_table + (size_t)pair * v.pt_cap;
-    if (ends_in_new_half_page(L_old, L_old + total_new))
-        clear_list_end<D>(pool_page(v, pt[(L_old + total_new) >> 6]), L_old + total_new, tid, 256);
+    if (ends_in_new_half_page(L_old, L_old + total_new)) {
+        const int lp = (L_old + total_new) >> 6;
+        const int page = !COUNT ? pt[lp] : lp >= first ? batch_page(v, s_pb, lp - first) : end_page;
+        clear_list_end<D>(pool_page(v, page), L_old + total_new, tid, 256);
+    }
 
     // (d) move the kept ring rows, 256 ring positions at a time; without MOVE only their ranks are
     //     wanted, for the prefix counts
@@ -472,7 +515,8 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
                                                       const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ vv,
                                                       const float* __restrict__ f) {
-    bulk_ring<D, SMALL, COUNT, MOVE>(v, cu, prefix, k, vv, f, blockIdx.x);
+    const HeadOfGroup at = head_of_group(blockIdx.x, v.B, v.Hkv);
+    bulk_ring<D, SMALL, COUNT, MOVE>(v, cu, prefix, k, vv, f, at.group * v.Hkv + at.head);
 }
 // Stage 2 of a prefill call and, in further workgroups, its staging rows: neither writes what the other
 // reads (ring, ring logits, token counts; lists and tables).  Both wait for memory most of their time.
@@ -485,7 +529,8 @@ __global__ __launch_bounds__(256) void spkv_stage_ring(SpkvView v, SpkvCu cu, in
                                                        const float* __restrict__ f, SpkvStage st) {
     const int id = (int)blockIdx.x - v.n_pairs;
     if (id < 0) {
-        bulk_ring<D, false, COUNT, MOVE>(v, cu, prefix, k, vv, f, blockIdx.x);
+        const HeadOfGroup at = head_of_group(blockIdx.x, v.B, v.Hkv);
+        bulk_ring<D, false, COUNT, MOVE>(v, cu, prefix, k, vv, f, at.group * v.Hkv + at.head);
     } else {
         const int pair = id / st.hps;
         stage_half_page<D>(v, k, vv, f, cu, st, pair, id - pair * st.hps);
@@ -627,8 +672,8 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
         return;
     }
     if (to.host != nullptr && blockIdx.x == 0 && blockIdx.y == 0) copy_lengths(v.kept_len, v.n_pairs, to);
-    const int pair = blockIdx.y, quad = blockIdx.x;
-    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
+    const HeadOfGroup at = head_of_group((int)(blockIdx.y * gridDim.x + blockIdx.x), v.B * (int)gridDim.x, v.Hkv);
+    const int b = at.group / (int)gridDim.x, quad = at.group - b * (int)gridDim.x, h = at.head, pair = b * v.Hkv + h;
     const int row0 = cu.v[b];
     const int n = cu.v[b + 1] - row0;
     const int j0 = quad * kScatterThreads;
