@@ -468,25 +468,24 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
     return n * 128 <= kGapFewChunkPairs * c->cfg.head_dim || sum >= (int64_t)items * kGapChunkItemHps ||
            2 * longest * n >= sum * (c->cfg.head_dim == 128 ? 3 : 4);
 }
-// Large caches in equal shares (spkv_decode_shares): two runs per compute unit, one where few pairs would have
-// many partial results each to merge.  From which size on, by what a wave with two half-pages in registers
-// costs at its start against what equal shares save; D = 64 has half the bytes to a half-page and the same
-// arithmetic.  Step replayed from a graph, items / shares, us: 8 heads of 128, 32 pairs of 18 MB 9.9 / 10.2, 26 MB
-// 11.3 / 10.3, 67 MB 16.6 / 15.6, 192 MB 38.0 / 33.1; 128 pairs of 49 MB 15.9 / 14.3, 266 MB 49.4 / 45.7; 512 pairs of
-// 193 MB 44.3 / 41.5, 988 MB 191 / 160; 8 pairs of 44 MB 13.6 / 14.4, 156 MB 31.4 / 29.8 (30.9 with two runs per
-// compute unit); head_dim 64: 128 pairs of 53 MB 14.6 / 16.3, 133 MB 27.6 / 27.4, 256 pairs of 265 MB 49.0 / 47.1, 105 MB
-// 24.0 / 24.4.  The multi-token step, whose partial results are four times as long, gains earlier: 4 drafts, 32
-// pairs of 26 MB 17.9 / 15.9, 67 MB 26.3 / 21.3, 256 pairs of 98 MB 37.4 / 28.8, 8 pairs of 18 MB 15.3 / 15.6; head_dim 64,
-// 128 pairs of 133 MB 36.5 / 32.3.  (Uneven lists too: 512 pairs, a quarter dense, a quarter local, 3.0 GB 468 / 455.)
+// Large caches in equal shares (spkv_decode_shares): two runs per compute unit.  From which size on, by what a wave
+// with two half-pages in registers costs at its start, and few pairs with many partial results each, against
+// what equal shares save; D = 64 has half the bytes to a half-page and the same arithmetic.  Step replayed from a graph,
+// items / shares, us: 8 heads of 128, 32 pairs of 18 MB 9.9 / 10.2, 26 MB 11.4 / 10.6, 67 MB 16.6 / 15.9, 192 MB
+// 38.2 / 33.5; 128 pairs of 49 MB 15.9 / 14.6, 266 MB 49.6 / 46.2; 512 pairs of 193 MB 44.1 / 41.6, 988 MB 190 / 160; 8 pairs
+// of 44 MB 13.6 / 14.2, 156 MB 31.4 / 30.9 (one run per compute unit 14.4, 32.0); head_dim 64: 128 pairs of 53 MB
+// 14.6 / 16.3, 133 MB 27.6 / 27.4, 256 pairs of 265 MB 49.0 / 47.1, 105 MB 24.0 / 24.4.  The multi-token step, whose
+// partial results are four times as long, gains earlier: 4 drafts, 32 pairs of 26 MB 18.2 / 16.2, 67 MB 26.4 / 21.7,
+// 256 pairs of 98 MB 37.1 / 28.9, 8 pairs of 18 MB 15.3 / 15.6; head_dim 64, 128 pairs of 133 MB 36.6 / 33.5.  (Uneven lists
+// too: 512 pairs, a quarter dense, a quarter local, 3.0 GB 468 / 452.)
 // Not where two sequences have the same lengths throughout: an item's place in its pair depends on the pair's
 // length and the call, a run's on the pairs before it as well, and copies of a sequence are given the same bits.
 constexpr int kShareFewPairs = 8;
-constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)96 << 20, kShareBytes64 = (int64_t)160 << 20;
+constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)144 << 20, kShareBytes64 = (int64_t)160 << 20;
 constexpr int64_t kShareBytesChunk = (int64_t)20 << 20, kShareBytesChunk64 = (int64_t)100 << 20;
 SpkvSplit share_split(const spkv_cache* c) {
-    const int n = c->carve.n_pairs, cus = c->compact_items / kCompactItemsPerCu;
-    const int runs = cus * (n <= kShareFewPairs && c->cfg.head_dim == 128 ? 1 : 2);
-    return SpkvSplit{1, runs + n, 1, 0, runs};
+    const int runs = 2 * (c->compact_items / kCompactItemsPerCu);
+    return SpkvSplit{1, runs + c->carve.n_pairs, 1, 0, runs};
 }
 // Do two sequences have the same lengths in every head?  (Copies of a sequence do.)  Those of one half-page
 // a head do not count: it is never cut.

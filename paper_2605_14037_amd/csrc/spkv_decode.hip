@@ -490,7 +490,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 // bytes, so that what a half-page waits for is a constant number of loads in flight.
 // 16 sequences of 32k, 484 MB, us a step: 82.3 as items of one pair each (2880 waves), 78.0 with 512 runs, 78.2
 // with 256, 79.3 with 768, 80.3 with 1024, 81.9 with 640; three half-pages in registers 79.2.  A plain read
-// of the same bytes takes 71 with 1792 workgroups, 72.7 with 2880.
+// of the same bytes takes 71 with 1792 workgroups, 72.7 with 2880.  The weights go in two bf16 parts
+// (attend_half_page), which 512 waves have the time for (256 of them do not: 8 pairs of 156 MB 30.1 -> 32.0).
 constexpr int kPairUnits = 1;    // a pair's units: its half-pages and one for what beginning it costs
 __device__ __forceinline__ int list_half_pages(int n) { return (n + kHalfTokens - 1) >> 5; }
 // Sum over the lanes up to and including this one.
@@ -714,7 +715,7 @@ __device__ __forceinline__ void attend_run(const SpkvView& v, const uint16_t* __
                         if (out) kill |= 1u << e;
                     }
                 }
-                attend_half_page<D>(t.k, t.v, qb, kill, any_kill, scale_log2e, acc, m, l);
+                attend_half_page<D, true>(t.k, t.v, qb, kill, any_kill, scale_log2e, acc, m, l);
             };
             HalfPage<D> t[NT];
             int hp = hp0;

@@ -114,8 +114,8 @@ def _unlike(pairs, kept):
 
 @pytest.mark.parametrize("cfg,kept,step,chunk", [
     (dict(batch=4), _unlike(32, 1410), True, True), (dict(batch=4), _unlike(32, 1310), False, True),     # 24 and 20 MiB
-    (dict(batch=4), _unlike(32, 1100), False, False), (dict(batch=1), _unlike(8, 24500), True, True),    # few pairs: 96
-    (dict(batch=1), _unlike(8, 24300), False, True), (dict(batch=64), _unlike(512, 2000), True, True),
+    (dict(batch=4), _unlike(32, 1100), False, False), (dict(batch=1), _unlike(8, 36800), True, True),    # few pairs: 144
+    (dict(batch=1), _unlike(8, 36600), False, True), (dict(batch=64), _unlike(512, 2000), True, True),
     (dict(batch=64), [2000 + p % 8 for p in range(512)], False, False),                                  # copies
     (dict(batch=65), _unlike(520, 2000), False, False),                                                  # too many pairs
     (dict(batch=16, head_dim=64), _unlike(128, 5000), True, True), (dict(batch=16, head_dim=64), _unlike(128, 4800), False, True),
@@ -123,7 +123,7 @@ def _unlike(pairs, kept):
 def test_large_caches_in_equal_shares(cfg, kept, step, chunk):
     """Every single-token call alike, by the kept bytes; an explicit partition or launch count keeps the items."""
     counts = [4] * cfg["batch"]
-    script = [["append", [30000] * cfg["batch"]], ["lengths", kept], ["stats"]]
+    script = [["append", [40000] * cfg["batch"]], ["lengths", kept], ["stats"]]
     calls = [["attend"], ["static"], ["step"], ["predict", 4096, 256], ["score", counts], ["chunk", counts]]
     got = record(dict(cfg, max_total_kept_tokens=1 << 27), script + calls)[2:]
     assert [c.rc for c in got] == [0] * 6
@@ -131,9 +131,8 @@ def test_large_caches_in_equal_shares(cfg, kept, step, chunk):
     for option in ([1, 64], [5, 1], [5, 4], [6, 1]):
         for c in record(dict(cfg, max_total_kept_tokens=1 << 27), script + [["option"] + option] + calls[:3])[3:]:
             assert not [n for n, _, _ in c.launches if "shares" in n]
-    if step:        # a workgroup per run and one for the table; slots for every run and pair
-        runs = 256 if cfg["batch"] == 1 else 512
-        assert got[0].launches[0][1][0] == runs + 1 and got[3].launches[0][1][0] == runs + 1 + 64 * -(-cfg["batch"] // 16)
+    if step:        # a workgroup per run, one for the table, those of the predictor
+        assert got[0].launches[0][1][0] == 513 and got[3].launches[0][1][0] == 513 + 64 * -(-cfg["batch"] // 16)
 
 
 # ------------------------------------------------------------------ utility predictor
