@@ -233,15 +233,23 @@ def _check(code, where):
         raise SPKVError(code, where)
 
 
+# The raw handle of a device's current stream.  Building a torch.cuda.Stream object to read it from
+# took 2.9 us of the 10 us that a short decode step cost the host; asked for directly 0.3 (a step of
+# one sequence of 2048 tokens 10.4 -> 6.9 us, append and attention as two calls 20.8 -> 15.5).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
-def _dev_ptr(t: torch.Tensor, dtype, shape, name):
-    if not t.is_cuda or t.dtype != dtype or not t.is_contiguous() or tuple(t.shape) != tuple(shape):
+def _dev_ptr(t: torch.Tensor, dtype, shape: tuple, name):
+    if not t.is_cuda or t.dtype != dtype or t.shape != shape or not t.is_contiguous():
         raise ValueError(f"{name}: need a contiguous cuda {dtype} tensor of shape {tuple(shape)}, "
                          f"got {t.dtype} {tuple(t.shape)} on {t.device}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()                    # (every entry point declares its argument types)
 
 
 class SPKVCache:
