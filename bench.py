@@ -556,7 +556,10 @@ def read_ceiling_leg(nbytes, n_workgroups, launches):
     """A plain streaming read (spkv_debug_read) of the same number of bytes, in scattered 32 KB
     runs (the cache's page size), by as many one-wave workgroups as the decode launch has work
     items, back to back over a region of at least 3 GiB (twice the bytes of a launch) so that
-    every launch reads cold memory."""
+    every launch reads cold memory.  At least seven workgroups per compute unit: the probe holds one
+    16 KB chunk a wave, and with the two waves per compute unit of a decode launch in equal shares
+    (two 16 KB half-pages each) it takes 86 us for the bytes it reads in 71."""
+    n_workgroups = max(n_workgroups, 7 * torch.cuda.get_device_properties(0).multi_processor_count)
     run_bytes = 32768
     region = max(3 << 30, (2 * int(nbytes) + (1 << 30)) // run_bytes * run_bytes)
     src = torch.empty(region, dtype=torch.uint8, device="cuda")
@@ -577,7 +580,7 @@ def read_ceiling_leg(nbytes, n_workgroups, launches):
     #                         the next timed leg was measured to slow that leg by 3-4 %)
     gbps = n_runs * run_bytes / (ms * 1e-3) / 1e9
     return {"what": "spkv_debug_read: non-temporal 16 KB chunk reads in scattered 32 KB runs, one-wave "
-                    "workgroups, no arithmetic; same bytes and workgroup count as the decode launch",
+                    "workgroups, no arithmetic; same bytes as the decode launch, its workgroup count or 7 per compute unit",
             "bytes_per_launch": n_runs * run_bytes, "workgroups": n_workgroups, "us_per_launch": ms * 1e3,
             "GBps": gbps, "frac_of_hbm_peak": gbps / HBM_PEAK_GBPS, "launches_timed": launches}
 
@@ -674,8 +677,9 @@ def decode_leg(wl, args, K, W, with_dense=True, cpu_seqs=0, keep_caches=False, c
         "us_per_step_forced_one_launch": forced[1], "us_per_step_forced_two_launches": forced[2],
         "roofline": {
             "bound": "hbm",
-            "kernel": (f"spkv_decode_split<{wl.head_dim}>: split-K over the kept lists (the first of the "
-                       "step's two launches; the second, spkv_combine_append, merges and appends)"
+            "kernel": (f"spkv_decode_shares<{wl.head_dim}> (large caches; else spkv_decode_split): split-K "
+                       "over the kept lists (the first of the step's two launches; the second, "
+                       "spkv_combine_append, merges and appends)"
                        if args.step_launches != 1 else
                        f"spkv_decode_split<{wl.head_dim}, step>: split-K + merge + append in one launch"),
             "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
