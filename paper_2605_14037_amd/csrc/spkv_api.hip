@@ -414,6 +414,7 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // (keep rates that depend on the head) every sequence adds the same uneven pattern -- in
 // units of whole workgroups -- until some XCD is handed more waves than it holds and runs
 // the surplus in a second round.  Hence the limit of kMergePairs pairs.
+// Large caches are cut into equal shares before any of this is asked (worth_shares, below).
 // Caches of more pairs take one item per workgroup, and where their lists are uneven
 // (worth_gapless) the gapless numbering (spkv_decode_split_compact) with seven items per
 // compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
