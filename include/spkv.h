@@ -336,7 +336,8 @@ int spkv_cache_release_sequence(spkv_cache_t* cache, int32_t b, void* stream);
  *   b2      device fp32 [n_kv_heads] or NULL         logits  device fp32 [n_tokens, n_kv_heads]
  *   workspace  device fp32 [n_tokens * d_hidden] (hidden activations; caller-owned scratch)
  * (weights in the row-major [out, in] layout of a linear layer).  d_model must be a multiple
- * of 128, d_hidden of 16.  Products of bf16 values accumulate in fp32.  Stateless: no cache
+ * of 128, d_hidden of 16.  Products of bf16 values accumulate in fp32; tokens of one call with equal
+ * hidden states get equal logits to the last bit, wherever they stand in it.  Stateless: no cache
  * involved; the output is what spkv_append / spkv_decode_step take as util_logits. */
 int spkv_utility_logits(const void* hidden, const void* w1, const float* b1, const void* w2,
                         const float* b2, float* logits, float* workspace, int32_t n_tokens,

@@ -173,20 +173,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // the L2 (292 MB come from behind it, of which the tokens are 268; worth 2 % of the time).
 // Chunk c (16 bytes) of row r lies at position c ^ ((r >> 1) & 7) of the row: the sixteen rows
 // an operand read touches at a time then cover all 64 banks once.
-// Where token rows lie whole multiples of 4 KB apart, workgroups in step with each other would
-// read the same 128 bytes of every row at a time, which are on few of the memory's channels: there
-// every workgroup of the launches that the memory bounds (more than 16 384 tokens, up to 128 units)
-// begins at a block of its own and goes round.  By 17 per workgroup: neighbours (other XCDs) start
-// far apart, and one workgroup in eight of an XCD reads the same blocks of W1.  Before / now, us:
-// 32 768 tokens of 4096 with 64 units 66.3 / 51.0 (5.3 TB/s), of 2048 38.5 / 32.8, 20 000 of 4096
-// with 128 units 53.8 / 51.6.  Elsewhere nothing to gain or a little to lose: 17 000 tokens of 2944
-// with 128 units 39.4 / 40.3; 256 units, 32 768 tokens of 4096 83.6 / 84.4 (the products bound it).
 // What bounds it, 32 768 tokens of 4096 -> 256 -> 8: the rows' way into LDS beside the products
 // (by counters the matrix units are busy 48 % of the SIMD time; waves wait 26 % of their time for
 // copies and the barrier and 44 % for an issue slot).  115 us with 64-token workgroups, two
 // stages in LDS and 16x16x32 products, 78 us now.  Stages half as wide and five ahead: 100 us
 // (the copies are bound by rows, not by latency).  The epilogue's loads go out together: one by
 // one, behind a branch each, they were 9 us of every call.
+// Every workgroup takes the blocks of d_model in the same order: equal hidden states have equal logits to the
+// last bit wherever they stand in a launch, and copies of a prompt keep the same tokens.  (With blocks in an
+// order of its own per workgroup, 32 768 tokens of 4096 with 64 units take 51 us instead of 66: token rows 8 KB apart
+// are on few memory channels when all read the same 128 bytes of them.)
 // Sums of kGemmFlush stages are added up outside the MFMA accumulators: the relative error
 // against 64 bits is 5.7e-8 (one chain over d_model: 1.55e-7) for 2 us.
 constexpr int kGemmK = 64;           // elements of d_model per stage
@@ -212,7 +208,6 @@ __global__ __launch_bounds__(TT * NHW) void spkv_predictor_gemm(
     const int t0 = blockIdx.x * TT;
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)s_raw;
     const int n_stages = d_model / kGemmK;                 // at least 2 (d_model is a multiple of 128)
-    const int first = TT == 128 && NHW <= 2 && d_model % 2048 == 0 ? (int)(blockIdx.x * 17u % (unsigned)n_stages) : 0;
     // this wave's copies: rows 8 i .. 8 i + 7 for i = wv, wv + NW, ...  (rows past d_hidden or
     // past the last token repeat the last one; their results are not used)
     const uint16_t* src[kCopies];
@@ -226,8 +221,7 @@ __global__ __launch_bounds__(TT * NHW) void spkv_predictor_gemm(
     // copies u0 .. u1 - 1 of stage st (past the end: the last stage again, never used, so that
     // the count of copies in flight stays the same)
     auto copy_stage = [&](int st, int buf, int u0, int u1) {
-        const int at = min(st, n_stages - 1) + first;
-        const int k0 = (at < n_stages ? at : at - n_stages) * kGemmK;
+        const int k0 = min(st, n_stages - 1) * kGemmK;
 #pragma unroll
         for (int u = 0; u < kCopies; ++u) {
             if (u < u0 || u >= u1) continue;

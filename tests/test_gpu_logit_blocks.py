@@ -1,6 +1,5 @@
-"""Gate logits whose workgroups walk the hidden states from blocks of their own (rows whole
-multiples of 4 KB apart, more than 16 384 tokens, up to 128 hidden units) against the oracle, with
-sizes on both sides of that rule."""
+"""Gate logits of many tokens, whose workgroups take 128 tokens each (more than 16 384 tokens, up to 256 hidden
+units), against the oracle, and equal hidden states at different places of a launch, in every kernel."""
 
 import numpy as np
 import pytest
@@ -14,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,dm,dh,Hk", [(16385, 2048, 64, 1), (20001, 2048, 80, 5), (16600, 6144, 16, 2),
                                         (16511, 4096, 128, 8), (16400, 1920, 128, 3)])
-def test_logits_from_a_block_of_its_own(n, dm, dh, Hk):
+def test_logits_of_many_tokens(n, dm, dh, Hk):
     """fp32 sums of dm + dh products of unit scale in another order: a few thousand roundings of
     6e-8 add up to less than 1e-5."""
     from oracle.spkv_oracle import utility_logits as oracle_logits
@@ -30,3 +29,18 @@ def test_logits_from_a_block_of_its_own(n, dm, dh, Hk):
                               for t in (x[torch.from_numpy(rows).cuda()], w1, b1, w2, b2)))
         assert np.isfinite(got).all()
         assert np.abs(got[rows] - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("n,dm,dh,Hk", [(20001, 4096, 64, 8), (16500, 2048, 128, 3), (17000, 4096, 256, 8), (33000, 2048, 16, 1),
+                                        (9000, 2048, 64, 4), (5000, 2048, 320, 2), (300, 4096, 48, 8)])
+def test_logits_do_not_depend_on_where_a_token_stands(n, dm, dh, Hk):
+    """Equal hidden states have the same logits to the last bit, in whatever workgroup and row of one they stand:
+    a logit at the threshold keeps the same tokens of every copy of a prompt."""
+    g = torch.Generator(device="cuda").manual_seed(n + dm + dh)
+    few = torch.randn(37, dm, generator=g, device="cuda").to(torch.bfloat16)
+    which = torch.randint(37, (n,), generator=g, device="cuda")
+    w1 = (torch.randn(dh, dm, generator=g, device="cuda") / dm ** 0.5).to(torch.bfloat16)
+    w2 = (torch.randn(Hk, dh, generator=g, device="cuda") / dh ** 0.5).to(torch.bfloat16)
+    got = spkv.utility_logits(few[which], w1, None, w2, None)
+    first = torch.stack([got[which == i][0] for i in range(37)])
+    assert torch.equal(got, first[which])
