@@ -190,25 +190,6 @@ struct BulkInfo {
 };
 static_assert(sizeof(BulkInfo) == kSpanOrderStride * 4, "order entries lie in the scratch of the pairs");
 
-// The heads of a sequence's tokens lie side by side, 4 bytes of logit each in 32 of a token (8 heads), so the
-// workgroups that look at the same tokens for different heads run on one XCD (ids go round-robin to
-// the eight): its L2 fetches the logits once, and what they write side by side leaves it as whole lines.  Workgroup
-// `id` of groups x heads: whole eights of groups, a group to an XCD; the rest, or less than eight groups where they
-// divide eight evenly, several XCDs to a group; else in turn.
-struct HeadOfGroup {
-    int group, head;
-};
-__device__ __forceinline__ HeadOfGroup head_of_group(int id, int groups, int heads) {
-    const int whole = groups & ~7, xcd = id & 7, k = id >> 3;
-    if (id < whole * heads) return HeadOfGroup{k / heads * 8 + xcd, k % heads};
-    const int rest = groups - whole, at = id - whole * heads;
-    if ((rest == 1 || rest == 2 || rest == 4) && heads % (8 / rest) == 0) {
-        const int each = heads * rest / 8;
-        return HeadOfGroup{whole + xcd % rest, xcd / rest * each + (at >> 3)};
-    }
-    return HeadOfGroup{whole + at / heads, at % heads};
-}
-
 // Stage 1: per (segment, pair): how many of the segment's new tokens pass the gate, and how
 // many of those also leave the window within this call (j < n - w).
 __global__ __launch_bounds__(256) void spkv_bulk_count(SpkvView v, const float* __restrict__ f,
@@ -515,8 +496,7 @@ __global__ __launch_bounds__(256) void spkv_bulk_ring(SpkvView v, SpkvCu cu, int
                                                       const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ vv,
                                                       const float* __restrict__ f) {
-    const HeadOfGroup at = head_of_group(blockIdx.x, v.B, v.Hkv);
-    bulk_ring<D, SMALL, COUNT, MOVE>(v, cu, prefix, k, vv, f, at.group * v.Hkv + at.head);
+    bulk_ring<D, SMALL, COUNT, MOVE>(v, cu, prefix, k, vv, f, blockIdx.x);
 }
 // Stage 2 of a prefill call and, in further workgroups, its staging rows: neither writes what the other
 // reads (ring, ring logits, token counts; lists and tables).  Both wait for memory most of their time.
@@ -529,8 +509,7 @@ __global__ __launch_bounds__(256) void spkv_stage_ring(SpkvView v, SpkvCu cu, in
                                                        const float* __restrict__ f, SpkvStage st) {
     const int id = (int)blockIdx.x - v.n_pairs;
     if (id < 0) {
-        const HeadOfGroup at = head_of_group(blockIdx.x, v.B, v.Hkv);
-        bulk_ring<D, false, COUNT, MOVE>(v, cu, prefix, k, vv, f, at.group * v.Hkv + at.head);
+        bulk_ring<D, false, COUNT, MOVE>(v, cu, prefix, k, vv, f, blockIdx.x);
     } else {
         const int pair = id / st.hps;
         stage_half_page<D>(v, k, vv, f, cu, st, pair, id - pair * st.hps);
@@ -657,7 +636,10 @@ __device__ __forceinline__ void order_spans(const SpkvView& v, const SpkvCu& cu,
 // bytes: 16 sequences x 4096 tokens, 8 heads of 128, a fifth of the pairs kept (77 MB read, 70
 // written) 50 us with 256 tokens per workgroup, one group at a time and V units stored in
 // pairs; 46 us now with the leaving ring rows, whose move took 7 of the 18 us of stage 2.
-// 256 tokens per workgroup 52 us, 1024 tokens 49.
+// 256 tokens per workgroup 52 us, 1024 tokens 49.  Workgroups are numbered pair by pair: with the heads of a
+// token (whose logits share a line) on one XCD, whole prompts of 16 sequences of 32k take 514 us instead of 520 in
+// pieces of 4096 and 1009 instead of 1026 of 1024, but 701 instead of 680 of 2048, 8 sequences 338 / 330, 3 heads of
+// 64 201 / 194, 5 heads of 128 258 / 248.
 constexpr int kScatterSegs = 2, kScatterThreads = kScatterSegs * kSegTokens;
 
 template <int D>
@@ -672,8 +654,8 @@ __global__ __launch_bounds__(kScatterThreads) void spkv_bulk_scatter(SpkvView v,
         return;
     }
     if (to.host != nullptr && blockIdx.x == 0 && blockIdx.y == 0) copy_lengths(v.kept_len, v.n_pairs, to);
-    const HeadOfGroup at = head_of_group((int)(blockIdx.y * gridDim.x + blockIdx.x), v.B * (int)gridDim.x, v.Hkv);
-    const int b = at.group / (int)gridDim.x, quad = at.group - b * (int)gridDim.x, h = at.head, pair = b * v.Hkv + h;
+    const int pair = blockIdx.y, quad = blockIdx.x;
+    const int b = pair / v.Hkv, h = pair - b * v.Hkv;
     const int row0 = cu.v[b];
     const int n = cu.v[b + 1] - row0;
     const int j0 = quad * kScatterThreads;
