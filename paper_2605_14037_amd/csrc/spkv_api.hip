@@ -394,7 +394,7 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
     sp.hp_per_item = (int32_t)per;
     sp.slots = (int32_t)((max_hp + per * mw - 1) / (per * mw)) | 1;   // odd: see spkv_decode_split
     sp.mw = mw;
-    sp.compact = sp.runs = 0;
+    sp.compact = sp.runs = sp.most = 0;
     if (n_items != nullptr) {
         *n_items = 0;
         for (int p = 0; p < n_pairs; ++p)
@@ -414,7 +414,7 @@ SpkvSplit choose_split_mw(const spkv_cache* c, int one_round_items, int64_t slot
 // (keep rates that depend on the head) every sequence adds the same uneven pattern -- in
 // units of whole workgroups -- until some XCD is handed more waves than it holds and runs
 // the surplus in a second round.  Hence the limit of kMergePairs pairs.
-// Large caches are cut into equal shares before any of this is asked (worth_shares, below).
+// Large caches are cut into equal shares before any of this is asked (share_split, below).
 // Caches of more pairs take one item per workgroup, and where their lists are uneven
 // (worth_gapless) the gapless numbering (spkv_decode_split_compact) with seven items per
 // compute unit, as far as its prefix sum reaches; an explicit item target, merge width or the
@@ -471,23 +471,25 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
 }
 // Large caches in equal shares (spkv_decode_shares): two runs per compute unit.  From which size on, by what a wave
 // with two half-pages in registers costs at its start, and few pairs with many partial results each, against
-// what equal shares save; D = 64 has half the bytes to a half-page and the same arithmetic.  Step replayed from a graph,
-// items / shares, us: 8 heads of 128, 32 pairs of 18 MB 9.9 / 10.2, 26 MB 11.4 / 10.6, 67 MB 16.6 / 15.9, 192 MB
-// 38.2 / 33.5; 128 pairs of 49 MB 15.9 / 14.6, 266 MB 49.6 / 46.2; 512 pairs of 193 MB 44.1 / 41.6, 988 MB 190 / 160; 8 pairs
-// of 44 MB 13.6 / 14.2, 156 MB 31.4 / 30.9 (one run per compute unit 14.4, 32.0); head_dim 64: 128 pairs of 53 MB
-// 14.6 / 16.3, 133 MB 27.6 / 27.4, 256 pairs of 265 MB 49.0 / 47.1, 105 MB 24.0 / 24.4.  The multi-token step, whose
-// partial results are four times as long, gains earlier: 4 drafts, 32 pairs of 26 MB 18.2 / 16.2, 67 MB 26.4 / 21.7,
-// 256 pairs of 98 MB 37.1 / 28.9, 8 pairs of 18 MB 15.3 / 15.6; head_dim 64, 128 pairs of 133 MB 36.6 / 33.5.  (Uneven lists
-// too: 512 pairs, a quarter dense, a quarter local, 3.0 GB 468 / 452.)
+// what equal shares save; D = 64 has half the bytes to a half-page and the same arithmetic.  Step replayed from a graph
+// over enough caches that every one comes cold, 4 query heads to a KV head, items / shares, us: 32 pairs of 18 MB
+// 11.4 / 11.4, 26 MB 13.2 / 12.4, 64 MB 19.4 / 18.3, 240 MB 48.7 / 44.1; 128 pairs of 18 MB 11.8 / 12.1, 26 MB 13.9 / 13.4, 100 MB
+// 26.6 / 25.0; 256 of 26 MB 15.0 / 15.1, 40 MB 17.9 / 17.2; 512 of 60 MB 23.9 / 23.5, 1 GB 200 / 167 (one dense head in
+// eight 174 / 170).  12 to 23 pairs, too many for the merge in sixteen waves to pay and with more to merge in four than more
+// pairs have, begin later: 16 pairs of 22 MB 11.6 / 12.5, 26 MB 13.5 / 13.6, 34 MB 15.1 / 14.6, with one query head to a KV
+// head 11.2 / 12.2, 12.7 / 13.0, 14.1 / 13.7 (but 10 pairs of 26 MB 14.5 / 13.6).  Up to 8 the line lies where the
+// shares were ahead with every merge in four waves; in sixteen they would be from 26 MB on (8 pairs 14.5 / 13.6,
+// one pair of 40 MB 22.3 / 20.2).  head_dim 64: 32 pairs of 110 MB 26.9 / 26.8, 170 MB 37.5 / 35.3; 128 of 110 MB 26.6 / 27.4, 170 MB
+// 36.8 / 35.9; 8 of 170 MB 37.0 / 36.0.  The multi-token step, whose partial results are four times as long, gains
+// earlier and with any number of pairs: 4 drafts, 1 pair of 40 MB 35.8 / 25.6, 8 pairs of 26 MB 21.2 / 17.9, 32 pairs of
+// 18 MB 17.0 / 16.3, 64 MB 28.2 / 23.4, 256 of 40 MB 24.5 / 22.4; head_dim 64, 128 pairs of 110 MB 35.6 / 32.6.
+// (Repeated on one cache, which stays in the last-level cache, all take 1 to 2 us less.)
 // Not where two sequences have the same lengths throughout: an item's place in its pair depends on the pair's
 // length and the call, a run's on the pairs before it as well, and copies of a sequence are given the same bits.
-constexpr int kShareFewPairs = 8;
-constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)144 << 20, kShareBytes64 = (int64_t)160 << 20;
+constexpr int kShareFewPairs = 8, kShareSomePairs = 12, kShareManyPairs = 24;
+constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)144 << 20, kShareBytesSomePairs = (int64_t)28 << 20,
+                  kShareBytes64 = (int64_t)160 << 20;
 constexpr int64_t kShareBytesChunk = (int64_t)20 << 20, kShareBytesChunk64 = (int64_t)100 << 20;
-SpkvSplit share_split(const spkv_cache* c) {
-    const int runs = 2 * (c->compact_items / kCompactItemsPerCu);
-    return SpkvSplit{1, runs + c->carve.n_pairs, 1, 0, runs};
-}
 // Do two sequences have the same lengths in every head?  (Copies of a sequence do.)  Those of one half-page
 // a head do not count: it is never cut.
 bool sequences_alike(const spkv_cache* c) {
@@ -508,24 +510,32 @@ bool sequences_alike(const spkv_cache* c) {
     std::sort(seen.begin(), seen.end());
     return std::adjacent_find(seen.begin(), seen.end()) != seen.end();
 }
-bool worth_shares(const spkv_cache* c, int64_t slots_total_cap, bool chunk) {
-    const int n = c->carve.n_pairs, D = c->cfg.head_dim;
-    if (n > kSharePairs || share_split(c).slots > slots_total_cap) return false;
-    int64_t hps = 0;
+// The equal shares of a call; runs = 0 where they are not taken.
+SpkvSplit share_split(const spkv_cache* c, int64_t slots_total_cap, bool chunk) {
+    const int n = c->carve.n_pairs, D = c->cfg.head_dim, runs = 2 * (c->compact_items / kCompactItemsPerCu);
+    if (n > kSharePairs || runs + n > slots_total_cap) return SpkvSplit{};
+    int64_t hps = 0, longest = 0;
     for (int p = 0; p < n; ++p) {
         const int Tw = std::min(c->T[p / c->cfg.n_kv_heads], c->cfg.window);
-        hps += (c->L_ub[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
+        const int64_t hp = (c->L_ub[p] + kHalfTokens - 1) / kHalfTokens + (Tw + kHalfTokens - 1) / kHalfTokens;
+        hps += hp;
+        longest = std::max(longest, hp);
     }
-    const int64_t least = D == 64 ? (chunk ? kShareBytesChunk64 : kShareBytes64)
-                                  : chunk ? kShareBytesChunk : n <= kShareFewPairs ? kShareBytesFewPairs : kShareBytes;
-    return hps * (kHalfTokens * 4 * D) >= least && !sequences_alike(c);
+    const int64_t step_least = n <= kShareFewPairs ? kShareBytesFewPairs
+                               : n >= kShareSomePairs && n < kShareManyPairs ? kShareBytesSomePairs : kShareBytes;
+    const int64_t least = D == 64 ? (chunk ? kShareBytesChunk64 : kShareBytes64) : chunk ? kShareBytesChunk : step_least;
+    if (hps * (kHalfTokens * 4 * D) < least || sequences_alike(c)) return SpkvSplit{};
+    return SpkvSplit{1, runs + n, 1, 0, runs, (int32_t)(longest * runs / std::max<int64_t>(1, hps) + 1)};
 }
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
     if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     int64_t items_one = 0;
     const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
     if (c->merge_waves == 1) return one;
-    if (c->item_target <= 0 && c->step_launches != 1 && worth_shares(c, slots_total_cap, false)) return share_split(c);
+    if (c->item_target <= 0 && c->step_launches != 1) {
+        const SpkvSplit sp = share_split(c, slots_total_cap, false);
+        if (sp.runs > 0) return sp;
+    }
     if (c->carve.n_pairs <= kMergePairs) {
         for (int mw = 4; mw > 1; mw >>= 1) {
             int64_t items = 0;
@@ -608,7 +618,7 @@ bool short_lists(const spkv_cache* c, hipStream_t s) {
 bool short_attention(const spkv_cache* c, hipStream_t s) { return !c->timing && !c->split_only && short_lists(c, s); }
 // The partition reported for such a call: one workgroup per pair.
 SpkvSplit short_split(const spkv_cache* c) {
-    return SpkvSplit{1 << 16, 1, spkv_short_waves(c->cfg.head_dim), 0, 0};
+    return SpkvSplit{1 << 16, 1, spkv_short_waves(c->cfg.head_dim), 0, 0, 0};
 }
 
 // Tokens sequence b receives in a call: from cu_seqlens, or one each (cu == nullptr).
@@ -720,7 +730,7 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
         c->compact_items = kCompactItemsPerCu * (cus > 0 ? cus : 256);
         c->chunk_round_items = 0;
     }
-    c->split = SpkvSplit{1, 1, 1, 0, 0};
+    c->split = SpkvSplit{1, 1, 1, 0, 0, 0};
     c->timing = false;
     c->split_only = false;
     c->n_timed = 0;
@@ -1102,9 +1112,8 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
     const bool compact = c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
     int64_t items = 0;
-    if (c->item_target <= 0 && worth_shares(c, slot_cap, true)) {
-        c->split = share_split(c);
-    } else {
+    c->split = c->item_target <= 0 ? share_split(c, slot_cap, true) : SpkvSplit{};
+    if (c->split.runs == 0) {
         c->split = choose_split_mw(c, compact ? chunk_items : c->chunk_round_items, slot_cap, 1, &items);
         if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
     }

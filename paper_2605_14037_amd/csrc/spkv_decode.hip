@@ -397,9 +397,13 @@ __device__ __forceinline__ void decode_split_item(const SpkvView& v, const uint1
 // Merge workgroups of 16 waves instead of 4: when pairs have more than 64 partials and the
 // merge launch has at most one workgroup per compute unit (few long sequences; measured on
 // 4 sequences of 128k with about 150 partials per pair: 1.1 us less per step; with 39 per
-// pair, 0.5 us more; with 512 merge workgroups, 3 us more).
+// pair, 0.5 us more; with 512 merge workgroups, 3 us more).  With equal shares, whose partial results
+// begin where a load says, from 48 in the longest list on.  Step, 4 / 16 waves, us: 8 pairs of 26 MB, 76 in the longest
+// 14.4 / 13.6, of 240 MB 46.1 / 45.5; 12 pairs of 40 MB, 52 16.6 / 15.6; 16 of 64 MB, 44 19.0 / 19.4; 24 of 64 MB, 29
+// 18.4 / 19.4; but one dense head in eight, 16 pairs of 26 MB, 200 17.3 / 15.4, 32 of 100 MB, 100 26.2 / 25.2, 64 of
+// 100 MB, 50 25.8 / 25.6.
 static bool wide_merge(const SpkvView& v, const SpkvSplit& sp) {
-    return (sp.runs > 0 ? sp.runs / v.n_pairs : sp.slots) > 64 && v.n_pairs * v.G <= 256;
+    return (sp.runs > 0 ? sp.most > 48 : sp.slots > 64) && v.n_pairs * v.G <= 256;
 }
 
 template <int D, int MODE, int MW>
@@ -478,7 +482,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void
 }
 
 // ------------------------------------------------------------------ equal shares
-// Large caches (host: worth_shares): the half-pages of all pairs, in order, are cut into SpkvSplit.runs equal
+// Large caches (host: share_split): the half-pages of all pairs, in order, are cut into SpkvSplit.runs equal
 // runs, one per one-wave workgroup.  A run may begin in one pair and end in another and leaves a partial result
 // in each; run i and pair p share partial slot i + p (no two overlaps have the same sum).  Every wave finds its
 // run from the exact lengths, so the runs stay equal in a graph replayed on growing lists; one workgroup more

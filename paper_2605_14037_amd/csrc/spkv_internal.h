@@ -122,6 +122,7 @@ struct SpkvSplit {
     int32_t compact;      // 0: workgroup id = pair * slots + item; else workgroups numbered without
                           // gaps (spkv_decode_split_compact), this many of them
     int32_t runs;         // > 0: equal shares instead (spkv_decode_shares), this many; slots: all there are
+    int32_t most;         // equal shares: partial results of the longest list, by the host's bound
 };
 
 // Inputs and outputs of the single-token kernels that finish a pair themselves.

@@ -135,6 +135,35 @@ def test_large_caches_in_equal_shares(cfg, kept, step, chunk):
         assert got[0].launches[0][1][0] == 513 and got[3].launches[0][1][0] == 513 + 64 * -(-cfg["batch"] // 16)
 
 
+@pytest.mark.parametrize("cfg,kept,waves", [
+    (dict(batch=1), _unlike(8, 40000), 16), (dict(batch=3, n_q_heads=12, n_kv_heads=4), _unlike(12, 9000), 4),     # 65, 43 of a list
+    (dict(batch=3, n_q_heads=12, n_kv_heads=4), [9000 + 100 * (p == 5) + 2000 * (p == 7) + p for p in range(12)], 16),
+    (dict(batch=2), [25000 + p if p % 8 == 0 else 500 for p in range(16)], 16),       # one dense head in eight
+    (dict(batch=8), [14000 + p if p % 8 == 0 else 500 for p in range(64)], 16), (dict(batch=4), _unlike(32, 3000), 4),
+    (dict(batch=9), [14000 + p if p % 8 == 0 else 500 for p in range(72)], 4)])       # more merging workgroups than compute units
+def test_merge_of_equal_shares_follows_the_longest_list(cfg, kept, waves):
+    """Waves by the most partial results of one list, not by the mean: 16 pairs of 26 MB, one dense head in eight, took
+    17.3 us a step merged by four waves and 15.4 by sixteen."""
+    script = [["append", [60000] * cfg["batch"]], ["lengths", kept], ["stats"]]
+    calls = [["attend"], ["static"], ["step"], ["predict", 4096, 256]]
+    got = record(dict(cfg, max_total_kept_tokens=1 << 26), script + calls)[2:]
+    assert [c.rc for c in got] == [0] * 4
+    d = f"<128, {waves}, 1>", f"<128, 0, {waves}, 1>", f"<128, 1, {waves}, 1>"
+    assert [c.launches[1][0] for c in got] == ["spkv_decode_combine" + d[0]] * 2 + ["spkv_combine_append" + d[1], "spkv_combine_append" + d[2]]
+
+
+@pytest.mark.parametrize("cfg,kept,shares", [
+    (dict(batch=2), _unlike(16, 3420), False), (dict(batch=2), _unlike(16, 3440), True),         # 28 MiB
+    (dict(batch=11, n_q_heads=8, n_kv_heads=1), _unlike(11, 4300), False), (dict(batch=11, n_q_heads=8, n_kv_heads=1), _unlike(11, 4400), True),
+    (dict(batch=12, n_q_heads=8, n_kv_heads=1), _unlike(12, 4600), False), (dict(batch=12, n_q_heads=8, n_kv_heads=1), _unlike(12, 4680), True),
+    (dict(batch=23, n_q_heads=8, n_kv_heads=1), _unlike(23, 2300), False), (dict(batch=24, n_q_heads=8, n_kv_heads=1), _unlike(24, 1980), True)])
+def test_equal_shares_of_12_to_23_pairs_begin_later(cfg, kept, shares):
+    """They have more partial results each to merge: 16 pairs of 22 MB 11.6 us in items, 12.5 in shares."""
+    script = [["append", [60000] * cfg["batch"]], ["lengths", kept], ["stats"], ["step"], ["attend"]]
+    for c in record(dict(cfg, max_total_kept_tokens=1 << 25), script)[2:]:
+        assert c.rc == 0 and c.launches[0][0].startswith("spkv_decode_shares<") == shares
+
+
 # ------------------------------------------------------------------ utility predictor
 @pytest.mark.parametrize("tokens,d_model,d_hidden,kernel", [
     (4096, 4096, 16, "spkv_predictor_hidden"), (4096, 4096, 48, "spkv_predictor_hidden"),
