@@ -176,6 +176,7 @@ struct spkv_cache {
     int compact_items;            // item target under the gapless numbering
     int chunk_round_items;        // as one_round_items, for the chunk kernel
     SpkvSplit split;              // partition used by the last decode call
+    mutable std::vector<uint64_t> seen;   // scratch of sequences_alike: room for every sequence
     bool timing;
     bool split_only;
     std::vector<hipEvent_t> events;   // pairs (before, after)
@@ -494,8 +495,8 @@ constexpr int64_t kShareBytesChunk = (int64_t)20 << 20, kShareBytesChunk64 = (in
 // a head do not count: it is never cut.
 bool sequences_alike(const spkv_cache* c) {
     const int B = c->cfg.batch, Hkv = c->cfg.n_kv_heads;
-    std::vector<uint64_t> seen;
-    seen.reserve(B);
+    std::vector<uint64_t>& seen = c->seen;
+    seen.clear();
     for (int b = 0; b < B; ++b) {
         uint64_t x = (uint64_t)c->T[b] * 0x9e3779b97f4a7c15ull;
         bool any = std::min(c->T[b], c->cfg.window) > kHalfTokens;
@@ -528,14 +529,13 @@ SpkvSplit share_split(const spkv_cache* c, int64_t slots_total_cap, bool chunk) 
     return SpkvSplit{1, runs + n, 1, 0, runs, (int32_t)(longest * runs / std::max<int64_t>(1, hps) + 1)};
 }
 SpkvSplit choose_split(const spkv_cache* c, int one_round_items, int64_t slots_total_cap) {
-    if (c->merge_waves > 1) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
-    int64_t items_one = 0;
-    const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
-    if (c->merge_waves == 1) return one;
+    if (c->merge_waves > 0) return choose_split_mw(c, one_round_items, slots_total_cap, c->merge_waves);
     if (c->item_target <= 0 && c->step_launches != 1) {
         const SpkvSplit sp = share_split(c, slots_total_cap, false);
         if (sp.runs > 0) return sp;
     }
+    int64_t items_one = 0;
+    const SpkvSplit one = choose_split_mw(c, one_round_items, slots_total_cap, 1, &items_one);
     if (c->carve.n_pairs <= kMergePairs) {
         for (int mw = 4; mw > 1; mw >>= 1) {
             int64_t items = 0;
@@ -714,6 +714,7 @@ int spkv_cache_create(const spkv_config_t* cfg, void* dev_arena, size_t arena_by
     c->sent = false;
     c->snap_ev.assign(cfg->batch, 0);
     c->since_exact.assign(cfg->batch, 0);
+    c->seen.reserve(cfg->batch);
     c->lists_known = true;
     c->snap_covers = false;
     c->chunk_since_prompt = false;
@@ -1108,12 +1109,12 @@ int chunk_call(spkv_cache_t* c, const void* k, const void* v, const float* util_
     }
     // every slot holds 16 columns of partials instead of G
     const int64_t slot_cap = (int64_t)c->carve.max_items * G / 16;
-    // May take the gapless numbering with few items (spkv_chunk_split<D, 1, true>).
-    const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
-    const bool compact = c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
-    int64_t items = 0;
     c->split = c->item_target <= 0 ? share_split(c, slot_cap, true) : SpkvSplit{};
     if (c->split.runs == 0) {
+        // May take the gapless numbering with few items (spkv_chunk_split<D, 1, true>).
+        const int chunk_items = c->compact_items / kCompactItemsPerCu * kCompactChunkItemsPerCu;
+        const bool compact = c->item_target <= 0 && worth_gapless_chunk(c, chunk_items);
+        int64_t items = 0;
         c->split = choose_split_mw(c, compact ? chunk_items : c->chunk_round_items, slot_cap, 1, &items);
         if (compact) c->split.compact = (int32_t)std::max<int64_t>(1, items);
     }

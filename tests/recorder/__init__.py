@@ -7,7 +7,8 @@ process of its own against hip_recorder.cpp, a HIP runtime that writes launches 
 Script entries: ["append" | "chunk" | "score" | "prefill", tokens per sequence] (prefill: and the workspace's bytes), ["step"], ["attend"],
 ["static"], ["predict", d_model, d_hidden], ["stats"], ["reset"], ["logits", tokens, d_model, d_hidden, heads],
 ["soft", tokens per sequence], ["advance", n], ["option", id, value], ["destroy"] (last; "stats" has an
-entry ("items", (n_work_items, 0), 0)); and what the runtime answers from
+entry ("items", (n_work_items, 0), 0)), ["allocations"] (an entry ("allocations", (n, 0), 0): what the library has asked of the host's
+allocator since the last such entry); and what the runtime answers from
 there on: ["lengths", per pair] (any read-back of device lengths), ["capture", status, error],
 ["prompt_lengths", 0 | 1] (whether what a prompt sends to the host arrives: of lengths set before it),
 ["sync_error", error] (of waiting for a stream),

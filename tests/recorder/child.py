@@ -56,6 +56,9 @@ def main():
         if op in ("capture", "event_ready", "prompt_lengths", "sync_error"):
             getattr(rt, "rec_" + op)(*a)
             continue
+        if op == "allocations":
+            calls.append([0, [["allocations", rt.rec_news(), 0, 0]]])
+            continue
         if op == "append":
             rc = lib.spkv_append(handle, at, at, at, cu(a[0]), None)
         elif op == "step":

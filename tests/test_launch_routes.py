@@ -164,6 +164,18 @@ def test_equal_shares_of_12_to_23_pairs_begin_later(cfg, kept, shares):
         assert c.rc == 0 and c.launches[0][0].startswith("spkv_decode_shares<") == shares
 
 
+@pytest.mark.parametrize("cfg", [dict(batch=64), dict(batch=4), dict(batch=2)])
+def test_calls_in_equal_shares_allocate_nothing(cfg):
+    """No item partition is worked out (a vector of all pairs and up to 64 passes over it) only to be dropped."""
+    pairs, ones = 8 * cfg["batch"], [4] * cfg["batch"]
+    script = [["append", [30000] * cfg["batch"]], ["lengths", _unlike(pairs, 6000)], ["stats"], ["step"], ["allocations"]]
+    for call in (["step"], ["attend"], ["static"], ["predict", 4096, 256], ["score", ones], ["chunk", ones]):
+        script += [call, ["allocations"]]
+    got = record(dict(cfg, max_total_kept_tokens=1 << 27), script)[4:]
+    assert [c.rc for c in got[::2]] == [0] * 6 and all("shares" in c.launches[0][0] for c in got[::2])
+    assert [c.launches[0][1][0] for c in got[1::2]] == [0] * 6
+
+
 # ------------------------------------------------------------------ utility predictor
 @pytest.mark.parametrize("tokens,d_model,d_hidden,kernel", [
     (4096, 4096, 16, "spkv_predictor_hidden"), (4096, 4096, 48, "spkv_predictor_hidden"),
