@@ -486,7 +486,10 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
 // 18 MB 17.0 / 16.3, 64 MB 28.2 / 23.4, 256 of 40 MB 24.5 / 22.4; head_dim 64, 128 pairs of 110 MB 35.6 / 32.6.
 // (Repeated on one cache, which stays in the last-level cache, all take 1 to 2 us less.)
 // Not where two sequences have the same lengths throughout: an item's place in its pair depends on the pair's
-// length and the call, a run's on the pairs before it as well, and copies of a sequence are given the same bits.
+// length and the call, a run's on the pairs before it as well, and copies of a sequence are given the same bits.  The host
+// knows lengths alone, so two unlike sequences whose contexts and kept lengths coincide (equal dense batches,
+// many sequences of one KV head) keep the items too, at the items' speed.  Copies fed by the same calls have the same bound;
+// a captured launch is not asked again when it is replayed.
 constexpr int kShareFewPairs = 8, kShareSomePairs = 12, kShareManyPairs = 24;
 constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)144 << 20, kShareBytesSomePairs = (int64_t)28 << 20,
                   kShareBytes64 = (int64_t)160 << 20;

@@ -164,6 +164,18 @@ def test_equal_shares_of_12_to_23_pairs_begin_later(cfg, kept, shares):
         assert c.rc == 0 and c.launches[0][0].startswith("spkv_decode_shares<") == shares
 
 
+@pytest.mark.parametrize("kept,contexts,shares", [
+    (_unlike(64, 3000), [16384] * 64, True),
+    ([3000 + p * 5 % 63 for p in range(64)], [16384] * 64, False),                        # two lists of one length, no copies
+    ([3000 + p * 5 % 63 for p in range(64)], [16384] * 63 + [16385], True),               # ... of unlike contexts
+    ([3000] * 64, [16384 + b for b in range(64)], True)])
+def test_sequences_of_equal_lengths_keep_the_items(kept, contexts, shares):
+    """One KV head: copies of a sequence cannot be told from two whose contexts and kept lengths coincide."""
+    calls = [["step"], ["attend"], ["predict", 4096, 256], ["score", [2] * 64]]
+    got = record(dict(batch=64, n_q_heads=4, n_kv_heads=1), [["append", contexts], ["lengths", kept], ["stats"]] + calls)[2:]
+    assert [(c.rc, "shares" in c.launches[0][0]) for c in got] == [(0, shares)] * 4
+
+
 @pytest.mark.parametrize("cfg", [dict(batch=64), dict(batch=4), dict(batch=2)])
 def test_calls_in_equal_shares_allocate_nothing(cfg):
     """No item partition is worked out (a vector of all pairs and up to 64 passes over it) only to be dropped."""
