@@ -37,3 +37,11 @@ def test_only_matching_tensors_pass(make, ok):
     else:
         with pytest.raises(ValueError, match="need a contiguous"):
             binding._dev_ptr(t, torch.bfloat16, (3, 5), "t")
+
+
+def test_strided_tensors_of_the_right_shape_are_refused():
+    for t in (torch.zeros(5, 3, dtype=torch.bfloat16, device="cuda").t(), torch.zeros(3, 10, dtype=torch.bfloat16, device="cuda")[:, ::2],
+              torch.zeros(6, 5, dtype=torch.bfloat16, device="cuda")[::2], torch.zeros(5, dtype=torch.bfloat16, device="cuda").expand(3, 5)):
+        assert t.shape == (3, 5) and t.dtype == torch.bfloat16
+        with pytest.raises(ValueError, match="need a contiguous"):
+            binding._dev_ptr(t, torch.bfloat16, (3, 5), "t")

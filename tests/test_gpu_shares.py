@@ -6,8 +6,12 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2605_14037_amd as spkv
+from oracle.spkv_oracle import SPKVOracle
 from paper_2605_14037_amd.inputs import TokenStream, small_workload, to_numpy_f32
 from tests import harness as H
+from tests.recorder import record
+from tests.test_gpu_list_ends import _poisoned_cache
 from tests.test_gpu_parity import _first_kernel
 
 pytestmark = pytest.mark.gpu
@@ -102,4 +106,151 @@ def test_equal_shares(B, Hk, G, D, w, ctx, keep):
         torch.cuda.synchronize()
         H.check_output(outs, oracle.decode(to_numpy_f32(q))[0], f"replay {i}")
     H.check_state(cache, oracle, wl, pairs=[(0, 0), (B - 1, Hk - 1)])
+    cache.close()
+
+
+@pytest.mark.parametrize("D,w,ctx", [(128, 70, 2700), (64, 40, 34000)])
+def test_nan_behind_list_ends_does_not_show(D, w, ctx):
+    """An arena full of NaN, entries with infinite values that a prune drops, a sequence released with an infinite
+    window whose successor's own is still filling: none of it may show in lists that equal shares walk through."""
+    B, Hk, G = 5, 6, 2
+    lens = [ctx + 31 * b for b in range(B)]
+    wl = small_workload("ends", B, Hk * G, Hk, D, lens, 0.9, window=w, seed=D)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = _poisoned_cache(wl, sum(lens) * Hk + B * Hk * 4200, 200), H.make_oracle(wl)
+    done, tau = [0] * B, float(torch.sigmoid(torch.tensor(0.2)))
+    while min(d - n for d, n in zip(done, lens)) < 0:
+        counts = [min(4000, n - d) for n, d in zip(lens, done)]
+        k, v, f, cu = stream.next_tokens(counts)
+        oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+        bad = v.clone()
+        for b in range(B):
+            inside = slice(cu[b], cu[b + 1] - w if done[b] + counts[b] == lens[b] else cu[b + 1])       # all but the window
+            bad[inside][f[inside] < 0.2] = float("inf")
+            if b == 2:
+                bad[cu[b + 1] - w:cu[b + 1]] = float("inf")
+        cache.append(k, bad, f, cu)
+        done = [d + c for d, c in zip(done, counts)]
+    for c in (cache, oracle):
+        c.set_tau(tau)
+        c.prune()
+        c.release_sequence(2)
+    k, v, f, cu = stream.next_tokens([0, 0, w // 2, 0, 0])
+    H.feed(cache, oracle, k, v, f, cu)
+    held = [w // 2 if b == 2 else lens[b] for b in range(B)]
+    assert any(n % 32 for n in oracle.kept_len().ravel())
+    for r, kind in enumerate(["attend", "step", "chunk", "step", "static", "predict"]):
+        n = {"attend": 0, "static": 0, "chunk": 5}.get(kind, 1)
+        k, v, f, cu = stream.next_tokens([n] * B)
+        q = stream.next_query(rows=B * max(1, n))
+        call = {"chunk": ["chunk", [n] * B], "predict": ["predict", 256, 32]}.get(kind, [kind])
+        assert "shares" in _first_kernel(cache, wl, held, call)
+        if kind == "attend":
+            out = cache.decode_attention(q)
+        elif kind == "static":
+            out = torch.empty_like(q)
+            cache.decode_attention_static(q, out)
+        elif kind == "chunk":
+            out = cache.decode_chunk(k, v, f, q, cu)
+        elif kind == "step":
+            out = cache.decode_step(k, v, f, q)
+        else:
+            x, w1 = (torch.randn(m, 256, device="cuda").to(torch.bfloat16) / 16 for m in (B, 32))
+            out, f = cache.decode_step_predict(x, w1, None, torch.ones(Hk, 32, dtype=torch.bfloat16, device="cuda"), None, k, v, q)
+        if n:
+            oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+            held = [t + n for t in held]
+        H.check_output(out, oracle.decode_chunk(to_numpy_f32(q), [max(1, n)] * B)[0], f"{r}: {kind}")
+    H.check_state(cache, oracle, wl, pairs=[(0, 0), (2, 1), (B - 1, Hk - 1)])
+    cache.close()
+
+
+def test_copies_of_a_sequence_get_the_same_bits():
+    """Sequences 1 and 3 of four get the same tokens by the same calls: their results are equal to the last bit in every
+    single-token call and narrow chunk, although lists of this size are otherwise cut in equal shares."""
+    B, Hk, G, D, w = 4, 8, 4, 128, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    cache = spkv.SPKVCache(B, Hk * G, Hk, D, max_context=8000, max_total_kept_tokens=B * Hk * 6000, window=w)
+
+    def tokens(counts):
+        def rows(n, *shape):
+            one = [torch.randn(n, *shape, generator=g, device="cuda") for _ in range(3)]
+            return one + [one[1]]
+        k, v, q = (torch.cat([t[:c] for t, c in zip(rows(max(counts), heads, D), counts)]).to(torch.bfloat16) for heads in (Hk, Hk, Hk * G))
+        f = torch.cat([t[:c] for t, c in zip(rows(max(counts), Hk), counts)]).contiguous()
+        return k, v, f, q, [sum(counts[:b]) for b in range(B + 1)]
+
+    def same(t, cu, what):
+        assert torch.equal(t[cu[1]:cu[2]], t[cu[3]:cu[4]]), what
+
+    for counts in ([4000, 3000, 2500, 3000], [900, 2900, 3100, 2900]):
+        k, v, f, q, cu = tokens(counts)
+        cache.append(k, v, f + 1.0, cu)
+    x, w1, w2 = (torch.randn(n, m, generator=g, device="cuda").to(torch.bfloat16) / 16 for n, m in ((B, 256), (32, 256), (Hk, 32)))
+    x[3] = x[1]
+    for step in range(3):
+        k, v, f, q, cu = tokens([1] * B)
+        out, lse = cache.decode_step(k, v, f, q, want_lse=True)
+        same(out, cu, f"step {step}")
+        same(lse, cu, f"step {step}")
+        same(cache.decode_attention(q), cu, f"attention {step}")
+        k, v, f, q, cu = tokens([1] * B)
+        for t in cache.decode_step_predict(x, w1, None, w2, None, k, v, q):
+            same(t, cu, f"predictor {step}")
+        k, v, f, q, cu = tokens([1 + b % 2 * 2 for b in range(B)])
+        same(cache.score_chunk(k, v, q, cu), cu, f"drafts {step}")
+        same(cache.decode_chunk(k, v, f, q, cu), cu, f"chunk {step}")
+    st, kept = cache.stats(with_kept_len=True)
+    assert kept[1] == kept[3] and kept[0] != kept[1] and st.kept_kv_bytes > 40 << 20
+    cache.close()
+
+
+def test_pages_beyond_4_gib():
+    """More than 4 GiB of kept pages in equal shares: 40 sequences of the same tokens, each seven shorter than the one
+    before it; the first and the last against the oracle, in steps, attention and a chunk."""
+    B, Hq, Hkv, D, w, ctx, piece = 40, 32, 8, 128, 128, 40000, 4000
+    cache = spkv.SPKVCache(B, Hq, Hkv, D, max_context=ctx + 64, max_total_kept_tokens=B * Hkv * (ctx + 64), window=w, tau=0.5)
+    oracle = SPKVOracle(2, Hq, Hkv, D, window=w, tau=0.5)
+    g = torch.Generator(device="cuda").manual_seed(4103)
+
+    def tokens(counts):
+        n = max(counts)
+        k, v, q = (torch.randn(n, h, D, generator=g, device="cuda").to(torch.bfloat16) for h in (Hkv, Hkv, Hq))
+        f = torch.randn(n, Hkv, generator=g, device="cuda")
+        f[:, :6] = f[:, :6].abs() + 0.25                # kept whatever the draw; the others about a third
+        f[:, 6:] -= 0.45
+        first, last = counts[0], counts[-1]
+        oracle.append(*(to_numpy_f32(torch.cat([t[:first], t[:last]])) for t in (k, v, f)), [0, first, first + last])
+        cu = [sum(counts[:b]) for b in range(B + 1)]
+        return [torch.cat([t[:c] for c in counts]).contiguous() for t in (k, v, f, q)] + [cu]
+
+    held = [0] * B
+    for counts in [[piece] * B] * (ctx // piece - 1) + [[piece - 7 * b for b in range(B)]]:
+        k, v, f, _, cu = tokens(counts)
+        cache.append(k, v, f, cu)
+        held = [t + n for t, n in zip(held, counts)]
+    for call in (["step"], ["attend"], ["chunk", [3] * B]):
+        st, kept = cache.stats(with_kept_len=True)
+        assert st.kept_kv_bytes > 1 << 32 and st.device_error == 0
+        got = record(dict(batch=B, max_total_kept_tokens=1 << 24), [["append", held], ["lengths", sum(kept, [])], ["stats"], call])[-1]
+        assert got.rc == 0 and "shares" in got.launches[0][0]
+        n = 3 if call[0] == "chunk" else 1
+        k, v, f, q, cu = tokens([n] * B)
+        held = [t + n for t in held]
+        if call[0] == "step":
+            out, lse = cache.decode_step(k, v, f, q, want_lse=True)
+        elif call[0] == "attend":
+            cache.append(k, v, f, cu)
+            out, lse = cache.decode_attention(q, want_lse=True)
+        else:
+            out, lse = cache.decode_chunk(k, v, f, q, cu, want_lse=True)
+        ends = [*range(n), *range((B - 1) * n, B * n)]
+        ref_out, ref_lse = oracle.decode_chunk(to_numpy_f32(q[ends]), [n, n])
+        H.check_output(out[ends], ref_out, call[0])
+        H.check_lse(lse[ends], ref_lse, call[0])
+        assert torch.isfinite(out.float()).all()
+    kept = cache.stats(with_kept_len=True)[1]
+    assert [kept[0], kept[-1]] == oracle.kept_len().tolist()
+    for b in (0, B - 1):
+        assert cache.kept_positions(b, 7) == oracle.kept_positions(b // (B - 1), 7).tolist()
     cache.close()
