@@ -31,9 +31,9 @@
  *     computed in fp64 from the fp32 tau and rounded once to fp32.  This is Eq. 2 moved
  *     through the (strictly increasing) sigmoid.  tau <= 0 keeps every pair, tau >= 1
  *     keeps none.  NaN logits are dropped.
- *   - A call repeated on the same state gives the same bits.  How the lists are cut, and with it the
- *     order of a result's fp32 sums, depends on all lists of the call: the same tokens in another
- *     cache, batch or call may differ in the last bits.  Copies within a cache -- sequences that were given the
+ *   - How the lists are cut, and with it the order of a result's fp32 sums, depends on all lists of the
+ *     call and on what the host knows of their lengths by then: results for the same tokens in another cache,
+ *     batch or call may differ in the last bits.  Copies within a cache -- sequences that were given the
  *     same tokens by the same calls -- get the same bits in single-token calls and in multi-token
  *     calls of up to 16 query columns (tokens x group size).  A captured launch keeps the cut that was
  *     chosen at capture: copies that a cache is filled with afterwards agree to rounding in a replay.
