@@ -109,6 +109,49 @@ def test_equal_shares(B, Hk, G, D, w, ctx, keep):
     cache.close()
 
 
+@pytest.mark.parametrize("B,Hk,G,D,ctx", [(64, 8, 1, 128, 300), (23, 3, 5, 128, 1500), (131, 1, 4, 64, 2900), (40, 7, 2, 128, 400)])
+def test_gaps_between_sequences_that_take_part(B, Hk, G, D, ctx):
+    """Drafts and chunks for few sequences far apart, whose runs cross all that lies between, and a step of a cache
+    in which only such few hold a token."""
+    few = [(0, B - 1), (B // 7, B // 2 + 3), (B - 1,), (5, 6, B - 4), tuple(range(2, B, 17)), (B // 3,)]
+    wl = small_workload("gaps", B, Hk * G, Hk, D, [ctx + 7 * b for b in range(B)], 1.0, window=32, seed=B)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl, extra_context=60), H.make_oracle(wl)
+    H.prefill(cache, oracle, stream, wl, 4096)
+    held = list(wl.ctx_lens)
+    for who in few:
+        counts = [3 if b in who else 0 for b in range(B)]
+        k, v, f, cu = stream.next_tokens(counts)
+        q = stream.next_query(rows=sum(counts))
+        assert _first_kernel(cache, wl, held, ["score", counts]).startswith("spkv_chunk_shares<")
+        scored = cache.score_chunk(k, v, q, cu)
+        out, lse = cache.decode_chunk(k, v, f, q, cu, want_lse=True)
+        oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+        held = [t + n for t, n in zip(held, counts)]
+        ref_out, ref_lse = oracle.decode_chunk(to_numpy_f32(q), counts)
+        H.check_output(out, ref_out, f"chunk {who}")
+        H.check_output(scored, ref_out, f"drafts {who}")
+        H.check_lse(lse, ref_lse, f"chunk {who}")
+    cache.close()
+    long = 60000 if D == 128 else 700000
+    lens = [(long + b) // (Hk * 2) if b in few[1] else 0 for b in range(B)]
+    wl = small_workload("few", B, Hk * G, Hk, D, lens, 1.0, window=32, seed=B)
+    stream = TokenStream(wl, device="cuda")
+    cache, oracle = H.make_cache(wl, extra_context=60), H.make_oracle(wl)
+    H.prefill(cache, oracle, stream, wl, 8192)
+    for step in range(2):
+        k, v, f, cu = stream.next_tokens([1] * B)
+        q = stream.next_query()
+        assert _first_kernel(cache, wl, [n + step for n in lens], ["step"]).startswith("spkv_decode_shares<")
+        out, lse = cache.decode_step(k, v, f, q, want_lse=True)
+        oracle.append(to_numpy_f32(k), to_numpy_f32(v), to_numpy_f32(f), cu)
+        ref_out, ref_lse = oracle.decode(to_numpy_f32(q))
+        H.check_output(out, ref_out, f"step {step}")
+        H.check_lse(lse, ref_lse, f"step {step}")
+    H.check_state(cache, oracle, wl, pairs=[(few[1][0], 0), (B - 1, Hk - 1)])
+    cache.close()
+
+
 @pytest.mark.parametrize("D,w,ctx", [(128, 70, 2700), (64, 40, 34000)])
 def test_nan_behind_list_ends_does_not_show(D, w, ctx):
     """An arena full of NaN, entries with infinite values that a prune drops, a sequence released with an infinite
