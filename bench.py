@@ -492,7 +492,7 @@ def layered_bench(wl, args):
             "GBps": kept / (graph_us * 1e-6) / 1e9,
             "frac_of_hbm_peak_step": kept / (graph_us * 1e-6) / 1e9 / HBM_PEAK_GBPS},
         "dense_cache": dense,
-        "roofline": {"bound": "hbm", "kernel": "spkv_decode_split<128>",
+        "roofline": {"bound": "hbm", "kernel": "spkv_decode_shares<128> (large caches; else spkv_decode_split)",
                      "achieved": kept / Lyr / kern_us / 1e3, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": kept / Lyr / kern_us / 1e3 / HBM_PEAK_GBPS, "traffic": None,
                      "algorithmic_bytes_per_launch": kept / Lyr, "kernel_avg_us": kern_us,

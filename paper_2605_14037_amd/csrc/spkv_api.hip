@@ -483,7 +483,8 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
 // one pair of 40 MB 22.3 / 20.2).  head_dim 64: 32 pairs of 110 MB 26.9 / 26.8, 170 MB 37.5 / 35.3; 128 of 110 MB 26.6 / 27.4, 170 MB
 // 36.8 / 35.9; 8 of 170 MB 37.0 / 36.0.  The multi-token step, whose partial results are four times as long, gains
 // earlier and with any number of pairs: 4 drafts, 1 pair of 40 MB 35.8 / 25.6, 8 pairs of 26 MB 21.2 / 17.9, 32 pairs of
-// 18 MB 17.0 / 16.3, 64 MB 28.2 / 23.4, 256 of 40 MB 24.5 / 22.4; head_dim 64, 128 pairs of 110 MB 35.6 / 32.6.
+// 18 MB 17.0 / 16.3, 64 MB 28.2 / 23.4, 256 of 40 MB 24.5 / 22.4; head_dim 64, 128 pairs of 110 MB 35.6 / 32.6.  (Lists
+// very unlike, a few long ones among many short: steps 1.0 to 2.0 times as fast as items, drafts 0.97 to 2.9.)
 // (Repeated on one cache, which stays in the last-level cache, all take 1 to 2 us less.)
 // Not where two sequences have the same lengths throughout: an item's place in its pair depends on the pair's
 // length and the call, a run's on the pairs before it as well, and copies of a sequence are given the same bits.  The host

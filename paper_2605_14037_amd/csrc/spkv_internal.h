@@ -20,7 +20,10 @@ constexpr int kSpanOrderPairs = 64, kSpanOrderAt = 4, kSpanOrderStride = 8;
 struct SpanCut {
     int32_t tokens, groups;           // tokens of a span (0: no order wanted), groups of pairs (a divisor of H_kv)
 };
-constexpr int kSharePairs = 512;      // most (sequence, head) pairs that are cut into equal shares
+// Most (sequence, head) pairs that are cut into equal shares: what every wave holds the lengths of while it looks for
+// its run, 256 pairs to two registers of four.  Room for 1024 costs 512 pairs nothing that shows (1 GB 166.5 / 167.8 us) and
+// 1024 pairs (items / shares) 100 MB 37.8 / 38.5, 200 MB 55.7 / 54.1, 400 MB 92 / 84, 1 GB 182 / 176: not taken so far.
+constexpr int kSharePairs = 512;
 constexpr int kCompactPairs = 1024;   // most (sequence, head) pairs the gapless numbering serves
 
 // A short chunk reads every list once.  Lists of more than half the last-level cache (256 MB)

@@ -258,7 +258,7 @@ __device__ __forceinline__ int block_excl_scan(int x, int* s_w, int& total) {
 // job for its pair (the per-segment counts from the logits, every wave's popcounts parked in
 // LDS), so that the call is two launches instead of three.  Bound by dependent round trips, so only three are
 // left: logits, counters and the stack of pages together, ring logits, the pool's atomic; counts, offsets and
-// lengths go from one barrier's popcounts to every wave's registers.  16 sequences x 4096 tokens 11.3 -> 9.5 us
+// lengths go from one barrier's popcounts to every wave's registers.  16 sequences x 4096 tokens 11.3 -> 9.7 us
 // (counts and offsets through memory, the counters before the logits, six barriers more before).
 constexpr int kCountSegs = 16;
 //
