@@ -476,11 +476,12 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
 // over enough caches that every one comes cold, 4 query heads to a KV head, items / shares, us: 32 pairs of 18 MB
 // 11.4 / 11.4, 26 MB 13.2 / 12.4, 64 MB 19.4 / 18.3, 240 MB 48.7 / 44.1; 128 pairs of 18 MB 11.8 / 12.1, 26 MB 13.9 / 13.4, 100 MB
 // 26.6 / 25.0; 256 of 26 MB 15.0 / 15.1, 40 MB 17.9 / 17.2; 512 of 60 MB 23.9 / 23.5, 1 GB 200 / 167 (one dense head in
-// eight 174 / 170).  12 to 23 pairs, too many for the merge in sixteen waves to pay and with more to merge in four than more
-// pairs have, begin later: 16 pairs of 22 MB 11.6 / 12.5, 26 MB 13.5 / 13.6, 34 MB 15.1 / 14.6, with one query head to a KV
-// head 11.2 / 12.2, 12.7 / 13.0, 14.1 / 13.7 (but 10 pairs of 26 MB 14.5 / 13.6).  Up to 8 the line lies where the
-// shares were ahead with every merge in four waves; in sixteen they would be from 26 MB on (8 pairs 14.5 / 13.6,
-// one pair of 40 MB 22.3 / 20.2).  head_dim 64: 32 pairs of 110 MB 26.9 / 26.8, 170 MB 37.5 / 35.3; 128 of 110 MB 26.6 / 27.4, 170 MB
+// eight 174 / 170).  Around the line 12 to 20 pairs have the most to merge: 26 MB, 1 / 2 / 4 / 8 query heads to a KV head, 12
+// pairs 13.1 13.2 13.7 14.4 / 13.5 13.6 13.7 14.0, 16 pairs 12.8 13.2 13.4 14.0 / 13.0 13.3 13.5 13.9, even at 29 MB; the step
+// with the predictor, 256 hidden units, is ahead everywhere: 14.9 15.6 15.9 16.6 / 12.9 13.8 13.8 14.1, 14.2 14.4 15.0 15.5 /
+// 13.1 13.6 13.8 14.2.  Up to 8 the line lies where the shares were ahead with every merge in four waves; in sixteen they
+// would be from 26 MB on (8 pairs 14.5 / 13.6, one pair of 40 MB 22.3 / 20.2).  head_dim 64: 32 pairs of 110 MB
+// 26.9 / 26.8, 170 MB 37.5 / 35.3; 128 of 110 MB 26.6 / 27.4, 170 MB
 // 36.8 / 35.9; 8 of 170 MB 37.0 / 36.0.  The multi-token step, whose partial results are four times as long, gains
 // earlier and with any number of pairs: 4 drafts, 1 pair of 40 MB 35.8 / 25.6, 8 pairs of 26 MB 21.2 / 17.9, 32 pairs of
 // 18 MB 17.0 / 16.3, 64 MB 28.2 / 23.4, 256 of 40 MB 24.5 / 22.4; head_dim 64, 128 pairs of 110 MB 35.6 / 32.6.  (Lists
@@ -491,9 +492,8 @@ bool worth_gapless_chunk(const spkv_cache* c, int items) {
 // knows lengths alone, so two unlike sequences whose contexts and kept lengths coincide (equal dense batches,
 // many sequences of one KV head) keep the items too, at the items' speed.  Copies fed by the same calls have the same bound;
 // a captured launch is not asked again when it is replayed.
-constexpr int kShareFewPairs = 8, kShareSomePairs = 12, kShareManyPairs = 24;
-constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)144 << 20, kShareBytesSomePairs = (int64_t)28 << 20,
-                  kShareBytes64 = (int64_t)160 << 20;
+constexpr int kShareFewPairs = 8;
+constexpr int64_t kShareBytes = (int64_t)24 << 20, kShareBytesFewPairs = (int64_t)144 << 20, kShareBytes64 = (int64_t)160 << 20;
 constexpr int64_t kShareBytesChunk = (int64_t)20 << 20, kShareBytesChunk64 = (int64_t)100 << 20;
 // Do two sequences have the same lengths in every head?  (Copies of a sequence do.)  Those of one half-page
 // a head do not count: it is never cut.
@@ -526,9 +526,8 @@ SpkvSplit share_split(const spkv_cache* c, int64_t slots_total_cap, bool chunk) 
         hps += hp;
         longest = std::max(longest, hp);
     }
-    const int64_t step_least = n <= kShareFewPairs ? kShareBytesFewPairs
-                               : n >= kShareSomePairs && n < kShareManyPairs ? kShareBytesSomePairs : kShareBytes;
-    const int64_t least = D == 64 ? (chunk ? kShareBytesChunk64 : kShareBytes64) : chunk ? kShareBytesChunk : step_least;
+    const int64_t least = D == 64 ? (chunk ? kShareBytesChunk64 : kShareBytes64)
+                                  : chunk ? kShareBytesChunk : n <= kShareFewPairs ? kShareBytesFewPairs : kShareBytes;
     if (hps * (kHalfTokens * 4 * D) < least || sequences_alike(c)) return SpkvSplit{};
     return SpkvSplit{1, runs + n, 1, 0, runs, (int32_t)(longest * runs / std::max<int64_t>(1, hps) + 1)};
 }
